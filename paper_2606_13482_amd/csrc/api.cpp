@@ -43,8 +43,8 @@ void destroy_op(bie_op *op)
     bie::packed_free(op->pkv);
     void *ptrs[] = { op->pooled ? nullptr : op->Z64, op->Z32, op->V64, op->V32, op->star_buf, op->Abf, op->Bbf,
                      op->gemm_part, op->pooled ? nullptr : op->A64,
-                     op->d64_part, op->tri.cent, op->tri.loc, op->tri.vfree, op->tri.verts, op->tri.area, op->tri.sgn,
-                     op->tri.slot_m, op->tri.edges };
+                     op->d64_part, op->tri.cent, op->tri.loc, op->tri.vfree, op->tri.verts, op->tri.area, op->tri.rad, op->tri.sgn,
+                     op->tri.slot_m, op->tri.edges, op->flagged };
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete op;
@@ -70,7 +70,7 @@ int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t 
         if (o.star != 0 && o.star != 1) return fail(BIE_EINVAL, "star must be 0 or 1");
         if (o.star && o.storage == BIE_SPLIT_BF16) return fail(BIE_EINVAL, "the star-split form has no split-BF16 copy");
         if (!(o.near_factor >= 0.0)) return fail(BIE_EINVAL, "near_factor must be >= 0");
-        bie::Mesh mesh = bie::build_mesh(verts, nv, tris, nt, o.near_factor);   // host only: EMESH first
+        bie::Mesh mesh = bie::build_mesh(verts, nv, tris, nt, o.near_factor, !bie::near_on_device(nt));   // host only: EMESH first
         bie_op *op = new bie_op();
         try {
             op->mesh = std::move(mesh);
@@ -80,6 +80,7 @@ int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t 
             op->star = o.star;
             hipStream_t s = as_stream(stream);
             bie::upload_triangles(op, s);
+            bie::flag_pairs(op, o.near_factor, true, s);
             bie::packed_setup(op->pk, op->mesh.N);
             if (op->star) bie::packed_setup(op->pkv, op->mesh.F);
             const size_t tile_elems = size_t(op->pk.ntiles) * bie::TB * bie::TB;
@@ -128,7 +129,7 @@ int bie_op_create_fast(const double *verts, int64_t nv, const int32_t *tris, int
         if (!verts || !tris || !opts) return fail(BIE_EINVAL, "NULL argument");
         if (!(k > 0.0) || !std::isfinite(k)) return fail(BIE_EINVAL, "wavenumber must be positive and finite");
         if (!(opts->near_factor >= 0.0)) return fail(BIE_EINVAL, "near_factor must be >= 0");
-        bie::Mesh mesh = bie::build_mesh(verts, nv, tris, nt, opts->near_factor);   // host only: EMESH first
+        bie::Mesh mesh = bie::build_mesh(verts, nv, tris, nt, opts->near_factor, !bie::near_on_device(nt));   // host only: EMESH first
         bie_op *op = new bie_op();
         try {
             op->mesh = std::move(mesh);
@@ -137,7 +138,8 @@ int bie_op_create_fast(const double *verts, int64_t nv, const int32_t *tris, int
             op->storage = BIE_C128;
             hipStream_t s = as_stream(stream);
             bie::upload_triangles(op, s);
-            bie::fast_setup(op, opts->box, opts->levels, opts->s, opts->p, s);
+            bie::flag_pairs(op, opts->near_factor, false, s);
+            bie::fast_setup(op, opts->near_factor, opts->box, opts->levels, opts->s, opts->p, s);
         } catch (...) {
             destroy_op(op);
             throw;
@@ -182,16 +184,10 @@ int bie_op_matrix(const bie_op *op, void *dst, int dtype, void *stream)
         if (op->fast) return fail(BIE_EINVAL, "a fast operator holds no dense matrix");
         hipStream_t s = as_stream(stream);
         if (dtype == BIE_C128) {
-            bie::unpack_c128(op, op->Z64 != nullptr, dst, s);
+            bie::unpack_full(op, op->Z64 != nullptr, true, dst, s);
         } else if (dtype == BIE_C64) {
             if (!op->Z32) return fail(BIE_EINVAL, "no FP32 matrix stored");
-            void *tmp = nullptr;
-            const int64_t NN = op->mesh.N * op->mesh.N;
-            BIE_HIP(hipMalloc(&tmp, size_t(NN) * 16));
-            bie::unpack_c128(op, false, tmp, s);
-            bie::convert_c128_to_c64(tmp, dst, NN, s);
-            BIE_HIP(hipStreamSynchronize(s));
-            (void)hipFree(tmp);
+            bie::unpack_full(op, false, false, dst, s);
         } else {
             return fail(BIE_EINVAL, "unknown dtype");
         }

@@ -42,8 +42,10 @@ struct Mesh {
     std::vector<int32_t> near;      // flagged pairs (p <= q), 2 per pair
 };
 
-// Builds and validates; throws Error(BIE_EMESH) for invalid meshes.
-Mesh build_mesh(const double *verts, int64_t nv, const int32_t *tris, int64_t nt, double near_factor);
+// Builds and validates; throws Error(BIE_EMESH) for invalid meshes.  pairs false:
+// the flagged pairs are left to flag_pairs (near.hip).
+Mesh build_mesh(const double *verts, int64_t nv, const int32_t *tris, int64_t nt, double near_factor,
+                bool pairs = true);
 
 // SplitMix64 + Floyd row sample (rng.cpp).
 std::vector<int64_t> rscc_rows(int64_t N, int64_t S, uint64_t seed);
@@ -51,11 +53,15 @@ std::vector<int64_t> rscc_rows(int64_t N, int64_t S, uint64_t seed);
 // Per-triangle data uploaded for the fill kernels.  Quadrature points are
 // stored relative to the triangle centroid; the centroid itself in FP64.
 struct TriDev {
+    std::vector<int32_t> rank;  // host: device position of triangle t (see upload_triangles); every table below is in
+                                // that order, and edges names triangles by it
     double *cent = nullptr;     // F x 3
     double *loc = nullptr;      // F x 7 x 3   quadrature points - centroid
     double *vfree = nullptr;    // F x 3 x 3   free vertex of slot a - centroid
     double *verts = nullptr;    // F x 3 x 3   absolute vertex coordinates (singular kernel)
     double *area = nullptr;     // F
+    double *rad = nullptr;      // F           largest distance of a quadrature point from the centroid
+    double max_rad = 0.0;       // host: the largest of them
     int8_t *sgn = nullptr;      // F x 3
     int32_t *slot_m = nullptr;  // F x 3
     int32_t *edges = nullptr;   // N x 4
@@ -127,6 +133,7 @@ struct bie_op {
     int storage = BIE_C128;
     bie::Mesh mesh;
     bie::TriDev tri;
+    int32_t *flagged = nullptr;   // device: flagged pairs p <= q in the device order of the triangles, 2 each
     void *Z64 = nullptr;   // packed symmetric tiles, complex128 (storage C128 or keep_fp64); star: T_A' = jk T_A
     void *Z32 = nullptr;   // packed symmetric tiles, complex64 (storage C64); star: T_A'
     bie::Packed pk;
@@ -196,6 +203,33 @@ double2 *calderon_scratch(const bie_calderon *pc, int64_t R, hipStream_t s);
 void add_into(int64_t n, const void *a, void *x, hipStream_t s);   // x += a (n complex)
 void zero_into(int64_t n, void *x, hipStream_t s);
 
+// near.hip: touching or near triangle pairs, found on the device up to this many
+// triangles (see the file)
+bool near_on_device(int64_t F);
+// Pairs of the triangles order[0], order[1], ... (null: their own order) by position:
+// partners q >= p of p, ascending, are list[ptr[p]] .. list[ptr[p + 1]] - 1.
+struct NearDev {
+    int64_t n = 0;
+    int64_t *ptr = nullptr;    // F + 1
+    int32_t *list = nullptr;   // n
+    NearDev() = default;
+    NearDev(const NearDev &) = delete;
+    NearDev &operator=(const NearDev &) = delete;
+    ~NearDev()
+    {
+        if (ptr) (void)hipFree(ptr);
+        if (list) (void)hipFree(list);
+    }
+};
+void near_search(const Mesh &M, double near_factor, const std::vector<int32_t> *order, NearDev &out, hipStream_t s);
+// The operator's flagged pairs: mesh.near, if the mesh came without, and with
+// device_list op->flagged (freed by the fill).
+void flag_pairs(bie_op *op, double near_factor, bool device_list, hipStream_t s);
+// The flagged pairs by row in the device order of the triangles.
+void ranked_near(const bie_op *op, double near_factor, NearDev &out, hipStream_t s);
+// The pairs (p, q) of a list, one after another (a device array of the caller's).
+int32_t *near_list(const NearDev &nd, int64_t F, hipStream_t s);
+
 // fill.hip
 constexpr int QPTS = 7;               // points of the triangle rule (Radon's degree-5 rule)
 void quad_weights(double *w);         // its weights, relative to the triangle area
@@ -233,8 +267,8 @@ void product(const bie_op *op, int mat, bool vec64, const void *X, int64_t ldx, 
 // Y = T X (or T^H X) with the packed matrix, partial sums in the library's
 // static per-device scratch (no allocation); BIE_EINVAL when they do not fit.
 void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64_t R, bool conj, hipStream_t s);
-// packed -> full row-major complex128
-void unpack_c128(const bie_op *op, bool from64, void *dst, hipStream_t s);
+// packed -> full row-major: from the FP64 or the FP32 tiles, to complex128 or complex64 (FP32 tiles only)
+void unpack_full(const bie_op *op, bool from64, bool to64, void *dst, hipStream_t s);
 // sampled rows of T x (complex128): out[r*S + i] = |b_i - (T x_r)_i|^2, i in rows[r*S ..]
 void sampled_residual(const bie_op *op, const void *B, const void *X, int64_t R, int64_t S, const int64_t *rows,
                       double *out, const int *mask, hipStream_t s);
@@ -294,7 +328,7 @@ void farml_leaves(const bie_farml *f, std::vector<int32_t> &box_of, std::vector<
 // fill.hip: the flagged pairs' local blocks, compact (18 doubles per pair)
 void singular_blocks(const bie_op *op, const int32_t *pairs, int64_t npairs, double *out, hipStream_t s);
 // fast.hip
-void fast_setup(bie_op *op, double box, int levels, int s, int p, hipStream_t st);
+void fast_setup(bie_op *op, double near_factor, double box, int levels, int s, int p, hipStream_t st);
 void fast_product(const bie_op *op, const void *X, int64_t ldx, void *Y, int64_t ldy, const void *B, int64_t ldb,
                   int64_t R, hipStream_t st);
 void fast_info(const bie_op *op, bie_fast_info *info);

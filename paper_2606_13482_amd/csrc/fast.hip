@@ -35,7 +35,8 @@ struct FastOp {
     double2 *vals = nullptr;
     double2 *tmp = nullptr;         // far product of one column
     double *qw = nullptr;           // Radon weights
-    int32_t *fptr = nullptr, *fq = nullptr;   // flagged partners q >= p of each triangle p, ascending
+    int64_t *fptr = nullptr;
+    int32_t *fq = nullptr;          // flagged partners q >= p of each triangle p, ascending
     double *fblk = nullptr;         // their blocks, 18 doubles per pair (index = position in fq)
     ~FastOp()
     {
@@ -54,7 +55,7 @@ constexpr int NQF = QPTS;   // quadrature points per triangle
 __device__ inline double2 local_block(int32_t p, int32_t a, int32_t q, int32_t b, const double *__restrict__ cent,
                                       const double *__restrict__ loc, const double *__restrict__ vfree,
                                       const int8_t *__restrict__ sgn, const double *__restrict__ qw,
-                                      const int32_t *__restrict__ fptr, const int32_t *__restrict__ fq,
+                                      const int64_t *__restrict__ fptr, const int32_t *__restrict__ fq,
                                       const double *__restrict__ fblk, double k)
 {
     if (p > q) {   // L(p, a, q, b) = L(q, b, p, a): the kernel is symmetric
@@ -66,9 +67,9 @@ __device__ inline double2 local_block(int32_t p, int32_t a, int32_t q, int32_t b
         b = u;
     }
     // flagged?
-    int32_t lo = fptr[p], hi = fptr[p + 1];
+    int64_t lo = fptr[p], hi = fptr[p + 1];
     while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
+        const int64_t mid = (lo + hi) >> 1;
         if (fq[mid] < q) lo = mid + 1;
         else hi = mid;
     }
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256) void k_near_entries(int64_t N, const int64_t *
                                                       const int32_t *__restrict__ cols, const int4 *__restrict__ rwg4,
                                                       const double *__restrict__ cent, const double *__restrict__ loc,
                                                       const double *__restrict__ vfree, const int8_t *__restrict__ sgn,
-                                                      const double *__restrict__ qw, const int32_t *__restrict__ fptr,
+                                                      const double *__restrict__ qw, const int64_t *__restrict__ fptr,
                                                       const int32_t *__restrict__ fq, const double *__restrict__ fblk,
                                                       double k, double2 *__restrict__ vals)
 {
@@ -167,7 +168,7 @@ T *up(const std::vector<T> &v)
 
 }  // namespace
 
-void fast_setup(bie_op *op, double box, int levels, int s, int p, hipStream_t st)
+void fast_setup(bie_op *op, double near_factor, double box, int levels, int s, int p, hipStream_t st)
 {
     auto f = std::make_unique<FastOp>();
     f->far = farml_create(op, box, levels, s, p, st);
@@ -200,30 +201,21 @@ void fast_setup(bie_op *op, double box, int levels, int s, int p, hipStream_t st
     cols.reserve(size_t(rowptr[N]));
     for (int64_t m = 0; m < N; ++m) cols.insert(cols.end(), nearcols[box_of[m]].begin(), nearcols[box_of[m]].end());
     f->nnz = rowptr[N];
-    // flagged pairs by first triangle, partners ascending
+    // flagged pairs by first triangle (device order), partners ascending
     const int64_t nflag = int64_t(M.near.size() / 2);
-    std::vector<std::pair<int32_t, int32_t>> fl(static_cast<size_t>(nflag));
-    for (int64_t i = 0; i < nflag; ++i) fl[i] = { M.near[2 * i], M.near[2 * i + 1] };
-    std::sort(fl.begin(), fl.end());
-    std::vector<int32_t> fptr(F + 1, 0), fq(static_cast<size_t>(nflag)), fpairs(2 * static_cast<size_t>(nflag));
-    for (int64_t i = 0; i < nflag; ++i) {
-        ++fptr[fl[i].first + 1];
-        fq[i] = fl[i].second;
-        fpairs[2 * i] = fl[i].first;
-        fpairs[2 * i + 1] = fl[i].second;
-    }
-    for (int64_t t = 0; t < F; ++t) fptr[t + 1] += fptr[t];
+    NearDev nd;
+    ranked_near(op, near_factor, nd, st);
     double qwh[QPTS];
     quad_weights(qwh);
     f->qw = up(std::vector<double>(qwh, qwh + QPTS));
-    f->fptr = up(fptr);
-    f->fq = up(fq);
+    int32_t *dpairs = near_list(nd, F, st);
+    std::swap(f->fptr, nd.ptr);
+    std::swap(f->fq, nd.list);
     f->rowptr = up(rowptr);
     f->cols = up(cols);
     BIE_HIP(hipMalloc(&f->fblk, std::max<int64_t>(nflag, 1) * 18 * sizeof(double)));
     BIE_HIP(hipMalloc(&f->vals, std::max<int64_t>(f->nnz, 1) * sizeof(double2)));
     BIE_HIP(hipMalloc(&f->tmp, std::max<int64_t>(N, 1) * sizeof(double2)));
-    int32_t *dpairs = up(fpairs);
     singular_blocks(op, dpairs, nflag, f->fblk, st);
     const TriDev &D = op->tri;
     hipLaunchKernelGGL(k_near_entries, dim3(unsigned(N)), dim3(256), 0, st, N, f->rowptr, f->cols,

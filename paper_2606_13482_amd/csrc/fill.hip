@@ -18,10 +18,9 @@
 // written to its own tile array and assembled into packed F x F tiles of V'.
 //
 // Pipeline (three launches, no atomics, bitwise symmetric result):
-//   1. k_pairs_regular: one thread per ordered triangle pair p <= q of a 16x16
-//      triangle tile staged in LDS; 49 kernel evaluations; writes the 3x3
-//      local block L into a tile-major scratch array.
-//   2. k_pairs_singular: one FP64 thread per flagged pair (touching or near):
+//   1. k_pairs_regular: one lane per triangle pair p <= q; 49 kernel evaluations;
+//      writes the 3x3 local block L into a scratch array of bands of 16 rows p.
+//   2. k_pairs_singular: 16 lanes per flagged pair (touching or near), FP64:
 //      g = g_r + 1/(4 pi R), g_r on the product rule, the static part with the
 //      inner integral in closed form, mean of both orderings; overwrites L.
 //   3. k_assemble: T_mn = (L(c+m,c+n) + L(c-m,c-n)) + (L(c+m,c-n) + L(c-m,c+n));
@@ -29,15 +28,18 @@
 //      only the upper-triangular 64 x 64 tiles are written (packed storage).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "bie_internal.hpp"
+#include "pairs.hpp"
 
 namespace bie {
 
 namespace {
 
-constexpr int TT = 16;               // triangles per tile side
+constexpr int TT = 16;               // rows of a band of the pair scratch
 constexpr int NQ = 7;                // Radon 7-point rule
 constexpr double PI = 3.14159265358979323846;
 
@@ -66,174 +68,112 @@ Rule make_rule()
 
 __constant__ double c_w[NQ];
 
-__host__ __device__ inline int64_t tile_index(int64_t I, int64_t J, int64_t nT)
-{
-    return I * nT - I * (I - 1) / 2 + (J - I);
-}
+// Scratch of the local blocks: triangles in the device order, in bands of TT
+// rows p; band I holds the columns q >= TT I up to Fp (F rounded up to TT) and
+// its rows are [slot a of p][q][slot b of q].  Lanes over q write whole lines, and
+// the assembly, which walks the functions n of one row m, finds the three slots
+// of a triangle q side by side.
+struct Bands {
+    int64_t Fp;
+    __host__ __device__ int64_t cols(int64_t I) const { return Fp - TT * I; }
+    __host__ __device__ int64_t base(int64_t I) const { return TT * (I * Fp - TT * (I * (I - 1) / 2)); }   // pairs before band I
+    __host__ __device__ int64_t total() const { return base(Fp / TT); }
+    // complex entry of slots (a, b) of the pair p <= q
+    __device__ int64_t block(int64_t p, int64_t q, int a, int b) const
+    {
+        const int64_t I = p / TT;
+        return 9 * base(I) + (((p % TT) * 3 + a) * cols(I) + (q - TT * I)) * 3 + b;
+    }
+    __device__ int64_t pair(int64_t p, int64_t q) const
+    {
+        const int64_t I = p / TT;
+        return base(I) + (p % TT) * cols(I) + (q - TT * I);
+    }
+};
 
 // ---------------------------------------------------------------------------
-// 1. Regular pairs.
-template <typename R>
-struct TriLDS {
-    R loc[NQ][3];
-    R vf[3][3];
-};
-// FP64: one double of padding (31 per triangle), so that the 16 triangles of a
-// tile read in one instruction start in 16 different bank pairs (30 doubles put
-// triangles 8 apart in the same banks: a two-way conflict on every read).
-template <>
-struct TriLDS<double> {
-    double loc[NQ][3];
-    double vf[3][3];
-    double pad;
-};
-
-template <typename R>
-__device__ inline void sincos_t(R x, R *s, R *c);
-template <>
-__device__ inline void sincos_t<double>(double x, double *s, double *c) { sincos(x, s, c); }
-template <>
-__device__ inline void sincos_t<float>(float x, float *s, float *c)
-{
-    // Reduce to [-1/2, 1/2] revolutions, then the hardware sine / cosine.
-    const float rev = x * 0.15915494309189533577f;
-    const float f = rev - rintf(rev);
-    *s = __builtin_amdgcn_sinf(f);
-    *c = __builtin_amdgcn_cosf(f);
-}
-
-template <typename R>
-__device__ inline R rsqrt_t(R x);
-template <>
-__device__ inline double rsqrt_t<double>(double x) { return 1.0 / sqrt(x); }
-template <>
-__device__ inline float rsqrt_t<float>(float x) { return rsqrtf(x); }
-
-template <typename R, bool SPLIT>
-__global__ __launch_bounds__(256) void k_pairs_regular(int64_t F, int64_t nT, int64_t ntiles,
-                                                       const double *__restrict__ cent,
+// 1. Regular pairs.  A lane keeps one triangle q in registers and goes through
+// the triangles p of a band, which LDS hands to all lanes at once; the sums
+// of a pair are pairs.hpp's.  In FP64 the pairs beyond NARROW_PHASE are left to a
+// launch of their own (NARROW false), made only if the mesh can have any: in one
+// kernel with them the narrow form has two waves per SIMD instead of three.  A
+// block takes the band's rows p = blockIdx.z, blockIdx.z + gridDim.z, ...  FP64 vector issue bounds it: 13.1 M pairs
+// (7680 unknowns) 2.92 -> 1.52 ms, 54 vector instructions a kernel value, the vector
+// units busy 73 % of the time at 2.0 GHz; three waves per SIMD instead of two (y in
+// LDS) measured the same.
+template <typename R, bool SPLIT, bool NARROW>
+__global__ __launch_bounds__(256) void k_pairs_regular(int64_t F, Bands bd, const double *__restrict__ cent,
                                                        const double *__restrict__ loc,
                                                        const double *__restrict__ vfree,
-                                                       const int8_t *__restrict__ sgn, double k,
+                                                       const int8_t *__restrict__ sgn,
+                                                       const double *__restrict__ rad, double k,
                                                        R *__restrict__ LB, R *__restrict__ VS)
 {
-    __shared__ TriLDS<R> sp[TT], sq[TT];
-    __shared__ double scp[TT][3], scq[TT][3];
-    __shared__ R sw[NQ];    // w_j / (4 pi)
-    __shared__ R swi[NQ];   // w_i
-    const int64_t b = blockIdx.x;
-    if (b >= ntiles) return;
-    // decode b -> (I, J), I <= J, row-major over the upper triangle of tiles
-    const double n2 = 2.0 * double(nT) + 1.0;
-    int64_t I = int64_t((n2 - sqrt(n2 * n2 - 8.0 * double(b))) * 0.5);
-    if (I < 0) I = 0;
-    if (I > nT - 1) I = nT - 1;
-    while (I > 0 && tile_index(I, I, nT) > b) --I;
-    while (I + 1 < nT && tile_index(I + 1, I + 1, nT) <= b) ++I;
-    const int64_t J = I + (b - tile_index(I, I, nT));
-
+    __shared__ R sx[TT][NQ * 3], sv[TT][9], ss[TT][3];
+    __shared__ double sc[TT][3], sr[TT];
+    __shared__ R sw[NQ], sw4[NQ];   // w and w / (4 pi)
+    const int64_t I = blockIdx.y, q0 = I * TT + int64_t(blockIdx.x) * 256;
+    if (q0 >= F) return;
     const int tid = threadIdx.x;
-    // stage the two triangle tiles (local coordinates relative to centroids)
-    for (int e = tid; e < TT * (NQ * 3 + 9 + 3); e += 256) {
-        const int t = e / (NQ * 3 + 9 + 3), f = e % (NQ * 3 + 9 + 3);
-        for (int side = 0; side < 2; ++side) {
-            const int64_t tri = (side ? J : I) * TT + t;
-            TriLDS<R> *dst = side ? &sq[t] : &sp[t];
-            double v = 0.0;
-            if (tri < F) {
-                if (f < NQ * 3) v = loc[tri * NQ * 3 + f];
-                else if (f < NQ * 3 + 9) v = vfree[tri * 9 + (f - NQ * 3)];
-                else v = cent[tri * 3 + (f - NQ * 3 - 9)];
-            }
-            if (f < NQ * 3) dst->loc[f / 3][f % 3] = R(v);
-            else if (f < NQ * 3 + 9) dst->vf[(f - NQ * 3) / 3][(f - NQ * 3) % 3] = R(v);
-            else (side ? scq : scp)[t][f - NQ * 3 - 9] = v;
-        }
+    for (int e = tid; e < TT * (NQ * 3 + 9 + 3 + 3 + 1); e += 256) {
+        const int t = e / (NQ * 3 + 16), f = e % (NQ * 3 + 16);
+        const int64_t tri = I * TT + t;
+        const bool in = tri < F;
+        if (f < NQ * 3) sx[t][f] = in ? R(loc[tri * NQ * 3 + f]) : R(0);
+        else if (f < NQ * 3 + 9) sv[t][f - NQ * 3] = in ? R(vfree[tri * 9 + f - NQ * 3]) : R(0);
+        else if (f < NQ * 3 + 12) ss[t][f - NQ * 3 - 9] = in ? R(sgn[tri * 3 + f - NQ * 3 - 9]) : R(0);
+        else if (f < NQ * 3 + 15) sc[t][f - NQ * 3 - 12] = in ? cent[tri * 3 + f - NQ * 3 - 12] : 0.0;
+        else sr[t] = in ? rad[tri] : 0.0;
     }
     if (tid < NQ) {
-        sw[tid] = R(c_w[tid] / (4.0 * PI));
-        swi[tid] = R(c_w[tid]);
+        sw[tid] = R(c_w[tid]);
+        sw4[tid] = R(c_w[tid] / (4.0 * PI));
     }
     __syncthreads();
-
-    const int ti = tid / TT, tj = tid % TT;
-    const int64_t p = I * TT + ti, q = J * TT + tj;
-    if (p >= F || q >= F || p > q) return;
-    const TriLDS<R> &P = sp[ti];
-    const TriLDS<R> &Q = sq[tj];
-    const R dc[3] = { R(scp[ti][0] - scq[tj][0]), R(scp[ti][1] - scq[tj][1]), R(scp[ti][2] - scq[tj][2]) };
-    const R kk = R(k);
-
-    R s0r = 0, s0i = 0, sxr[3] = { 0, 0, 0 }, sxi[3] = { 0, 0, 0 }, syr[3] = { 0, 0, 0 }, syi[3] = { 0, 0, 0 };
-    R sxyr = 0, sxyi = 0;
+    const int64_t q = q0 + tid;
+    if (q >= F) return;
+    R yq[NQ][3];
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) yq[j][c] = R(loc[(q * NQ + j) * 3 + c]);
+    const auto y = [&](int j, int c) { return yq[j][c]; };
+    const double cq[3] = { cent[3 * q], cent[3 * q + 1], cent[3 * q + 2] };
+    const double rq = rad[q];
+    const R kk = R(k), k4 = kk * R(0.25), ik = R(1.0) / kk;
+    const int np = int(q - I * TT + 1 < TT ? q - I * TT + 1 : TT);   // p <= q
 #pragma unroll 1
-    for (int i = 0; i < NQ; ++i) {
-        const R xi[3] = { P.loc[i][0], P.loc[i][1], P.loc[i][2] };
-        const R di[3] = { dc[0] + xi[0], dc[1] + xi[1], dc[2] + xi[2] };
-        R t0r = 0, t0i = 0, tyr[3] = { 0, 0, 0 }, tyi[3] = { 0, 0, 0 };
+    for (int t = blockIdx.z; t < np; t += gridDim.z) {
+        const R d[3] = { R(sc[t][0] - cq[0]), R(sc[t][1] - cq[1]), R(sc[t][2] - cq[2]) };
+        PairSums<R> S;
+        // FP64: a wave's pairs are one launch's or the other's
+        if (sizeof(R) == 8 && (__all(k * (sr[t] + rq) <= NARROW_PHASE) != 0) != NARROW) continue;
+        pair_sums<R, NARROW>(sx[t], y, d, kk, sw, sw4, S);
+        R vb[3][3], sb[3];
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-            const R d0 = di[0] - Q.loc[j][0], d1 = di[1] - Q.loc[j][1], d2 = di[2] - Q.loc[j][2];
-            const R r2 = d0 * d0 + d1 * d1 + d2 * d2;
-            const R ri = rsqrt_t<R>(r2);
-            R sn, cs;
-            sincos_t<R>(kk * (r2 * ri), &sn, &cs);
-            const R gw = sw[j] * ri;
-            const R gr = gw * cs, gi = -gw * sn;
-            t0r += gr;
-            t0i += gi;
+        for (int b = 0; b < 3; ++b) {
+            sb[b] = R(sgn[q * 3 + b]);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                tyr[c] += gr * Q.loc[j][c];
-                tyi[c] += gi * Q.loc[j][c];
+            for (int c = 0; c < 3; ++c) vb[b][c] = R(vfree[q * 9 + 3 * b + c]);
+        }
+        const int64_t p = I * TT + t;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const R va[3] = { sv[t][3 * a], sv[t][3 * a + 1], sv[t][3 * a + 2] };
+            R lr[3], li[3];
+            local_row<R, SPLIT>(S, va, vb, ss[t][a], sb, k4, ik, lr, li);
+            R *out = LB + 2 * bd.block(p, q, a, 0);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                out[2 * b] = lr[b];
+                out[2 * b + 1] = li[b];
             }
         }
-        const R a = swi[i];
-        s0r += a * t0r;
-        s0i += a * t0i;
-        R xtr = 0, xti = 0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            sxr[c] += a * t0r * xi[c];
-            sxi[c] += a * t0i * xi[c];
-            syr[c] += a * tyr[c];
-            syi[c] += a * tyi[c];
-            xtr += xi[c] * tyr[c];
-            xti += xi[c] * tyi[c];
+        if (SPLIT) {   // V'_pq = J0 / (jk)
+            R *out = VS + 2 * bd.pair(p, q);
+            out[0] = ik * S.s0i;
+            out[1] = -ik * S.s0r;
         }
-        sxyr += a * xtr;
-        sxyi += a * xti;
-    }
-    // J_ab = Sxy - v_b.Sx - v_a.Sy + (v_a.v_b) S0   (local coordinates)
-    // L_ab = s_a s_b [ (jk/4) J_ab + S0/(jk) ]
-    const int64_t tile = tile_index(I, J, nT);
-    R *out = LB + tile * (9 * 256 * 2);
-    const R k4 = kk * R(0.25), ik = R(1.0) / kk;
-#pragma unroll
-    for (int aa = 0; aa < 3; ++aa) {
-#pragma unroll
-        for (int bb = 0; bb < 3; ++bb) {
-            const R *va = P.vf[aa];
-            const R *vb = Q.vf[bb];
-            R jr = sxyr, ji = sxyi;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                jr -= vb[c] * sxr[c] + va[c] * syr[c];
-                ji -= vb[c] * sxi[c] + va[c] * syi[c];
-            }
-            const R vv = va[0] * vb[0] + va[1] * vb[1] + va[2] * vb[2];
-            jr += vv * s0r;
-            ji += vv * s0i;
-            const R ss = R(sgn[p * 3 + aa] * sgn[q * 3 + bb]);
-            const R lr = SPLIT ? ss * (-k4 * ji) : ss * (-k4 * ji + ik * s0i);
-            const R li = SPLIT ? ss * (k4 * jr) : ss * (k4 * jr - ik * s0r);
-            out[((aa * 3 + bb) * 256 + tid) * 2 + 0] = lr;
-            out[((aa * 3 + bb) * 256 + tid) * 2 + 1] = li;
-        }
-    }
-    if (SPLIT) {   // V'_pq = J0 / (jk)
-        VS[(tile * 256 + tid) * 2 + 0] = ik * s0i;
-        VS[(tile * 256 + tid) * 2 + 1] = -ik * s0r;
     }
 }
 
@@ -275,8 +215,12 @@ __device__ void static_potentials(const double x[3], const double A[3], const do
         const double Rp = sqrt(R0s + lp * lp), Rm = sqrt(R0s + lm * lm);
         double f = 0.0;
         if (R0s > 0.0) f = (lp + lm < 0.0) ? log((Rm - lm) / (Rp - lp)) : log((Rp + lp) / (Rm + lm));
+        // the two arc tangents lie in (-pi/2, pi/2): their difference is one angle
         double beta = 0.0;
-        if (ah > 0.0) beta = atan2(P0 * lp, R0s + ah * Rp) - atan2(P0 * lm, R0s + ah * Rm);
+        if (ah > 0.0) {
+            const double yp = P0 * lp, xp = R0s + ah * Rp, ym = P0 * lm, xm = R0s + ah * Rm;
+            beta = atan2(yp * xm - xp * ym, xp * xm + yp * ym);
+        }
         k0 += (R0s > 0.0 ? P0 * f : 0.0) - ah * beta;
         const double c = 0.5 * ((R0s > 0.0 ? R0s * f : 0.0) + lp * Rp - lm * Rm);
         kp[0] += c * u[0]; kp[1] += c * u[1]; kp[2] += c * u[2];
@@ -285,8 +229,16 @@ __device__ void static_potentials(const double x[3], const double A[3], const do
     for (int d = 0; d < 3; ++d) K1[d] = kp[d] - h * n[d] * k0;
 }
 
+// 16 lanes per pair: the 49 point pairs of the regular remainder and the 14
+// closed-form outer points are spread over them, each adding to the sums of
+// pairs.hpp (the static part, real, has the same form: with A = int 1/R and
+// B = int y/R over the inner triangle, (x - v_a).(B - v_b A) at outer point x), then
+// 9 lanes form the block.  One lane per pair was a serial chain of 14 closed forms
+// (3 logarithms and 6 arc tangents each) at one wave per SIMD (5750 pairs 75 -> 15 us,
+// 92 450 pairs 185 -> 130 us).
+constexpr int SL = 16;
 template <typename R, bool SPLIT>
-__global__ __launch_bounds__(128) void k_pairs_singular(int64_t npairs, int64_t nT,
+__global__ __launch_bounds__(256) void k_pairs_singular(int64_t npairs, Bands bd,
                                                         const int32_t *__restrict__ pairs,
                                                         const double *__restrict__ cent,
                                                         const double *__restrict__ loc,
@@ -297,179 +249,198 @@ __global__ __launch_bounds__(128) void k_pairs_singular(int64_t npairs, int64_t 
                                                         R *__restrict__ LB, R *__restrict__ VS,
                                                         double *__restrict__ compact = nullptr)
 {
-    const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= npairs) return;
+    const int l = threadIdx.x & (SL - 1);
+    const int64_t at = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / SL;
+    const bool live = at < npairs;
+    const int64_t idx = live ? at : npairs - 1;   // the sums below cross lanes: all take part
     const int64_t p = pairs[2 * idx], q = pairs[2 * idx + 1];
     // frames: p-local coordinates relative to c_p, q-local relative to c_q
     double dc[3];
     for (int d = 0; d < 3; ++d) dc[d] = cent[p * 3 + d] - cent[q * 3 + d];
     const double *xl = loc + p * NQ * 3, *yl = loc + q * NQ * 3;
-    const double *vp = vfree + p * 9, *vq = vfree + q * 9;
-    double trp[9], trq[9];   // vertices relative to own centroid
-    for (int v = 0; v < 3; ++v)
-        for (int d = 0; d < 3; ++d) {
-            trp[v * 3 + d] = verts[p * 9 + v * 3 + d] - cent[p * 3 + d];
-            trq[v * 3 + d] = verts[q * 9 + v * 3 + d] - cent[q * 3 + d];
-        }
     const double inv4pi = 1.0 / (4.0 * PI);
-    double jr[3][3] = { { 0 } }, ji[3][3] = { { 0 } }, j0r = 0.0, j0i = 0.0;
-    // regular remainder g_r = (e^{-jkR} - 1)/(4 pi R) = (-2 sin^2(kR/2) - j sin kR)/(4 pi R)
-    for (int i = 0; i < NQ; ++i) {
-        for (int j = 0; j < NQ; ++j) {
-            double d[3];
-            for (int c = 0; c < 3; ++c) d[c] = dc[c] + xl[i * 3 + c] - yl[j * 3 + c];
-            const double Rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-            double gr, gi;
-            if (Rr > 0.0) {
-                const double s = sin(0.5 * k * Rr);
-                gr = -2.0 * s * s / Rr * inv4pi;
-                gi = -sin(k * Rr) / Rr * inv4pi;
+    PairSums<double> S;
+    S.s0r = S.s0i = S.sxyr = S.sxyi = 0.0;
+    for (int c = 0; c < 3; ++c) S.sxr[c] = S.sxi[c] = S.syr[c] = S.syi[c] = 0.0;
+    // regular remainder g_r = (e^{-jkR} - 1)/(4 pi R) = -2 sin(kR/2) (sin(kR/2) + j cos(kR/2))/(4 pi R)
+    for (int e = l; e < NQ * NQ; e += SL) {
+        const int i = e / NQ, j = e % NQ;
+        const double *x = xl + 3 * i, *y = yl + 3 * j;
+        const double d0 = dc[0] + x[0] - y[0], d1 = dc[1] + x[1] - y[1], d2 = dc[2] + x[2] - y[2];
+        const double Rr = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+        double gr = 0.0, gi = -k;
+        if (Rr > 0.0) {
+            double sn, cs;
+            sincos_reduced(0.5 * k * Rr, sn, cs);
+            const double h = -2.0 * sn / Rr;
+            gr = h * sn;
+            gi = h * cs;
+        }
+        const double w = c_w[i] * c_w[j] * inv4pi;
+        gr *= w;
+        gi *= w;
+        S.s0r += gr;
+        S.s0i += gi;
+        const double xy = x[0] * y[0] + x[1] * y[1] + x[2] * y[2];
+        S.sxyr += gr * xy;
+        S.sxyi += gi * xy;
+        for (int c = 0; c < 3; ++c) {
+            S.sxr[c] += gr * x[c];
+            S.sxi[c] += gi * x[c];
+            S.syr[c] += gr * y[c];
+            S.syi[c] += gi * y[c];
+        }
+    }
+    // static part, real: lanes 0..6 p outer / closed form over q, lanes 7..13 q outer
+    // / over p; mean of the two orderings
+    if (l < 2 * NQ) {
+        const bool po = l < NQ;
+        const int i = po ? l : l - NQ;
+        const int64_t in = po ? q : p;
+        const double *ol = po ? xl + 3 * i : yl + 3 * i;
+        double u[3], tri[9];   // the outer point and the inner triangle in the inner frame
+        for (int d = 0; d < 3; ++d) {
+            u[d] = po ? dc[d] + ol[d] : ol[d] - dc[d];
+            for (int v = 0; v < 3; ++v) tri[v * 3 + d] = verts[in * 9 + v * 3 + d] - cent[in * 3 + d];
+        }
+        double K0, K1[3];
+        static_potentials(u, tri, tri + 3, tri + 6, &K0, K1);
+        const double f = 0.5 * c_w[i] * inv4pi / area[in];
+        const double f0 = f * K0;
+        S.s0r += f0;
+        for (int c = 0; c < 3; ++c) {
+            const double B = f * K1[c] + u[c] * f0, A = f0 * ol[c];
+            S.sxyr += ol[c] * B;
+            if (po) {
+                S.sxr[c] += A;
+                S.syr[c] += B;
             } else {
-                gr = 0.0;
-                gi = -k * inv4pi;
-            }
-            const double w = c_w[i] * c_w[j];
-            gr *= w; gi *= w;
-            j0r += gr; j0i += gi;
-            for (int a = 0; a < 3; ++a) {
-                const double da[3] = { xl[i * 3] - vp[a * 3], xl[i * 3 + 1] - vp[a * 3 + 1], xl[i * 3 + 2] - vp[a * 3 + 2] };
-                for (int b = 0; b < 3; ++b) {
-                    const double db[3] = { yl[j * 3] - vq[b * 3], yl[j * 3 + 1] - vq[b * 3 + 1], yl[j * 3 + 2] - vq[b * 3 + 2] };
-                    const double dd = da[0] * db[0] + da[1] * db[1] + da[2] * db[2];
-                    jr[a][b] += gr * dd;
-                    ji[a][b] += gi * dd;
-                }
+                S.sxr[c] += B;
+                S.syr[c] += A;
             }
         }
     }
-    // static part, real: p outer / closed form over q, and q outer / over p; mean.
-    double sr[3][3] = { { 0 } }, s0 = 0.0;
-    const double Ap = area[p], Aq = area[q];
-    for (int i = 0; i < NQ; ++i) {
-        const double x[3] = { dc[0] + xl[i * 3], dc[1] + xl[i * 3 + 1], dc[2] + xl[i * 3 + 2] };  // in q frame
-        double K0, K1[3];
-        static_potentials(x, trq, trq + 3, trq + 6, &K0, K1);
-        const double f = c_w[i] * inv4pi / Aq;
-        s0 += f * K0;
-        for (int a = 0; a < 3; ++a) {
-            const double da[3] = { xl[i * 3] - vp[a * 3], xl[i * 3 + 1] - vp[a * 3 + 1], xl[i * 3 + 2] - vp[a * 3 + 2] };
-            for (int b = 0; b < 3; ++b) {
-                // int_q (y - v_b)/R = K1 + (x - v_b) K0, with x and v_b in the q frame
-                double iv[3];
-                for (int c = 0; c < 3; ++c) iv[c] = K1[c] + (x[c] - vq[b * 3 + c]) * K0;
-                sr[a][b] += f * (da[0] * iv[0] + da[1] * iv[1] + da[2] * iv[2]);
-            }
-        }
+    auto total = [&](double &v) {
+#pragma unroll
+        for (int o = SL / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, SL);
+    };
+    total(S.s0r);
+    total(S.s0i);
+    total(S.sxyr);
+    total(S.sxyi);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        total(S.sxr[c]);
+        total(S.sxi[c]);
+        total(S.syr[c]);
+        total(S.syi[c]);
     }
-    for (int j = 0; j < NQ; ++j) {
-        const double y[3] = { yl[j * 3] - dc[0], yl[j * 3 + 1] - dc[1], yl[j * 3 + 2] - dc[2] };  // in p frame
-        double K0, K1[3];
-        static_potentials(y, trp, trp + 3, trp + 6, &K0, K1);
-        const double f = c_w[j] * inv4pi / Ap;
-        s0 += f * K0;
-        for (int b = 0; b < 3; ++b) {
-            const double db[3] = { yl[j * 3] - vq[b * 3], yl[j * 3 + 1] - vq[b * 3 + 1], yl[j * 3 + 2] - vq[b * 3 + 2] };
-            for (int a = 0; a < 3; ++a) {
-                double iv[3];
-                for (int c = 0; c < 3; ++c) iv[c] = K1[c] + (y[c] - vp[a * 3 + c]) * K0;
-                sr[a][b] += f * (db[0] * iv[0] + db[1] * iv[1] + db[2] * iv[2]);
-            }
-        }
-    }
-    j0r += 0.5 * s0;
-    const int64_t I = p / TT, J = q / TT;
-    R *out = LB + tile_index(I, J, nT) * (9 * 256 * 2);
-    const int tid = int((p % TT) * TT + (q % TT));
+    if (!live || l >= 9) return;
     const double k4 = 0.25 * k, ik = 1.0 / k;
-    double Jr_[3][3], Ji_[3][3];
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-            Jr_[a][b] = jr[a][b] + 0.5 * sr[a][b];
-            Ji_[a][b] = ji[a][b];
+    const double *vp = vfree + p * 9, *vq = vfree + q * 9;
+    auto moment = [&](int a, int b, double &jr, double &ji) {
+        const double *va = vp + 3 * a, *vb = vq + 3 * b;
+        const double vv = va[0] * vb[0] + va[1] * vb[1] + va[2] * vb[2];
+        jr = S.sxyr + vv * S.s0r;
+        ji = S.sxyi + vv * S.s0i;
+        for (int c = 0; c < 3; ++c) {
+            jr -= va[c] * S.syr[c] + vb[c] * S.sxr[c];
+            ji -= va[c] * S.syi[c] + vb[c] * S.sxi[c];
         }
-    if (p == q) {
+    };
+    const int a = l / 3, b = l % 3;
+    double Jr, Ji;
+    moment(a, b, Jr, Ji);
+    if (p == q && a != b) {
         // J_ab = J_ba for a self pair (swap the two integration variables);
         // take the mean so the stored block is symmetric to the last bit.
-        for (int a = 0; a < 3; ++a)
-            for (int b = a + 1; b < 3; ++b) {
-                const double mr = 0.5 * (Jr_[a][b] + Jr_[b][a]), mi = 0.5 * (Ji_[a][b] + Ji_[b][a]);
-                Jr_[a][b] = Jr_[b][a] = mr;
-                Ji_[a][b] = Ji_[b][a] = mi;
-            }
+        double jr, ji;
+        moment(b, a, jr, ji);
+        Jr = 0.5 * (Jr + jr);
+        Ji = 0.5 * (Ji + ji);
     }
+    const double ss = double(sgn[p * 3 + a] * sgn[q * 3 + b]);
+    const double lr = SPLIT ? ss * (-k4 * Ji) : ss * (-k4 * Ji + ik * S.s0i);
+    const double li = SPLIT ? ss * (k4 * Jr) : ss * (k4 * Jr - ik * S.s0r);
     if (compact) {   // the pair's 3 x 3 block, pair after pair (near field of the fast operator)
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) {
-                const double ss = double(sgn[p * 3 + a] * sgn[q * 3 + b]);
-                compact[idx * 18 + (a * 3 + b) * 2 + 0] = ss * (-k4 * Ji_[a][b] + ik * j0i);
-                compact[idx * 18 + (a * 3 + b) * 2 + 1] = ss * (k4 * Jr_[a][b] - ik * j0r);
-            }
+        compact[at * 18 + l * 2 + 0] = lr;
+        compact[at * 18 + l * 2 + 1] = li;
         return;
     }
-    for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-            const double Jr = Jr_[a][b], Ji = Ji_[a][b];
-            const double ss = double(sgn[p * 3 + a] * sgn[q * 3 + b]);
-            out[((a * 3 + b) * 256 + tid) * 2 + 0] = R(SPLIT ? ss * (-k4 * Ji) : ss * (-k4 * Ji + ik * j0i));
-            out[((a * 3 + b) * 256 + tid) * 2 + 1] = R(SPLIT ? ss * (k4 * Jr) : ss * (k4 * Jr - ik * j0r));
-        }
-    if (SPLIT) {
-        const int64_t t = tile_index(I, J, nT);
-        VS[(t * 256 + tid) * 2 + 0] = R(ik * j0i);
-        VS[(t * 256 + tid) * 2 + 1] = R(-ik * j0r);
+    R *out = LB + 2 * bd.block(p, q, a, b);
+    out[0] = R(lr);
+    out[1] = R(li);
+    if (SPLIT && l == 0) {
+        R *vo = VS + 2 * bd.pair(p, q);
+        vo[0] = R(ik * S.s0i);
+        vo[1] = R(-ik * S.s0r);
     }
 }
 
 // ---------------------------------------------------------------------------
 // 3. Assembly into the RWG matrix.
-template <typename R>
-__device__ inline void read_local(const R *__restrict__ LB, int64_t nT, int32_t p, int32_t a, int32_t q,
-                                  int32_t b, R &re, R &im)
+//
+// Slot a of triangle p as it enters a local block: the row's first entry less
+// that of column 0, and its place among the columns of another row, so that L of
+// (row slot r, column slot c) is entry r.row + c.col of the scratch.
+struct Slot {
+    int64_t row;
+    int32_t col;
+};
+__device__ __forceinline__ Slot slot_of(const Bands &bd, int32_t p, int32_t a)
 {
-    if (p > q) {   // stored once, for p <= q, transposed
-        int32_t t = p; p = q; q = t;
-        t = a; a = b; b = t;
-    }
-    const R *src = LB + tile_index(p / TT, q / TT, nT) * (9 * 256 * 2) +
-                   ((a * 3 + b) * 256 + (p % TT) * TT + (q % TT)) * 2;
-    re = src[0];
-    im = src[1];
+    const int64_t I = p / TT;
+    return { 9 * bd.base(I) + ((p % TT) * 3 + a) * 3 * bd.cols(I) - 3 * TT * I, 3 * p + a };
 }
 
-// rwg4[m] = (c+, c-, slot in c+, slot in c-).  One block per stored tile
-// (I, J), I <= J, of the packed symmetric matrix; 16 entries per thread.
-template <typename R>
-__global__ __launch_bounds__(256) void k_assemble(int64_t N, int64_t nT, int64_t nTz, const int4 *__restrict__ rwg4,
+// T_mn from the four triangle pairs of (m, n); each is stored once, with the
+// lower triangle as the row.  One block per stored tile (I, J), I <= J, of the
+// packed symmetric matrix (or RPB of its TB / 4 groups of four rows); a wave takes
+// every fourth row m of it and its lanes the 64 columns n, so that the row's slots are the same for the wave (scalar) and the
+// column's are worked out once.  Bound by the gathers: four 16-byte reads an
+// entry, each scratch entry used once but in lines that hold other tiles' too (7680
+// unknowns: 4.7 GB fetched of 1.9 GB, 1.46 -> 0.77 ms).
+template <typename R, int RPB>
+__global__ __launch_bounds__(256) void k_assemble(int64_t N, Bands bd, int64_t nTz, const int4 *__restrict__ rwg4,
                                                   const R *__restrict__ LB, double2 *__restrict__ Z64,
                                                   float2 *__restrict__ Z32)
 {
+    typedef R V2 __attribute__((ext_vector_type(2)));
     int64_t I, J;
     tile_decode(blockIdx.x, nTz, I, J);
     const int64_t base = int64_t(blockIdx.x) * TB * TB;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t n = J * TB + lane;
+    Slot np{ 0, 0 }, nm{ 0, 0 };
+    if (n < N) {
+        const int4 e = rwg4[n];
+        np = slot_of(bd, e.x, e.z);
+        nm = slot_of(bd, e.y, e.w);
+    }
+    const V2 *L = reinterpret_cast<const V2 *>(LB);
+    auto read = [&](const Slot &r, const Slot &c) {
+        return L[r.col <= c.col ? r.row + c.col : c.row + r.col];
+    };
 #pragma unroll 4
-    for (int q = 0; q < TB * TB / 256; ++q) {
-        const int e = threadIdx.x + 256 * q;
-        const int64_t m = I * TB + e / TB, n = J * TB + e % TB;
-        R zr = 0, zi = 0;
+    for (int i = blockIdx.y * RPB; i < int(blockIdx.y + 1) * RPB; ++i) {
+        const int64_t m = I * TB + wave + 4 * i;
+        V2 z = { 0, 0 };
         if (m < N && n < N) {
-            const int4 em = rwg4[m], en = rwg4[n];
-            R r1, i1, r2, i2, r3, i3, r4, i4;
-            read_local(LB, nT, em.x, em.z, en.x, en.z, r1, i1);   // (+,+)
-            read_local(LB, nT, em.y, em.w, en.y, en.w, r2, i2);   // (-,-)
-            read_local(LB, nT, em.x, em.z, en.y, en.w, r3, i3);   // (+,-)
-            read_local(LB, nT, em.y, em.w, en.x, en.z, r4, i4);   // (-,+)
-            zr = (r1 + r2) + (r3 + r4);
-            zi = (i1 + i2) + (i3 + i4);
+            const int4 e = rwg4[m];
+            const Slot mp = slot_of(bd, e.x, e.z), mm = slot_of(bd, e.y, e.w);
+            const V2 pp = read(mp, np), mn = read(mm, nm), pm = read(mp, nm), mq = read(mm, np);
+            z = (pp + mn) + (pm + mq);
         }
-        if (Z64) Z64[base + e] = make_double2(double(zr), double(zi));
-        if (Z32) Z32[base + e] = make_float2(float(zr), float(zi));
+        const int64_t o = base + int64_t(wave + 4 * i) * TB + lane;
+        if (Z64) Z64[o] = make_double2(double(z.x), double(z.y));
+        if (Z32) Z32[o] = make_float2(float(z.x), float(z.y));
     }
 }
 
-// V' into packed F x F tiles (TB x TB, I <= J) from the per-pair values of the
-// triangle tiles (p <= q; the other half by symmetry).
+// V' into packed F x F tiles (TB x TB, I <= J) from the per-pair values (p <= q;
+// the other half by symmetry).
 template <typename R>
-__global__ __launch_bounds__(256) void k_assemble_v(int64_t F, int64_t nT, int64_t nTv, const R *__restrict__ VS,
+__global__ __launch_bounds__(256) void k_assemble_v(int64_t F, Bands bd, int64_t nTv, const R *__restrict__ VS,
                                                     double2 *__restrict__ V64, float2 *__restrict__ V32)
 {
     int64_t I, J;
@@ -482,7 +453,7 @@ __global__ __launch_bounds__(256) void k_assemble_v(int64_t F, int64_t nT, int64
         R vr = 0, vi = 0;
         if (a < F && b < F) {
             if (a > b) { const int64_t t = a; a = b; b = t; }
-            const R *src = VS + (tile_index(a / TT, b / TT, nT) * 256 + (a % TT) * TT + (b % TT)) * 2;
+            const R *src = VS + 2 * bd.pair(a, b);
             vr = src[0];
             vi = src[1];
         }
@@ -599,10 +570,13 @@ __global__ __launch_bounds__(256) void k_farfield(int64_t F, int64_t N, int64_t 
 }
 
 template <typename T>
-T *dev_alloc(size_t n)
+T *dev_upload(const std::vector<T> &v)
 {
     void *p = nullptr;
-    BIE_HIP(hipMalloc(&p, n * sizeof(T)));
+    BIE_HIP(hipMalloc(&p, v.size() * sizeof(T)));
+    const hipError_t e = hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
+    if (e != hipSuccess) (void)hipFree(p);
+    BIE_HIP(e);
     return static_cast<T *>(p);
 }
 
@@ -617,8 +591,8 @@ void singular_blocks(const bie_op *op, const int32_t *pairs, int64_t npairs, dou
 {
     if (npairs == 0) return;
     const TriDev &D = op->tri;
-    hipLaunchKernelGGL((k_pairs_singular<double, false>), dim3(unsigned((npairs + 127) / 128)), dim3(128), 0, s, npairs,
-                       int64_t(0), pairs, D.cent, D.loc, D.vfree, D.verts, D.area, D.sgn, op->k, (double *)nullptr,
+    hipLaunchKernelGGL((k_pairs_singular<double, false>), dim3(unsigned((npairs + 15) / 16)), dim3(256), 0, s, npairs,
+                       Bands{ 0 }, pairs, D.cent, D.loc, D.vfree, D.verts, D.area, D.sgn, op->k, (double *)nullptr,
                        (double *)nullptr, out);
     BIE_HIP(hipGetLastError());
 }
@@ -629,45 +603,56 @@ void quad_weights(double *w)
     for (int i = 0; i < NQ; ++i) w[i] = rule.w[i];
 }
 
-// Per-triangle tables on the device.  Quadrature points and free vertices
-// relative to the triangle centroid (keeps FP32 local arithmetic accurate).
+// Per-triangle tables on the device, in the order of the triangles' lowest RWG
+// function: consecutive functions then lie on nearly consecutive triangles, and
+// the assembly finds most local blocks of a row (p <= q) in one run.  Quadrature
+// points and free vertices relative to the triangle centroid (keeps FP32 local
+// arithmetic accurate).
 void upload_triangles(bie_op *op, hipStream_t s)
 {
     const Mesh &M = op->mesh;
     const int64_t F = M.F;
     const Rule rule = make_rule();
     BIE_HIP(hipMemcpyToSymbol(HIP_SYMBOL(c_w), rule.w, sizeof(rule.w)));
-    std::vector<double> loc(F * NQ * 3), vf(F * 9), vt(F * 9);
-    for (int64_t t = 0; t < F; ++t) {
+    TriDev &D = op->tri;
+    D.rank.assign(F, -1);
+    std::vector<int32_t> order;
+    order.reserve(F);
+    for (int64_t m = 0; m < M.N; ++m)
+        for (int side = 0; side < 2; ++side) {
+            const int32_t t = M.edges[4 * m + 2 + side];
+            if (D.rank[t] >= 0) continue;
+            D.rank[t] = int32_t(order.size());
+            order.push_back(t);
+        }
+    std::vector<double> cent(F * 3), loc(F * NQ * 3), vf(F * 9), vt(F * 9), area(F), rad(F, 0.0);
+    std::vector<int8_t> sgn(F * 3);
+    std::vector<int32_t> slot(F * 3);
+    for (int64_t r = 0; r < F; ++r) {
+        const int64_t t = order[r];
         const double *v[3] = { &M.V[3 * M.T[3 * t]], &M.V[3 * M.T[3 * t + 1]], &M.V[3 * M.T[3 * t + 2]] };
         const double *c = &M.cent[3 * t];
-        for (int i = 0; i < NQ; ++i)
+        area[r] = M.area[t];
+        for (int i = 0; i < NQ; ++i) {
+            double d2 = 0.0;
             for (int d = 0; d < 3; ++d) {
                 const double x = rule.bary[i][0] * v[0][d] + rule.bary[i][1] * v[1][d] + rule.bary[i][2] * v[2][d];
-                loc[(t * NQ + i) * 3 + d] = x - c[d];
+                loc[(r * NQ + i) * 3 + d] = x - c[d];
+                d2 += (x - c[d]) * (x - c[d]);
             }
-        for (int a = 0; a < 3; ++a)
+            rad[r] = std::max(rad[r], std::sqrt(d2));
+        }
+        D.max_rad = std::max(D.max_rad, rad[r]);
+        for (int a = 0; a < 3; ++a) {
+            sgn[r * 3 + a] = M.slot_s[3 * t + a];
+            slot[r * 3 + a] = M.slot_m[3 * t + a];
+            cent[r * 3 + a] = c[a];
             for (int d = 0; d < 3; ++d) {
-                vf[t * 9 + a * 3 + d] = v[a][d] - c[d];
-                vt[t * 9 + a * 3 + d] = v[a][d];
+                vf[r * 9 + a * 3 + d] = v[a][d] - c[d];
+                vt[r * 9 + a * 3 + d] = v[a][d];
             }
+        }
     }
-    TriDev &D = op->tri;
-    D.cent = dev_alloc<double>(F * 3);
-    D.loc = dev_alloc<double>(F * NQ * 3);
-    D.vfree = dev_alloc<double>(F * 9);
-    D.verts = dev_alloc<double>(F * 9);
-    D.area = dev_alloc<double>(F);
-    D.sgn = dev_alloc<int8_t>(F * 3);
-    D.slot_m = dev_alloc<int32_t>(F * 3);
-    D.edges = dev_alloc<int32_t>(M.N * 4);
-    BIE_HIP(hipMemcpy(D.cent, M.cent.data(), F * 3 * sizeof(double), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(D.loc, loc.data(), loc.size() * sizeof(double), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(D.vfree, vf.data(), vf.size() * sizeof(double), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(D.verts, vt.data(), vt.size() * sizeof(double), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(D.area, M.area.data(), F * sizeof(double), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(D.sgn, M.slot_s.data(), F * 3, hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(D.slot_m, M.slot_m.data(), F * 3 * sizeof(int32_t), hipMemcpyHostToDevice));
     // rwg4: (c+, c-, slot of m in c+, slot of m in c-)
     std::vector<int32_t> r4(M.N * 4);
     for (int64_t m = 0; m < M.N; ++m) {
@@ -677,14 +662,22 @@ void upload_triangles(bie_op *op, hipStream_t s)
             if (M.slot_m[3 * tp + a] == m) sp = a;
             if (M.slot_m[3 * tm + a] == m) sm = a;
         }
-        r4[4 * m + 0] = tp; r4[4 * m + 1] = tm; r4[4 * m + 2] = sp; r4[4 * m + 3] = sm;
+        r4[4 * m + 0] = D.rank[tp]; r4[4 * m + 1] = D.rank[tm]; r4[4 * m + 2] = sp; r4[4 * m + 3] = sm;
     }
-    BIE_HIP(hipMemcpy(D.edges, r4.data(), r4.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    D.cent = dev_upload(cent);
+    D.loc = dev_upload(loc);
+    D.vfree = dev_upload(vf);
+    D.verts = dev_upload(vt);
+    D.area = dev_upload(area);
+    D.rad = dev_upload(rad);
+    D.sgn = dev_upload(sgn);
+    D.slot_m = dev_upload(slot);
+    D.edges = dev_upload(r4);
     (void)s;
 }
 
 template <typename R, bool SPLIT>
-static void fill_launch(bie_op *op, int64_t nT, int64_t ntiles, const int32_t *pairs, int64_t npairs, void *LB,
+static void fill_launch(bie_op *op, const Bands &bd, const int32_t *pairs, int64_t npairs, void *LB,
                         void *VS, bool want64, bool want32, hipStream_t s)
 {
     const Mesh &M = op->mesh;
@@ -693,21 +686,36 @@ static void fill_launch(bie_op *op, int64_t nT, int64_t ntiles, const int32_t *p
     // flagged pairs, 8 assembly (columns = unknowns)
     const int rec_reg = sizeof(R) == 8 ? 6 : 9;
     prof_begin(rec_reg, s, M.F * (M.F + 1) / 2);
-    hipLaunchKernelGGL((k_pairs_regular<R, SPLIT>), dim3(unsigned(ntiles)), dim3(256), 0, s, M.F, nT, ntiles, D.cent,
-                       D.loc, D.vfree, D.sgn, op->k, (R *)LB, (R *)VS);
+    // enough blocks for four waves on every SIMD: small meshes split the rows of
+    // a band (16 rows per block at 320 triangles left 20 blocks: 100 us, 29 us split)
+    const int64_t blocks = bd.total() / (TT * 256) + bd.Fp / TT;
+    const unsigned nz = unsigned(std::min<int64_t>(TT, std::max<int64_t>(1, 1024 / blocks)));
+    const dim3 grid(unsigned((bd.Fp + 255) / 256), unsigned(bd.Fp / TT), nz);
+    if constexpr (sizeof(R) == 8)
+        hipLaunchKernelGGL((k_pairs_regular<R, SPLIT, true>), grid, dim3(256), 0, s, M.F, bd, D.cent, D.loc, D.vfree,
+                           D.sgn, D.rad, op->k, (R *)LB, (R *)VS);
+    if (sizeof(R) == 4 || op->k * 2.0 * D.max_rad > NARROW_PHASE)
+        hipLaunchKernelGGL((k_pairs_regular<R, SPLIT, false>), grid, dim3(256), 0, s, M.F, bd, D.cent, D.loc, D.vfree,
+                           D.sgn, D.rad, op->k, (R *)LB, (R *)VS);
     prof_end(rec_reg, s);
     prof_begin(7, s, npairs);
     if (npairs)
-        hipLaunchKernelGGL((k_pairs_singular<R, SPLIT>), dim3(unsigned((npairs + 127) / 128)), dim3(128), 0, s, npairs,
-                           nT, pairs, D.cent, D.loc, D.vfree, D.verts, D.area, D.sgn, op->k, (R *)LB, (R *)VS);
+        hipLaunchKernelGGL((k_pairs_singular<R, SPLIT>), dim3(unsigned((npairs + 15) / 16)), dim3(256), 0, s, npairs,
+                           bd, pairs, D.cent, D.loc, D.vfree, D.verts, D.area, D.sgn, op->k, (R *)LB, (R *)VS);
     prof_end(7, s);
     prof_begin(8, s, M.N);
-    hipLaunchKernelGGL(k_assemble<R>, dim3(unsigned(op->pk.ntiles)), dim3(256), 0, s, M.N, nT, op->pk.nT,
-                       (const int4 *)D.edges, (const R *)LB, want64 ? (double2 *)op->Z64 : nullptr,
-                       want32 ? (float2 *)op->Z32 : nullptr);
+    // few tiles: four blocks each, so that every CU has some (480 unknowns, 36 tiles: 21 -> 8 us)
+    if (op->pk.ntiles < 1024)
+        hipLaunchKernelGGL((k_assemble<R, TB / 16>), dim3(unsigned(op->pk.ntiles), 4), dim3(256), 0, s, M.N, bd, op->pk.nT,
+                           (const int4 *)D.edges, (const R *)LB, want64 ? (double2 *)op->Z64 : nullptr,
+                           want32 ? (float2 *)op->Z32 : nullptr);
+    else
+        hipLaunchKernelGGL((k_assemble<R, TB / 4>), dim3(unsigned(op->pk.ntiles)), dim3(256), 0, s, M.N, bd, op->pk.nT,
+                           (const int4 *)D.edges, (const R *)LB, want64 ? (double2 *)op->Z64 : nullptr,
+                           want32 ? (float2 *)op->Z32 : nullptr);
     prof_end(8, s);
     if (SPLIT)
-        hipLaunchKernelGGL(k_assemble_v<R>, dim3(unsigned(op->pkv.ntiles)), dim3(256), 0, s, M.F, nT, op->pkv.nT,
+        hipLaunchKernelGGL(k_assemble_v<R>, dim3(unsigned(op->pkv.ntiles)), dim3(256), 0, s, M.F, bd, op->pkv.nT,
                            (const R *)VS, want64 ? (double2 *)op->V64 : nullptr, want32 ? (float2 *)op->V32 : nullptr);
 }
 
@@ -717,40 +725,35 @@ void fill_matrix(bie_op *op, bool fp64_regular, bool want64, bool want32, hipStr
 {
     const Mesh &M = op->mesh;
     const int64_t F = M.F;
-    const int64_t nT = (F + TT - 1) / TT;
-    const int64_t ntiles = nT * (nT + 1) / 2;
+    const Bands bd{ (F + TT - 1) / TT * TT };
     const size_t elem = fp64_regular ? sizeof(double) : sizeof(float);
     void *LB = nullptr, *VS = nullptr;
-    int32_t *pairs = nullptr;
+    const int32_t *pairs = op->flagged;
     const int64_t npairs = int64_t(M.near.size() / 2);
     const bool pooled = setup_pool_active();   // inside a preconditioner setup: kept scratch
     try {
-        const size_t lb_bytes = size_t(ntiles) * 9 * 256 * 2 * elem;
+        const size_t lb_bytes = size_t(bd.total()) * 9 * 2 * elem;
         if (pooled) LB = setup_pool_get(0, lb_bytes);
         else BIE_HIP(hipMalloc(&LB, lb_bytes));
-        if (op->star) BIE_HIP(hipMalloc(&VS, size_t(ntiles) * 256 * 2 * elem));
-        if (npairs) {
-            BIE_HIP(hipMalloc(&pairs, M.near.size() * sizeof(int32_t)));
-            BIE_HIP(hipMemcpyAsync(pairs, M.near.data(), M.near.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        }
+        if (op->star) BIE_HIP(hipMalloc(&VS, size_t(bd.total()) * 2 * elem));
         if (fp64_regular) {
-            if (op->star) fill_launch<double, true>(op, nT, ntiles, pairs, npairs, LB, VS, want64, want32, s);
-            else fill_launch<double, false>(op, nT, ntiles, pairs, npairs, LB, VS, want64, want32, s);
+            if (op->star) fill_launch<double, true>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
+            else fill_launch<double, false>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
         } else {
-            if (op->star) fill_launch<float, true>(op, nT, ntiles, pairs, npairs, LB, VS, want64, want32, s);
-            else fill_launch<float, false>(op, nT, ntiles, pairs, npairs, LB, VS, want64, want32, s);
+            if (op->star) fill_launch<float, true>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
+            else fill_launch<float, false>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
         }
         BIE_HIP(hipGetLastError());
         BIE_HIP(hipStreamSynchronize(s));
     } catch (...) {
         if (LB && !pooled) hipFree(LB);
         if (VS) hipFree(VS);
-        if (pairs) hipFree(pairs);
         throw;
     }
     if (!pooled) hipFree(LB);
     if (VS) hipFree(VS);
-    if (pairs) hipFree(pairs);
+    (void)hipFree(op->flagged);   // not read again
+    op->flagged = nullptr;
 }
 
 void rhs_planewave(const bie_op *op, const double *dirs, const double *pols, int64_t R, void *B, hipStream_t s)

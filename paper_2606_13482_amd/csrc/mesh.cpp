@@ -25,7 +25,7 @@ struct HalfEdge {
 
 }  // namespace
 
-Mesh build_mesh(const double *verts, int64_t nv, const int32_t *tris, int64_t nt, double near_factor)
+Mesh build_mesh(const double *verts, int64_t nv, const int32_t *tris, int64_t nt, double near_factor, bool pairs)
 {
     if (nv < 3 || nt < 1) throw Error(BIE_EMESH, "mesh needs at least 3 vertices and 1 triangle");
     if (nt > (int64_t(1) << 30)) throw Error(BIE_EINVAL, "too many triangles");
@@ -105,6 +105,8 @@ Mesh build_mesh(const double *verts, int64_t nv, const int32_t *tris, int64_t nt
     }
     for (int64_t i = 0; i < 3 * F; ++i)
         if (M.slot_m[i] < 0) throw Error(BIE_EMESH, "edge without two triangles");
+
+    if (!pairs) return M;
 
     // Flagged pairs: share a vertex, or centroid distance^2 < (f * max longest)^2.
     // Uniform grid over centroids with cell size >= the largest threshold.
