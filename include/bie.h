@@ -400,20 +400,14 @@ typedef struct {
     double setup_ms;           /* wall time of bie_calderon_create */
 } bie_calderon_info;
 
-/* Builds M for an assembled operator (not star-split) with N <= 12288.  Fills
- * the refined mesh on the device (the fill's pair scratch, 1152 N^2 bytes,
- * beside the refined FP64 matrix, 288 N^2; then that matrix, its dense copy,
- * 576 N^2, and five N x N work matrices; the pair scratch stays allocated
- * through the rest of the setup only when free device memory allows, else it
- * is freed after the fill, so the peak is at most 1440 N^2 bytes when memory
- * is short), forms T_BC in column chunks, solves
- * with G for all N columns (Chebyshev iteration, CG on the normal equations if
- * it fails; the environment variable BIE_CALDERON_GRAM=cgnr selects CG on the
- * normal equations from the start, for comparison and tests) and stores M
- * (16 N^2 / 2 bytes).  The operator must outlive the preconditioner.  The
- * setup's three largest buffers are kept per device while any preconditioner
- * lives and reused by the next setup (freed when the last one is destroyed);
- * setups run one at a time.  BIE_ENUMERIC if a Gram solve misses 1e-13. */
+/* Builds M for an assembled operator (not star-split) with N <= 12288.  T_BC is
+ * integrated on the refined mesh cell pair by cell pair, without the refined mesh's
+ * matrix (work arrays: 48 N^2 bytes and 144 B per flagged refined pair), G's solves
+ * run for all N columns (Chebyshev iteration, CG on the normal equations if it fails,
+ * with 48 N^2 bytes more; the environment variable BIE_CALDERON_GRAM=cgnr selects CG
+ * on the normal equations from the start, for comparison and tests), and M is stored
+ * (16 N^2 / 2 bytes).  The operator must outlive the preconditioner.  Setups run one
+ * at a time.  BIE_ENUMERIC if a Gram solve misses 1e-13. */
 int bie_calderon_create(const bie_op *op, void *stream, bie_calderon **out);
 /* Y = M X for R complex128 vectors (device, R x N each, vectors contiguous); FP64
  * throughout (packed product below 8 vectors, the FP64 matrix cores from 8). */

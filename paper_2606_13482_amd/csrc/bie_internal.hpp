@@ -154,7 +154,6 @@ struct bie_op {
     size_t d64_part_elems = 0;
     bie::Workspace *ws = nullptr;
     void *bcache = nullptr;       // block GMRES buffers, arenas and side streams (bgmres.hip), kept between solves
-    int pooled = 0;               // Z64 and A64 belong to the preconditioner setup pool (not freed with the op)
     bie::FastOp *fast = nullptr;  // fast operator: sparse near field + multilevel far field (fast.hip)
 };
 
@@ -175,12 +174,6 @@ void tune_packed(bie_op *op, hipStream_t s);
 
 // bgmres.hip: release the block solver's cached buffers of an operator.
 void free_block_cache(bie_op *op);
-
-// calderon.hip: the large transient buffers of preconditioner setups (slot 0 the
-// fill's pair scratch, 1 the refined packed matrix, 2 its dense copy), kept
-// between setups while any preconditioner lives.  Active only inside a setup.
-bool setup_pool_active();
-void *setup_pool_get(int slot, size_t bytes);
 
 // calderon.hip: the multiplicative Calderon preconditioner.
 bie_calderon *calderon_create(const bie_op *op, hipStream_t s);
@@ -233,7 +226,7 @@ int32_t *near_list(const NearDev &nd, int64_t F, hipStream_t s);
 // fill.hip
 constexpr int QPTS = 7;               // points of the triangle rule (Radon's degree-5 rule)
 void quad_weights(double *w);         // its weights, relative to the triangle area
-void upload_triangles(bie_op *op, hipStream_t s);
+void upload_triangles(bie_op *op, hipStream_t s, const std::vector<int32_t> *order = nullptr);
 void fill_matrix(bie_op *op, bool fp64_regular, bool want64, bool want32, hipStream_t s);
 void rhs_planewave(const bie_op *op, const double *dirs, const double *pols, int64_t R, void *B,
                    hipStream_t s);

@@ -18,10 +18,8 @@
 //     the previous one plus the child's share of the charge;
 //   * mixed Gram matrix G_mn = <n x b_m, f_n> (host, CSR): exact with the
 //     three-edge-midpoint rule on each refined triangle (quadratic integrand);
-//   * T_BC = C Z_b C^T (device): Z_b from the FP64 fill of the refined mesh; in
-//     column chunks, each BC function's column of Z_b C^T gathered from the rows
-//     of Z_b's dense FP64 copy (Z_b is symmetric) that its coefficients name, then
-//     the sparse map C on the left;
+//   * T_BC = C Z_b C^T (device), Z_b the EFIE matrix of the refined mesh, from the
+//     local blocks of the refined triangle pairs, cell by cell, without Z_b;
 //   * G^{-1} applied to all N columns at once by Chebyshev iteration on the
 //     interval that holds G's spectrum (CG on the normal equations if it fails),
 //     twice with a transpose in between, on row-major blocks so that the sparse
@@ -35,6 +33,7 @@
 #include <unordered_map>
 
 #include "bie_internal.hpp"
+#include "pairs.hpp"
 
 struct bie_calderon {
     const bie_op *op = nullptr;   // operator it was built for (mesh and k)
@@ -43,7 +42,6 @@ struct bie_calderon {
     void *tmp = nullptr;          // 2 x tmp_R x N complex128 for the preconditioned solve
     int64_t tmp_R = 0;
     bie_calderon_info info{};
-    bool counted = false;         // holds a reference on the setup pool
 };
 
 namespace bie {
@@ -51,41 +49,7 @@ namespace {
 
 constexpr int CT = 256;
 
-// Setup pool: freeing tens of GB costs about 30 ms per GB on this runtime once
-// many buffers have come and gone, so the three largest transient buffers of a
-// setup are kept (per device) for the next one while any preconditioner lives.
-// Setups are serialised: they share these buffers.
-struct SetupPool {
-    void *buf[3] = {};
-    size_t cap[3] = {};
-};
-std::mutex g_setup_mu;        // one setup at a time
-std::mutex g_pool_mu;
-std::map<int, SetupPool> g_pool;
-int g_live = 0;               // live preconditioners
-thread_local bool g_pool_on = false;
-
-// frees one slot of this device's pool (the next setup that needs it allocates it again)
-void setup_pool_drop(int slot)
-{
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    int dev = 0;
-    BIE_HIP(hipGetDevice(&dev));
-    auto it = g_pool.find(dev);
-    if (it == g_pool.end() || !it->second.buf[slot]) return;
-    (void)hipFree(it->second.buf[slot]);
-    it->second.buf[slot] = nullptr;
-    it->second.cap[slot] = 0;
-}
-
-void setup_pool_release()
-{
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    for (auto &kv : g_pool)
-        for (int i = 0; i < 3; ++i)
-            if (kv.second.buf[i]) (void)hipFree(kv.second.buf[i]);
-    g_pool.clear();
-}
+std::mutex g_setup_mu;   // one setup at a time: a setup's work arrays are the largest part of its memory
 
 struct Csr {
     std::vector<int64_t> ptr;
@@ -118,25 +82,6 @@ struct CsrDev {
 
 // ----------------------------------------------------------------------------- kernels
 
-// Y[:, c] = A X[:, c] for a real CSR matrix A and complex columns (grid.y = columns).
-__global__ __launch_bounds__(CT) void k_csr_cols(int64_t rows, const int64_t *__restrict__ ptr,
-                                                 const int32_t *__restrict__ idx, const double *__restrict__ val,
-                                                 const double2 *__restrict__ X, int64_t ldx, double2 *__restrict__ Y,
-                                                 int64_t ldy)
-{
-    const int64_t i = int64_t(blockIdx.x) * CT + threadIdx.x;
-    if (i >= rows) return;
-    const double2 *x = X + int64_t(blockIdx.y) * ldx;
-    double re = 0.0, im = 0.0;
-    for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
-        const double a = val[k];
-        const double2 v = x[idx[k]];
-        re += a * v.x;
-        im += a * v.y;
-    }
-    Y[int64_t(blockIdx.y) * ldy + i] = make_double2(re, im);
-}
-
 // Y = A X for a real CSR matrix A and n x nc complex matrices stored row-major
 // (entry (i, c) at i nc + c): a wave takes 64 consecutive columns of one row, so
 // each nonzero reads 1 KiB contiguously.  Grid: rows x column blocks, rows
@@ -156,26 +101,6 @@ __global__ __launch_bounds__(CT) void k_csr_rm(const int64_t *__restrict__ ptr, 
         im += a * v.y;
     }
     Y[i * nc + c] = make_double2(re, im);
-}
-
-// Column c of Yc = Z_b (row j0 + c of C)^T for the symmetric refined matrix Z_b, from
-// its dense FP64 operand (row e at e Kp, (Re, Im) pairs): the combination of the
-// rows e of the BC map's nonzeros, read contiguously (grid: row blocks x columns).
-__global__ __launch_bounds__(CT) void k_bc_gather(const double *__restrict__ A64, int64_t Kp, int64_t Nb,
-                                                  const int64_t *__restrict__ ptr, const int32_t *__restrict__ idx,
-                                                  const double *__restrict__ val, int64_t j0, double2 *__restrict__ Yc,
-                                                  int64_t ld)
-{
-    const int64_t i = int64_t(blockIdx.x) * CT + threadIdx.x, c = blockIdx.y;
-    if (i >= Nb) return;
-    double re = 0.0, im = 0.0;
-    for (int64_t k = ptr[j0 + c]; k < ptr[j0 + c + 1]; ++k) {
-        const double a = val[k];
-        const double2 z = *reinterpret_cast<const double2 *>(A64 + int64_t(idx[k]) * Kp + 2 * i);
-        re += a * z.x;
-        im += a * z.y;
-    }
-    Yc[c * ld + i] = make_double2(re, im);
 }
 
 __global__ void k_fill0(int64_t n, double2 *__restrict__ a)
@@ -225,33 +150,6 @@ __global__ __launch_bounds__(CT) void k_cg_xr(int64_t n, const double *__restric
         r.y -= a * w.y;
         X[e] = x;
         Rr[e] = r;
-    }
-}
-
-// Chebyshev step on row-major blocks (coefficients shared by every column):
-// X += D; R -= W (W = G D); D = c1 D + c2 R.
-__global__ __launch_bounds__(CT) void k_cheb(int64_t nn, double c1, double c2, const double2 *__restrict__ W,
-                                             double2 *__restrict__ D, double2 *__restrict__ X, double2 *__restrict__ Rr)
-{
-    for (int64_t e = int64_t(blockIdx.x) * CT + threadIdx.x; e < nn; e += int64_t(gridDim.x) * CT) {
-        const double2 d = D[e], w = W[e];
-        double2 x = X[e], r = Rr[e];
-        x.x += d.x;
-        x.y += d.y;
-        r.x -= w.x;
-        r.y -= w.y;
-        X[e] = x;
-        Rr[e] = r;
-        D[e] = make_double2(c1 * d.x + c2 * r.x, c1 * d.y + c2 * r.y);
-    }
-}
-
-__global__ __launch_bounds__(CT) void k_scale_copy(int64_t nn, double a, const double2 *__restrict__ Xs,
-                                                   double2 *__restrict__ Y)
-{
-    for (int64_t e = int64_t(blockIdx.x) * CT + threadIdx.x; e < nn; e += int64_t(gridDim.x) * CT) {
-        const double2 v = Xs[e];
-        Y[e] = make_double2(a * v.x, a * v.y);
     }
 }
 
@@ -318,6 +216,185 @@ __global__ __launch_bounds__(256) void k_add_cols(int64_t n, const double2 *__re
         y.y += v.y;
         x[e] = y;
     }
+}
+
+// ----------------------------------------------------------------------------- the dual matrix
+//
+// T_BC without the refined mesh's matrix.  The children of a vertex's dual cell (its
+// refined triangles, one after another in the device order) carry the halves of the
+// BC functions of the vertex's edges: with c_i(s, a) the coefficient, in the i-th of
+// those functions, of the refined RWG function of slot a of child s,
+//     D_vw(i, j) = sum_{s in v, a} sum_{t in w, b} c_i(s, a) L(s, a; t, b) c_j(t, b)
+// and T_BC(m, n) is the sum of the four D over the end vertices of m and of n.  A
+// block of the kernel takes one cell v and up to CB children t of whole cells w >= v,
+// one per lane; a lane goes through the children s of v (their data in scalar
+// registers; staged in LDS they cost a block per CU, 8.7 ms), adding c_i(s, .) L(s; t) to E_i(b) in registers, and the block then
+// contracts E with c_j through LDS.  Each pair is computed once and leaves 36
+// numbers per cell pair instead of nine per triangle pair: the refined matrix
+// (36 N^2 entries), its pair scratch and its dense copy, 1440 N^2 bytes with a fill,
+// an assembly, a copy and a gather over them, are 32 N^2 bytes and one kernel.
+// FP64 vector issue bounds it: 2592
+// unknowns, 53.7 M refined pairs 6.9 ms; those four took 20 ms.
+constexpr int CB = 128;   // children t per block
+// CI functions of v per block (a vertex with more edges takes more blocks): 6, the
+// degree of a regular mesh's vertices, when none has more; otherwise 8.  E lies in
+// LDS, 48 CI bytes a lane, which sets the waves in flight: 2 per SIMD with 6, 1.5
+// with 8; in registers it left one (2592 unknowns: 7.9 ms with 8, 6.9 with 6 here).
+
+// One cell, or a part of one with more than CB children: children t0 .. t0 + nt - 1,
+// deg edges, their rows h0 .. h0 + deg - 1 among all cells' rows, coefficients
+// c_i(s, a) at cf + ((s - t0) dp + i) 3 + a (dp: deg rounded up to CI,
+// zeros beyond).
+struct Cell {
+    int32_t t0, nt, deg, dp;
+    int64_t h0, cf;
+};
+
+// NARROW: the pairs within NARROW_PHASE and the flagged ones, D stored; otherwise
+// the rest, added to it.
+template <bool NARROW, int CI>
+__global__ __launch_bounds__(CB) __attribute__((amdgpu_waves_per_eu(2))) void k_cells(const Cell *__restrict__ cells, const int32_t *__restrict__ group,
+                                              const int32_t *__restrict__ cell_of, const int32_t *__restrict__ row_cell,
+                                              const double *__restrict__ coef, const int64_t *__restrict__ rowoff,
+                                              const double *__restrict__ cent, const double *__restrict__ loc,
+                                              const double *__restrict__ vfree, const int8_t *__restrict__ sgn,
+                                              const double *__restrict__ rad, const double *__restrict__ longest,
+                                              const double *__restrict__ qw, const int64_t *__restrict__ fptr,
+                                              const int32_t *__restrict__ fq, const double *__restrict__ fblk,
+                                              double near_factor, double k, double2 *__restrict__ D)
+{
+    __shared__ double2 sE[CI * 3][CB];
+    __shared__ double sw[QPTS], sw4[QPTS];
+    const int32_t v = blockIdx.y, w0 = group[blockIdx.x], w1 = group[blockIdx.x + 1];   // cells w0 .. w1 - 1
+    if (w1 <= v) return;
+    const Cell V = cells[v];
+    const int i0 = blockIdx.z * CI;
+    if (i0 >= V.deg) return;
+    const int tid = threadIdx.x;
+    if (tid < QPTS) {
+        sw[tid] = qw[tid];
+        sw4[tid] = qw[tid] / (4.0 * M_PI);
+    }
+    __syncthreads();
+    const int32_t tb = cells[w0].t0, te = cells[w1 - 1].t0 + cells[w1 - 1].nt;
+    const int32_t t = tb + tid;
+    const bool live = t < te && cell_of[t] >= v;
+    for (int i = 0; i < CI * 3; ++i) sE[i][tid] = make_double2(0.0, 0.0);
+    double y[QPTS][3], ct[3] = { 0.0, 0.0, 0.0 }, rt = 0.0, lt = 0.0;
+    if (live) {
+#pragma unroll
+        for (int j = 0; j < QPTS; ++j)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) y[j][c] = loc[(int64_t(t) * QPTS + j) * 3 + c];
+        for (int c = 0; c < 3; ++c) ct[c] = cent[3 * int64_t(t) + c];
+        rt = rad[t];
+        lt = longest[t];
+    }
+    const auto yq = [&](int j, int c) { return y[j][c]; };
+    const double k4 = 0.25 * k, ik = 1.0 / k;
+    if (live) {
+#pragma unroll 1
+        for (int32_t s = V.t0; s < V.t0 + V.nt; ++s) {   // uniform: child s comes through scalar registers
+            const double d[3] = { cent[3 * int64_t(s)] - ct[0], cent[3 * int64_t(s) + 1] - ct[1],
+                                  cent[3 * int64_t(s) + 2] - ct[2] };
+            const double dd = d[0] * d[0] + d[1] * d[1] + d[2] * d[2], thr = near_factor * fmax(longest[s], lt);
+            // a flagged pair shares a vertex (centroids within 4/3 of the longest edge) or is near
+            const double *blk = nullptr;
+            if (dd < thr * thr * (1.0 + 1e-9)) {
+                const int32_t p = min(s, t), q = max(s, t);
+                int64_t lo = fptr[p], hi = fptr[p + 1];
+                const int64_t end = hi;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if (fq[mid] < q) lo = mid + 1;
+                    else hi = mid;
+                }
+                if (lo < end && fq[lo] == q) blk = fblk + lo * 18;
+            }
+            const bool narrow = k * (rad[s] + rt) <= NARROW_PHASE;
+            const bool mine = NARROW ? narrow || blk : !narrow && !blk;
+            if (!__any(mine)) continue;
+            PairSums<double> S;
+            pair_sums<double, NARROW>(loc + int64_t(s) * QPTS * 3, yq, d, k, sw, sw4, S);
+            double vb[3][3], sb[3];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                sb[b] = double(sgn[3 * int64_t(t) + b]);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) vb[b][c] = vfree[9 * int64_t(t) + 3 * b + c];
+            }
+            const double *cf = coef + V.cf + (int64_t(s - V.t0) * V.dp + i0) * 3;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double va[3] = { vfree[9 * int64_t(s) + 3 * a], vfree[9 * int64_t(s) + 3 * a + 1],
+                                       vfree[9 * int64_t(s) + 3 * a + 2] };
+                double lr[3], li[3];
+                local_row<double, false>(S, va, vb, double(sgn[3 * int64_t(s) + a]), sb, k4, ik, lr, li);
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    if (NARROW && blk) {   // stored with the lower triangle as the row
+                        const double *e = blk + 2 * (s <= t ? a * 3 + b : b * 3 + a);
+                        lr[b] = e[0];
+                        li[b] = e[1];
+                    }
+                    lr[b] = mine ? lr[b] : 0.0;
+                    li[b] = mine ? li[b] : 0.0;
+                }
+#pragma unroll
+                for (int i = 0; i < CI; ++i) {
+                    const double c = cf[3 * i + a];
+#pragma unroll
+                    for (int b = 0; b < 3; ++b) {
+                        double2 &z = sE[3 * i + b][tid];   // the lane's own
+                        z.x += c * lr[b];
+                        z.y += c * li[b];
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int32_t wf = max(w0, v);
+    const int64_t hb = cells[wf].h0, nh = cells[w1 - 1].h0 + cells[w1 - 1].deg - hb;
+    const int ni = min(CI, V.deg - i0);
+    for (int64_t e = tid; e < nh * ni; e += CB) {
+        const int i = int(e / nh);
+        const int64_t h = hb + e % nh;
+        const Cell W = cells[row_cell[h]];
+        const int j = int(h - W.h0);
+        double re = 0.0, im = 0.0;
+        for (int u = 0; u < W.nt; ++u)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const double c = coef[W.cf + (int64_t(u) * W.dp + j) * 3 + b];
+                const double2 z = sE[3 * i + b][W.t0 - tb + u];
+                re += c * z.x;
+                im += c * z.y;
+            }
+        double2 *o = D + rowoff[V.h0 + i0 + i] + h;
+        *o = NARROW ? make_double2(re, im) : make_double2(o->x + re, o->y + im);
+    }
+}
+
+// T_BC(m, n) = sum over the rows h of m and h' of n (two ends, the parts of their
+// cells) of D(h, h'), stored for h <= h'; hrow: rows of function m at hptr[m] ..
+__global__ __launch_bounds__(CT) void k_cells_sum(int64_t n, const int32_t *__restrict__ hptr,
+                                                  const int32_t *__restrict__ hrow, const int64_t *__restrict__ rowoff,
+                                                  const double2 *__restrict__ D, double2 *__restrict__ T)
+{
+    const int64_t m = blockIdx.y, c = int64_t(blockIdx.x) * CT + threadIdx.x;
+    if (c >= n) return;
+    double re = 0.0, im = 0.0;
+    for (int32_t a = hptr[m]; a < hptr[m + 1]; ++a) {
+        const int64_t h = hrow[a];
+        for (int32_t b = hptr[c]; b < hptr[c + 1]; ++b) {
+            const int64_t g = hrow[b];
+            const double2 z = D[h <= g ? rowoff[h] + g : rowoff[g] + h];
+            re += z.x;
+            im += z.y;
+        }
+    }
+    T[m * n + c] = make_double2(re, im);
 }
 
 // ----------------------------------------------------------------------------- host geometry
@@ -545,155 +622,440 @@ void gram_solve(const CsrDev &G, const CsrDev &Gt, int64_t n, double2 *Rr, doubl
 // Iterative Methods for Sparse Linear Systems, Sec. 12.3).  The spectrum of the
 // mixed Gram matrix lies in [1/3, 1) up to imaginary parts near 1e-3 on every mesh
 // tried (spheres, ellipsoids up to 1:2:3, rounded cubes, area ratios up to 6):
-// one sparse product per step and no reductions, about 0.3 per step.  The residual
-// is checked every 4 steps; if it has not fallen by half since the last check (a
-// spectrum outside the interval), false is returned and R, X are undefined.
+// one sparse product per step and no inner products, about 0.3 per step.
 constexpr double GA = 0.30, GB = 1.05;
 
-bool gram_solve_cheb(const CsrDev &G, int64_t n, double2 *Rr, double2 *X, double2 *D, double2 *W, double *sc,
-                     hipStream_t s, int64_t &iters, double &relres)
+// G in slices of 64 rows, entry e of a slice's rows side by side (width: the longest
+// row; the others padded with zeros at their own column).
+struct SlicedDev {
+    int64_t rows = 0;
+    int32_t *ptr = nullptr;    // first entry column of slice b; slices + 1
+    uint16_t *idx = nullptr;   // [entry column][64]
+    double *val = nullptr;
+    void upload(const Csr &c)
+    {
+        rows = int64_t(c.ptr.size()) - 1;
+        const int64_t ns = (rows + 63) / 64;
+        std::vector<int32_t> p(1, 0);
+        std::vector<uint16_t> ix;
+        std::vector<double> vl;
+        for (int64_t b = 0; b < ns; ++b) {
+            int64_t w = 0;
+            for (int64_t i = 64 * b; i < std::min(rows, 64 * b + 64); ++i) w = std::max(w, c.ptr[i + 1] - c.ptr[i]);
+            const size_t at = vl.size();
+            ix.resize(at + size_t(w) * 64, 0);
+            vl.resize(at + size_t(w) * 64, 0.0);
+            for (int64_t i = 64 * b; i < std::min(rows, 64 * b + 64); ++i)
+                for (int64_t e = 0; e < w; ++e) {
+                    const bool in = e < c.ptr[i + 1] - c.ptr[i];
+                    ix[at + size_t(e * 64 + i - 64 * b)] = uint16_t(in ? c.idx[c.ptr[i] + e] : i);
+                    if (in) vl[at + size_t(e * 64 + i - 64 * b)] = c.val[c.ptr[i] + e];
+                }
+            p.push_back(p.back() + int32_t(w));
+        }
+        BIE_HIP(hipMalloc(&ptr, p.size() * sizeof(int32_t)));
+        BIE_HIP(hipMalloc(&idx, ix.size() * sizeof(uint16_t)));
+        BIE_HIP(hipMalloc(&val, vl.size() * sizeof(double)));
+        BIE_HIP(hipMemcpy(ptr, p.data(), p.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        BIE_HIP(hipMemcpy(idx, ix.data(), ix.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+        BIE_HIP(hipMemcpy(val, vl.data(), vl.size() * sizeof(double), hipMemcpyHostToDevice));
+    }
+    ~SlicedDev()
+    {
+        if (ptr) (void)hipFree(ptr);
+        if (idx) (void)hipFree(idx);
+        if (val) (void)hipFree(val);
+    }
+};
+
+// The columns are independent and G is real, so a block solves for NV real vectors
+// by itself from the first step to the last: the direction D lies in LDS (the only
+// array that neighbours read), X and the residual R in registers (rows tid,
+// tid + 1024, ..., J of them), and nothing but G's 0.6 MB (L2) and the columns'
+// first read and last write leaves the CU.  Steps over whole N x N blocks moved
+// them through memory about ten times a step (2592 unknowns, 28 steps: 9.2 -> 1.95 ms).
+// Column c of B is row c of the array Bt, column c of X row c of Xt.  NV = 2, 4, 8:
+// NV / 2 complex columns; NV = 1: the real or the imaginary part of one.  The
+// residual is checked every 4 steps; a block whose residual has not fallen by half
+// since its last check (a spectrum outside the interval) reports failure.
+struct GramStat {
+    double relres;
+    int32_t iters, ok;
+};
+
+template <int J, int NV>
+__global__ __launch_bounds__(1024) void k_gram_cheb(int n, const int32_t *__restrict__ sptr,
+                                                    const uint16_t *__restrict__ sidx, const double *__restrict__ sval,
+                                                    const double *__restrict__ Bt, double *__restrict__ Xt,
+                                                    GramStat *__restrict__ stat)
 {
-    const int64_t nn = n * n;
-    double *rr = sc + 3 * n, *bb = sc + 4 * n, *part = sc + 5 * n;
-    const unsigned cb = unsigned((n + CT - 1) / CT);
-    const dim3 mm(unsigned(n), cb);
-    const unsigned ew = unsigned(std::min<int64_t>((nn + CT - 1) / CT, 16384));
-    auto colsq = [&](const double2 *A, double *out) {
-        hipLaunchKernelGGL(k_colsq_part, dim3(cb, NSLICE), dim3(CT), 0, s, n, A, part);
-        hipLaunchKernelGGL(k_colsq_fin, dim3(cb), dim3(CT), 0, s, n, NSLICE, (const double *)part, out);
-    };
+    constexpr int UN = NV >= 8 ? 1 : NV == 4 ? 2 : 4;   // entries in flight (registers)
+    __shared__ double d[J * 1024 * NV];
+    __shared__ double part[16][NV];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double theta = 0.5 * (GB + GA), delta = 0.5 * (GB - GA), sigma = theta / delta;
-    hipLaunchKernelGGL(k_fill0, dim3(2048), dim3(256), 0, s, nn, X);
-    colsq(Rr, bb);
-    hipLaunchKernelGGL(k_scale_copy, dim3(ew), dim3(CT), 0, s, nn, 1.0 / theta, (const double2 *)Rr, D);
-    BIE_HIP(hipGetLastError());
-    std::vector<double> hb(n), hr(n);
-    BIE_HIP(hipMemcpyAsync(hb.data(), bb, n * sizeof(double), hipMemcpyDeviceToHost, s));
-    BIE_HIP(hipStreamSynchronize(s));
-    const double target = 1e-13;
-    double rho = 1.0 / sigma, last = 1.0;
-    relres = 1.0;
-    for (iters = 1; iters <= 200; ++iters) {
-        const double rhon = 1.0 / (2.0 * sigma - rho);
-        hipLaunchKernelGGL(k_csr_rm, mm, dim3(CT), 0, s, G.ptr, G.idx, G.val, n, D, W);   // W = G D
-        hipLaunchKernelGGL(k_cheb, dim3(ew), dim3(CT), 0, s, nn, rhon * rho, 2.0 * rhon / delta, W, D, X, Rr);
-        BIE_HIP(hipGetLastError());
-        rho = rhon;
-        if (iters % 4 == 0) {
-            colsq(Rr, rr);
-            BIE_HIP(hipMemcpyAsync(hr.data(), rr, n * sizeof(double), hipMemcpyDeviceToHost, s));
-            BIE_HIP(hipStreamSynchronize(s));
-            relres = 0.0;
-            for (int64_t c = 0; c < n; ++c)
-                if (hb[c] > 0.0) relres = std::max(relres, std::sqrt(hr[c] / hb[c]));
-            if (relres <= target) return true;
-            if (!(relres < 0.5 * last)) return false;
-            last = relres;
+    // value v of row i: part v & 1 (or blockIdx & 1) of column c
+    auto at = [&](int i, int v) -> int64_t {
+        const int64_t c = NV == 1 ? blockIdx.x >> 1 : int64_t(blockIdx.x) * (NV / 2) + (v >> 1);
+        return c < n && i < n ? 2 * (c * n + i) + (NV == 1 ? blockIdx.x & 1 : v & 1) : -1;
+    };
+    double x[J][NV], r[J][NV];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = j * 1024 + tid;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int64_t o = at(i, v);
+            r[j][v] = o >= 0 ? Bt[o] : 0.0;
+            x[j][v] = 0.0;
+            d[i * NV + v] = r[j][v] * (1.0 / theta);
         }
     }
-    return false;
+    // sums of r^2 over the rows, in the same order for every lane
+    auto squares = [&](double (&s)[NV]) {
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            double a = 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) a += r[j][v] * r[j][v];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+            if (lane == 0) part[w][v] = a;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) s[v] = 0.0;
+#pragma unroll 1
+        for (int u = 0; u < 16; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) s[v] += part[u][v];
+    };
+    double bb[NV], rr[NV];
+    squares(bb);
+    double rho = 1.0 / sigma, last = 1.0, rel = 1.0;
+    int it = 1, ok = 0;
+    for (; it <= 200; ++it) {
+        __syncthreads();   // D is written
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int b = j * 16 + w;   // slice of this wave's rows (uniform)
+            if (64 * b >= n) break;
+            double a[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) a[v] = 0.0;
+            const int e1 = sptr[b + 1];
+#pragma unroll UN
+            for (int e = sptr[b]; e < e1; ++e) {
+                const int k = sidx[e * 64 + lane];
+                const double g = sval[e * 64 + lane];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) a[v] += g * d[k * NV + v];
+            }
+#pragma unroll
+            for (int v = 0; v < NV; ++v) r[j][v] -= a[v];
+        }
+        const double rhon = 1.0 / (2.0 * sigma - rho), c1 = rhon * rho, c2 = 2.0 * rhon / delta;
+        rho = rhon;
+        __syncthreads();   // D is read
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                double &dd = d[(j * 1024 + tid) * NV + v];
+                x[j][v] += dd;
+                dd = c1 * dd + c2 * r[j][v];
+            }
+        if (it % 4) continue;
+        squares(rr);
+        rel = 0.0;
+        bool finite = true;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (bb[v] != 0.0) {   // a NaN column too
+                const double q = sqrt(rr[v] / bb[v]);
+                finite = finite && q < 1e300;
+                rel = fmax(rel, q);
+            }
+        ok = finite && rel <= 1e-13;
+        if (ok || !finite || !(rel < 0.5 * last)) break;
+        last = rel;
+    }
+    if (tid == 0) stat[blockIdx.x] = { rel, it, ok };
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int64_t o = at(j * 1024 + tid, v);
+            if (o >= 0) Xt[o] = x[j][v];
+        }
 }
 
-// G X = B: Chebyshev, or CG on the normal equations from the saved B if it fails.
-void gram_solve_any(const CsrDev &G, const CsrDev &Gt, int64_t n, double2 *Rr, double2 *X, double2 *P, double2 *W,
-                    double2 *Bs, double *sc, hipStream_t s, int64_t &iters, double &relres)
+// Row c of Xt = G^{-1} (row c of Bt) for all n rows; false if a column failed.  NV:
+// as many vectors as LDS (160 KB) and 128 registers a lane hold; each of them reads
+// G once per step.
+bool gram_solve_cheb(const SlicedDev &G, int64_t n, const double2 *Bt, double2 *Xt, hipStream_t s, int64_t &iters,
+                     double &relres)
 {
-    const int64_t nn = n * n;
-    const unsigned ew = unsigned(std::min<int64_t>((nn + CT - 1) / CT, 16384));
-    const char *env = getenv("BIE_CALDERON_GRAM");
-    if (env && std::string(env) == "cgnr") {
-        gram_solve(G, Gt, n, Rr, X, P, W, sc, s, iters, relres);
-        return;
+    const int64_t J = (n + 1023) / 1024;
+    const int64_t nv = J <= 2 ? 8 : J <= 4 ? 4 : J <= 9 ? 2 : 1;
+    const int64_t nblk = (2 * n + nv - 1) / nv;
+    GramStat *ds = nullptr;
+    BIE_HIP(hipMalloc(&ds, size_t(nblk) * sizeof(GramStat)));
+    std::vector<GramStat> h(nblk);
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(unsigned(nblk)), dim3(1024), 0, s, int(n), G.ptr, G.idx, G.val, (const double *)Bt,
+                           (double *)Xt, ds);
+    };
+    switch (J) {
+    case 1: run(k_gram_cheb<1, 8>); break;
+    case 2: run(k_gram_cheb<2, 8>); break;
+    case 3: run(k_gram_cheb<3, 4>); break;
+    case 4: run(k_gram_cheb<4, 4>); break;
+    case 5: run(k_gram_cheb<5, 2>); break;
+    case 6: run(k_gram_cheb<6, 2>); break;
+    case 7: run(k_gram_cheb<7, 2>); break;
+    case 8: run(k_gram_cheb<8, 2>); break;
+    case 9: run(k_gram_cheb<9, 2>); break;
+    case 10: run(k_gram_cheb<10, 1>); break;
+    case 11: run(k_gram_cheb<11, 1>); break;
+    default: run(k_gram_cheb<12, 1>); break;   // CALDERON_MAX_N = 12 * 1024
     }
-    hipLaunchKernelGGL(k_scale_copy, dim3(ew), dim3(CT), 0, s, nn, 1.0, (const double2 *)Rr, Bs);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), ds, h.size() * sizeof(GramStat), hipMemcpyDeviceToHost, s);
+    const hipError_t e2 = hipStreamSynchronize(s);
+    (void)hipFree(ds);
+    BIE_HIP(e);
+    BIE_HIP(e2);
+    bool ok = true;
+    iters = 0;
+    relres = 0.0;
+    for (const GramStat &g : h) {
+        ok = ok && g.ok;
+        iters = std::max<int64_t>(iters, g.iters);
+        relres = std::max(relres, g.relres);
+    }
+    return ok;
+}
+
+void transpose(int64_t n, const double2 *A, double2 *B, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_transpose, dim3(unsigned((n + 31) / 32), unsigned((n + 31) / 32)), dim3(32, 8), 0, s, n, A, B);
     BIE_HIP(hipGetLastError());
-    if (gram_solve_cheb(G, n, Rr, X, P, W, sc, s, iters, relres)) return;
+}
+
+// Row c of Xt = G^{-1} (row c of Bt): Chebyshev, or CG on the normal equations if it
+// fails (with BIE_CALDERON_GRAM=cgnr from the start).  Bt is kept.
+void gram_solve_any(const SlicedDev &Gs, const Csr &G, const Csr &Gt, int64_t n, const double2 *Bt, double2 *Xt,
+                    hipStream_t s, int64_t &iters, double &relres)
+{
+    const char *env = getenv("BIE_CALDERON_GRAM");
+    const bool cg = env && std::string(env) == "cgnr";
+    iters = 0;
+    if (!cg && gram_solve_cheb(Gs, n, Bt, Xt, s, iters, relres)) return;
+    CsrDev dG, dGt;
+    dG.upload(G);
+    dGt.upload(Gt);
+    const size_t nn = size_t(n) * size_t(n);
+    struct Work {
+        void *p[4] = {};
+        ~Work()
+        {
+            for (void *q : p)
+                if (q) (void)hipFree(q);
+        }
+    } wk;
+    for (int i = 0; i < 3; ++i) BIE_HIP(hipMalloc(&wk.p[i], nn * sizeof(double2)));
+    BIE_HIP(hipMalloc(&wk.p[3], size_t((5 + NSLICE) * n) * sizeof(double)));
+    double2 *Rr = static_cast<double2 *>(wk.p[0]), *X = static_cast<double2 *>(wk.p[1]),
+            *P = static_cast<double2 *>(wk.p[2]);
     int64_t it2 = 0;
-    hipLaunchKernelGGL(k_scale_copy, dim3(ew), dim3(CT), 0, s, nn, 1.0, (const double2 *)Bs, Rr);
-    gram_solve(G, Gt, n, Rr, X, P, W, sc, s, it2, relres);
+    transpose(n, Bt, Rr, s);
+    gram_solve(dG, dGt, n, Rr, X, P, Xt, static_cast<double *>(wk.p[3]), s, it2, relres);   // Xt as its product array
+    transpose(n, X, Xt, s);
+    BIE_HIP(hipStreamSynchronize(s));
     iters += it2;
 }
 
 }  // namespace
 
-// Largest N for which the preconditioner is built.  The refined mesh has 6 N
-// unknowns and 4 N triangles: its fill's pair scratch (144 B per triangle pair,
-// 1152 N^2 bytes) beside its packed FP64 matrix (288 N^2) is the peak of the
-// fill, 217 GB at this N; then the packed matrix and its dense copy (864 N^2)
-// with five N x N work matrices (80 N^2).  The pool keeps the pair scratch for
-// the next setup only while the rest of the setup fits beside it (checked with
-// hipMemGetInfo after the fill); otherwise it is freed first, so the peak stays
-// max(1440, 944) N^2 bytes.
-constexpr int64_t CALDERON_MAX_N = 12288;
-
-bool setup_pool_active() { return g_pool_on; }
-
-void *setup_pool_get(int slot, size_t bytes)
-{
-    std::lock_guard<std::mutex> lk(g_pool_mu);
-    int dev = 0;
-    BIE_HIP(hipGetDevice(&dev));
-    SetupPool &p = g_pool[dev];
-    if (p.cap[slot] < bytes) {
-        if (p.buf[slot]) (void)hipFree(p.buf[slot]);
-        p.buf[slot] = nullptr;
-        p.cap[slot] = 0;
-        BIE_HIP(hipMalloc(&p.buf[slot], bytes));
-        p.cap[slot] = bytes;
+struct DualWork {   // the setup's largest array: D, later two n x n blocks
+    void *p = nullptr;
+    ~DualWork()
+    {
+        if (p) (void)hipFree(p);
     }
-    return p.buf[slot];
+};
+
+// device copies of host tables, freed together
+struct Bufs {
+    std::vector<void *> p;
+    ~Bufs()
+    {
+        for (void *q : p) (void)hipFree(q);
+    }
+    template <typename T>
+    T *up(const std::vector<T> &v)
+    {
+        void *q = nullptr;
+        BIE_HIP(hipMalloc(&q, std::max<size_t>(1, v.size()) * sizeof(T)));
+        p.push_back(q);
+        BIE_HIP(hipMemcpy(q, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+        return static_cast<T *>(q);
+    }
+};
+
+// T_BC (row-major n x n) of the BC functions C on the refined mesh of opb.
+void dual_matrix(const Mesh &M, const bie_op *opb, const Csr &C, DualWork &work, double2 *T, hipStream_t s)
+{
+    const Mesh &B = opb->mesh;
+    const TriDev &td = opb->tri;
+    const int64_t N = M.N, Fb = B.F;
+    const double near_factor = 2.0;   // the fill's default
+    // edges of every vertex, and its children (the device order runs cell by cell)
+    std::vector<std::vector<int32_t>> inc(M.nv);
+    for (int64_t m = 0; m < N; ++m)
+        for (int e = 0; e < 2; ++e) inc[M.edges[4 * m + e]].push_back(int32_t(m));
+    size_t maxdeg = 1;
+    for (const auto &e : inc) maxdeg = std::max(maxdeg, e.size());
+    const int ci = maxdeg <= 6 ? 6 : 8;
+    std::vector<int32_t> tri_at(Fb), cell_of(Fb), row_cell, group(1, 0), hptr(N + 1, 0), hrow;
+    for (int64_t t = 0; t < Fb; ++t) tri_at[td.rank[t]] = int32_t(t);
+    std::vector<Cell> cells;
+    std::vector<double> coef, longest(Fb);
+    std::vector<int64_t> rowoff;
+    std::vector<std::vector<int32_t>> rows_of(N);
+    int32_t r = 0, gchildren = 0;
+    for (int64_t v = 0; v < M.nv; ++v) {
+        int32_t left = 2 * int32_t(inc[v].size());   // two children per triangle, a triangle per edge
+        while (left > 0) {
+            Cell c;
+            c.t0 = r;
+            c.nt = std::min(left, int32_t(CB));
+            c.deg = int32_t(inc[v].size());
+            c.dp = (c.deg + ci - 1) / ci * ci;
+            c.h0 = int64_t(row_cell.size());
+            c.cf = int64_t(coef.size());
+            const int32_t id = int32_t(cells.size());
+            if (gchildren + c.nt > CB) {
+                group.push_back(id);
+                gchildren = 0;
+            }
+            gchildren += c.nt;
+            coef.resize(coef.size() + size_t(c.nt) * c.dp * 3, 0.0);
+            for (int32_t u = 0; u < c.nt; ++u) {
+                const int32_t t = tri_at[r + u];
+                if (B.T[3 * t] != v && B.T[3 * t + 1] != v) throw Error(BIE_EMESH, "refined triangles out of cell order");
+                cell_of[r + u] = id;
+                longest[r + u] = B.longest[t];
+                for (int i = 0; i < c.deg; ++i) {
+                    const int32_t m = inc[v][i];
+                    const int32_t *x0 = C.idx.data() + C.ptr[m], *x1 = C.idx.data() + C.ptr[m + 1];
+                    for (int a = 0; a < 3; ++a) {
+                        const int32_t e = B.slot_m[3 * t + a];
+                        const int32_t *x = std::lower_bound(x0, x1, e);
+                        if (x < x1 && *x == e) coef[c.cf + (size_t(u) * c.dp + i) * 3 + a] = C.val[x - C.idx.data()];
+                    }
+                }
+            }
+            for (int i = 0; i < c.deg; ++i) {
+                rows_of[inc[v][i]].push_back(int32_t(row_cell.size()));
+                row_cell.push_back(id);
+            }
+            cells.push_back(c);
+            r += c.nt;
+            left -= c.nt;
+        }
+    }
+    if (r != Fb) throw Error(BIE_EMESH, "dual cells do not cover the refined mesh");
+    group.push_back(int32_t(cells.size()));
+    const int64_t H = int64_t(row_cell.size());
+    rowoff.resize(H);
+    int64_t total = 0;
+    for (int64_t h = 0; h < H; ++h) {   // row h: columns from its own cell's first on
+        const int64_t c0 = cells[row_cell[h]].h0;
+        rowoff[h] = total - c0;
+        total += H - c0;
+    }
+    for (int64_t m = 0; m < N; ++m) {
+        hrow.insert(hrow.end(), rows_of[m].begin(), rows_of[m].end());
+        hptr[m + 1] = int32_t(hrow.size());
+    }
+    BIE_HIP(hipMalloc(&work.p, std::max(size_t(total), 2 * size_t(N) * size_t(N)) * sizeof(double2)));
+    double2 *D = static_cast<double2 *>(work.p);
+    double qwh[QPTS];
+    quad_weights(qwh);
+
+    NearDev nd;
+    ranked_near(opb, near_factor, nd, s);
+    Bufs bufs;
+    const Cell *dc = bufs.up(cells);
+    const int32_t *dg = bufs.up(group), *dco = bufs.up(cell_of), *drc = bufs.up(row_cell), *dhp = bufs.up(hptr),
+                  *dhr = bufs.up(hrow);
+    const double *dcf = bufs.up(coef), *dl = bufs.up(longest), *dqw = bufs.up(std::vector<double>(qwh, qwh + QPTS));
+    const int64_t *dro = bufs.up(rowoff);
+    int32_t *pairs = near_list(nd, Fb, s);
+    bufs.p.push_back(pairs);
+    void *fb = nullptr;
+    BIE_HIP(hipMalloc(&fb, std::max<int64_t>(1, nd.n) * 18 * sizeof(double)));
+    bufs.p.push_back(fb);
+    singular_blocks(opb, pairs, nd.n, static_cast<double *>(fb), s);
+    const dim3 grid(unsigned(group.size() - 1), unsigned(cells.size()), unsigned((maxdeg + ci - 1) / ci));
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(CB), 0, s, dc, dg, dco, drc, dcf, dro, td.cent, td.loc, td.vfree, td.sgn,
+                           td.rad, dl, dqw, nd.ptr, nd.list, (const double *)fb, near_factor, opb->k, D);
+    };
+    const bool wide = opb->k * 2.0 * td.max_rad > NARROW_PHASE;
+    if (ci == 6) {
+        run(k_cells<true, 6>);
+        if (wide) run(k_cells<false, 6>);
+    } else {
+        run(k_cells<true, 8>);
+        if (wide) run(k_cells<false, 8>);
+    }
+    hipLaunchKernelGGL(k_cells_sum, dim3(unsigned((N + CT - 1) / CT), unsigned(N)), dim3(CT), 0, s, N, dhp, dhr, dro,
+                       (const double2 *)D, T);
+    BIE_HIP(hipGetLastError());
+    BIE_HIP(hipStreamSynchronize(s));
 }
+
+// Largest N for which the preconditioner is built (the rows a block of the Gram
+// solves holds; its memory, 48 N^2 bytes of work arrays beside M, would allow more).
+constexpr int64_t CALDERON_MAX_N = 12288;
 
 bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
 {
     std::lock_guard<std::mutex> serial(g_setup_mu);
-    struct PoolScope {
-        PoolScope() { g_pool_on = true; }
-        ~PoolScope()
-        {
-            g_pool_on = false;
-            bool none;
-            {
-                std::lock_guard<std::mutex> lk(g_pool_mu);
-                none = g_live == 0;
-            }
-            if (none) setup_pool_release();   // a failed first setup keeps nothing
-        }
-    } scope;
     const auto t0 = std::chrono::steady_clock::now();
     const Mesh &M = op->mesh;
     const int64_t N = M.N;
-    if (N > CALDERON_MAX_N) throw Error(BIE_EINVAL, "Calderon preconditioner: N above 12288 (refined dense matrix too large)");
+    if (N > CALDERON_MAX_N) throw Error(BIE_EINVAL, "Calderon preconditioner: N above 12288");
     if (op->star) throw Error(BIE_EINVAL, "Calderon preconditioner: needs an assembled operator");
     std::vector<double> Vb;
     std::vector<int32_t> Tb;
     refine(M, Vb, Tb);
-    bie_op *opb = nullptr;
-    bie_fill_opts fo{};
-    fo.storage = BIE_C128;
-    fo.near_factor = 2.0;
-    int rc = bie_op_create(Vb.data(), int64_t(Vb.size() / 3), Tb.data(), int64_t(Tb.size() / 3), op->k, &fo, s, &opb);
-    if (rc != BIE_OK) throw Error(rc, std::string("Calderon preconditioner, refined mesh: ") + bie_last_error());
-    std::unique_ptr<bie_op, void (*)(bie_op *)> hold(opb, bie_op_destroy);
+    std::unique_ptr<bie_op, void (*)(bie_op *)> hold(new bie_op(), bie_op_destroy);
+    bie_op *opb = hold.get();
+    const int64_t Fb = int64_t(Tb.size() / 3);
+    opb->mesh = build_mesh(Vb.data(), int64_t(Vb.size() / 3), Tb.data(), Fb, 2.0, !near_on_device(Fb));
+    opb->device = op->device;
+    opb->k = op->k;
     const int64_t Nb = opb->mesh.N;
     if (Nb != 9 * M.F) throw Error(BIE_EMESH, "refined mesh has an unexpected edge count");
     {
-        // the fill's pair scratch (pool slot 0) is not read again in this setup:
-        // keep it for the next one only if the refined matrix's dense copy, the
-        // work matrices and M's storage still fit beside it
-        size_t freeb = 0, totb = 0;
-        BIE_HIP(hipMemGetInfo(&freeb, &totb));
-        const double n2 = double(N) * double(N);
-        const double later = 16.0 * double(Nb) * double(Nb) + (5 * 16 + 8 + 16 + 8 + 16) * n2 + double(size_t(4) << 30);
-        if (double(freeb) < later) setup_pool_drop(0);
+        // refined triangles cell by cell: child 2 i (2 i + 1) of a triangle lies at its corner i (i + 1)
+        std::vector<int32_t> count(M.nv + 1, 0), order(Fb);
+        auto corner = [&](int64_t t) { return M.T[3 * (t / 6) + (t % 6 / 2 + t % 2) % 3]; };
+        for (int64_t t = 0; t < Fb; ++t) ++count[corner(t) + 1];
+        for (int64_t v = 0; v < M.nv; ++v) count[v + 1] += count[v];
+        for (int64_t t = 0; t < Fb; ++t) order[count[corner(t)]++] = int32_t(t);
+        upload_triangles(opb, s, &order);
     }
 
     Csr C, G, Gt;
     bc_and_gram(M, opb->mesh, C, G, Gt);
-    CsrDev dC, dG, dGt;
-    dC.upload(C);
+    SlicedDev dG;
     dG.upload(G);
-    dGt.upload(Gt);
 
     std::unique_ptr<bie_calderon, void (*)(bie_calderon *)> pc(new bie_calderon(), calderon_destroy);
     pc->op = op;
@@ -702,57 +1064,18 @@ bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
     pc->info.nnz_bc = int64_t(C.idx.size());
     pc->info.nnz_gram = int64_t(G.idx.size());
 
-    // dense work, n x n each: T_BC / residual, X, P (Chebyshev direction), W, and the
-    // saved right-hand side for the fallback; column scalars and partial sums
+    // T_BC, then A1^T = (G^{-1} T_BC)^T (T_BC symmetric: its columns are its rows),
+    // A1, and M' = G^{-1} A1^T, transposed; M is symmetric, so either will do
     const int64_t nn = N * N;
-    double2 *buf[5] = {};
-    double *scal = nullptr;
-    struct Free {
-        double2 **b;
-        double **sc;
-        ~Free()
-        {
-            for (int i = 0; i < 5; ++i)
-                if (b[i]) (void)hipFree(b[i]);
-            if (*sc) (void)hipFree(*sc);
-        }
-    } guard{ buf, &scal };
-    for (int i = 0; i < 5; ++i) BIE_HIP(hipMalloc(&buf[i], size_t(nn) * sizeof(double2)));
-    BIE_HIP(hipMalloc(&scal, size_t((5 + NSLICE) * N) * sizeof(double)));
-
-    // T_BC in column chunks: Yc = Z_b C^T[:, chunk] gathered from the rows of the
-    // refined matrix's dense FP64 operand (Z_b symmetric: column e = row e), then
-    // T_BC[:, chunk] = C Yc
-    {
-        dense64_setup(opb, s);
-        const int64_t ch = std::min<int64_t>(N, 512);
-        double2 *Yc = nullptr;
-        BIE_HIP(hipMalloc(&Yc, size_t(Nb * ch) * sizeof(double2)));
-        struct F2 {
-            double2 *p;
-            ~F2() { if (p) (void)hipFree(p); }
-        } fy{ Yc };
-        for (int64_t j0 = 0; j0 < N; j0 += ch) {
-            const int64_t nc = std::min(ch, N - j0);
-            hipLaunchKernelGGL(k_bc_gather, dim3(unsigned((Nb + CT - 1) / CT), unsigned(nc)), dim3(CT), 0, s,
-                               (const double *)opb->A64, opb->d64_Kp, Nb, dC.ptr, dC.idx, dC.val, j0, Yc, Nb);
-            BIE_HIP(hipGetLastError());
-            hipLaunchKernelGGL(k_csr_cols, dim3(unsigned((N + CT - 1) / CT), unsigned(nc)), dim3(CT), 0, s, N, dC.ptr,
-                               dC.idx, dC.val, Yc, Nb, buf[0] + j0 * N, N);
-            BIE_HIP(hipGetLastError());
-        }
-        BIE_HIP(hipStreamSynchronize(s));
-    }
-    hold.reset();   // the refined operator is no longer needed
-
-    // A1 = G^{-1} T_BC (into buf1); M' = G^{-1} A1^T (into buf1 again, A1^T in buf0)
-    gram_solve_any(dG, dGt, N, buf[0], buf[1], buf[2], buf[3], buf[4], scal, s, pc->info.cg_iters[0],
-                   pc->info.cg_relres[0]);
-    hipLaunchKernelGGL(k_transpose, dim3(unsigned((N + 31) / 32), unsigned((N + 31) / 32)), dim3(32, 8), 0, s, N,
-                       buf[1], buf[0]);
-    BIE_HIP(hipGetLastError());
-    gram_solve_any(dG, dGt, N, buf[0], buf[1], buf[2], buf[3], buf[4], scal, s, pc->info.cg_iters[1],
-                   pc->info.cg_relres[1]);
+    DualWork work, tbc;
+    BIE_HIP(hipMalloc(&tbc.p, size_t(nn) * sizeof(double2)));
+    double2 *T = static_cast<double2 *>(tbc.p);
+    dual_matrix(M, opb, C, work, T, s);
+    hold.reset();   // the refined mesh is no longer needed
+    double2 *X = static_cast<double2 *>(work.p), *Y = X + nn;
+    gram_solve_any(dG, G, Gt, N, T, X, s, pc->info.cg_iters[0], pc->info.cg_relres[0]);
+    transpose(N, X, Y, s);
+    gram_solve_any(dG, G, Gt, N, Y, T, s, pc->info.cg_iters[1], pc->info.cg_relres[1]);
 
     // M = -(M' + M'^T)/2 in packed tiles
     bie_op *v = new bie_op();
@@ -764,16 +1087,11 @@ bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
     packed_setup(v->pk, N);
     BIE_HIP(hipMalloc(&v->Z64, size_t(v->pk.ntiles) * TB * TB * sizeof(double2)));
     hipLaunchKernelGGL(k_pack_sym, dim3(unsigned(v->pk.nT), unsigned(v->pk.nT)), dim3(256), 0, s, N, v->pk.nT,
-                       buf[1], -1.0, (double2 *)v->Z64);
+                       T, -1.0, (double2 *)v->Z64);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipStreamSynchronize(s));
     if (op->Abf) calderon_tm(pc.get(), s);   // block products of the preconditioned mixed solves
     pc->info.setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-    {
-        std::lock_guard<std::mutex> lk(g_pool_mu);
-        ++g_live;
-        pc->counted = true;
-    }
     return pc.release();
 }
 
@@ -820,21 +1138,7 @@ void calderon_destroy(bie_calderon *pc)
     if (pc->view) bie_op_destroy(pc->view);   // every buffer the products made on it too
     if (pc->tm) bie_op_destroy(pc->tm);
     if (pc->tmp) (void)hipFree(pc->tmp);
-    bool last = false;
-    if (pc->counted) {
-        std::lock_guard<std::mutex> lk(g_pool_mu);
-        last = --g_live == 0;
-    }
     delete pc;
-    if (last) {   // wait for a setup in progress on another thread, which may be using the pool
-        std::lock_guard<std::mutex> serial(g_setup_mu);
-        bool none;
-        {
-            std::lock_guard<std::mutex> lk(g_pool_mu);
-            none = g_live == 0;
-        }
-        if (none) setup_pool_release();
-    }
 }
 
 const bie_op *calderon_operator(const bie_calderon *pc) { return pc->op; }

@@ -603,12 +603,12 @@ void quad_weights(double *w)
     for (int i = 0; i < NQ; ++i) w[i] = rule.w[i];
 }
 
-// Per-triangle tables on the device, in the order of the triangles' lowest RWG
-// function: consecutive functions then lie on nearly consecutive triangles, and
+// Per-triangle tables on the device, in the given order or that of the triangles'
+// lowest RWG function: consecutive functions then lie on nearly consecutive triangles, and
 // the assembly finds most local blocks of a row (p <= q) in one run.  Quadrature
 // points and free vertices relative to the triangle centroid (keeps FP32 local
 // arithmetic accurate).
-void upload_triangles(bie_op *op, hipStream_t s)
+void upload_triangles(bie_op *op, hipStream_t s, const std::vector<int32_t> *given)
 {
     const Mesh &M = op->mesh;
     const int64_t F = M.F;
@@ -618,7 +618,11 @@ void upload_triangles(bie_op *op, hipStream_t s)
     D.rank.assign(F, -1);
     std::vector<int32_t> order;
     order.reserve(F);
-    for (int64_t m = 0; m < M.N; ++m)
+    if (given) {
+        order = *given;
+        for (int64_t r = 0; r < F; ++r) D.rank[order[r]] = int32_t(r);
+    }
+    for (int64_t m = 0; m < M.N && !given; ++m)
         for (int side = 0; side < 2; ++side) {
             const int32_t t = M.edges[4 * m + 2 + side];
             if (D.rank[t] >= 0) continue;
@@ -730,11 +734,9 @@ void fill_matrix(bie_op *op, bool fp64_regular, bool want64, bool want32, hipStr
     void *LB = nullptr, *VS = nullptr;
     const int32_t *pairs = op->flagged;
     const int64_t npairs = int64_t(M.near.size() / 2);
-    const bool pooled = setup_pool_active();   // inside a preconditioner setup: kept scratch
     try {
         const size_t lb_bytes = size_t(bd.total()) * 9 * 2 * elem;
-        if (pooled) LB = setup_pool_get(0, lb_bytes);
-        else BIE_HIP(hipMalloc(&LB, lb_bytes));
+        BIE_HIP(hipMalloc(&LB, lb_bytes));
         if (op->star) BIE_HIP(hipMalloc(&VS, size_t(bd.total()) * 2 * elem));
         if (fp64_regular) {
             if (op->star) fill_launch<double, true>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
@@ -746,11 +748,11 @@ void fill_matrix(bie_op *op, bool fp64_regular, bool want64, bool want32, hipStr
         BIE_HIP(hipGetLastError());
         BIE_HIP(hipStreamSynchronize(s));
     } catch (...) {
-        if (LB && !pooled) hipFree(LB);
+        if (LB) hipFree(LB);
         if (VS) hipFree(VS);
         throw;
     }
-    if (!pooled) hipFree(LB);
+    hipFree(LB);
     if (VS) hipFree(VS);
     (void)hipFree(op->flagged);   // not read again
     op->flagged = nullptr;
