@@ -120,6 +120,19 @@ struct Cx<float> {
     using type = nf2;
 };
 
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// (ar, ai) += z x, in the one order that every tile pass uses
+template <typename T>
+__device__ __forceinline__ void cmad(T &ar, T &ai, T zr, T zi, T xr, T xi)
+{
+    ar = fma_(zr, xr, ar);
+    ar = fma_(-zi, xi, ar);
+    ai = fma_(zr, xi, ai);
+    ai = fma_(zi, xr, ai);
+}
+
 template <typename T>
 __device__ inline T wsum(T v)
 {
@@ -201,7 +214,7 @@ __device__ __forceinline__ void tile_pass(const M *__restrict__ Zp, int64_t N, i
     T rar[16], rai[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) { rar[i] = 0; rai[i] = 0; }
-    __shared__ V2 red[2][4][TB];
+    __shared__ V2 red[2][8][TB];
 
     // x_J of lane's column, loaded with the tile it multiplies (a load issued
     // just before its use would expose its latency once per tile)
@@ -238,25 +251,26 @@ __device__ __forceinline__ void tile_pass(const M *__restrict__ Zp, int64_t N, i
 #pragma unroll
             for (int i = 0; i < 16; ++i) cur[i] = NT ? __builtin_nontemporal_load(tile + i * TB) : tile[i * TB];
         }
-        T car = 0, cai = 0;
+        // column sums by groups of 8 rows (the rows of a wave of the several-vector
+        // pass, whose columns equal this pass's bit for bit)
+        T car[2] = { 0, 0 }, cai[2] = { 0, 0 };
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const T zr = T(cur[i].x), zi = CONJ ? -T(cur[i].y) : T(cur[i].y);
-            rar[i] += zr * xj.x - zi * xj.y;
-            rai[i] += zr * xj.y + zi * xj.x;
-            car += zr * xir[i] - zi * xii[i];
-            cai += zr * xii[i] + zi * xir[i];
+            cmad(rar[i], rai[i], zr, zi, xj.x, xj.y);
+            cmad(car[i >> 3], cai[i >> 3], zr, zi, xir[i], xii[i]);
         }
         if (J != I) {   // uniform over the block
             // double-buffered by tile parity: one barrier per tile; the barrier of
             // the next tile orders this tile's reads before the buffer is reused
             const int par = (J - J0) & 1;
-            red[par][wave][lane] = V2{ car, cai };
+            red[par][2 * wave][lane] = V2{ car[0], cai[0] };
+            red[par][2 * wave + 1][lane] = V2{ car[1], cai[1] };
             __syncthreads();
             if (wave == ((J - J0) & 3)) {
                 V2 a = red[par][0][lane];
 #pragma unroll
-                for (int w = 1; w < 4; ++w) a += red[par][w][lane];
+                for (int w = 1; w < 8; ++w) a += red[par][w][lane];
                 pv[(seg[J] + I) * TB + lane] = a;
             }
         }
@@ -295,6 +309,127 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         tile_pass<M, T, CONJ, PREFETCH, NT>(Zp, N, nT, I, J0, J1, u - unit_ptr[I], seg,
                                         reinterpret_cast<const V2 *>(X) + v * ldx,
                                         reinterpret_cast<V2 *>(part) + v * nslots * TB);
+    }
+}
+
+// The same for several vectors: a block of 8 waves takes a run for NC of them at
+// once, each wave 8 rows of the row block, so that a tile read serves NC products
+// (one block per vector read the matrix R times: 6 FP64 vectors at 5202 unknowns
+// 238 -> 88 us, 16 at 7680 1283 -> 463 us).  The row sums of NC vectors fill the registers (2 waves per SIMD at
+// NC = 3); x of the tile rows comes from LDS, the same address for every lane.  The
+// groups of one run start together on one XCD, so that its L2 serves all but one of
+// them.  NT: as in the single-vector pass.  Every column has the bits of a product
+// of its own.
+template <typename M, typename T, bool CONJ, int NC, bool NT>
+__global__ __launch_bounds__(512) void k_sym_tiles_n(int nruns, const M *__restrict__ Zp, int64_t N, int64_t nT,
+                                                     const int32_t *__restrict__ units,
+                                                     const int32_t *__restrict__ unit_ptr,
+                                                     const int32_t *__restrict__ run_ptr,
+                                                     const int64_t *__restrict__ seg, int64_t nslots, int G, int64_t R,
+                                                     const T *__restrict__ Xp, int64_t ldx, T *__restrict__ part,
+                                                     const int *__restrict__ skip, int64_t sks)
+{
+    using V2 = typename Cx<T>::type;
+    using MV = typename Cx<M>::type;
+    __shared__ V2 red[2][NC][8][TB];
+    __shared__ V2 sx[TB][NC];
+    // consecutive blocks go to the 8 XCDs in turn: the G groups of a run are 8 apart
+    const int r8 = blockIdx.x % (8 * G);
+    const int32_t run = blockIdx.x / (8 * G) * 8 + r8 % 8;
+    if (run >= nruns) return;
+    const int64_t c0 = int64_t(r8 / 8) * NC;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    bool live[NC], any = false;   // uniform; columns beyond R repeat the last one and store nothing
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        live[c] = c0 + c < R && !(skip && skip[(c0 + c) * sks]);
+        any = any || live[c];
+    }
+    if (!any) return;
+    const V2 *x[NC];
+    V2 *pv[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int64_t col = c0 + c < R ? c0 + c : R - 1;
+        x[c] = reinterpret_cast<const V2 *>(Xp) + col * ldx;
+        pv[c] = reinterpret_cast<V2 *>(part) + col * nslots * TB;
+    }
+    const MV *Z = reinterpret_cast<const MV *>(Zp);
+    for (int32_t u = run_ptr[run]; u < run_ptr[run + 1]; ++u) {
+        const int32_t I = units[3 * u], J0 = units[3 * u + 1], J1 = units[3 * u + 2];
+        __syncthreads();   // the previous unit's LDS reads are done
+        for (int e = threadIdx.x; e < TB * NC; e += 512) {
+            const int64_t m = int64_t(I) * TB + e / NC;
+            V2 v = { 0, 0 };
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (e % NC == c && m < N) v = x[c][m];
+            sx[e / NC][e % NC] = v;
+        }
+        __syncthreads();
+        T rar[8][NC], rai[8][NC];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) rar[i][c] = rai[i][c] = 0;
+        MV t[8];
+        const auto load = [&](int32_t J) {
+            const MV *tile = Z + tile_of(I, J, nT) * TB * TB + (wave * 8) * TB + lane;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = NT ? __builtin_nontemporal_load(tile + i * TB) : tile[i * TB];
+        };
+        load(J0);
+        for (int32_t J = J0; J < J1; ++J) {
+            asm volatile("" ::: "memory");   // x of the tile rows is read from LDS for every tile: no registers for it
+            MV cur[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) cur[i] = t[i];
+            V2 xj[NC];
+            const int64_t n = int64_t(J) * TB + lane;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                xj[c] = V2{ 0, 0 };
+                if (n < N) xj[c] = x[c][n];
+            }
+            if (J + 1 < J1) load(J + 1);
+            T car[NC], cai[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) car[c] = cai[c] = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const T zr = T(cur[i].x), zi = CONJ ? -T(cur[i].y) : T(cur[i].y);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const V2 xi = sx[wave * 8 + i][c];
+                    cmad(rar[i][c], rai[i][c], zr, zi, xj[c].x, xj[c].y);
+                    cmad(car[c], cai[c], zr, zi, xi.x, xi.y);
+                }
+            }
+            if (J != I) {   // uniform over the block
+                const int par = (J - J0) & 1;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) red[par][c][wave][lane] = V2{ car[c], cai[c] };
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    if (wave == ((J - J0 + c) & 7) && live[c]) {
+                        V2 a = red[par][c][0][lane];
+#pragma unroll
+                        for (int w = 1; w < 8; ++w) a += red[par][c][w][lane];
+                        pv[c][(seg[J] + I) * TB + lane] = a;
+                    }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            T pr[8], pi[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { pr[i] = rar[i][c]; pi[i] = rai[i][c]; }
+            wave_sum8(pr, pi);
+            if ((lane & 7) == 0 && live[c])
+                pv[c][(seg[I] + I + u - unit_ptr[I]) * TB + wave * 8 + (lane >> 3)] = V2{ pr[0], pi[0] };
+        }
     }
 }
 
@@ -910,7 +1045,27 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
     // non-temporal tile loads for the FP64 matrix, cached loads for the FP32
     // one (measured: 92 vs 144 us, 52 vs 47 us at N = 7680)
     constexpr bool NT = sizeof(M) == 8;
-    if (sym_prefetch())
+    // Several vectors share the tile reads in groups of up to 3 (FP64 vectors; 4
+    // spill) or 4, as even as they come.  A matrix with fewer blocks than two per CU
+    // over all vectors stays in the caches, and one block per vector fills more CUs
+    // (480 unknowns, 16 vectors: 16 us either way; 1152: 31 against 29 us).
+    constexpr int MAXNC = sizeof(T) == 8 ? 3 : 4;
+    auto several = [&](auto kern, int nc) {
+        const int64_t G = (R + nc - 1) / nc;
+        hipLaunchKernelGGL(kern, dim3(unsigned((pk.nruns + 7) / 8 * 8 * G)), dim3(512), 0, s, int(pk.nruns), (const M *)Z,
+                           pk.N, pk.nT, pk.units, pk.unit_ptr, pk.run_ptr, pk.seg, pk.nslots, int(G), R, (const T *)X, ldx,
+                           (T *)part, skip, sks);
+    };
+    if (R > 1 && pk.nruns * R >= 512) {
+        const int64_t G = (R + MAXNC - 1) / MAXNC, nc = (R + G - 1) / G;
+        // a matrix beyond the 256 MB last-level cache is streamed past it (7680
+        // unknowns, FP64, 6 vectors: 179 against 226 us; 5202, within it: 107 against 86)
+        const bool stream = pk.ntiles * TB * TB * int64_t(2 * sizeof(M)) > (int64_t(256) << 20);
+        if (nc == 2) stream ? several(k_sym_tiles_n<M, T, CONJ, 2, true>, 2) : several(k_sym_tiles_n<M, T, CONJ, 2, false>, 2);
+        else if (nc == 3) stream ? several(k_sym_tiles_n<M, T, CONJ, 3, true>, 3) : several(k_sym_tiles_n<M, T, CONJ, 3, false>, 3);
+        else if constexpr (MAXNC == 4)
+            stream ? several(k_sym_tiles_n<M, T, CONJ, 4, true>, 4) : several(k_sym_tiles_n<M, T, CONJ, 4, false>, 4);
+    } else if (sym_prefetch())
         hipLaunchKernelGGL((k_sym_tiles<M, T, CONJ, true, NT>), grid, dim3(256), 0, s, (const M *)Z, pk.N, pk.nT,
                            pk.units, pk.unit_ptr, pk.run_ptr, pk.seg, pk.nslots, (const T *)X, ldx, (T *)part,
                            skip, sks);
