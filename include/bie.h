@@ -102,12 +102,12 @@ void bie_op_destroy(bie_op *op);
  * leaves) over the pairs of far leaf cubes; N holds the entries T_mn between
  * the RWG functions of near leaf cubes (index distance <= 1), computed as the
  * dense fill computes them (Radon 7-point rule on both triangles, the singular
- * treatment on the pairs flagged by near_factor, as bie_op_create) and kept in
- * CSR.  The operator serves bie_apply (complex128, no conjugate), bie_solve
+ * treatment on the pairs flagged by near_factor, as bie_op_create) and kept row by
+ * row, the columns once per cube.  The operator serves bie_apply (complex128, no conjugate), bie_solve
  * (GMRES, precision 0, SCC, no preconditioner), bie_rhs_planewave, bie_farfield,
  * bie_rcs and the far-field entry points; the calls that need a stored matrix
  * (bie_op_matrix, the allocation-free product, batched solves, the Calderon
- * preconditioner, block GMRES, CGNR, RSCC) return BIE_EINVAL.  Memory: 20 B per
+ * preconditioner, block GMRES, CGNR, RSCC) return BIE_EINVAL.  Memory: 16 B per
  * near entry, 144 B per flagged pair, and the far field's. */
 typedef struct {
     double box;            /* leaf cube side (m) */
@@ -491,8 +491,8 @@ void bie_far_destroy(bie_far *far);
  * the test functions.  The product covers exactly the pairs of far leaf cubes,
  * the same set as bie_far with the same box.  p odd (1, 3, 5); at most 18
  * equidistant splines and 16 interpolation points per axis on any level.
- * Memory per level: about 4 (2 L^3 + 2 n^3 + nst^3) x 16 B per cube (L = 16 or
- * 32, the FFT size) plus L^3 x 16 B per distinct cube offset. */
+ * Memory per level: about 8 (L^3 + n^3) x 16 B per cube (L = 2 nst - 1 points of
+ * the transforms per axis) plus L^3 x 16 B per distinct cube offset up to signs. */
 typedef struct bie_farml bie_farml;
 typedef struct {
     double box;            /* leaf cube side (m), > 0 */

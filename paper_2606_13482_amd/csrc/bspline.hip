@@ -651,186 +651,321 @@ void far_destroy(bie_far *f) { delete f; }
 // Product y = Z~_far x, Z~_far covering the pairs of far leaf boxes:
 //   leaf moments     M_0[X] = sum_{m in X} x_m m_eq[m]  (equidistant splines),
 //   upward           M_l[P] = sum_{children X} (C_x (x) C_y (x) C_z) M_l-1[X],
-//   transform        M~_l = (A (x) A (x) A) M_l,  A = B_stab^-1 C_stab,
-//   translation      Z~_l[X] = w_d sum_{Y in IL_l(X)} G_XY M~_l[Y] by FFT: G_XY
-//                    is three-level Toeplitz (Sec. III-C), its symbol K_o one
-//                    array per box offset o, so Z^_X = sum_Y K^_o . M^_Y per
-//                    frequency (linear convolution in L^3 >= (2 nst - 1)^3),
-//   back             L_l[X] = (A^T)^(x)3 Z~_l[X] + (C^T)^(x)3 L_l+1[parent X],
+//   spectra          M^_l = (W (x) W (x) W) M_l,  W = DFT_L [A; 0],  A = B_stab^-1 C_stab,
+//   translation      Z^_l[X] = sum_{Y in IL_l(X)} K^_XY . M^_l[Y] per frequency: G_XY is
+//                    three-level Toeplitz (Sec. III-C), its symbol K^_o one array
+//                    per box offset o (linear convolution in L = 2 nst - 1 per axis),
+//   back             L_l[X] = w_d (V (x) V (x) V) Z^_l[X] + (C^T)^(x)3 L_l+1[parent X],
+//                    V = A^T [DFT_L^-1]_{0..nst-1},
 //   test functions   y_m = sum_d m_eq[m][d] . L_0[box m][d].
 // IL_l(X): boxes Y with Chebyshev index distance > 1 whose parents are within
 // distance 1 (at the top level every far box); w = jk for the three vector
 // parts, 1/(jk) for the divergence part.
+//
+// The Fourier transforms are products with W and V: the axes are short (n <= 18
+// splines, L <= 31), so a matrix of L x n complex numbers does the stabilising
+// transformation, the padding and the transform of an axis in one pass over LDS, and
+// L needs no round size (25 instead of 32 points at 13 splines: 0.48 of the volume
+// that every translation goes through).  K^_o is kept for offsets without negative
+// parts; a reversed component reverses its frequency axis.
 // ============================================================================
 namespace {
 
-constexpr int MLT = 18;                                    // most equidistant splines per axis, any level
-constexpr int MLQ = (MLT * MLT * MLT + 255) / 256;         // output entries per thread of k_ml_tensor
+constexpr int MLT = 18;   // most equidistant splines per axis, any level
+constexpr int AT = 4;     // output planes per block of k_ml_map
+__host__ __device__ constexpr int pad4(int n) { return (n + 3) / 4 * 4; }
 
 // out[ob] (=, or += if acc) sum_{t in ptr[ob] .. ptr[ob+1])
-//     (P_bx (x) P_by (x) P_bz) in[box[t]],  P_0 = m0, P_1 = m1 (nout x nin),
-// b = the child bits of entry t (x: 4, y: 2, z: 1; none if bits is null);
-// per box 4 complex components of nin^3 (nout^3) entries; block (ob, 2 d + part).
-__global__ __launch_bounds__(256) void k_ml_tensor(int nin, int nout, const double *__restrict__ m0,
-                                                   const double *__restrict__ m1, const int32_t *__restrict__ ptr,
-                                                   const int32_t *__restrict__ box, const int32_t *__restrict__ bits,
-                                                   const double *__restrict__ in, double *__restrict__ out, int acc)
+//     (P_bx (x) P_by (x) P_bz) in[box[t]],  P_0 = m0, P_1 = m1 (nout x nin, stored
+// [nin][pad4(nout)]: one scalar load fetches the entries of BG outputs),
+// per box 4 complex components of nin^3 (nout^3) entries; CW: complex matrices.
+// Block (ob, d, planes AT blockIdx.z ..): x first, into AT planes of nin^2 in LDS,
+// then y and z.  A wave holds the matrix entries of BG outputs in scalar registers
+// and its lanes the (plane, line) pairs, so one LDS read feeds BG complex products.
+// ptr null: box ob alone.
+template <bool CW>
+struct MapEl;
+template <>
+struct MapEl<true> {
+    using type = double2;
+};
+template <>
+struct MapEl<false> {
+    using type = double;
+};
+__device__ __forceinline__ void map_mad(double2 &a, const double2 &w, const double2 &v)
 {
-    __shared__ double b0[MLT * MLT * MLT], b1[MLT * MLT * MLT], b2[MLT * MLT * MLT];
+    a.x = __builtin_fma(w.x, v.x, a.x);
+    a.x = __builtin_fma(-w.y, v.y, a.x);
+    a.y = __builtin_fma(w.x, v.y, a.y);
+    a.y = __builtin_fma(w.y, v.x, a.y);
+}
+__device__ __forceinline__ void map_mad(double2 &a, const double &w, const double2 &v)
+{
+    a.x = __builtin_fma(w, v.x, a.x);
+    a.y = __builtin_fma(w, v.y, a.y);
+}
+
+template <bool CW>
+__global__ __launch_bounds__(256) void k_ml_map(int nin, int nout, const typename MapEl<CW>::type *__restrict__ m0,
+                                                const typename MapEl<CW>::type *__restrict__ m1,
+                                                const int32_t *__restrict__ ptr, const int32_t *__restrict__ box,
+                                                const int32_t *__restrict__ bits, const double2 *__restrict__ in,
+                                                double2 *__restrict__ out, int acc)
+{
+    using El = typename MapEl<CW>::type;
+    constexpr int BG = AT;
+    extern __shared__ double2 lds[];
     const int64_t ob = blockIdx.x;
-    const int d = blockIdx.y >> 1, part = blockIdx.y & 1;
-    const int tid = threadIdx.x;
-    const int nin2 = nin * nin, nin3 = nin2 * nin, nout3 = nout * nout * nout;
-    double a[MLQ];
-#pragma unroll
-    for (int q = 0; q < MLQ; ++q) a[q] = 0.0;
-    for (int32_t t = ptr[ob]; t < ptr[ob + 1]; ++t) {
-        const int32_t ib = box[t];
+    const int d = blockIdx.y, a0 = blockIdx.z * AT, na = min(AT, nout - a0);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n2 = nin * nin, np = nin | 1, mo = pad4(nout);   // odd row lengths: rows start in different LDS banks
+    double2 *T = lds;                    // [AT][nin][nin]
+    double2 *U = lds + AT * n2;          // [AT][nout][np]
+    double2 *dst = out + (ob * 4 + d) * int64_t(nout) * nout * nout + int64_t(a0) * nout * nout;
+    const int32_t t0 = ptr ? ptr[ob] : 0, t1 = ptr ? ptr[ob + 1] : 1;
+    for (int32_t t = t0; t < t1; ++t) {
+        const int64_t ib = ptr ? box[t] : ob;
         const int bt = bits ? bits[t] : 0;
-        const double *Px = (bt & 4) ? m1 : m0, *Py = (bt & 2) ? m1 : m0, *Pz = (bt & 1) ? m1 : m0;
-        __syncthreads();
-        const double *src = in + 2 * ((int64_t(ib) * 4 + d) * nin3) + part;
-        for (int e = tid; e < nin3; e += 256) b0[e] = src[2 * int64_t(e)];
-        __syncthreads();
-        for (int e = tid; e < nout * nin2; e += 256) {   // along x
-            const int i = e / nin2, rr = e % nin2;
-            double v = 0.0;
-            for (int q = 0; q < nin; ++q) v += Px[i * nin + q] * b0[q * nin2 + rr];
-            b1[e] = v;
+        const El *Px = (bt & 4) ? m1 : m0, *Py = (bt & 2) ? m1 : m0, *Pz = (bt & 1) ? m1 : m0;
+        const double2 *src = in + (ib * 4 + d) * int64_t(n2) * nin;
+        __syncthreads();   // the previous entry's planes are read
+        for (int e = tid; e < n2; e += 256) {
+            double2 s[AT];
+#pragma unroll
+            for (int q = 0; q < AT; ++q) s[q] = make_double2(0.0, 0.0);
+#pragma unroll 4
+            for (int i = 0; i < nin; ++i) {
+                const double2 v = src[i * n2 + e];
+#pragma unroll
+                for (int q = 0; q < AT; ++q) map_mad(s[q], Px[i * mo + a0 + q], v);
+            }
+#pragma unroll
+            for (int q = 0; q < AT; ++q) T[q * n2 + e] = s[q];
         }
         __syncthreads();
-        for (int e = tid; e < nout * nout * nin; e += 256) {   // along y
-            const int i = e / (nout * nin), j = (e / nin) % nout, z = e % nin;
-            double v = 0.0;
-            for (int q = 0; q < nin; ++q) v += Py[j * nin + q] * b1[(i * nin + q) * nin + z];
-            b2[e] = v;
-        }
+        for (int b0 = w * BG; b0 < nout; b0 += 4 * BG)   // along y: lanes (plane, z)
+            for (int e = lane; e < na * nin; e += 64) {
+                const int q = e / nin, z = e % nin;
+                double2 s[BG];
+#pragma unroll
+                for (int g = 0; g < BG; ++g) s[g] = make_double2(0.0, 0.0);
+#pragma unroll 4
+                for (int j = 0; j < nin; ++j) {
+                    const double2 v = T[q * n2 + j * nin + z];
+#pragma unroll
+                    for (int g = 0; g < BG; ++g) map_mad(s[g], Py[j * mo + b0 + g], v);
+                }
+#pragma unroll
+                for (int g = 0; g < BG; ++g)
+                    if (b0 + g < nout) U[(q * nout + b0 + g) * np + z] = s[g];
+            }
         __syncthreads();
+        for (int c0 = w * BG; c0 < nout; c0 += 4 * BG)   // along z: lanes (plane, y)
+            for (int e = lane; e < na * nout; e += 64) {
+                double2 s[BG];
 #pragma unroll
-        for (int q = 0; q < MLQ; ++q) {   // along z
-            const int e = tid + 256 * q;
-            if (e >= nout3) break;
-            const int ij = e / nout, k = e % nout;
-            double v = 0.0;
-            for (int z = 0; z < nin; ++z) v += Pz[k * nin + z] * b2[ij * nin + z];
-            a[q] += v;
-        }
-    }
-    double *dst = out + 2 * ((ob * 4 + d) * nout3) + part;
+                for (int g = 0; g < BG; ++g) s[g] = make_double2(0.0, 0.0);
+#pragma unroll 4
+                for (int z = 0; z < nin; ++z) {
+                    const double2 v = U[e * np + z];
 #pragma unroll
-    for (int q = 0; q < MLQ; ++q) {
-        const int e = tid + 256 * q;
-        if (e >= nout3) break;
-        dst[2 * int64_t(e)] = acc ? dst[2 * int64_t(e)] + a[q] : a[q];
-    }
-}
-
-// F[vol] = Mt[vol] (nst^3) zero-padded to L^3.
-__global__ __launch_bounds__(256) void k_ml_pad(int nst, int L, int64_t nvol, const double2 *__restrict__ Mt,
-                                                double2 *__restrict__ F)
-{
-    const int64_t L3 = int64_t(L) * L * L, total = nvol * L3;
-    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
-        const int64_t v = e / L3;
-        const int r = int(e % L3), i = r / (L * L), j = (r / L) % L, k = r % L;
-        F[e] = (i < nst && j < nst && k < nst) ? Mt[v * nst * nst * nst + (i * nst + j) * nst + k]
-                                               : make_double2(0.0, 0.0);
-    }
-}
-
-// Zt[vol][i] = w_d F[vol][i] / L^3 for i in [0, nst)^3 (d = vol % 4).
-__global__ __launch_bounds__(256) void k_ml_crop(int nst, int L, int64_t nvol, double k,
-                                                 const double2 *__restrict__ F, double2 *__restrict__ Zt)
-{
-    const int64_t n3 = int64_t(nst) * nst * nst, total = nvol * n3;
-    const double sc = 1.0 / (double(L) * L * L);
-    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
-        const int64_t v = e / n3;
-        const int r = int(e % n3), i = r / (nst * nst), j = (r / nst) % nst, q = r % nst;
-        const double2 f = F[v * L * L * L + (i * L + j) * L + q];
-        const double fr = f.x * sc, fi = f.y * sc;
-        // jk (a + jb) = -k b + j k a;  (a + jb) / (jk) = b / k - j a / k
-        Zt[e] = (v % 4) < 3 ? make_double2(-k * fi, k * fr) : make_double2(fi / k, -fr / k);
-    }
-}
-
-// In-place 1D FFTs of length L along one axis of nvol L^3 volumes (z fastest),
-// one line per thread: radix 2, input in bit-reversed order, twiddles
-// tw[j] = exp(-2 pi i j / L) (conjugated for the inverse, unscaled).
-template <int L>
-__global__ __launch_bounds__(256) void k_ml_fft(double2 *__restrict__ data, int64_t nvol, int axis, int inverse,
-                                                const double2 *__restrict__ tw)
-{
-    const int64_t line = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (line >= nvol * L * L) return;
-    const int64_t vol = line / (L * L);
-    const int q = int(line % (L * L));
-    int64_t base, stride;
-    if (axis == 0) {
-        base = vol * L * L * L + q;
-        stride = L * L;
-    } else if (axis == 1) {
-        base = vol * L * L * L + int64_t(q / L) * L * L + q % L;
-        stride = L;
-    } else {
-        base = vol * L * L * L + int64_t(q) * L;
-        stride = 1;
-    }
-    constexpr int LB = L == 16 ? 4 : 5;
-    double2 v[L];
+                    for (int g = 0; g < BG; ++g) map_mad(s[g], Pz[z * mo + c0 + g], v);
+                }
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-        int r = 0;
-#pragma unroll
-        for (int b = 0; b < LB; ++b) r |= ((i >> b) & 1) << (LB - 1 - b);
-        v[r] = data[base + i * stride];
-    }
-    const double sg = inverse ? -1.0 : 1.0;
-#pragma unroll
-    for (int len = 2; len <= L; len <<= 1) {
-        const int half = len / 2;
-#pragma unroll
-        for (int s0 = 0; s0 < L; s0 += len)
-#pragma unroll
-            for (int j = 0; j < half; ++j) {
-                const double2 w = tw[j * (L / len)];
-                const double wr = w.x, wi = sg * w.y;
-                const double2 u = v[s0 + j], t0 = v[s0 + j + half];
-                const double tr = wr * t0.x - wi * t0.y, ti = wr * t0.y + wi * t0.x;
-                v[s0 + j] = make_double2(u.x + tr, u.y + ti);
-                v[s0 + j + half] = make_double2(u.x - tr, u.y - ti);
+                for (int g = 0; g < BG; ++g)
+                    if (c0 + g < nout) {   // the entry's own lane: the next t adds to it
+                        double2 *o = dst + int64_t(e) * nout + c0 + g;
+                        if (acc || t > t0) {
+                            s[g].x += o->x;
+                            s[g].y += o->y;
+                        }
+                        *o = s[g];
+                    }
             }
     }
-#pragma unroll
-    for (int i = 0; i < L; ++i) data[base + i * stride] = v[i];
 }
 
-// Fz[X][d][f] = sum_{t in ptr[X] .. ptr[X+1]) Kh[off[t]][f] F[src[t]][d][f]
-__global__ __launch_bounds__(256) void k_ml_accum(int64_t L3, const int32_t *__restrict__ ptr,
-                                                  const int32_t *__restrict__ src, const int32_t *__restrict__ off,
+// out[box] = w_d (V (x) V (x) V) in[box] from L^3 frequencies to n^3 splines (V stored
+// [L][MAXN_], MAXN_ >= n).  Block (box, d): the input's planes in groups of SL through LDS (z, then
+// y), each plane's n x n result added to the lane's n outputs along x in registers,
+// so that the large side is read once.
+constexpr int SL = 4;
+template <int MAXN_>
+__global__ __launch_bounds__(384) void k_ml_back(int L, int n, double k, const double2 *__restrict__ V,
+                                                 const double2 *__restrict__ in, double2 *__restrict__ out)
+{
+    constexpr int BG = 3;   // 6 waves x 3 outputs cover 18
+    extern __shared__ double2 lds[];
+    const int64_t box = blockIdx.x;
+    const int d = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int Lp = L, np = n | 1, n2 = n * n;   // odd row lengths (L = 2 nst - 1)
+    double2 *S = lds;                      // [SL][L][L]
+    double2 *U = S + SL * L * Lp;          // [SL][L][np]
+    double2 *Y = S;                        // [SL][n][n], over S
+    const double2 *src = in + (box * 4 + d) * int64_t(L) * L * L;
+    double2 a[MAXN_];
+#pragma unroll
+    for (int i = 0; i < MAXN_; ++i) a[i] = make_double2(0.0, 0.0);
+    for (int x0 = 0; x0 < L; x0 += SL) {
+        const int ns = min(SL, L - x0);
+        __syncthreads();
+        for (int e = tid; e < ns * L * L; e += 384) S[e] = src[int64_t(x0) * L * L + e];
+        __syncthreads();
+        const int c0 = w * BG;
+        if (c0 < n)
+            for (int e = lane; e < ns * L; e += 64) {   // along z: lanes (plane, y)
+                double2 s[BG];
+#pragma unroll
+                for (int g = 0; g < BG; ++g) s[g] = make_double2(0.0, 0.0);
+#pragma unroll 4
+                for (int z = 0; z < L; ++z) {
+                    const double2 v = S[e * Lp + z];
+#pragma unroll
+                    for (int g = 0; g < BG; ++g) map_mad(s[g], V[z * MAXN_ + c0 + g], v);
+                }
+#pragma unroll
+                for (int g = 0; g < BG; ++g)
+                    if (c0 + g < n) U[e * np + c0 + g] = s[g];
+            }
+        __syncthreads();
+        if (c0 < n)
+            for (int e = lane; e < ns * n; e += 64) {   // along y: lanes (plane, z)
+                const int q = e / n, z = e % n;
+                double2 s[BG];
+#pragma unroll
+                for (int g = 0; g < BG; ++g) s[g] = make_double2(0.0, 0.0);
+#pragma unroll 4
+                for (int y = 0; y < L; ++y) {
+                    const double2 v = U[(q * L + y) * np + z];
+#pragma unroll
+                    for (int g = 0; g < BG; ++g) map_mad(s[g], V[y * MAXN_ + c0 + g], v);
+                }
+#pragma unroll
+                for (int g = 0; g < BG; ++g)
+                    if (c0 + g < n) Y[q * n2 + (c0 + g) * n + z] = s[g];
+            }
+        __syncthreads();
+        if (tid < n2)
+            for (int q = 0; q < ns; ++q) {
+                const double2 v = Y[q * n2 + tid];
+#pragma unroll
+                for (int i = 0; i < MAXN_; ++i) map_mad(a[i], V[(x0 + q) * MAXN_ + i], v);
+            }
+    }
+    if (tid < n2) {
+        double2 *dst = out + (box * 4 + d) * int64_t(n) * n2 + tid;
+#pragma unroll
+        for (int i = 0; i < MAXN_; ++i)
+            if (i < n)   // jk (a + jb) = -k b + j k a;  (a + jb) / (jk) = b / k - j a / k
+                dst[i * n2] = d < 3 ? make_double2(-k * a[i].y, k * a[i].x) : make_double2(a[i].y / k, -a[i].x / k);
+    }
+}
+
+// One axis of the symbols' transform: out[..f..] = sum_i tw[(f i) mod L] in[..i..]
+// (stride L^2, L or 1); once per operator.
+__global__ __launch_bounds__(256) void k_ml_dft(int L, int64_t total, int64_t stride, const double2 *__restrict__ tw,
+                                                const double2 *__restrict__ in, double2 *__restrict__ out)
+{
+    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
+        const int f = int(e / stride % L);
+        const double2 *src = in + (e - f * stride);
+        double2 s = make_double2(0.0, 0.0);
+        int p = 0;
+        for (int i = 0; i < L; ++i) {
+            map_mad(s, tw[p], src[i * stride]);
+            p += f;
+            if (p >= L) p -= L;
+        }
+        out[e] = s;
+    }
+}
+
+// Fz[X][d][f] = sum over the sources Y of X of K^_XY[f] F[Y][d][f].  A wave takes 64
+// frequencies of TX target boxes, next to each other in Morton order: the children
+// of one parent share most of their sources, so a source's four values serve up to TX
+// products.  Group g has the targets gdst[TX g] .. (-1: none) and the entries
+// gent[8 gptr[g]] ..: a source and per target the code 8 (symbol) + (reversed axes),
+// or -1 where the pair is not translated.  The next source's values and symbols are
+// loaded during the current one's products, and the entry after it before those.  Blocks of one frequency range follow
+// each other on one XCD: its symbols and sources (0.6 MB at 100 boxes) stay in that
+// L2, where one block per target and 256 frequencies read 80 bytes a product from
+// the last-level cache (30720 unknowns, two levels: 2370 -> 535 us, of it the smaller
+// transforms a factor 1.7; 16 TB/s from the L2s, 82 % hits, and a fourth wave per
+// SIMD doubles the time).
+constexpr int TX = 4;
+__global__ __launch_bounds__(256) void k_ml_accum(int L, const int32_t *__restrict__ gdst, int ngroup, int nfc, int ngb,
+                                                  const int32_t *__restrict__ gptr, const int32_t *__restrict__ gent,
                                                   const double2 *__restrict__ Kh, const double2 *__restrict__ F,
                                                   double2 *__restrict__ Fz)
 {
-    const int64_t X = blockIdx.x;
-    const int64_t f = int64_t(blockIdx.y) * 256 + threadIdx.x;
-    if (f >= L3) return;
-    double2 a[4] = { { 0, 0 }, { 0, 0 }, { 0, 0 }, { 0, 0 } };
-    for (int32_t t = ptr[X]; t < ptr[X + 1]; ++t) {
-        const double2 kk = Kh[int64_t(off[t]) * L3 + f];
-        const double2 *m = F + int64_t(src[t]) * 4 * L3 + f;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = blockIdx.x / 8, fc = r / ngb * 8 + blockIdx.x % 8, g = r % ngb * 4 + w;
+    if (fc >= nfc || g >= ngroup) return;
+    const int L2 = L * L, L3 = L2 * L;
+    const int f = min(fc * 64 + lane, L3 - 1);   // the last range repeats its last frequency and does not store it
+    const int fx = f / L2, fy = f / L % L, fz = f % L;
+    const int x0 = fx * L2, x1 = (fx ? L - fx : 0) * L2, y0 = fy * L, y1 = (fy ? L - fy : 0) * L, z0 = fz,
+              z1 = fz ? L - fz : 0;
+    double2 a[TX][4], v[4], kk[TX], vn[4], kn[TX];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const double2 v = m[d * L3];
-            a[d].x += kk.x * v.x - kk.y * v.y;
-            a[d].y += kk.x * v.y + kk.y * v.x;
+    for (int t = 0; t < TX; ++t)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) a[t][d] = make_double2(0.0, 0.0);
+    const int32_t e0 = gptr[g], e1 = gptr[g + 1];
+    struct Entry {
+        int32_t src, code[TX];
+    };
+    const auto entry = [&](int32_t e) {
+        Entry q;
+        const int32_t *p = gent + 8 * int64_t(min(e, e1 - 1));
+        q.src = p[0];
+#pragma unroll
+        for (int t = 0; t < TX; ++t) q.code[t] = p[1 + t];
+        return q;
+    };
+    const auto load = [&](const Entry &q, double2 (&vv)[4], double2 (&kv)[TX]) {
+        const double2 *m = F + int64_t(q.src) * 4 * L3 + f;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) vv[d] = m[int64_t(d) * L3];
+#pragma unroll
+        for (int t = 0; t < TX; ++t) {
+            const int32_t c = max(q.code[t], 0);
+            kv[t] = Kh[int64_t(c >> 3) * L3 + ((c & 4) ? x1 : x0) + ((c & 2) ? y1 : y0) + ((c & 1) ? z1 : z0)];
+        }
+    };
+    if (e0 < e1) {
+        Entry cur = entry(e0), nxt = entry(e0 + 1);
+        load(cur, v, kk);
+        for (int32_t e = e0; e < e1; ++e) {
+            const Entry after = entry(e + 2);
+            if (e + 1 < e1) load(nxt, vn, kn);
+#pragma unroll
+            for (int t = 0; t < TX; ++t)
+                if (cur.code[t] >= 0)   // uniform
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) map_mad(a[t][d], kk[t], v[d]);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) v[d] = vn[d];
+#pragma unroll
+            for (int t = 0; t < TX; ++t) kk[t] = kn[t];
+            cur = nxt;
+            nxt = after;
         }
     }
+    if (fc * 64 + lane >= L3) return;
 #pragma unroll
-    for (int d = 0; d < 4; ++d) Fz[(X * 4 + d) * L3 + f] = a[d];
+    for (int t = 0; t < TX; ++t) {
+        const int64_t X = gdst[g * TX + t];
+        if (X >= 0)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) Fz[(X * 4 + d) * L3 + f] = a[t][d];
+    }
 }
 
-// K_o on the circular grid: entry (i, j, k) holds g(h |o + (di, dj, dk)|) with
-// di = i (i < nst) or i - L (i > L - nst), else 0.
+// K_o on the circular grid of L = 2 nst - 1 points: entry (i, j, k) holds
+// g(h |o + (di, dj, dk)|) with di = i (i < nst) or i - L.
 __global__ __launch_bounds__(256) void k_ml_ktab(int L, int nst, int64_t noff, const int32_t *__restrict__ offs,
                                                  double h, double k, double2 *__restrict__ K)
 {
@@ -838,53 +973,199 @@ __global__ __launch_bounds__(256) void k_ml_ktab(int L, int nst, int64_t noff, c
     for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
         const int64_t o = e / L3;
         const int r = int(e % L3), idx[3] = { r / (L * L), (r / L) % L, r % L };
-        double2 val = make_double2(0.0, 0.0);
-        bool ok = true;
         double dd[3];
-        for (int a = 0; a < 3; ++a) {
-            const int i = idx[a];
-            const int di = i < nst ? i : (i > L - nst ? i - L : 0);
-            ok = ok && (i < nst || i > L - nst);
-            dd[a] = double(offs[3 * o + a] + di);
-        }
-        if (ok) {
-            const double R = h * sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
-            double sn, cs;
-            sincos(k * R, &sn, &cs);
-            const double g = 1.0 / (4.0 * M_PI * R);
-            val = make_double2(g * cs, -g * sn);
-        }
-        K[e] = val;
+        for (int a = 0; a < 3; ++a) dd[a] = double(offs[3 * o + a] + (idx[a] < nst ? idx[a] : idx[a] - L));
+        const double R = h * sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
+        double sn, cs;
+        sincos(k * R, &sn, &cs);
+        const double g = 1.0 / (4.0 * M_PI * R);
+        K[e] = make_double2(g * cs, -g * sn);
     }
 }
 
-// y_m = sum_d sum_e m_eq[m][d][e] L_0[box m][d][e]
-__global__ __launch_bounds__(256) void k_ml_disaggregate(int n3, int64_t N, const int32_t *__restrict__ box_of,
-                                                         const double *__restrict__ meq, const double2 *__restrict__ Lq,
-                                                         double2 *__restrict__ Y)
+// Leaf moments.  A function's points touch p + 1 splines per axis and span, so its
+// moments fill a small block of the n^3 splines (216 to 512 of 1000 to 1728): first
+// spline and length per axis, then 4 components of that block, one after another.
+struct MlBlock {
+    int64_t at;              // its first moment
+    int16_t lo[3], len[3];   // first spline and splines per axis
+    int32_t pad;
+    __host__ __device__ int size() const { return int(len[0]) * len[1] * len[2]; }
+    // spline of the block's entry k among the n^3 (quotients of numbers below 2^13 by
+    // way of FP32: an integer division is ten times as many instructions)
+    __device__ int spline(int k, int n) const
+    {
+        const int l2 = len[2], r = int((float(k) + 0.5f) * __builtin_amdgcn_rcpf(float(l2)));
+        const int i = int((float(r) + 0.5f) * __builtin_amdgcn_rcpf(float(len[1])));
+        return ((lo[0] + i) * n + lo[1] + r - i * len[1]) * n + lo[2] + k - r * l2;
+    }
+};
+
+// splines touched by function m (at: left to the host)
+__global__ __launch_bounds__(256) void k_ml_extent(BsConst c, int64_t N, const int4 *__restrict__ rwg4,
+                                                   const double *__restrict__ cent, const double *__restrict__ loc,
+                                                   const double *__restrict__ box_lo, const int32_t *__restrict__ box_of,
+                                                   MlBlock *__restrict__ blk)
+{
+    const int64_t m = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (m >= N) return;
+    const int4 e = rwg4[m];
+    const double *lo = box_lo + 3 * int64_t(box_of[m]);
+    MlBlock b{};
+    for (int ax = 0; ax < 3; ++ax) {
+        int s0 = c.n, s1 = 0;
+        for (int q = 0; q < NPT; ++q) {
+            const int t = q < bie::QPTS ? e.x : e.y;
+            const double x = cent[3 * t + ax] + loc[(int64_t(t) * bie::QPTS + q % bie::QPTS) * 3 + ax];
+            double Nv[MAXP + 1];
+            const int span = nonzero_splines(c.knots, c.n, c.p, fmin(fmax((x - lo[ax]) / c.a, c.lo), c.hi), Nv);
+            s0 = min(s0, span);
+            s1 = max(s1, span);
+        }
+        b.lo[ax] = int16_t(s0 - c.p);
+        b.len[ax] = int16_t(s1 - s0 + c.p + 1);
+    }
+    blk[m] = b;
+}
+
+// the block's moments: one block of threads per function
+__global__ __launch_bounds__(256) void k_ml_moments(BsConst c, const MlBlock *__restrict__ blk,
+                                                    const int4 *__restrict__ rwg4, const double *__restrict__ cent,
+                                                    const double *__restrict__ loc, const double *__restrict__ vfree,
+                                                    const double *__restrict__ qw, const double *__restrict__ box_lo,
+                                                    const int32_t *__restrict__ box_of, double *__restrict__ mt)
 {
     const int64_t m = blockIdx.x;
-    const double *mm = meq + m * 4 * int64_t(n3);
-    const double2 *l = Lq + int64_t(box_of[m]) * 4 * n3;
-    double sr = 0.0, si = 0.0;
-    for (int e = threadIdx.x; e < 4 * n3; e += 256) {
-        const double v = mm[e];
-        const double2 w = l[e];
-        sr += v * w.x;
-        si += v * w.y;
-    }
-    __shared__ double red[2][256];
-    red[0][threadIdx.x] = sr;
-    red[1][threadIdx.x] = si;
+    __shared__ double bt[NPT][3][MLT];
+    __shared__ double coef[NPT][4];
+    const int4 e = rwg4[m];
+    const MlBlock b = blk[m];
+    const double *lo = box_lo + 3 * int64_t(box_of[m]);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < NPT * 3 * MLT; i += 256) (&bt[0][0][0])[i] = 0.0;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (int(threadIdx.x) < o) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + o];
-            red[1][threadIdx.x] += red[1][threadIdx.x + o];
+    if (tid < NPT * 3) {
+        const int q = tid / 3, ax = tid % 3;
+        const int t = q < bie::QPTS ? e.x : e.y;
+        const double x = cent[3 * t + ax] + loc[(int64_t(t) * bie::QPTS + q % bie::QPTS) * 3 + ax];
+        double Nv[MAXP + 1];
+        const int span = nonzero_splines(c.knots, c.n, c.p, fmin(fmax((x - lo[ax]) / c.a, c.lo), c.hi), Nv);
+        for (int l = 0; l <= c.p; ++l) bt[q][ax][span - c.p + l - b.lo[ax]] = Nv[l];
+    } else if (tid >= 64 && tid < 64 + NPT) {
+        const int q = tid - 64;
+        const bool plus = q < bie::QPTS;
+        const int t = plus ? e.x : e.y, slot = plus ? e.z : e.w, qq = q % bie::QPTS;
+        const double sw = (plus ? 1.0 : -1.0) * qw[qq];
+        for (int d = 0; d < 3; ++d)
+            coef[q][d] = 0.5 * sw * (loc[(int64_t(t) * bie::QPTS + qq) * 3 + d] - vfree[int64_t(t) * 9 + slot * 3 + d]);
+        coef[q][3] = sw;
+    }
+    __syncthreads();
+    const int nk = b.size(), l2 = b.len[2], l12 = b.len[1] * l2;
+    double *o = mt + b.at;
+    for (int k = tid; k < nk; k += 256) {
+        const int k1 = k / l12, k2 = k / l2 % b.len[1], k3 = k % l2;
+        double s[4] = { 0.0, 0.0, 0.0, 0.0 };
+        for (int q = 0; q < NPT; ++q) {
+            const double v = bt[q][0][k1] * bt[q][1][k2] * bt[q][2][k3];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) s[d] += coef[q][d] * v;
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) o[d * nk + k] = s[d];
+    }
+}
+
+// M_0[Y][d] = sum of x_m m_eq[m][d] over the members m of cube Y.  Block (Y, d): the
+// cube's n^3 sums in LDS; the members' blocks are added one after another (a fixed
+// order), the moments of the next GP members loaded meanwhile.
+constexpr int GM = 64;   // members whose places and x are staged at a time
+constexpr int GP = 4;
+__global__ __launch_bounds__(256) void k_ml_gather(int n, const int32_t *__restrict__ mem_ptr,
+                                                   const int32_t *__restrict__ mem, const MlBlock *__restrict__ blk,
+                                                   const double *__restrict__ mt, const double2 *__restrict__ X,
+                                                   double2 *__restrict__ M)
+{
+    extern __shared__ double2 lds[];
+    __shared__ MlBlock sb[GM];
+    __shared__ double2 sx[GM];
+    const int64_t Y = blockIdx.x;
+    const int d = blockIdx.y, tid = threadIdx.x, n3 = n * n * n;
+    for (int e = tid; e < n3; e += 256) lds[e] = make_double2(0.0, 0.0);
+    const int32_t b0 = mem_ptr[Y], b1 = mem_ptr[Y + 1];
+    for (int32_t c0 = b0; c0 < b1; c0 += GM) {
+        const int nc = min(GM, b1 - c0);
+        __syncthreads();
+        if (tid < nc) {
+            const int32_t m = mem[c0 + tid];
+            sb[tid] = blk[m];
+            sx[tid] = X[m];
         }
         __syncthreads();
+        double v[GP];   // this lane's first moment of members t, t + 1, ...
+        const auto load = [&](int t) {
+            const int nk = t < nc ? sb[t].size() : 0;
+            return tid < nk ? mt[sb[t].at + d * nk + tid] : 0.0;
+        };
+#pragma unroll
+        for (int u = 0; u < GP; ++u) v[u] = load(u);
+        for (int t0 = 0; t0 < nc; t0 += GP) {
+            double next[GP];
+#pragma unroll
+            for (int u = 0; u < GP; ++u) next[u] = load(t0 + GP + u);
+#pragma unroll
+            for (int u = 0; u < GP; ++u) {
+                const int t = t0 + u;
+                if (t >= nc) break;   // uniform
+                const MlBlock b = sb[t];
+                const double2 x = sx[t];
+                const int nk = b.size();
+                for (int k = tid; k < nk; k += 256) {
+                    const double c = k == tid ? v[u] : mt[b.at + d * nk + k];
+                    double2 &s = lds[b.spline(k, n)];
+                    s.x += c * x.x;
+                    s.y += c * x.y;
+                }
+                __syncthreads();   // the next member may add to the same sums
+            }
+#pragma unroll
+            for (int u = 0; u < GP; ++u) v[u] = next[u];
+        }
     }
-    if (threadIdx.x == 0) Y[m] = make_double2(red[0][0], red[1][0]);
+    __syncthreads();
+    double2 *out = M + (Y * 4 + d) * n3;
+    for (int e = tid; e < n3; e += 256) out[e] = lds[e];
+}
+
+// y_m = sum_d sum_e m_eq[m][d][e] L_0[box m][d][e], one wave per function
+__global__ __launch_bounds__(256) void k_ml_test(int n, int64_t N, const int32_t *__restrict__ box_of,
+                                                 const MlBlock *__restrict__ blk, const double *__restrict__ mt,
+                                                 const double2 *__restrict__ Lq, double2 *__restrict__ Y)
+{
+    const int64_t m = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (m >= N) return;
+    const MlBlock b = blk[m];
+    const int nk = b.size(), n3 = n * n * n;
+    const double *mm = mt + b.at;
+    const double2 *l = Lq + int64_t(box_of[m]) * 4 * n3;
+    double sr = 0.0, si = 0.0;
+    for (int k = lane; k < nk; k += 64) {
+        const int at = b.spline(k, n);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const double v = mm[d * nk + k];
+            const double2 q = l[d * n3 + at];
+            sr += v * q.x;
+            si += v * q.y;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sr += __shfl_xor(sr, o, 64);
+        si += __shfl_xor(si, o, 64);
+    }
+    if (lane == 0) Y[m] = make_double2(sr, si);
 }
 
 // Restriction of the parent's splines (knots u_par) to the child's interval
@@ -946,49 +1227,68 @@ std::vector<double> transpose(const std::vector<double> &M, int rows, int cols)
     return T;
 }
 
+// rows of a row-major matrix padded to pad4(cols) entries
+std::vector<double> padded(const std::vector<double> &M, int rows, int cols)
+{
+    std::vector<double> P(size_t(rows) * pad4(cols), 0.0);
+    for (int i = 0; i < rows; ++i)
+        for (int j = 0; j < cols; ++j) P[size_t(i) * pad4(cols) + j] = M[size_t(i) * cols + j];
+    return P;
+}
+
 struct MlLevel {
     int s = 0, sb = 0, n = 0, nst = 0, L = 0;
     double a = 0.0, h = 0.0;
     int64_t nbox = 0, npairs = 0, noff = 0;
+    int ngroup = 0;
     std::vector<int32_t> h_ijk;
-    double *A = nullptr, *AT = nullptr, *C[2] = { nullptr, nullptr }, *CT[2] = { nullptr, nullptr };
-    int32_t *self_ptr = nullptr, *self_box = nullptr;
+    double2 *W = nullptr, *V = nullptr;                                     // see k_ml_map, k_ml_back
+    double *C[2] = { nullptr, nullptr }, *CT[2] = { nullptr, nullptr };
     int32_t *kid_ptr = nullptr, *kid_box = nullptr, *kid_bits = nullptr;    // children on the level below
     int32_t *par_ptr = nullptr, *par_box = nullptr, *par_bits = nullptr;    // parent on the level above
-    int32_t *il_ptr = nullptr, *il_src = nullptr, *il_off = nullptr;
-    double2 *Kh = nullptr, *tw = nullptr;
-    double2 *M = nullptr, *Mt = nullptr, *F = nullptr, *Fz = nullptr, *Lq = nullptr;
+    int32_t *gptr = nullptr, *gent = nullptr, *gdst = nullptr;   // translations, see k_ml_accum
+    double2 *Kh = nullptr;
+    double2 *M = nullptr, *F = nullptr, *Fz = nullptr, *Lq = nullptr;
     void free_all()
     {
-        for (void *p : { (void *)A, (void *)AT, (void *)C[0], (void *)C[1], (void *)CT[0], (void *)CT[1],
-                         (void *)self_ptr, (void *)self_box, (void *)kid_ptr, (void *)kid_box, (void *)kid_bits,
-                         (void *)par_ptr, (void *)par_box, (void *)par_bits, (void *)il_ptr, (void *)il_src,
-                         (void *)il_off, (void *)Kh, (void *)tw, (void *)M, (void *)Mt, (void *)F, (void *)Fz,
-                         (void *)Lq })
+        for (void *p : { (void *)W, (void *)V, (void *)C[0], (void *)C[1], (void *)CT[0], (void *)CT[1],
+                         (void *)kid_ptr, (void *)kid_box, (void *)kid_bits, (void *)par_ptr, (void *)par_box,
+                         (void *)par_bits, (void *)gptr, (void *)gent, (void *)gdst, (void *)Kh, (void *)M, (void *)F,
+                         (void *)Fz, (void *)Lq })
             if (p) (void)hipFree(p);
     }
 };
 
-void fft3(const MlLevel &lv, double2 *data, int64_t nvol, bool inverse, hipStream_t st)
+// launch with the dynamic LDS that the sizes need (beyond 64 KB it is asked for)
+template <typename K, typename... Args>
+void launch_lds(K kern, dim3 grid, dim3 block, size_t lds, hipStream_t st, Args... args)
 {
-    const int64_t lines = nvol * lv.L * lv.L;
-    const dim3 grid(unsigned((lines + 255) / 256));
-    for (int axis = 0; axis < 3; ++axis) {
-        if (lv.L == 16)
-            hipLaunchKernelGGL(k_ml_fft<16>, grid, dim3(256), 0, st, data, nvol, axis, int(inverse), (const double2 *)lv.tw);
-        else
-            hipLaunchKernelGGL(k_ml_fft<32>, grid, dim3(256), 0, st, data, nvol, axis, int(inverse), (const double2 *)lv.tw);
-    }
+    if (lds > (size_t(64) << 10))
+        BIE_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    int(lds)));
+    hipLaunchKernelGGL(kern, grid, block, lds, st, args...);
     BIE_HIP(hipGetLastError());
 }
 
-void tensor(int nin, int nout, const double *m0, const double *m1, const int32_t *ptr, const int32_t *box,
-            const int32_t *bits, const double2 *in, double2 *out, int64_t nout_boxes, bool acc, hipStream_t st)
+// nout_boxes boxes through k_ml_map
+template <bool CW, typename El>
+void map_boxes(int nin, int nout, const El *m0, const El *m1, const int32_t *ptr, const int32_t *box, const int32_t *bits,
+               const double2 *in, double2 *out, int64_t nout_boxes, bool acc, hipStream_t st)
 {
     if (nout_boxes == 0) return;
-    hipLaunchKernelGGL(k_ml_tensor, dim3(unsigned(nout_boxes), 8), dim3(256), 0, st, nin, nout, m0, m1, ptr, box, bits,
-                       (const double *)in, (double *)out, int(acc));
-    BIE_HIP(hipGetLastError());
+    const size_t lds = size_t(AT) * (size_t(nin) * nin + size_t(nout) * (nin | 1)) * sizeof(double2);
+    launch_lds(k_ml_map<CW>, dim3(unsigned(nout_boxes), 4, unsigned((nout + AT - 1) / AT)), dim3(256), lds, st, nin, nout,
+               m0, m1, ptr, box, bits, in, out, int(acc));
+}
+
+void back_boxes(const MlLevel &L, double k, hipStream_t st)
+{
+    if (L.nbox == 0) return;
+    const size_t lds = size_t(SL) * L.L * (L.L + (L.n | 1)) * sizeof(double2);
+    const dim3 grid(unsigned(L.nbox), 4), block(384);
+    if (L.n <= 12) launch_lds(k_ml_back<12>, grid, block, lds, st, L.L, L.n, k, (const double2 *)L.V, (const double2 *)L.Fz, L.Lq);
+    else if (L.n <= 15) launch_lds(k_ml_back<15>, grid, block, lds, st, L.L, L.n, k, (const double2 *)L.V, (const double2 *)L.Fz, L.Lq);
+    else launch_lds(k_ml_back<18>, grid, block, lds, st, L.L, L.n, k, (const double2 *)L.V, (const double2 *)L.Fz, L.Lq);
 }
 
 }  // namespace
@@ -999,13 +1299,14 @@ struct bie_farml {
     double origin[3] = { 0, 0, 0 }, prot = 0.0;
     std::vector<MlLevel> lv;
     std::vector<int32_t> h_box_of;
-    BsConst c0{};                   // leaf moments with the equidistant splines (A = identity)
-    double *meq = nullptr, *knots = nullptr, *ident = nullptr, *box_lo = nullptr, *qw = nullptr;
+    BsConst c0{};                   // the leaves' equidistant splines
+    double *meq = nullptr, *knots = nullptr, *box_lo = nullptr, *qw = nullptr;
+    MlBlock *blk = nullptr;         // moments of function m: meq + blk[m].at
     int32_t *box_of = nullptr, *mem_ptr = nullptr, *mem = nullptr;
     ~bie_farml()
     {
         for (auto &l : lv) l.free_all();
-        for (void *q : { (void *)meq, (void *)knots, (void *)ident, (void *)box_lo, (void *)qw, (void *)box_of,
+        for (void *q : { (void *)meq, (void *)blk, (void *)knots, (void *)box_lo, (void *)qw, (void *)box_of,
                          (void *)mem_ptr, (void *)mem })
             if (q) (void)hipFree(q);
     }
@@ -1072,8 +1373,8 @@ bie_farml *farml_create(const bie_op *op, double a, int levels, int s, int p, hi
         L.n = maps.back().n;
         L.nst = maps.back().nst;
         if (L.n > MLT) throw Error(BIE_EINVAL, "too many splines per box on level " + std::to_string(l));
-        L.L = 2 * L.nst - 1 <= 16 ? 16 : (2 * L.nst - 1 <= 32 ? 32 : 0);
-        if (!L.L) throw Error(BIE_EINVAL, "too many interpolation points per box on level " + std::to_string(l));
+        L.L = 2 * L.nst - 1;
+        if (L.nst > 16) throw Error(BIE_EINVAL, "too many interpolation points per box on level " + std::to_string(l));
         L.h = L.a / double(L.s - p);   // odd p: the points lie on the knots
     }
     // boxes per level
@@ -1098,12 +1399,6 @@ bie_farml *farml_create(const bie_op *op, double a, int levels, int s, int p, hi
         MlLevel &L = f->lv[l];
         const int64_t nb = L.nbox;
         const int32_t *B = L.h_ijk.data();
-        // identity lists
-        std::vector<int32_t> sp(nb + 1), sbx(nb);
-        for (int32_t b = 0; b <= nb; ++b) sp[b] = b;
-        for (int32_t b = 0; b < nb; ++b) sbx[b] = b;
-        L.self_ptr = upload(sp);
-        L.self_box = upload(sbx);
         // parent of each box (level above) and children of each box (level below)
         if (l + 1 < levels) {
             std::vector<int32_t> pp(nb + 1), pb(nb), pbits(nb);
@@ -1141,72 +1436,113 @@ bie_farml *farml_create(const bie_op *op, double a, int levels, int s, int p, hi
                 std::vector<double> uch(mc.ueq.size());
                 for (size_t i = 0; i < uch.size(); ++i) uch[i] = 0.5 * c + 0.5 * mc.ueq[i];
                 const std::vector<double> Cm = restrict_splines(mp.ueq, p, uch);
-                L.C[c] = upload(Cm);
-                L.CT[c] = upload(transpose(Cm, mp.n, mc.n));
+                L.C[c] = upload(padded(Cm, mp.n, mc.n));
+                L.CT[c] = upload(padded(transpose(Cm, mp.n, mc.n), mc.n, mp.n));
             }
         }
-        L.A = upload(maps[l].A);
-        L.AT = upload(transpose(maps[l].A, L.nst, L.n));
-        // interaction list by target, box offsets
-        std::map<std::array<int32_t, 3>, int32_t> offs;
-        std::vector<int32_t> ip(1, 0), isrc, ioff, hoffs;
-        for (int32_t X = 0; X < nb; ++X) {
-            for (int32_t Y = 0; Y < nb; ++Y) {
-                if (cheb(B + 3 * X, B + 3 * Y) <= 1) continue;
-                if (l + 1 < levels) {
-                    const int32_t px[3] = { B[3 * X] >> 1, B[3 * X + 1] >> 1, B[3 * X + 2] >> 1 };
-                    const int32_t py[3] = { B[3 * Y] >> 1, B[3 * Y + 1] >> 1, B[3 * Y + 2] >> 1 };
-                    if (cheb(px, py) > 1) continue;
-                }
-                const std::array<int32_t, 3> o{ B[3 * X] - B[3 * Y], B[3 * X + 1] - B[3 * Y + 1],
-                                                B[3 * X + 2] - B[3 * Y + 2] };
-                auto it = offs.find(o);
-                if (it == offs.end()) {
-                    it = offs.emplace(o, int32_t(offs.size())).first;
-                    for (int d = 0; d < 3; ++d) hoffs.push_back(o[d] * (L.s - p));   // in lattice steps
-                }
-                isrc.push_back(Y);
-                ioff.push_back(it->second);
-            }
-            ip.push_back(int32_t(isrc.size()));
-        }
-        L.npairs = int64_t(isrc.size());
-        L.noff = int64_t(offs.size());
-        L.il_ptr = upload(ip);
-        L.il_src = upload(isrc);
-        L.il_off = upload(ioff);
-        // FFT twiddles and the kernel symbols of the offsets
-        std::vector<double2> tw(L.L / 2);
-        for (int j = 0; j < L.L / 2; ++j) {
+        // W = DFT_L [A; 0] (stored [n][L]) and V = A^T [DFT_L^-1] = conj(W)^T / L (stored [L][n])
+        const int mo = pad4(L.L), mn = L.n <= 12 ? 12 : L.n <= 15 ? 15 : 18;   // row lengths of W and V
+        std::vector<double2> tw(L.L), W(size_t(L.n) * mo), V(size_t(mn) * L.L);
+        for (int j = 0; j < L.L; ++j) {
             const double ang = -2.0 * M_PI * double(j) / double(L.L);
             tw[j] = make_double2(std::cos(ang), std::sin(ang));
         }
-        L.tw = upload(tw);
+        for (int i = 0; i < L.n; ++i)
+            for (int fr = 0; fr < L.L; ++fr) {
+                double re = 0.0, im = 0.0;
+                for (int q = 0; q < L.nst; ++q) {
+                    const double A = maps[l].A[size_t(q) * L.n + i];
+                    re += A * tw[(fr * q) % L.L].x;
+                    im += A * tw[(fr * q) % L.L].y;
+                }
+                W[size_t(i) * mo + fr] = make_double2(re, im);
+                V[size_t(fr) * mn + i] = make_double2(re / L.L, -im / L.L);
+            }
+        L.W = upload(W);
+        L.V = upload(V);
+        // translations: the sources of TX targets, one symbol per offset without signs
+        auto morton = [&](int32_t b) {
+            uint64_t key = 0;
+            for (int bit = 20; bit >= 0; --bit)
+                for (int d = 0; d < 3; ++d) key = 2 * key + ((B[3 * b + d] >> bit) & 1);
+            return key;
+        };
+        std::vector<std::pair<uint64_t, int32_t>> by(nb);
+        for (int32_t b = 0; b < nb; ++b) by[b] = { morton(b), b };
+        std::sort(by.begin(), by.end());
+        std::vector<int32_t> gd((nb + TX - 1) / TX * TX, -1);
+        for (int64_t b = 0; b < nb; ++b) gd[b] = by[b].second;
+        std::map<std::array<int32_t, 3>, int32_t> offs;
+        std::vector<int32_t> gp(1, 0), ge, hoffs;
+        for (size_t g = 0; g < gd.size(); g += TX) {
+            for (int64_t u = 0; u < nb; ++u) {
+                const int32_t Y = by[u].second;
+                int32_t code[TX];
+                bool any = false;
+                for (int t = 0; t < TX; ++t) {
+                    code[t] = -1;
+                    const int32_t X = gd[g + t];
+                    if (X < 0 || cheb(B + 3 * X, B + 3 * Y) <= 1) continue;
+                    if (l + 1 < levels) {
+                        const int32_t px[3] = { B[3 * X] >> 1, B[3 * X + 1] >> 1, B[3 * X + 2] >> 1 };
+                        const int32_t py[3] = { B[3 * Y] >> 1, B[3 * Y + 1] >> 1, B[3 * Y + 2] >> 1 };
+                        if (cheb(px, py) > 1) continue;
+                    }
+                    std::array<int32_t, 3> o;
+                    int flip = 0;
+                    for (int d = 0; d < 3; ++d) {
+                        const int32_t v = B[3 * X + d] - B[3 * Y + d];
+                        o[d] = std::abs(v);
+                        flip |= v < 0 ? 4 >> d : 0;
+                    }
+                    auto it = offs.find(o);
+                    if (it == offs.end()) {
+                        it = offs.emplace(o, int32_t(offs.size())).first;
+                        for (int d = 0; d < 3; ++d) hoffs.push_back(o[d] * (L.s - p));   // in lattice steps
+                    }
+                    code[t] = 8 * it->second + flip;
+                    any = true;
+                    ++L.npairs;
+                }
+                if (!any) continue;
+                ge.push_back(Y);
+                ge.insert(ge.end(), code, code + TX);
+                ge.insert(ge.end(), 7 - TX, 0);
+            }
+            gp.push_back(int32_t(ge.size() / 8));
+        }
+        L.noff = int64_t(offs.size());
+        L.ngroup = int(gp.size()) - 1;
+        L.gptr = upload(gp);
+        L.gent = upload(ge);
+        L.gdst = upload(gd);
         const int64_t L3 = int64_t(L.L) * L.L * L.L;
         if (L.noff) {
+            const int64_t total = L.noff * L3;
             int32_t *doffs = upload(hoffs);
-            L.Kh = dalloc<double2>(size_t(L.noff * L3));
-            hipLaunchKernelGGL(k_ml_ktab, dim3(unsigned(std::min<int64_t>((L.noff * L3 + 255) / 256, 65535))), dim3(256),
-                               0, st, L.L, L.nst, L.noff, doffs, L.h, op->k, L.Kh);
+            double2 *dtw = upload(tw), *tmp = dalloc<double2>(size_t(total));
+            L.Kh = dalloc<double2>(size_t(total));
+            const dim3 grid(unsigned(std::min<int64_t>((total + 255) / 256, 65535)));
+            hipLaunchKernelGGL(k_ml_ktab, grid, dim3(256), 0, st, L.L, L.nst, L.noff, doffs, L.h, op->k, tmp);
+            hipLaunchKernelGGL(k_ml_dft, grid, dim3(256), 0, st, L.L, total, int64_t(1), dtw, tmp, L.Kh);
+            hipLaunchKernelGGL(k_ml_dft, grid, dim3(256), 0, st, L.L, total, int64_t(L.L), dtw, L.Kh, tmp);
+            hipLaunchKernelGGL(k_ml_dft, grid, dim3(256), 0, st, L.L, total, int64_t(L.L) * L.L, dtw, tmp, L.Kh);
             BIE_HIP(hipGetLastError());
-            fft3(L, L.Kh, L.noff, false, st);
             BIE_HIP(hipStreamSynchronize(st));
             (void)hipFree(doffs);
+            (void)hipFree(dtw);
+            (void)hipFree(tmp);
         }
         // work arrays (one vector)
         L.M = dalloc<double2>(size_t(nb) * 4 * L.n * L.n * L.n);
         L.Lq = dalloc<double2>(size_t(nb) * 4 * L.n * L.n * L.n);
-        L.Mt = dalloc<double2>(size_t(nb) * 4 * L.nst * L.nst * L.nst);
         L.F = dalloc<double2>(size_t(nb) * 4 * L3);
         L.Fz = dalloc<double2>(size_t(nb) * 4 * L3);
     }
-    // leaf moments with the equidistant splines (A = identity), members of the leaf boxes
+    // leaf moments with the equidistant splines, members of the leaf boxes
     const MlLevel &L0 = f->lv[0];
     const SplineMap &m0 = maps[0];
-    std::vector<double> I(size_t(L0.n) * L0.n, 0.0);
-    for (int i = 0; i < L0.n; ++i) I[size_t(i) * L0.n + i] = 1.0;
     f->knots = upload(m0.ueq);
-    f->ident = upload(I);
     BsConst &c = f->c0;
     c.p = p;
     c.a = a;
@@ -1216,7 +1552,7 @@ bie_farml *farml_create(const bie_op *op, double a, int levels, int s, int p, hi
     c.lo = m0.lo;
     c.hi = m0.hi;
     c.knots = f->knots;
-    c.A = f->ident;
+    c.A = nullptr;
     std::vector<double> blo(3 * size_t(L0.nbox));
     for (int32_t b = 0; b < L0.nbox; ++b)
         for (int d = 0; d < 3; ++d) blo[3 * b + d] = f->origin[d] + a * L0.h_ijk[3 * b + d];
@@ -1233,9 +1569,22 @@ bie_farml *farml_create(const bie_op *op, double a, int levels, int s, int p, hi
     f->box_of = upload(f->h_box_of);
     f->mem_ptr = upload(cnt);
     f->mem = upload(mem);
-    f->meq = dalloc<double>(size_t(N) * 4 * c.npts);
     const TriDev &D = op->tri;
-    hipLaunchKernelGGL(k_bs_moments, dim3(unsigned(N)), dim3(256), 0, st, c, N, (const int4 *)D.edges, D.cent, D.loc,
+    f->blk = dalloc<MlBlock>(size_t(N));
+    hipLaunchKernelGGL(k_ml_extent, dim3(unsigned((N + 255) / 256)), dim3(256), 0, st, c, N, (const int4 *)D.edges, D.cent,
+                       D.loc, f->box_lo, f->box_of, f->blk);
+    BIE_HIP(hipGetLastError());
+    std::vector<MlBlock> hb(N);
+    BIE_HIP(hipMemcpyAsync(hb.data(), f->blk, size_t(N) * sizeof(MlBlock), hipMemcpyDeviceToHost, st));
+    BIE_HIP(hipStreamSynchronize(st));
+    int64_t nmom = 0;
+    for (MlBlock &b : hb) {
+        b.at = nmom;
+        nmom += 4 * int64_t(b.size());
+    }
+    BIE_HIP(hipMemcpyAsync(f->blk, hb.data(), size_t(N) * sizeof(MlBlock), hipMemcpyHostToDevice, st));
+    f->meq = dalloc<double>(size_t(nmom));
+    hipLaunchKernelGGL(k_ml_moments, dim3(unsigned(N)), dim3(256), 0, st, c, f->blk, (const int4 *)D.edges, D.cent, D.loc,
                        D.vfree, f->qw, f->box_lo, f->box_of, f->meq);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipStreamSynchronize(st));
@@ -1248,37 +1597,33 @@ void farml_apply(bie_farml *f, const void *X, void *Y, int64_t R, hipStream_t st
     const int top = f->levels - 1;
     for (int64_t r = 0; r < R; ++r) {
         MlLevel &L0 = f->lv[0];
-        hipLaunchKernelGGL(k_bs_aggregate, dim3(unsigned(L0.nbox), 1), dim3(256), 0, st, f->c0.npts, N, L0.nbox,
-                           f->mem_ptr, f->mem, f->meq, (const double2 *)X + r * N, L0.M);
-        BIE_HIP(hipGetLastError());
+        launch_lds(k_ml_gather, dim3(unsigned(L0.nbox), 4), dim3(256), size_t(f->c0.npts) * sizeof(double2), st, L0.n,
+                   (const int32_t *)f->mem_ptr, (const int32_t *)f->mem, (const MlBlock *)f->blk, (const double *)f->meq,
+                   (const double2 *)X + r * N, L0.M);
         for (int l = 1; l <= top; ++l) {
             MlLevel &L = f->lv[l];
             const MlLevel &Lc = f->lv[l - 1];
-            tensor(Lc.n, L.n, L.C[0], L.C[1], L.kid_ptr, L.kid_box, L.kid_bits, Lc.M, L.M, L.nbox, false, st);
+            map_boxes<false>(Lc.n, L.n, (const double *)L.CT[0], (const double *)L.CT[1], L.kid_ptr, L.kid_box, L.kid_bits,
+                             Lc.M, L.M, L.nbox, false, st);
         }
         for (int l = 0; l <= top; ++l) {
             MlLevel &L = f->lv[l];
-            const int64_t nvol = L.nbox * 4, L3 = int64_t(L.L) * L.L * L.L;
-            tensor(L.n, L.nst, L.A, L.A, L.self_ptr, L.self_box, nullptr, L.M, L.Mt, L.nbox, false, st);
-            hipLaunchKernelGGL(k_ml_pad, dim3(unsigned(std::min<int64_t>((nvol * L3 + 255) / 256, 65535))), dim3(256), 0,
-                               st, L.nst, L.L, nvol, L.Mt, L.F);
-            fft3(L, L.F, nvol, false, st);
-            hipLaunchKernelGGL(k_ml_accum, dim3(unsigned(L.nbox), unsigned((L3 + 255) / 256)), dim3(256), 0, st, L3,
-                               L.il_ptr, L.il_src, L.il_off, (const double2 *)L.Kh, (const double2 *)L.F, L.Fz);
-            fft3(L, L.Fz, nvol, true, st);
-            const int64_t n3 = int64_t(L.nst) * L.nst * L.nst;
-            hipLaunchKernelGGL(k_ml_crop, dim3(unsigned(std::min<int64_t>((nvol * n3 + 255) / 256, 65535))), dim3(256), 0,
-                               st, L.nst, L.L, nvol, f->op->k, (const double2 *)L.Fz, L.Mt);
+            map_boxes<true>(L.n, L.L, (const double2 *)L.W, (const double2 *)L.W, nullptr, nullptr, nullptr, L.M, L.F,
+                            L.nbox, false, st);
+            const int nfc = (L.L * L.L * L.L + 63) / 64, ngb = (L.ngroup + 3) / 4;
+            hipLaunchKernelGGL(k_ml_accum, dim3(unsigned(8 * ngb * ((nfc + 7) / 8))), dim3(256), 0, st, L.L,
+                               L.gdst, L.ngroup, nfc, ngb, L.gptr, L.gent, (const double2 *)L.Kh, (const double2 *)L.F, L.Fz);
             BIE_HIP(hipGetLastError());
-            tensor(L.nst, L.n, L.AT, L.AT, L.self_ptr, L.self_box, nullptr, L.Mt, L.Lq, L.nbox, false, st);
+            back_boxes(L, f->op->k, st);
         }
         for (int l = top - 1; l >= 0; --l) {
             MlLevel &L = f->lv[l];
             const MlLevel &Lp = f->lv[l + 1];
-            tensor(Lp.n, L.n, Lp.CT[0], Lp.CT[1], L.par_ptr, L.par_box, L.par_bits, Lp.Lq, L.Lq, L.nbox, true, st);
+            map_boxes<false>(Lp.n, L.n, (const double *)Lp.C[0], (const double *)Lp.C[1], L.par_ptr, L.par_box, L.par_bits,
+                             Lp.Lq, L.Lq, L.nbox, true, st);
         }
-        hipLaunchKernelGGL(k_ml_disaggregate, dim3(unsigned(N)), dim3(256), 0, st, f->c0.npts, N, f->box_of, f->meq,
-                           (const double2 *)L0.Lq, (double2 *)Y + r * N);
+        hipLaunchKernelGGL(k_ml_test, dim3(unsigned((N + 3) / 4)), dim3(256), 0, st, L0.n, N, f->box_of,
+                           (const MlBlock *)f->blk, (const double *)f->meq, (const double2 *)L0.Lq, (double2 *)Y + r * N);
         BIE_HIP(hipGetLastError());
     }
 }

@@ -10,8 +10,9 @@
 // touching or near, the fill's singular treatment (the flagged pairs' blocks are
 // computed once, pair by pair, by the fill's own kernel); then
 //     T_mn = (L(+,+) + L(-,-)) + (L(+,-) + L(-,+)).
-// N is kept in CSR by row (column indices ascending) and applied one wave per
-// row.  Memory: the near entries (16 B + 4 B each), the flagged blocks (144 B
+// N is kept row by row (columns ascending); the rows of one cube have the same
+// columns, so these are kept once per cube.  Applied one wave per row.  Memory: the
+// near entries (16 B each) and the cubes' columns (4 B each), the flagged blocks (144 B
 // per pair), the far field's moments and level arrays; nothing of size N^2.
 #include <hip/hip_runtime.h>
 
@@ -23,6 +24,7 @@
 #include <vector>
 
 #include "bie_internal.hpp"
+#include "pairs.hpp"
 
 namespace bie {
 
@@ -31,6 +33,7 @@ struct FastOp {
     int64_t nnz = 0, cubes = 0;
     int levels = 0;
     int64_t *rowptr = nullptr;
+    int64_t *colptr = nullptr;      // N: first column of row m's cube in cols
     int32_t *cols = nullptr;
     double2 *vals = nullptr;
     double2 *tmp = nullptr;         // far product of one column
@@ -41,13 +44,15 @@ struct FastOp {
     ~FastOp()
     {
         if (far) farml_destroy(far);
-        for (void *p : { (void *)rowptr, (void *)cols, (void *)vals, (void *)tmp, (void *)qw, (void *)fptr, (void *)fq,
+        for (void *p : { (void *)rowptr, (void *)colptr, (void *)cols, (void *)vals, (void *)tmp, (void *)qw, (void *)fptr, (void *)fq,
                          (void *)fblk })
             if (p) (void)hipFree(p);
     }
 };
 
 namespace {
+
+typedef double nd2 __attribute__((ext_vector_type(2)));
 
 constexpr int NQF = QPTS;   // quadrature points per triangle
 
@@ -92,10 +97,10 @@ __device__ inline double2 local_block(int32_t p, int32_t a, int32_t q, int32_t b
         for (int j = 0; j < NQF; ++j) {
             const double d0 = dc[0] + xi[0] - yl[3 * j], d1 = dc[1] + xi[1] - yl[3 * j + 1],
                          d2 = dc[2] + xi[2] - yl[3 * j + 2];
-            const double R = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+            const double r2 = d0 * d0 + d1 * d1 + d2 * d2, ri = rsqrt_fast(r2);
             double sn, cs;
-            sincos(k * R, &sn, &cs);
-            const double w = qw[i] * qw[j] * inv4pi / R;
+            sincos_reduced(k * (r2 * ri), sn, cs);
+            const double w = qw[i] * qw[j] * inv4pi * ri;
             const double gr = w * cs, gi = -w * sn;
             const double dd = da[0] * (yl[3 * j] - vb[0]) + da[1] * (yl[3 * j + 1] - vb[1]) + da[2] * (yl[3 * j + 2] - vb[2]);
             s0r += gr;
@@ -111,7 +116,7 @@ __device__ inline double2 local_block(int32_t p, int32_t a, int32_t q, int32_t b
 
 // The near entries of row m (one block per row, threads over its entries).
 __global__ __launch_bounds__(256) void k_near_entries(int64_t N, const int64_t *__restrict__ rowptr,
-                                                      const int32_t *__restrict__ cols, const int4 *__restrict__ rwg4,
+                                                      const int64_t *__restrict__ colptr, const int32_t *__restrict__ cols, const int4 *__restrict__ rwg4,
                                                       const double *__restrict__ cent, const double *__restrict__ loc,
                                                       const double *__restrict__ vfree, const int8_t *__restrict__ sgn,
                                                       const double *__restrict__ qw, const int64_t *__restrict__ fptr,
@@ -121,8 +126,9 @@ __global__ __launch_bounds__(256) void k_near_entries(int64_t N, const int64_t *
     const int64_t m = blockIdx.x;
     if (m >= N) return;
     const int4 em = rwg4[m];
+    const int64_t first = colptr[m] - rowptr[m];
     for (int64_t e = rowptr[m] + threadIdx.x; e < rowptr[m + 1]; e += 256) {
-        const int4 en = rwg4[cols[e]];
+        const int4 en = rwg4[cols[first + e]];
         const double2 l1 = local_block(em.x, em.z, en.x, en.z, cent, loc, vfree, sgn, qw, fptr, fq, fblk, k);   // (+,+)
         const double2 l2 = local_block(em.y, em.w, en.y, en.w, cent, loc, vfree, sgn, qw, fptr, fq, fblk, k);   // (-,-)
         const double2 l3 = local_block(em.x, em.z, en.y, en.w, cent, loc, vfree, sgn, qw, fptr, fq, fblk, k);   // (+,-)
@@ -133,7 +139,7 @@ __global__ __launch_bounds__(256) void k_near_entries(int64_t N, const int64_t *
 
 // y_m = (B_m -) (sum_e vals[e] x[cols[e]] + far_m), one wave per row.
 __global__ __launch_bounds__(256) void k_near_apply(int64_t N, const int64_t *__restrict__ rowptr,
-                                                    const int32_t *__restrict__ cols, const double2 *__restrict__ vals,
+                                                    const int64_t *__restrict__ colptr, const int32_t *__restrict__ cols, const double2 *__restrict__ vals,
                                                     const double2 *__restrict__ x, const double2 *__restrict__ far,
                                                     const double2 *__restrict__ B, double2 *__restrict__ y)
 {
@@ -141,8 +147,12 @@ __global__ __launch_bounds__(256) void k_near_apply(int64_t N, const int64_t *__
     const int lane = threadIdx.x & 63;
     if (m >= N) return;
     double ar = 0.0, ai = 0.0;
-    for (int64_t e = rowptr[m] + lane; e < rowptr[m + 1]; e += 64) {
-        const double2 v = vals[e], xv = x[cols[e]];
+    const int64_t e0 = rowptr[m], e1 = rowptr[m + 1];
+    const int32_t *c = cols + (colptr[m] - e0);
+#pragma unroll 4
+    for (int64_t e = e0 + lane; e < e1; e += 64) {
+        const nd2 w = __builtin_nontemporal_load(reinterpret_cast<const nd2 *>(vals) + e);   // read once a product
+        const double2 v = make_double2(w.x, w.y), xv = x[c[e]];
         ar += v.x * xv.x - v.y * xv.y;
         ai += v.x * xv.y + v.y * xv.x;
     }
@@ -198,8 +208,12 @@ void fast_setup(bie_op *op, double near_factor, double box, int levels, int s, i
         std::sort(c.begin(), c.end());
     }
     for (int64_t m = 0; m < N; ++m) rowptr[m + 1] = rowptr[m] + int64_t(nearcols[box_of[m]].size());
-    cols.reserve(size_t(rowptr[N]));
-    for (int64_t m = 0; m < N; ++m) cols.insert(cols.end(), nearcols[box_of[m]].begin(), nearcols[box_of[m]].end());
+    std::vector<int64_t> cubecol(nb), colptr(N);
+    for (int32_t b = 0; b < nb; ++b) {
+        cubecol[b] = int64_t(cols.size());
+        cols.insert(cols.end(), nearcols[b].begin(), nearcols[b].end());
+    }
+    for (int64_t m = 0; m < N; ++m) colptr[m] = cubecol[box_of[m]];
     f->nnz = rowptr[N];
     // flagged pairs by first triangle (device order), partners ascending
     const int64_t nflag = int64_t(M.near.size() / 2);
@@ -212,13 +226,14 @@ void fast_setup(bie_op *op, double near_factor, double box, int levels, int s, i
     std::swap(f->fptr, nd.ptr);
     std::swap(f->fq, nd.list);
     f->rowptr = up(rowptr);
+    f->colptr = up(colptr);
     f->cols = up(cols);
     BIE_HIP(hipMalloc(&f->fblk, std::max<int64_t>(nflag, 1) * 18 * sizeof(double)));
     BIE_HIP(hipMalloc(&f->vals, std::max<int64_t>(f->nnz, 1) * sizeof(double2)));
     BIE_HIP(hipMalloc(&f->tmp, std::max<int64_t>(N, 1) * sizeof(double2)));
     singular_blocks(op, dpairs, nflag, f->fblk, st);
     const TriDev &D = op->tri;
-    hipLaunchKernelGGL(k_near_entries, dim3(unsigned(N)), dim3(256), 0, st, N, f->rowptr, f->cols,
+    hipLaunchKernelGGL(k_near_entries, dim3(unsigned(N)), dim3(256), 0, st, N, f->rowptr, f->colptr, f->cols,
                        (const int4 *)D.edges, D.cent, D.loc, D.vfree, D.sgn, f->qw, f->fptr, f->fq, f->fblk, op->k,
                        f->vals);
     BIE_HIP(hipGetLastError());
@@ -235,7 +250,7 @@ void fast_product(const bie_op *op, const void *X, int64_t ldx, void *Y, int64_t
     for (int64_t r = 0; r < R; ++r) {
         const double2 *x = static_cast<const double2 *>(X) + r * ldx;
         farml_apply(f->far, x, f->tmp, 1, st);
-        hipLaunchKernelGGL(k_near_apply, dim3(unsigned((N + 3) / 4)), dim3(256), 0, st, N, f->rowptr, f->cols, f->vals,
+        hipLaunchKernelGGL(k_near_apply, dim3(unsigned((N + 3) / 4)), dim3(256), 0, st, N, f->rowptr, f->colptr, f->cols, f->vals,
                            x, (const double2 *)f->tmp, B ? static_cast<const double2 *>(B) + r * ldb : nullptr,
                            static_cast<double2 *>(Y) + r * ldy);
         BIE_HIP(hipGetLastError());
