@@ -464,108 +464,207 @@ __global__ __launch_bounds__(256) void k_assemble_v(int64_t F, Bands bd, int64_t
 
 // ---------------------------------------------------------------------------
 // Plane-wave excitation:  e_m = sum_{p in m} (s_p/2) sum_i w_i (x_i - v_p).pol exp(-jk d.x_i)
+// A lane keeps the 7 points of one side of its function for RB waves, whose
+// directions and polarisations are the same for all lanes (scalar).  Bound by the
+// sines and cosines (7680 unknowns, 256 waves: 77 us; a lane to each
+// function and wave with the library's sincos 156).
+template <int RB>
 __global__ __launch_bounds__(256) void k_rhs(int64_t N, int64_t R, const int4 *__restrict__ rwg4,
                                              const int8_t *__restrict__ sgn, const double *__restrict__ cent,
                                              const double *__restrict__ loc, const double *__restrict__ vfree,
                                              const double *__restrict__ dirs, const double *__restrict__ pols,
                                              double k, double2 *__restrict__ B)
 {
-    const int64_t m = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t r = blockIdx.y;
-    if (m >= N || r >= R) return;
+    const int64_t m = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, r0 = int64_t(blockIdx.y) * RB;
+    if (m >= N) return;
     const int4 e = rwg4[m];
-    const double d[3] = { dirs[3 * r], dirs[3 * r + 1], dirs[3 * r + 2] };
-    const double pl[3] = { pols[3 * r], pols[3 * r + 1], pols[3 * r + 2] };
-    double br = 0.0, bi = 0.0;
+    double br[RB], bi[RB];
+#pragma unroll
+    for (int u = 0; u < RB; ++u) br[u] = bi[u] = 0.0;
+#pragma unroll 1
     for (int side = 0; side < 2; ++side) {
         const int64_t t = side ? e.y : e.x;
         const int a = side ? e.w : e.z;
         const double s = 0.5 * double(sgn[t * 3 + a]);
-        double tr = 0.0, ti = 0.0;
-        for (int i = 0; i < NQ; ++i) {
-            double x[3], dv = 0.0, ph = 0.0;
-            for (int c = 0; c < 3; ++c) {
-                x[c] = cent[t * 3 + c] + loc[(t * NQ + i) * 3 + c];
-                dv += (loc[(t * NQ + i) * 3 + c] - vfree[t * 9 + a * 3 + c]) * pl[c];
-                ph += d[c] * x[c];
-            }
-            double sn, cs;
-            sincos(k * ph, &sn, &cs);
-            tr += c_w[i] * dv * cs;
-            ti -= c_w[i] * dv * sn;
+        double x[NQ][3], c[3], v[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            c[q] = cent[t * 3 + q];
+            v[q] = vfree[t * 9 + a * 3 + q];
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) x[i][q] = loc[(t * NQ + i) * 3 + q];
         }
-        br += s * tr;
-        bi += s * ti;
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+            if (r0 + u >= R) break;
+            const double *d = dirs + 3 * (r0 + u), *pl = pols + 3 * (r0 + u);
+            double tr = 0.0, ti = 0.0;
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                double dv = 0.0, ph = 0.0;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    dv += (x[i][q] - v[q]) * pl[q];
+                    ph += d[q] * (c[q] + x[i][q]);
+                }
+                double sn, cs;
+                sincos_reduced(k * ph, sn, cs);
+                tr += c_w[i] * dv * cs;
+                ti -= c_w[i] * dv * sn;
+            }
+            br[u] += s * tr;
+            bi[u] += s * ti;
+        }
     }
-    B[r * N + m] = make_double2(br, bi);
+#pragma unroll
+    for (int u = 0; u < RB; ++u)
+        if (r0 + u < R) B[(r0 + u) * N + m] = make_double2(br[u], bi[u]);
 }
 
 // Radiation vector F(o) = int j(y) exp(jk o.y) dS = sum_t sum_i w_i J_t(y_i) exp(jk o.y_i),
-// J_t(y) = sum_a x_{m(t,a)} s_a (y - v_a)/2.  One block per (vector, direction).
-// RCS: write the bistatic RCS (k^2 / (4 pi)) |r x F|^2 of direction r (unit)
-// instead of F: the part of F transverse to r, squared.
-template <bool RCS>
-__global__ __launch_bounds__(256) void k_farfield(int64_t F, int64_t N, int64_t M,
-                                                  const int32_t *__restrict__ slot_m,
-                                                  const int8_t *__restrict__ sgn, const double *__restrict__ cent,
-                                                  const double *__restrict__ loc, const double *__restrict__ vfree,
-                                                  const double *__restrict__ obs, double k,
-                                                  const double2 *__restrict__ X, void *__restrict__ outv)
+// J_t(y) = sum_a x_{m(t,a)} s_a (y - v_a)/2 = b y - a with b = sum_a x_a s_a / 2 and
+// a = sum_a x_a s_a v_a / 2 (y, v relative to the centroid), so that
+//     F(o) = sum_t b_t P1_t(o) - a_t P0_t(o),  P0 = sum_i w_i exp(jk o.y_i), P1 = sum_i w_i y_i exp(..):
+// the exponentials depend on the direction alone and the vectors enter by a
+// contraction over the triangles.
+//
+// (b, a) of every triangle and vector: 8 doubles at ((t R) + r) 8.
+__global__ __launch_bounds__(256) void k_far_coef(int64_t F, int64_t N, int64_t R, const int32_t *__restrict__ slot_m,
+                                                  const int8_t *__restrict__ sgn, const double *__restrict__ vfree,
+                                                  const double2 *__restrict__ X, double *__restrict__ coef)
 {
-    const int64_t mo = blockIdx.x, r = blockIdx.y;
-    const double o[3] = { obs[3 * mo], obs[3 * mo + 1], obs[3 * mo + 2] };
-    const double2 *x = X + r * N;
-    double acc[6] = { 0, 0, 0, 0, 0, 0 };
-    for (int64_t t = threadIdx.x; t < F; t += blockDim.x) {
-        double2 xa[3];
-        double sa[3];
-        for (int a = 0; a < 3; ++a) {
-            xa[a] = x[slot_m[t * 3 + a]];
-            sa[a] = 0.5 * double(sgn[t * 3 + a]);
+    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x, r = blockIdx.y;
+    if (t >= F) return;
+    double q[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
+    for (int a = 0; a < 3; ++a) {
+        const double2 x = X[r * N + slot_m[t * 3 + a]];
+        const double s = 0.5 * double(sgn[t * 3 + a]);
+        q[0] += s * x.x;
+        q[1] += s * x.y;
+        for (int c = 0; c < 3; ++c) {
+            const double v = s * vfree[t * 9 + a * 3 + c];
+            q[2 + 2 * c] += v * x.x;
+            q[3 + 2 * c] += v * x.y;
         }
-        for (int i = 0; i < NQ; ++i) {
-            double ph = 0.0;
-            for (int c = 0; c < 3; ++c) ph += o[c] * (cent[t * 3 + c] + loc[(t * NQ + i) * 3 + c]);
-            double sn, cs;
-            sincos(k * ph, &sn, &cs);
-            for (int c = 0; c < 3; ++c) {
-                double jr = 0.0, ji = 0.0;
-                for (int a = 0; a < 3; ++a) {
-                    const double dv = sa[a] * (loc[(t * NQ + i) * 3 + c] - vfree[t * 9 + a * 3 + c]);
-                    jr += xa[a].x * dv;
-                    ji += xa[a].y * dv;
+    }
+    for (int i = 0; i < 8; ++i) coef[(t * R + r) * 8 + i] = q[i];
+}
+
+// Partial sums of F over the triangles of split z.  Lanes are 64 directions.  Of every
+// FT = 8 triangles each of the four waves evaluates P0 and P1 of two into LDS, then
+// takes its VW of the block's 4 VW vectors through all eight, with the coefficients in
+// scalar registers: the exponentials are evaluated once for 32 vectors and no wave
+// holds more than 8 vectors' sums.  FP64 vector issue bounds it: 7 sines and cosines
+// per triangle and direction and 24 multiply-adds per vector (one block per vector and
+// direction evaluated the exponentials for every vector; 7680 unknowns, 32 vectors,
+// 361 directions: 3812 us, now 131; waves that kept their exponentials and 16 vectors each, one
+// to a SIMD: 427 us).
+constexpr int FT = 8;
+template <int VW>
+__global__ __launch_bounds__(256) void k_far_sum(int64_t F, int64_t R, int64_t M, int64_t per, const double *__restrict__ cent,
+                                                 const double *__restrict__ loc, const double *__restrict__ obs, double k,
+                                                 const double *__restrict__ coef, double *__restrict__ part)
+{
+    __shared__ double P[2][FT][8][64];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t mo = int64_t(blockIdx.x) * 64 + lane, r0 = (int64_t(blockIdx.y) * 4 + w) * VW, ml = mo < M ? mo : M - 1;
+    const double o[3] = { k * obs[3 * ml], k * obs[3 * ml + 1], k * obs[3 * ml + 2] };
+    double f[VW][6];
+#pragma unroll
+    for (int r = 0; r < VW; ++r)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) f[r][c] = 0.0;
+    const int64_t t0 = int64_t(blockIdx.z) * per, t1 = min(F, t0 + per);
+    int buf = 0;
+    for (int64_t tb = t0; tb < t1; tb += FT, buf ^= 1) {
+        const int nt = int(min(int64_t(FT), t1 - tb));
+        for (int u = w; u < nt; u += 4) {
+            const int64_t t = tb + u;
+            const double *y = loc + t * NQ * 3;
+            const double ph = o[0] * cent[3 * t] + o[1] * cent[3 * t + 1] + o[2] * cent[3 * t + 2];
+            double p[8] = { 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0 };
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                double sn, cs;
+                sincos_reduced(ph + (o[0] * y[3 * i] + o[1] * y[3 * i + 1] + o[2] * y[3 * i + 2]), sn, cs);
+                sn *= c_w[i];
+                cs *= c_w[i];
+                p[0] += cs;
+                p[1] += sn;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    p[2 + 2 * c] += cs * y[3 * i + c];
+                    p[3 + 2 * c] += sn * y[3 * i + c];
                 }
-                acc[2 * c] += c_w[i] * (jr * cs - ji * sn);
-                acc[2 * c + 1] += c_w[i] * (jr * sn + ji * cs);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) P[buf][u][i][lane] = p[i];
+        }
+        __syncthreads();   // one for each buffer: the next pass writes the other
+        for (int u = 0; u < nt; ++u) {
+            double p[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) p[i] = P[buf][u][i][lane];
+#pragma unroll
+            for (int r = 0; r < VW; ++r) {
+                const double *q = coef + ((tb + u) * R + min(r0 + r, R - 1)) * 8;   // beyond R: the last, not stored
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    f[r][2 * c] = __builtin_fma(q[0], p[2 + 2 * c], f[r][2 * c]);
+                    f[r][2 * c] = __builtin_fma(-q[1], p[3 + 2 * c], f[r][2 * c]);
+                    f[r][2 * c] = __builtin_fma(-q[2 + 2 * c], p[0], f[r][2 * c]);
+                    f[r][2 * c] = __builtin_fma(q[3 + 2 * c], p[1], f[r][2 * c]);
+                    f[r][2 * c + 1] = __builtin_fma(q[0], p[3 + 2 * c], f[r][2 * c + 1]);
+                    f[r][2 * c + 1] = __builtin_fma(q[1], p[2 + 2 * c], f[r][2 * c + 1]);
+                    f[r][2 * c + 1] = __builtin_fma(-q[2 + 2 * c], p[1], f[r][2 * c + 1]);
+                    f[r][2 * c + 1] = __builtin_fma(-q[3 + 2 * c], p[0], f[r][2 * c + 1]);
+                }
             }
         }
     }
-    __shared__ double red[6][256];
-    for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = acc[c];
+    if (mo >= M) return;
+#pragma unroll
+    for (int r = 0; r < VW; ++r)
+        if (r0 + r < R)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) part[((int64_t(blockIdx.z) * R + r0 + r) * 6 + c) * M + mo] = f[r][c];
+}
+
+// The splits' sums in order; F itself, or with RCS the bistatic RCS (k^2 / (4 pi)) |r x F|^2 of
+// direction r (unit): the part of F transverse to r, squared.
+template <bool RCS, typename O>
+__global__ __launch_bounds__(256) void k_far_out(int64_t nm, int64_t ld, int64_t splits, const double *__restrict__ part,
+                                                const double *__restrict__ obs, double k, O *__restrict__ out)
+{
+    __shared__ double red[3][6][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;   // each wave a quarter of the splits
+    const int64_t mo = int64_t(blockIdx.x) * 64 + lane, r = blockIdx.y, R = gridDim.y, q = (splits + 3) / 4;
+    double f[6] = { 0, 0, 0, 0, 0, 0 };
+    if (mo < nm)
+#pragma unroll 4
+        for (int64_t z = w * q; z < min(splits, (w + 1) * q); ++z)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) f[c] += part[((z * R + r) * 6 + c) * nm + mo];
+    if (w)
+        for (int c = 0; c < 6; ++c) red[w - 1][c][lane] = f[c];
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (int(threadIdx.x) < s)
-            for (int c = 0; c < 6; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + s];
-        __syncthreads();
-    }
-    if (RCS) {
-        if (threadIdx.x == 0) {
-            // r . F, then |F - (r . F) r|^2
-            double dr = 0.0, di = 0.0;
-            for (int c = 0; c < 3; ++c) {
-                dr += o[c] * red[2 * c][0];
-                di += o[c] * red[2 * c + 1][0];
-            }
-            double t2 = 0.0;
-            for (int c = 0; c < 3; ++c) {
-                const double tr = red[2 * c][0] - dr * o[c], ti = red[2 * c + 1][0] - di * o[c];
-                t2 += tr * tr + ti * ti;
-            }
-            static_cast<double *>(outv)[r * M + mo] = k * k / (4.0 * M_PI) * t2;
+    if (w || mo >= nm) return;
+    for (int u = 0; u < 3; ++u)
+        for (int c = 0; c < 6; ++c) f[c] += red[u][c][lane];
+    if constexpr (RCS) {
+        const double o[3] = { obs[3 * mo], obs[3 * mo + 1], obs[3 * mo + 2] };
+        double dr = 0.0, di = 0.0, t2 = 0.0;
+        for (int c = 0; c < 3; ++c) {
+            dr += o[c] * f[2 * c];
+            di += o[c] * f[2 * c + 1];
         }
-    } else if (threadIdx.x < 3) {
-        static_cast<double2 *>(outv)[(r * M + mo) * 3 + threadIdx.x] =
-            make_double2(red[2 * threadIdx.x][0], red[2 * threadIdx.x + 1][0]);
+        for (int c = 0; c < 3; ++c) {
+            const double tr = f[2 * c] - dr * o[c], ti = f[2 * c + 1] - di * o[c];
+            t2 += tr * tr + ti * ti;
+        }
+        out[r * ld + mo] = k * k / (4.0 * M_PI) * t2;
+    } else {
+        for (int c = 0; c < 3; ++c) out[(r * ld + mo) * 3 + c] = make_double2(f[2 * c], f[2 * c + 1]);
     }
 }
 
@@ -766,8 +865,15 @@ void rhs_planewave(const bie_op *op, const double *dirs, const double *pols, int
     BIE_HIP(hipMemcpy(dd, dirs, 3 * R * sizeof(double), hipMemcpyHostToDevice));
     BIE_HIP(hipMemcpy(dd + 3 * R, pols, 3 * R * sizeof(double), hipMemcpyHostToDevice));
     const TriDev &D = op->tri;
-    hipLaunchKernelGGL(k_rhs, dim3(unsigned((N + 255) / 256), unsigned(R)), dim3(256), 0, s, N, R,
-                       (const int4 *)D.edges, D.sgn, D.cent, D.loc, D.vfree, dd, dd + 3 * R, op->k, (double2 *)B);
+    // four waves per lane once that leaves four blocks for each CU; below that one wave per
+    // lane, for the blocks (256 waves on 7680 functions: four 77 us, one 156 with the old form)
+    const unsigned nb = unsigned((N + 255) / 256);
+    auto rhs = [&](auto kern, int rb) {
+        hipLaunchKernelGGL(kern, dim3(nb, unsigned((R + rb - 1) / rb)), dim3(256), 0, s, N, R, (const int4 *)D.edges,
+                           D.sgn, D.cent, D.loc, D.vfree, dd, dd + 3 * R, op->k, (double2 *)B);
+    };
+    if (nb * R >= 4096) rhs(k_rhs<4>, 4);
+    else rhs(k_rhs<1>, 1);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipStreamSynchronize(s));
     hipFree(dd);
@@ -776,19 +882,71 @@ void rhs_planewave(const bie_op *op, const double *dirs, const double *pols, int
 void farfield(const bie_op *op, const void *X, int64_t R, const double *obs, int64_t M, void *out, bool rcs,
               hipStream_t s)
 {
-    double *dobs = nullptr;
-    BIE_HIP(hipMalloc(&dobs, 3 * M * sizeof(double)));
-    BIE_HIP(hipMemcpy(dobs, obs, 3 * M * sizeof(double), hipMemcpyHostToDevice));
     const TriDev &D = op->tri;
-    if (rcs)
-        hipLaunchKernelGGL(k_farfield<true>, dim3(unsigned(M), unsigned(R)), dim3(256), 0, s, op->mesh.F, op->mesh.N,
-                           M, D.slot_m, D.sgn, D.cent, D.loc, D.vfree, dobs, op->k, (const double2 *)X, out);
-    else
-        hipLaunchKernelGGL(k_farfield<false>, dim3(unsigned(M), unsigned(R)), dim3(256), 0, s, op->mesh.F, op->mesh.N,
-                           M, D.slot_m, D.sgn, D.cent, D.loc, D.vfree, dobs, op->k, (const double2 *)X, out);
-    const hipError_t e = hipGetLastError();
+    const int64_t F = op->mesh.F, N = op->mesh.N;
+    // Vectors per wave: as many as the registers hold, the fewest that cover R.
+    // Triangle splits: two blocks on each of the 256 CUs.  The coefficients and the
+    // partial sums of one pass fill at most 64 MB each; more vectors or directions
+    // go in several passes over the same buffers, and where even that is not to be
+    // had in much smaller ones.
+    struct Plan {
+        int VW;
+        int64_t nr, nm, per, splits;
+        size_t coef, part;
+    };
+    auto plan = [&](int64_t limit) {
+        Plan p;
+        p.nr = std::min(R, std::max<int64_t>(1, limit / (8 * F)));
+        p.VW = p.nr > 16 ? 8 : p.nr > 8 ? 4 : p.nr > 4 ? 2 : 1;
+        const int64_t by = (p.nr + 4 * p.VW - 1) / (4 * p.VW), most = std::max<int64_t>(64, limit / (6 * p.nr) / 64 * 64);
+        p.nm = std::min(M, most);
+        const int64_t bx = (p.nm + 63) / 64;
+        const int64_t want = std::max<int64_t>(1, std::min({ (F + 15) / 16, 512 / (bx * by), most / p.nm }));
+        p.per = (F + want - 1) / want;
+        p.splits = (F + p.per - 1) / p.per;
+        p.coef = size_t(8 * F * p.nr);
+        p.part = size_t(6 * p.splits * p.nr * p.nm);
+        return p;
+    };
+    double *w = nullptr;
+    Plan p = {};
+    const size_t nobs = size_t(3 * M);
+    hipError_t e = hipErrorOutOfMemory;
+    for (int64_t limit : { int64_t(1) << 23, int64_t(1) << 19, int64_t(0) }) {
+        p = plan(limit);
+        e = hipMalloc(&w, (nobs + p.coef + p.part) * sizeof(double));
+        if (e != hipErrorOutOfMemory) break;
+        (void)hipGetLastError();
+    }
+    BIE_HIP(e);
+    double *dobs = w, *coef = w + nobs, *part = coef + p.coef;
+    e = hipMemcpy(dobs, obs, nobs * sizeof(double), hipMemcpyHostToDevice);
+    for (int64_t r0 = 0; r0 < R && e == hipSuccess; r0 += p.nr) {
+        const int64_t nr = std::min(p.nr, R - r0);
+        hipLaunchKernelGGL(k_far_coef, dim3(unsigned((F + 255) / 256), unsigned(nr)), dim3(256), 0, s, F, N, nr, D.slot_m,
+                           D.sgn, D.vfree, (const double2 *)X + r0 * N, coef);
+        for (int64_t m0 = 0; m0 < M; m0 += p.nm) {
+            const int64_t nm = std::min(p.nm, M - m0);
+            const unsigned bx = unsigned((nm + 63) / 64), by = unsigned((nr + 4 * p.VW - 1) / (4 * p.VW));
+            auto sum = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3(bx, by, unsigned(p.splits)), dim3(256), 0, s, F, nr, nm, p.per, D.cent,
+                                   D.loc, dobs + 3 * m0, op->k, coef, part);
+            };
+            if (p.VW == 8) sum(k_far_sum<8>);
+            else if (p.VW == 4) sum(k_far_sum<4>);
+            else if (p.VW == 2) sum(k_far_sum<2>);
+            else sum(k_far_sum<1>);
+            auto put = [&](auto kern, auto *to) {
+                hipLaunchKernelGGL(kern, dim3(bx, unsigned(nr)), dim3(256), 0, s, nm, M, p.splits, part, dobs + 3 * m0,
+                                   op->k, to);
+            };
+            if (rcs) put(k_far_out<true, double>, static_cast<double *>(out) + r0 * M + m0);
+            else put(k_far_out<false, double2>, static_cast<double2 *>(out) + (r0 * M + m0) * 3);
+        }
+        e = hipGetLastError();
+    }
     const hipError_t e2 = hipStreamSynchronize(s);
-    (void)hipFree(dobs);
+    (void)hipFree(w);
     BIE_HIP(e);
     BIE_HIP(e2);
 }
