@@ -52,7 +52,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int GBM = 256, GBN = 256, GBK = 16;   // block tile rows, columns; K stage
+constexpr int GBM = 256, GBN = 256, GBK = 16;   // block tile rows, (widest) columns; K stage
 
 // XCD-aware tile order: workgroups are dealt to the 8 XCDs round robin by
 // linear id p, so logical tile L = (p % 8) Q + p / 8 (Q = P / 8) gives each XCD
@@ -214,16 +214,16 @@ __device__ inline void lds_dma16(const void *g, void *l)
 // significant bits) and rounds the vectors to BF16 (2^-9 relative): the form
 // for the inner corrections of iterative refinement, whose tolerance is far
 // above that rounding; the B lo plane is then not loaded.
-template <int TERMS, int WM, int WN, int NS>
-__global__ __launch_bounds__(64 * (GBM / WM) * (GBN / WN)) void k_gemm_split(
+template <int TERMS, int WM, int WN, int NS, int BN>
+__global__ __launch_bounds__(64 * (GBM / WM) * (BN / WN)) void k_gemm_split(
     const __bf16 *__restrict__ Ah, const __bf16 *__restrict__ Al, const __bf16 *__restrict__ Bh,
     const __bf16 *__restrict__ Bl, int64_t Kp, int64_t Mp, int64_t NCp, float *__restrict__ P)
 {
-    constexpr int TIw = WM / 32, TJw = WN / 32, NWN = GBN / WN, W = (GBM / WM) * (GBN / WN);
-    constexpr int SA = GBM / 32, SB = GBN / 32;                  // tiles of A and of B per plane and stage
+    constexpr int TIw = WM / 32, TJw = WN / 32, NWN = BN / WN, W = (GBM / WM) * (BN / WN);
+    constexpr int SA = GBM / 32, SB = BN / 32;                  // tiles of A and of B per plane and stage
     constexpr int LOADS = 2 * SA + (TERMS == 3 ? 2 : 1) * SB;   // DMA instructions per stage
-    static_assert(LOADS % W == 0 && NS >= 3, "stage loads are shared evenly by the waves");
-    constexpr int LPW = LOADS / W;
+    static_assert(NS >= 3, "a stage is in flight while two are in use");
+    constexpr int LPW = (LOADS + W - 1) / W;                    // a wave without a last one repeats the stage's
     constexpr int STAGE = (2 * SA + 2 * SB) * 512;              // BF16 per stage buffer
     __shared__ __attribute__((aligned(1024))) __bf16 lds[NS][STAGE];
     const int lane = threadIdx.x & 63;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64 * (GBM / WM) * (GBN / WN)) void k_gemm_split(
     const int wm = wave / NWN, wn = wave % NWN;
     unsigned bx, by, bz;
     xcd_tile(bx, by, bz);
-    const int64_t m0 = int64_t(bx) * GBM, c0 = int64_t(by) * GBN;
+    const int64_t m0 = int64_t(bx) * GBM, c0 = int64_t(by) * BN;
     const int64_t nst = Kp / GBK;
 
     // the DMA instructions of this wave: tile q of the stage, its source (stage
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * (GBM / WM) * (GBN / WN)) void k_gemm_split(
     int dst[LPW];
 #pragma unroll
     for (int q = 0; q < LPW; ++q) {
-        const int i = wave + W * q;
+        const int i = min(wave + W * q, LOADS - 1);
         if (i < 2 * SA) {
             const int p = i / SA, t = i % SA;
             src[q] = (p ? Al : Ah) + (m0 / 32 + t) * nst * 512;
@@ -359,29 +359,47 @@ __global__ __launch_bounds__(64 * (GBM / WM) * (GBN / WN)) void k_gemm_split(
 }
 
 // Y[v][m] = sum_z (P[z][m][2r], P[z][m][2r+1]) (or Bsub[v][m] - that), v = cols ?
-// cols[r] : r, for a tile of 64 rows x 32 right-hand sides; the slices are
-// summed in FP64.
+// cols[r] : r, for a tile of RM = 16 rows x 32 right-hand sides; the slices are
+// summed in FP64 in their order.  A read of the partial tiles from the last-level
+// cache: each thread asks for eight slices of its four entries at a time, and 16
+// rows make 1.7 blocks per CU at 3528 x 64 (18 slices: 21 us; 64 rows and one
+// slice after the other 76).
+constexpr int RM = 16;
 template <typename PT>
 __global__ __launch_bounds__(256) void k_gemm_reduce(const PT *__restrict__ P, int KS, int64_t Mp, int64_t NCp,
                                                      int64_t N, int64_t R, const int *__restrict__ cols,
                                                      double2 *__restrict__ Y, int64_t ldy,
                                                      const double2 *__restrict__ Bsub, int64_t ldb)
 {
-    __shared__ double sd[64][65];   // [column][row]
-    const int t = threadIdx.x;
-    const int64_t m0 = int64_t(blockIdx.x) * 64, cb = int64_t(blockIdx.y) * 64;
-    const int cl = t & 63;
-#pragma unroll 4
-    for (int it = 0; it < 16; ++it) {
-        const int ml = it * 4 + (t >> 6);
-        double v = 0.0;
-        for (int z = 0; z < KS; ++z) v += double(P[(int64_t(z) * Mp + m0 + ml) * NCp + cb + cl]);
-        sd[cl][ml] = v;
+    __shared__ double sd[64][RM + 1];   // [column][row]
+    const int t = threadIdx.x, cl = t & 63, w = t >> 6;
+    const int64_t m0 = int64_t(blockIdx.x) * RM, cb = int64_t(blockIdx.y) * 64;
+    const PT *Pc = P + (m0 + w) * NCp + cb + cl;
+    double v[RM / 4];
+#pragma unroll
+    for (int it = 0; it < RM / 4; ++it) v[it] = 0.0;
+    int z = 0;
+    for (; z + 8 <= KS; z += 8) {
+        PT x[8][RM / 4];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int it = 0; it < RM / 4; ++it) x[u][it] = Pc[(int64_t(z + u) * Mp + 4 * it) * NCp];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int it = 0; it < RM / 4; ++it) v[it] += double(x[u][it]);
     }
+#pragma unroll 2
+    for (; z < KS; ++z)
+#pragma unroll
+        for (int it = 0; it < RM / 4; ++it) v[it] += double(Pc[(int64_t(z) * Mp + 4 * it) * NCp]);
+#pragma unroll
+    for (int it = 0; it < RM / 4; ++it) sd[cl][4 * it + w] = v[it];
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-        const int idx = it * 256 + t, rl = idx >> 6, ml = idx & 63;
+    for (int it = 0; it < RM / 8; ++it) {
+        const int idx = it * 256 + t, rl = idx / RM, ml = idx % RM;
         const int64_t r = cb / 2 + rl, m = m0 + ml;
         if (r >= R || m >= N) continue;
         const int64_t v = cols ? int64_t(cols[r]) : r;
@@ -392,6 +410,15 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(const PT *__restrict__ P, i
         }
         Y[v * ldy + m] = y;
     }
+}
+
+template <typename PT>
+void launch_reduce(const PT *P, int KS, int64_t Mp, int64_t NCp, int64_t N, int64_t R, const int *cols, void *Y,
+                   int64_t ldy, const void *Bsub, int64_t ldb, hipStream_t s)
+{
+    // columns of right-hand sides only, not the padding beyond them
+    hipLaunchKernelGGL(k_gemm_reduce<PT>, dim3(unsigned(Mp / RM), unsigned((2 * R + 63) / 64)), dim3(256), 0, s, P, KS,
+                       Mp, NCp, N, R, cols, (double2 *)Y, ldy, (const double2 *)Bsub, ldb);
 }
 
 // ---------------------------------------------------------------------------
@@ -541,15 +568,15 @@ int gemm_splitk(int64_t blocks, int64_t nst, int want = 0)
     return int(std::max<int64_t>(1, std::min<int64_t>(ks, 64)));
 }
 
-template <int WM, int WN, int NS>
+template <int WM, int WN, int NS, int BN>
 void launch_split(int terms, dim3 grid, hipStream_t s, const __bf16 *Ah, const __bf16 *Al, const __bf16 *Bh,
                   const __bf16 *Bl, int64_t Kp, int64_t Mp, int64_t NCp, float *P)
 {
-    constexpr int NT = 64 * (GBM / WM) * (GBN / WN);
+    constexpr int NT = 64 * (GBM / WM) * (BN / WN);
     if (terms == 3)
-        hipLaunchKernelGGL((k_gemm_split<3, WM, WN, NS>), grid, dim3(NT), 0, s, Ah, Al, Bh, Bl, Kp, Mp, NCp, P);
+        hipLaunchKernelGGL((k_gemm_split<3, WM, WN, NS, BN>), grid, dim3(NT), 0, s, Ah, Al, Bh, Bl, Kp, Mp, NCp, P);
     else
-        hipLaunchKernelGGL((k_gemm_split<2, WM, WN, NS>), grid, dim3(NT), 0, s, Ah, Al, Bh, Bl, Kp, Mp, NCp, P);
+        hipLaunchKernelGGL((k_gemm_split<2, WM, WN, NS, BN>), grid, dim3(NT), 0, s, Ah, Al, Bh, Bl, Kp, Mp, NCp, P);
 }
 
 typedef void (*SplitLaunch)(int, dim3, hipStream_t, const __bf16 *, const __bf16 *, const __bf16 *, const __bf16 *,
@@ -557,8 +584,22 @@ typedef void (*SplitLaunch)(int, dim3, hipStream_t, const __bf16 *, const __bf16
 // wave tiles of the 256 x 256 block: 128 x 64 (default), 64 x 128, 128 x 128
 // (accumulators in AGPRs); BIE_GEMM_CFG = 0, 1, 2 fixes one (measurement),
 // else the autotuner picks per shape
-const SplitLaunch kSplitLaunch[] = { launch_split<128, 64, 4>, launch_split<64, 128, 4>, launch_split<128, 128, 4> };
+const SplitLaunch kSplitLaunch[] = { launch_split<128, 64, 4, 256>, launch_split<64, 128, 4, 256>,
+                                     launch_split<128, 128, 4, 256> };
 constexpr int kSplitCfgs = int(sizeof(kSplitLaunch) / sizeof(kSplitLaunch[0]));
+
+// Up to 64 (32) right-hand sides take 256 x 128 (256 x 64) blocks of four waves:
+// the matrix planes are read once either way, and the wider block multiplies and
+// writes padding only (3528 unknowns, 64 vectors: 27 us, 256 x 256 38 us).
+// The sums of a column do not depend on the width.
+int64_t split_width(int64_t NCp) { return std::min<int64_t>(NCp, GBN); }
+int split_cfgs(int64_t NCp) { return split_width(NCp) == GBN ? kSplitCfgs : 1; }
+SplitLaunch split_launch(int64_t NCp, int cfg)
+{
+    if (split_width(NCp) == 64) return launch_split<64, 64, 4, 64>;
+    if (split_width(NCp) == 128) return launch_split<128, 64, 4, 128>;
+    return kSplitLaunch[cfg];
+}
 
 int split_cfg_env()
 {
@@ -574,16 +615,16 @@ int split_cfg_env()
 void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s, const __bf16 *Ah, const __bf16 *Al,
                   const __bf16 *Bh, const __bf16 *Bl, bie_op *op, int &cfg, int &ks)
 {
-    const int64_t blocks = (Mp / GBM) * (NCp / GBN), nst = Kp / GBK;
+    const int64_t width = split_width(NCp), blocks = (Mp / GBM) * (NCp / width), nst = Kp / GBK;
     cfg = split_cfg_env();
     ks = gemm_splitk(blocks, nst);
     const bool env_fixed = cfg >= 0 || env_int("BIE_GEMM_SPLITK", 0) > 0;
-    if (cfg < 0) cfg = 0;
+    if (cfg < 0 || cfg >= split_cfgs(NCp)) cfg = 0;
     if (env_fixed || !tune_enabled()) return;
     const std::string key = "gemm_split:" + std::to_string(Mp) + "x" + std::to_string(Kp) + ":" +
                             std::to_string(NCp) + ":t" + std::to_string(terms);
     std::vector<int> v;
-    const bool have = tune_get(key, v) && v.size() == 2 && v[0] >= 0 && v[0] < kSplitCfgs && v[1] >= 1;
+    const bool have = tune_get(key, v) && v.size() == 2 && v[0] >= 0 && v[0] < split_cfgs(NCp) && v[1] >= 1;
     if (!have && stream_capturing(s)) return;   // no timing inside a captured graph: the defaults
     if (!have) {
         std::vector<int> kss;
@@ -592,7 +633,7 @@ void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s,
             if (std::find(kss.begin(), kss.end(), k2) == kss.end()) kss.push_back(k2);
         }
         const int kmax = *std::max_element(kss.begin(), kss.end());
-        const size_t pelems = size_t(kmax) * size_t(Mp) * size_t(NCp);
+        const size_t pelems = size_t(kmax) * size_t(Mp) * size_t((NCp + GBN - 1) / GBN * GBN);
         if (op->gemm_part_elems < pelems) {
             BIE_HIP(hipStreamSynchronize(s));
             if (op->gemm_part) (void)hipFree(op->gemm_part);
@@ -604,12 +645,12 @@ void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s,
         float *P = static_cast<float *>(op->gemm_part);
         float best = 0.f;
         v = { 0, ks };
-        for (int c = 0; c < kSplitCfgs; ++c)
+        for (int c = 0; c < split_cfgs(NCp); ++c)
             for (int k2 : kss) {
                 // the split-K reduction reads KS partial tiles: charged at 5 TB/s
                 const float red = float(double(k2) * Mp * NCp * 4.0 / 5e12 * 1e3);
                 const float ms = time_launches(s, 2, [&]() {
-                    kSplitLaunch[c](terms, dim3(unsigned(Mp / GBM), unsigned(NCp / GBN), unsigned(k2)), s, Ah, Al, Bh,
+                    split_launch(NCp, c)(terms, dim3(unsigned(Mp / GBM), unsigned(NCp / width), unsigned(k2)), s, Ah, Al, Bh,
                                     Bl, Kp, Mp, NCp, P);
                 }) + red;
                 if (best == 0.f || ms < best) {
@@ -627,7 +668,10 @@ void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s,
 
 int64_t gemm_pad_rows(int64_t N) { return (N + GBM - 1) / GBM * GBM; }
 int64_t gemm_pad_k(int64_t N) { return (2 * N + GBK - 1) / GBK * GBK; }
-int64_t gemm_pad_cols(int64_t R) { return (2 * R + GBN - 1) / GBN * GBN; }
+// The vectors' staging and the partial sums are allocated for whole 256-column blocks, so
+// that growing the number of vectors within one asks for no new memory (under capture).
+static int64_t wide_cols(int64_t R) { return (2 * R + GBN - 1) / GBN * GBN; }
+int64_t gemm_pad_cols(int64_t R) { return R <= 32 ? 64 : R <= 64 ? 128 : wide_cols(R); }
 
 // Split-BF16 copy of the FP64 matrix (A planes, hi then lo, tiled).
 void split_matrix(bie_op *op, hipStream_t s)
@@ -665,8 +709,9 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
         if (op->Bbf) (void)hipFree(op->Bbf);
         op->Bbf = nullptr;
         op->bstage_cols = 0;
-        BIE_HIP(hipMalloc(&op->Bbf, 2 * plane * sizeof(__bf16)));
-        op->bstage_cols = NCp;
+        const int64_t cap = wide_cols(R);
+        BIE_HIP(hipMalloc(&op->Bbf, 2 * size_t(cap) * size_t(Kp) * sizeof(__bf16)));
+        op->bstage_cols = cap;
     }
     __bf16 *Bh = static_cast<__bf16 *>(op->Bbf), *Bl = Bh + plane;
     const __bf16 *Ah = static_cast<const __bf16 *>(op->Abf), *Al = Ah + size_t(Mp) * size_t(Kp);
@@ -693,16 +738,16 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
         if (op->gemm_part) (void)hipFree(op->gemm_part);
         op->gemm_part = nullptr;
         op->gemm_part_elems = 0;
-        BIE_HIP(hipMalloc(&op->gemm_part, pelems * sizeof(float)));
-        op->gemm_part_elems = pelems;
+        const size_t cap = size_t(KS) * size_t(Mp) * size_t(wide_cols(R));
+        BIE_HIP(hipMalloc(&op->gemm_part, cap * sizeof(float)));
+        op->gemm_part_elems = cap;
     }
     float *P = static_cast<float *>(op->gemm_part);
     prof_begin(1, s, R);
-    kSplitLaunch[cfg](terms, dim3(unsigned(Mp / GBM), unsigned(NCp / GBN), unsigned(KS)), s, Ah, Al, Bh, Bl, Kp, Mp,
-                      NCp, P);
+    split_launch(NCp, cfg)(terms, dim3(unsigned(Mp / GBM), unsigned(NCp / split_width(NCp)), unsigned(KS)), s, Ah, Al,
+                           Bh, Bl, Kp, Mp, NCp, P);
     prof_end(1, s);
-    hipLaunchKernelGGL(k_gemm_reduce<float>, dim3(unsigned(Mp / 64), unsigned(NCp / 64)), dim3(256), 0, s, P, KS, Mp,
-                       NCp, N, R, cols, (double2 *)Y, ldy, (const double2 *)Bsub, ldb);
+    launch_reduce(P, KS, Mp, NCp, N, R, cols, Y, ldy, Bsub, ldb, s);
     BIE_HIP(hipGetLastError());
 }
 
@@ -801,8 +846,7 @@ void gemm64_product(const bie_op *opc, const void *X, int64_t ldx, void *Y, int6
     prof_begin(2, s, R);
     hipLaunchKernelGGL(k_gemm64, dim3(unsigned(Mp / DBM), unsigned(NCp / DBN), unsigned(ks)), dim3(256), 0, s,
                        (const double *)op->A64, Kp, N, (const double2 *)X, ldx, cols, R, Mp, NCp, P);
-    hipLaunchKernelGGL(k_gemm_reduce<double>, dim3(unsigned(Mp / 64), unsigned(NCp / 64)), dim3(256), 0, s, P,
-                       int(ks), Mp, NCp, N, R, cols, (double2 *)Y, ldy, (const double2 *)Bsub, ldb);
+    launch_reduce(P, int(ks), Mp, NCp, N, R, cols, Y, ldy, Bsub, ldb, s);
     prof_end(2, s);
     BIE_HIP(hipGetLastError());
 }
