@@ -466,8 +466,8 @@ __global__ __launch_bounds__(256) void k_assemble_v(int64_t F, Bands bd, int64_t
 // Plane-wave excitation:  e_m = sum_{p in m} (s_p/2) sum_i w_i (x_i - v_p).pol exp(-jk d.x_i)
 // A lane keeps the 7 points of one side of its function for RB waves, whose
 // directions and polarisations are the same for all lanes (scalar).  Bound by the
-// sines and cosines (7680 unknowns, 256 waves: 77 us; a lane to each
-// function and wave with the library's sincos 156).
+// sines and cosines (7680 unknowns, 256 waves: 79 us; a lane to each function and
+// wave, points read again for each, 156).
 template <int RB>
 __global__ __launch_bounds__(256) void k_rhs(int64_t N, int64_t R, const int4 *__restrict__ rwg4,
                                              const int8_t *__restrict__ sgn, const double *__restrict__ cent,
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256) void k_rhs(int64_t N, int64_t R, const int4 *_
                     ph += d[q] * (c[q] + x[i][q]);
                 }
                 double sn, cs;
-                sincos_reduced(k * ph, sn, cs);
+                sincos(k * ph, &sn, &cs);
                 tr += c_w[i] * dv * cs;
                 ti -= c_w[i] * dv * sn;
             }
@@ -865,8 +865,7 @@ void rhs_planewave(const bie_op *op, const double *dirs, const double *pols, int
     BIE_HIP(hipMemcpy(dd, dirs, 3 * R * sizeof(double), hipMemcpyHostToDevice));
     BIE_HIP(hipMemcpy(dd + 3 * R, pols, 3 * R * sizeof(double), hipMemcpyHostToDevice));
     const TriDev &D = op->tri;
-    // four waves per lane once that leaves four blocks for each CU; below that one wave per
-    // lane, for the blocks (256 waves on 7680 functions: four 77 us, one 156 with the old form)
+    // four waves per lane once that leaves four blocks for each CU, else one for more blocks
     const unsigned nb = unsigned((N + 255) / 256);
     auto rhs = [&](auto kern, int rb) {
         hipLaunchKernelGGL(kern, dim3(nb, unsigned((R + rb - 1) / rb)), dim3(256), 0, s, N, R, (const int4 *)D.edges,
