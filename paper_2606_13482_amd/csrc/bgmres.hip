@@ -46,6 +46,7 @@ namespace {
 constexpr int BMAX = 32;    // right-hand sides per group, at most
 constexpr int DT = 128;     // basis vectors per tile of the dot kernel
 constexpr int DS = 16;      // rows per LDS stage of the dot kernel
+constexpr int64_t LS_EARLY = 256;   // columns of a step up to which its least-squares update is queued with it
 constexpr double DELTA = 1e-6;
 
 __device__ inline double2 to_d2(double2 v) { return v; }
@@ -123,6 +124,23 @@ __device__ inline double2 cmulc(double2 a, double2 b)   // conj(a) * b
 __device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ inline double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ inline double2 cscale(double s, double2 a) { return make_double2(s * a.x, s * a.y); }
+
+// The value of lane ^ 1 (0xB1), lane ^ 2 (0x4E) or 7 - lane of each 8 lanes (0x141).
+template <int CTRL> __device__ inline double lane_move(double v)
+{
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, false),
+                                                __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, false)));
+}
+// Sum over each 8 lanes, the same in all of them.
+__device__ inline double sum8(double v)
+{
+    v += lane_move<0xB1>(v);
+    v += lane_move<0x4E>(v);
+    return v + lane_move<0x141>(v);
+}
+__device__ inline double2 pick(bool c, double2 a, double2 b) { return make_double2(c ? a.x : b.x, c ? a.y : b.y); }
+__device__ inline double2 sum8(double2 v) { return make_double2(sum8(v.x), sum8(v.y)); }
 
 // Dot item: dst[(k0 + v) * ld + b] = sum_n conj(A_{k0+v}[n]) B_b[n] for v < kc, b < nb.
 // Basis vector k is at A + ((k / ar) * astride + k % ar) * N (blocks of ar
@@ -1201,12 +1219,10 @@ struct GDev {
     double2 *G1, *G2;   // Gram matrices of T V_j before the passes and of W after the last one, r x r
     double2 *Rt;        // block column j at Rt + j * (m+1) r r: rows 0 .. (j+2) r of Hbar, reduced in place
     double2 *U;         // Householder vectors of block column j: 2r x r at U + j * 2 r r
-    double2 *T;         // triangular factor of those reflectors (Q = I - U T U^H): r x r at T + j r r
-    double2 *Mw;        // M = U T^H of block column j (Q^H x = x - M U^H x): 2r x r at Mw + j * 2 r r
+    double2 *Mw;        // M = U T^H of block column j (Q = I - U T U^H, Q^H x = x - M U^H x): 2r x r at Mw + j * 2 r r
     double2 *Tinv;      // R^{-1} of the current step, r x r
     double2 *Gv;        // E_1 S with the reflectors applied, ((m+1) r) x q
     double2 *Y;         // least-squares solution times the column scales, (m r) x q
-    double *est;        // per-column residual estimate (scaled units)
     double *scale;      // per-column residual norm at the start of the cycle
     int *flag;          // [0] second Gram-Schmidt pass needed, [2 + (j & 1)] partial breakdown at step j
     int r, q;
@@ -1224,23 +1240,95 @@ __global__ __launch_bounds__(64) void k_bflag(GDev *__restrict__ gd, const int *
     if (a == 0) g.flag[0] = any != 0ull;
 }
 
+// Barrier for data in LDS alone: global loads and stores stay in flight.
+__device__ inline void lds_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// 1 / x and 1 / sqrt(x), x > 0, from the hardware estimates and two Newton steps
+// (about one unit in the last place); beyond the range where the steps' products
+// are normal numbers, by division.
+__device__ inline double recip(double x)
+{
+    if (!(x > 1e-290 && x < 1e290)) return 1.0 / x;
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+__device__ inline double recip_sqrt(double x)
+{
+    if (!(x > 1e-290 && x < 1e290)) return 1.0 / std::sqrt(x);
+    double y = __builtin_amdgcn_rsq(x);
+    y = __builtin_fma(y * 0.5, __builtin_fma(-(x * y), y, 1.0), y);
+    return __builtin_fma(y * 0.5, __builtin_fma(-(x * y), y, 1.0), y);
+}
+
+// Y = the inverse of the lower triangle of L (BMAX x BMAX, in LDS, complete beyond
+// the matrix with zeros), with 1 / L_ii = dinv[i]; a zero there gives a zero row and
+// column.  By blocks of doubling size, Y_21 = -Y_22 (L_21 Y_11): five levels with
+// two barriers each.  tmp: BMAX x BMAX.  All 256 threads; ends with a barrier.
+__device__ inline void lower_inverse(const double2 (*L)[BMAX + 1], const double *dinv, double2 (*Y)[BMAX + 1],
+                                     double2 (*tmp)[BMAX + 1])
+{
+    const int t = threadIdx.x;
+    for (int e = t; e < BMAX * BMAX; e += 256)
+        Y[e / BMAX][e % BMAX] = make_double2(e / BMAX == e % BMAX ? dinv[e % BMAX] : 0.0, 0.0);
+    lds_barrier();
+#pragma unroll
+    for (int lg = 0; lg < 5; ++lg) {
+        const int n = 1 << lg, o = t >> (2 * lg), i = (t >> lg) & (n - 1), c = t & (n - 1);
+        const int c0 = 2 * n * o, r0 = c0 + n;   // block pair o: rows r0 .., columns c0 ..
+        const bool on = t < 16 * n;
+        double2 v = make_double2(0.0, 0.0);
+        if (on) {
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) v = cadd(v, cmul(L[r0 + i][c0 + k], Y[c0 + k][c0 + c]));
+            tmp[r0 + i][c0 + c] = v;
+        }
+        lds_barrier();
+        if (on) {
+            v = make_double2(0.0, 0.0);
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) v = csub(v, cmul(Y[r0 + i][r0 + k], tmp[r0 + k][c0 + c]));
+            Y[r0 + i][c0 + c] = v;
+        }
+        lds_barrier();
+    }
+}
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+__device__ inline d4 mfma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
 // Complete Hbar(:, j) = [C1 + C2; R] (C1 already in place) with R^H R = G2 (Cholesky of the Gram
 // matrix of W after the last pass), and R^{-1} for the next basis block.  A
 // pivot at or below delta^2 times the largest squared column norm of T V_j
 // (G2_aa + sum_k |H_ka|^2: the part removed plus the part kept) marks a partial
 // breakdown; that direction gets a zero row in R.
+//
+// One workgroup on a serial chain of r pivots: eight lanes hold a row of G2 in
+// registers, the pivot's column goes through LDS, one barrier per pivot; the
+// inverse by blocks (matrices in LDS, three barriers a pivot and the inverse row
+// by row: 46 us at r = 32, now 19).
 __global__ __launch_bounds__(256) void k_bchol(GDev *__restrict__ gd, const int *__restrict__ gids, int j, int m,
-                                               double delta)
+                                               double delta, bool passes)
 {
     GDev g = gd[gids[blockIdx.x]];
-    const int r = g.r, K = (j + 1) * r, t = threadIdx.x;
-    const bool two = g.flag[0] != 0;
-    __shared__ double2 Gs[BMAX][BMAX + 1];
+    const int r = g.r, K = (j + 1) * r, t = threadIdx.x, row = t >> 3, l = t & 7;
+    const bool two = passes && g.flag[0] != 0;
+    __shared__ double2 C[BMAX][BMAX + 1];   // column k: G(i, k) when k was the pivot, i >= k
     __shared__ double2 L[BMAX][BMAX + 1];
-    __shared__ double2 Ti[BMAX][BMAX + 1];
+    __shared__ double2 Y[BMAX][BMAX + 1];
+    __shared__ double dinv[BMAX];           // 1 / L_kk, 0 for a broken pivot
     __shared__ double gmax;
-    __shared__ int brk;
     double2 *H = g.Rt + int64_t(j) * (m + 1) * r * r;   // ((m+1) r) x r, row-major
+    double2 x[4];                                       // G(row, l + 8u)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        x[u] = row < r && l + 8 * u < r ? g.G2[row * r + l + 8 * u] : make_double2(0.0, 0.0);
     if (two)   // the first pass wrote its coefficients into H directly
         for (int e = t; e < K * r; e += 256) H[e] = cadd(H[e], g.C2[e]);
     __shared__ double cn[8][BMAX];
@@ -1277,300 +1365,342 @@ __global__ __launch_bounds__(256) void k_bchol(GDev *__restrict__ gd, const int 
         }
         cn[part][a] = (s0 + s1) + (s2 + s3);
     }
-    for (int e = t; e < BMAX * (BMAX + 1); e += 256) {
-        (&L[0][0])[e] = make_double2(0.0, 0.0);
-        (&Ti[0][0])[e] = make_double2(0.0, 0.0);
-    }
-    for (int e = t; e < r * r; e += 256) Gs[e / r][e % r] = g.G2[e];
     __syncthreads();
-    if (t == 0) {
+    if (t < 64) {
         double mx = 0.0;
-        for (int a = 0; a < r; ++a) {
-            double sv = Gs[a][a].x;
-            for (int q = 0; q < 8; ++q) sv += cn[q][a];
-            mx = fmax(mx, sv);
+        if (t < r) {
+            mx = g.G2[t * r + t].x;
+            for (int q = 0; q < 8; ++q) mx += cn[q][t];
         }
-        gmax = mx;
-        brk = 0;
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        if (t == 0) gmax = mx;
     }
     __syncthreads();
-    // right-looking Cholesky of the lower triangle of Gs (G2 = L L^H), one
-    // barrier per column: every thread reads the pivot, column k of L and the
-    // trailing update G(i, l) -= G(i, k) conj(G(l, k)) / G(k, k) (l > k, the
-    // columns the update writes) come from column k of Gs in the same phase
-    for (int k = 0; k < r; ++k) {
-        const double p = Gs[k][k].x;
-        const bool ok = p > delta * delta * gmax;
-        const double d = ok ? std::sqrt(p) : 0.0;
-        if (t == 0 && !ok) brk = 1;
-        if (t >= k && t < r)
-            L[t][k] = t == k ? make_double2(d, 0.0) : (ok ? cscale(1.0 / d, Gs[t][k]) : make_double2(0.0, 0.0));
-        if (ok) {
-            const double ip = 1.0 / p;
-            for (int e = t; e < r * r; e += 256) {
-                const int i = e / r, l = e % r;
-                if (l > k && l <= i)
-                    Gs[i][l] = csub(Gs[i][l], cscale(ip, cmul(Gs[i][k], make_double2(Gs[l][k].x, -Gs[l][k].y))));
+    // right-looking Cholesky of the lower triangle (G2 = L L^H): column k goes to
+    // LDS, then G(i, l) -= G(i, k) conj(G(l, k)) / G(k, k) for l > k in registers
+    const double least = delta * delta * gmax;
+    bool broken = false;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll 1
+        for (int ki = 0; ki < 8; ++ki) {
+            const int k = 8 * kb + ki;
+            if (k >= r) break;
+            if (l == ki) C[row][k] = x[kb];
+            lds_barrier();
+            const double p = C[k][k].x;
+            if (!(p > least)) {
+                broken = true;
+                continue;
+            }
+            const double2 c = cscale(recip(p), C[row][k]);
+#pragma unroll
+            for (int u = kb; u < 4; ++u) {
+                const double2 d = C[l + 8 * u][k];
+                if (u > kb || l > ki) x[u] = csub(x[u], cmul(c, make_double2(d.x, -d.y)));
             }
         }
-        __syncthreads();
-    }
-    // R = L^H into rows K .. K + r of H
-    for (int e = t; e < r * r; e += 256) {
-        const int a = e / r, b = e % r;
-        const double2 v = b >= a ? make_double2(L[b][a].x, -L[b][a].y) : make_double2(0.0, 0.0);
-        H[int64_t(K + a) * r + b] = v;
-    }
-    // L^{-1} by forward substitution, row i at a time, 8 lanes per column c <= i
-    // (Gs is free now and holds it); R^{-1} = (L^{-1})^H; zero for broken pivots
-    for (int i = 0; i < r; ++i) {
-        const int c = t >> 3, part = t & 7;
-        double2 sv = make_double2(0.0, 0.0);
-        if (c <= i && c < r)
-            for (int l = c + part; l < i; l += 8) sv = cadd(sv, cmul(L[i][l], Gs[l][c]));
-        for (int o = 4; o > 0; o >>= 1) {
-            sv.x += __shfl_xor(sv.x, o, 8);
-            sv.y += __shfl_xor(sv.y, o, 8);
-        }
-        if (part == 0 && c <= i && c < r) {
-            const double lii = L[i][i].x;
-            const double2 rhs = c == i ? make_double2(1.0, 0.0) : make_double2(0.0, 0.0);
-            Gs[i][c] = lii > 0.0 ? cscale(1.0 / lii, csub(rhs, sv)) : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-    }
-    for (int e = t; e < r * r; e += 256) {
-        const int a = e / r, b = e % r;
-        Ti[a][b] = b >= a ? make_double2(Gs[b][a].x, -Gs[b][a].y) : make_double2(0.0, 0.0);
+    __syncthreads();
+    // L(i, k) = G(i, k) / sqrt(G(k, k)), R = L^H into rows K .. K + r of H
+    if (t < BMAX) {
+        const double p = t < r ? C[t][t].x : 0.0;
+        dinv[t] = t < r && p > least ? 1.0 / std::sqrt(p) : 0.0;
     }
     __syncthreads();
-    for (int e = t; e < r * r; e += 256) g.Tinv[e] = Ti[e / r][e % r];
-    if (t == 0) g.flag[2 + (j & 1)] = brk;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = l + 8 * u;
+        double2 v = make_double2(0.0, 0.0);
+        if (row < r && k <= row) v = k == row ? make_double2(C[k][k].x * dinv[k], 0.0) : cscale(dinv[k], C[row][k]);
+        if (!(dinv[k] > 0.0)) v = make_double2(0.0, 0.0);
+        L[row][k] = v;
+        if (row < r && k < r) H[int64_t(K + k) * r + row] = make_double2(v.x, -v.y);
+    }
+    lds_barrier();
+    lower_inverse(L, dinv, Y, C);   // R^{-1} = (L^{-1})^H; zero for broken pivots
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = l + 8 * u;
+        if (row < r && k < r) g.Tinv[row * r + k] = make_double2(Y[k][row].x, -Y[k][row].y);
+    }
+    if (t == 0) g.flag[2 + (j & 1)] = broken;
 }
 
-// Apply Q^H = I - U T^H U^H (U: 2r x r, T: r x r upper) to X (2r x nc) in LDS.
-// All 256 threads take part; W1, W2 are r x nc scratch.
-template <int XC>
-__device__ void wy_apply(double2 (*X)[XC], double2 (*Us)[BMAX + 1], double2 (*Ts)[BMAX + 1], double2 (*W1)[XC],
-                         double2 (*W2)[XC], int r, int nc)
-{
-    const int t = threadIdx.x;
-    for (int e = t; e < r * nc; e += 256) {   // W1 = U^H X
-        const int a = e / nc, c = e % nc;
-        double2 sv = make_double2(0.0, 0.0);
-        for (int i = a; i < 2 * r; ++i) sv = cadd(sv, cmulc(Us[i][a], X[i][c]));
-        W1[a][c] = sv;
-    }
-    __syncthreads();
-    for (int e = t; e < r * nc; e += 256) {   // W2 = T^H W1
-        const int a = e / nc, c = e % nc;
-        double2 sv = make_double2(0.0, 0.0);
-        for (int b = 0; b <= a; ++b) sv = cadd(sv, cmulc(Ts[b][a], W1[b][c]));
-        W2[a][c] = sv;
-    }
-    __syncthreads();
-    for (int e = t; e < 2 * r * nc; e += 256) {   // X -= U W2
-        const int i = e / nc, c = e % nc;
-        double2 sv = X[i][c];
-        const int amax = min(i, r - 1);
-        for (int a = 0; a <= amax; ++a) sv = csub(sv, cmul(Us[i][a], W2[a][c]));
-        X[i][c] = sv;
-    }
-    __syncthreads();
-}
-
-constexpr int CS = 8;   // columns of the new block column per workgroup of k_bls_apply
-static_assert(BMAX * CS <= 256, "k_bls_apply keeps one entry of the r x CS row window per thread");
+constexpr int CS = 16;   // columns of the new block column per workgroup of k_bls_apply
 
 // The reflectors of block columns 0 .. j-1 applied, in order, to the new block
 // column of Hbar as x -= M_i (U_i^H x); the columns are independent, CS of them
 // per workgroup.  Block i works on rows ir .. ir + 2r: its upper half is final
 // afterwards and is written back, its lower half stays in LDS as the next
-// block's upper half; U and M of the next block are loaded into registers
-// while the current block is applied.
+// block's upper half (a ring of 2r rows).  Both products on the FP64 matrix cores:
+// every entry of U and M is used once per workgroup, so its fragment goes from
+// global memory into registers, one block ahead, and only X and U^H X pass through
+// LDS (a serial chain of j blocks; vector instructions on operands staged in LDS:
+// 5.0 us a block at r = 32, now 4.0).
+// W1 = U^H X: waves 0, 1 the real and imaginary parts of rows 0 .. 15, waves 2, 3
+// of rows 16 .. 31; X -= M W1: 16 rows of the window per wave.
 __global__ __launch_bounds__(256) void k_bls_apply(GDev *__restrict__ gd, const int *__restrict__ gids, int j, int m)
 {
     GDev g = gd[gids[blockIdx.x]];
     const int r = g.r, c0 = blockIdx.y * CS, nc = min(CS, r - c0), t = threadIdx.x;
     if (nc <= 0 || j == 0) return;
-    __shared__ double2 X[2 * BMAX][CS + 1];
-    __shared__ double2 Us[2 * BMAX][BMAX + 1];
-    __shared__ double2 Ms[2 * BMAX][BMAX + 1];
-    __shared__ double2 W1[BMAX][CS + 1];
+    __shared__ double2 X[2 * BMAX][CS + 1];   // row w of the window at (w + base) mod 2r
+    __shared__ double Wr[BMAX][CS + 1], Wi[BMAX][CS + 1];
+    const int lane = t & 63, wv = t >> 6, f = lane & 15, kq = lane >> 4, at = 16 * (wv >> 1), part = wv & 1;
     double2 *H = g.Rt + int64_t(j) * (m + 1) * r * r;
-    const int nu = 2 * r * r;   // entries of U (and of M) per block column, <= 2048
-    double2 pu[8], pm[8];
-    double2 ph = make_double2(0.0, 0.0);   // the row entry t of the next lower half (r nc <= 256 entries)
-    auto fetch = [&](int i) {
-        const double2 *Ui = g.U + int64_t(i) * nu, *Mi = g.Mw + int64_t(i) * nu;
+    const int nu = 2 * r * r;
+    double2 U[16], M[8], next[4];   // fragments of U^H and M; rows entering the window after this block
+    auto fetch_u = [&](int i) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = t + 256 * u;
-            pu[u] = e < nu ? Ui[e] : make_double2(0.0, 0.0);
-            pm[u] = e < nu ? Mi[e] : make_double2(0.0, 0.0);
+        for (int ks = 0; ks < 16; ++ks) {
+            const int w = 4 * ks + kq, a = at + f;
+            U[ks] = w < 2 * r && a < r ? g.U[int64_t(i) * nu + w * r + a] : make_double2(0.0, 0.0);
         }
-        // rows (i + 1) r .. + r of the column block, the lower half of block i's window
-        // (untouched until then: this workgroup writes only rows below the window)
-        if (i + 1 <= j && t < r * nc) ph = H[int64_t((i + 1) * r + t / nc) * r + c0 + t % nc];
     };
-    fetch(0);
-    for (int e = t; e < 2 * r * nc; e += 256) X[e / nc][e % nc] = H[int64_t(e / nc) * r + c0 + e % nc];
-    for (int i = 0; i < j; ++i) {
-        __syncthreads();
+    auto fetch_m = [&](int i) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = t + 256 * u;
-            if (e < nu) {
-                Us[e / r][e % r] = pu[u];
-                Ms[e / r][e % r] = pm[u];
-            }
+        for (int ks = 0; ks < 8; ++ks) {
+            const int w = 16 * wv + f, a = 4 * ks + kq;
+            M[ks] = w < 2 * r && a < r ? g.Mw[int64_t(i) * nu + w * r + a] : make_double2(0.0, 0.0);
         }
-        __syncthreads();
-        if (i + 1 < j) fetch(i + 1);
-        for (int e = t; e < r * nc; e += 256) {   // W1 = U^H X, four independent partial sums
-            const int a = e / nc, c = e % nc;
-            double2 s0 = make_double2(0.0, 0.0), s1 = s0, s2 = s0, s3 = s0;
-            int row = a;
-            for (; row + 3 < 2 * r; row += 4) {
-                s0 = cadd(s0, cmulc(Us[row][a], X[row][c]));
-                s1 = cadd(s1, cmulc(Us[row + 1][a], X[row + 1][c]));
-                s2 = cadd(s2, cmulc(Us[row + 2][a], X[row + 2][c]));
-                s3 = cadd(s3, cmulc(Us[row + 3][a], X[row + 3][c]));
-            }
-            for (; row < 2 * r; ++row) s0 = cadd(s0, cmulc(Us[row][a], X[row][c]));
-            W1[a][c] = cadd(cadd(s0, s1), cadd(s2, s3));
+    };
+    auto fetch_rows = [&](int i) {   // for each row w < r of this lane's tile: row (i + 2) r + w of H
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int w = 16 * wv + kq + 4 * q;
+            next[q] = w < r && f < nc && i + 1 < j ? H[int64_t((i + 2) * r + w) * r + c0 + f] : make_double2(0.0, 0.0);
         }
-        __syncthreads();
-        for (int e = t; e < 2 * r * nc; e += 256) {   // X -= M W1, four independent partial sums
-            const int row = e / nc, c = e % nc;
-            const int amax = min(row, r - 1);
-            double2 s0 = make_double2(0.0, 0.0), s1 = s0, s2 = s0, s3 = s0;
-            int a = 0;
-            for (; a + 3 <= amax; a += 4) {
-                s0 = cadd(s0, cmul(Ms[row][a], W1[a][c]));
-                s1 = cadd(s1, cmul(Ms[row][a + 1], W1[a + 1][c]));
-                s2 = cadd(s2, cmul(Ms[row][a + 2], W1[a + 2][c]));
-                s3 = cadd(s3, cmul(Ms[row][a + 3], W1[a + 3][c]));
+    };
+    fetch_u(0);
+    fetch_m(0);
+    fetch_rows(0);
+    for (int e = t; e < 2 * BMAX * CS; e += 256) {
+        const int w = e / CS, c = e % CS;
+        X[w][c] = w < 2 * r && c < nc ? H[int64_t(w) * r + c0 + c] : make_double2(0.0, 0.0);
+    }
+    int base = 0;
+    auto ring = [&](int w) {
+        const int p = w + base;
+        return w >= 2 * r ? w : p >= 2 * r ? p - 2 * r : p;
+    };
+    for (int i = 0; i < j; ++i) {
+        lds_barrier();
+        {
+            d4 s0 = { 0.0, 0.0, 0.0, 0.0 }, s1 = s0;   // Re: Ur Xr + Ui Xi, Im: Ur Xi - Ui Xr
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) {
+                const double2 x = X[ring(4 * ks + kq)][f];
+                s0 = mfma64(U[ks].x, part ? x.y : x.x, s0);
+                s1 = mfma64(U[ks].y, part ? -x.x : x.y, s1);
             }
-            for (; a <= amax; ++a) s0 = cadd(s0, cmul(Ms[row][a], W1[a][c]));
-            X[row][c] = csub(X[row][c], cadd(cadd(s0, s1), cadd(s2, s3)));
+            if (i + 1 < j) fetch_u(i + 1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) (part ? Wi : Wr)[at + kq + 4 * q][f] = s0[q] + s1[q];
         }
-        __syncthreads();
-        // rows ir .. ir + r are final; shift the lower half up and take the next rows
-        // (fetched with block i + 1's reflectors)
-        if (i + 1 < j) {
-            if (t < r * nc) {
-                const int row = t / nc, c = t % nc;
-                H[int64_t(i * r + row) * r + c0 + c] = X[row][c];
-                X[row][c] = X[r + row][c];
-                X[r + row][c] = ph;
-            }
-        } else {
-            for (int e = t; e < 2 * r * nc; e += 256) H[int64_t(i * r + e / nc) * r + c0 + e % nc] = X[e / nc][e % nc];
+        lds_barrier();
+        d4 xr, xi;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double2 x = X[ring(16 * wv + kq + 4 * q)][f];
+            xr[q] = x.x;
+            xi[q] = x.y;
         }
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const double br = Wr[4 * ks + kq][f], bi = Wi[4 * ks + kq][f];
+            xr = mfma64(-M[ks].x, br, xr);
+            xi = mfma64(-M[ks].x, bi, xi);
+            xr = mfma64(M[ks].y, bi, xr);
+            xi = mfma64(-M[ks].y, br, xi);
+        }
+        if (i + 1 < j) fetch_m(i + 1);
+        // rows below r of the window are final and make room for the rows entering it
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int w = 16 * wv + kq + 4 * q;
+            const double2 x = make_double2(xr[q], xi[q]);
+            if (w < 2 * r && f < nc && (w < r || i + 1 == j)) H[int64_t(i * r + w) * r + c0 + f] = x;
+            X[ring(w)][f] = pick(w < r, next[q], x);
+        }
+        if (i + 1 < j) fetch_rows(i + 1);
+        base = base ? 0 : r;
     }
 }
 
 // New reflectors for rows jr .. jr + 2r of the new block column of Hbar (the
 // earlier ones already applied), their triangular factor, the same applied to
-// E_1 S, and the residual estimates.  One workgroup per group.
-__global__ __launch_bounds__(256) void k_bls_qr(GDev *__restrict__ gd, const int *__restrict__ gids, int j, int m)
+// E_1 S, and the residual estimates, which go to host memory with the step's
+// breakdown mark.  One workgroup per group, bound by the serial chain of r
+// reflectors: eight lanes hold a column (rows l + 8u) in registers; the lanes of
+// column k form its reflector and put it into LDS, and after one barrier every
+// column takes its product with it: the columns right of k the update, those left
+// of k (which hold their own reflectors by now) the entry of U^H U that the
+// triangular factor T = (diag(1 / beta) + triu(U^H U, 1))^{-1} needs.  M = U T^H
+// and its application on the FP64 matrix cores (columns in LDS, three barriers a
+// reflector, two a column of T, vector instructions throughout: 148 us at r = 32;
+// now 51).
+__global__ __launch_bounds__(256) void k_bls_qr(GDev *__restrict__ gd, const int *__restrict__ gids, int j, int m,
+                                                double *__restrict__ est, int *__restrict__ mark)
 {
-    GDev g = gd[gids[blockIdx.x]];
-    const int r = g.r, q = g.q, t = threadIdx.x;
-    __shared__ double2 X[2 * BMAX][BMAX + 1];
-    __shared__ double2 Us[2 * BMAX][BMAX + 1];
-    __shared__ double2 Ts[BMAX][BMAX + 1];
-    __shared__ double2 W1[BMAX][BMAX + 1];
-    __shared__ double2 W2[BMAX][BMAX + 1];
-    __shared__ double2 alpha_s;
-    __shared__ double beta_s;
-    double2 *H = g.Rt + int64_t(j) * (m + 1) * r * r;
-    // Householder QR of rows jr .. jr + 2r
-    for (int e = t; e < 2 * r * r; e += 256) {
-        X[e / r][e % r] = H[int64_t(j) * r * r + e];
-        Us[e / r][e % r] = make_double2(0.0, 0.0);
-    }
-    for (int e = t; e < r * r; e += 256) Ts[e / r][e % r] = make_double2(0.0, 0.0);
-    __syncthreads();
-    for (int k = 0; k < r; ++k) {
-        if (t < 64) {   // one wave: the reflector of column k
-            double s = 0.0;
-            for (int i = k + t; i < 2 * r; i += 64) s += X[i][k].x * X[i][k].x + X[i][k].y * X[i][k].y;
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-            const double nx = std::sqrt(s);
-            const double2 x0 = X[k][k];
-            const double ax0 = std::sqrt(x0.x * x0.x + x0.y * x0.y);
-            const double2 ph = ax0 > 0.0 ? make_double2(x0.x / ax0, x0.y / ax0) : make_double2(1.0, 0.0);
-            const double2 al = make_double2(-ph.x * nx, -ph.y * nx);
-            // v = x - alpha e_1; |v|^2 = |x|^2 - 2 Re(conj(alpha) x0) + |alpha|^2 = 2 nx (nx + |x0|)
-            const double vv = 2.0 * nx * (nx + ax0);
-            for (int i = k + t; i < 2 * r; i += 64) Us[i][k] = i == k ? csub(X[k][k], al) : X[i][k];
-            if (t == 0) {
-                alpha_s = al;
-                beta_s = vv > 0.0 ? 2.0 / vv : 0.0;
-                Ts[k][k] = make_double2(vv > 0.0 ? 2.0 / vv : 0.0, 0.0);
+    const int gid = gids[blockIdx.x];
+    GDev g = gd[gid];
+    const int r = g.r, q = g.q, t = threadIdx.x, c = t >> 3, l = t & 7;
+    const int lane = t & 63, wv = t >> 6, f = lane & 15, kq = lane >> 4;
+    __shared__ double2 Us[2 * BMAX][BMAX + 1];   // U, then M
+    __shared__ double2 Gs[2 * BMAX][BMAX + 1];   // E_1 S rows jr .. jr + 2r
+    __shared__ double2 W[BMAX][BMAX + 1];        // tril((U^H U)^T, -1), then U^H (E_1 S)
+    __shared__ double2 Tt[BMAX][BMAX + 1];       // T^T
+    __shared__ double bet[BMAX];
+    const double2 zero = make_double2(0.0, 0.0);
+    double2 *H = g.Rt + int64_t(j) * (m + 1) * r * r + int64_t(j) * r * r, *Gv = g.Gv + int64_t(j) * r * q;
+    double2 *Uj = g.U + int64_t(j) * 2 * r * r, *Mj = g.Mw + int64_t(j) * 2 * r * r;
+    double2 x[8], gx[8], rd = zero;   // the column; of E_1 S; its diagonal entry of R
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = c < r && l + 8 * u < 2 * r ? H[(l + 8 * u) * r + c] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) gx[u] = c < q && l + 8 * u < 2 * r ? Gv[(l + 8 * u) * q + c] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) Us[l + 8 * u][c] = zero;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) W[l + 8 * u][c] = zero;
+    if (t < BMAX) bet[t] = 0.0;
+    lds_barrier();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll 1
+        for (int ki = 0; ki < 8; ++ki) {
+            const int k = 8 * kb + ki;
+            if (k >= r) break;
+            if (c == k) {
+                double s0 = 0.0, s1 = 0.0;
+                const double2 xd = pick(l >= ki, x[kb], zero), xk = pick(l == ki, x[kb], zero);
+                s0 = xd.x * xd.x;
+                s1 = xd.y * xd.y;
+#pragma unroll
+                for (int u = kb + 1; u < 8; ++u) {
+                    s0 = __builtin_fma(x[u].x, x[u].x, s0);
+                    s1 = __builtin_fma(x[u].y, x[u].y, s1);
+                }
+                const double n2 = sum8(s0 + s1);
+                const double2 x0 = sum8(xk);   // one lane holds it, the others zero
+                const double a2 = x0.x * x0.x + x0.y * x0.y;
+                const double nx = n2 > 0.0 ? n2 * recip_sqrt(n2) : n2, ia = a2 > 0.0 ? recip_sqrt(a2) : 0.0;
+                const double2 al = a2 > 0.0 ? make_double2(-x0.x * ia * nx, -x0.y * ia * nx) : make_double2(-nx, 0.0);
+                // v = x - alpha e_1; |v|^2 = |x|^2 - 2 Re(conj(alpha) x0) + |alpha|^2 = 2 nx (nx + |x0|)
+                const double hv = nx * (nx + a2 * ia);
+                if (l == 0) bet[k] = hv > 0.0 ? recip(hv) : 0.0;
+                rd = al;
+                x[kb] = pick(l == ki, csub(x0, al), x[kb]);
+                Us[l + 8 * kb][k] = pick(l < ki, zero, x[kb]);
+#pragma unroll
+                for (int u = kb + 1; u < 8; ++u) Us[l + 8 * u][k] = x[u];
+            }
+            lds_barrier();
+            double2 v[8], s = zero;
+#pragma unroll
+            for (int u = kb; u < 8; ++u) v[u] = Us[l + 8 * u][k];
+#pragma unroll
+            for (int u = kb; u < 8; ++u) s = cadd(s, cmulc(v[u], x[u]));
+            s = sum8(s);
+            if (c > k) {   // x -= beta v (v^H x)
+                s = cscale(bet[k], s);
+#pragma unroll
+                for (int u = kb; u < 8; ++u) x[u] = csub(x[u], cmul(v[u], s));
+            } else if (c < k && l == 0) {
+                W[k][c] = make_double2(s.x, -s.y);   // u_c^H u_k
             }
         }
-        __syncthreads();
-        const double beta = beta_s;
-        // apply to columns k+1 .. r-1: x -= beta v (v^H x), one column per thread group of 8
-        for (int c = k + 1 + (t >> 3); c < r; c += 32) {
-            const int l = t & 7;
-            double2 s = make_double2(0.0, 0.0);
-            for (int i = k + l; i < 2 * r; i += 8) s = cadd(s, cmulc(Us[i][k], X[i][c]));
-            for (int o = 4; o > 0; o >>= 1) {
-                s.x += __shfl_xor(s.x, o, 8);
-                s.y += __shfl_xor(s.y, o, 8);
+    // x: R above the diagonal, the reflector from it on
+    if (c < r)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = l + 8 * u;
+            if (i < 2 * r) {
+                H[i * r + c] = pick(i < c, x[u], pick(i == c, rd, zero));
+                Uj[i * r + c] = pick(i < c, zero, x[u]);
             }
-            for (int i = k + l; i < 2 * r; i += 8) X[i][c] = csub(X[i][c], cscale(beta, cmul(Us[i][k], s)));
         }
-        __syncthreads();
-        if (t == 0) X[k][k] = alpha_s;
-        for (int i = k + 1 + t; i < 2 * r; i += 256) X[i][k] = make_double2(0.0, 0.0);
-        __syncthreads();
-    }
-    // T of the new reflectors: T(0:k, k) = -beta_k T(0:k, 0:k) (U(:, 0:k)^H u_k)
-    for (int e = t; e < r * r; e += 256) {   // W1 = U^H U (upper part used)
-        const int a = e / r, b = e % r;
-        double2 s = make_double2(0.0, 0.0);
-        if (a < b)
-            for (int i = b; i < 2 * r; ++i) s = cadd(s, cmulc(Us[i][a], Us[i][b]));
-        W1[a][b] = s;
-    }
-    __syncthreads();
-    for (int k = 1; k < r; ++k) {
-        if (t < k) {
-            double2 s = make_double2(0.0, 0.0);
-            for (int l = t; l < k; ++l) s = cadd(s, cmul(Ts[t][l], W1[l][k]));
-            W2[t][0] = cscale(-Ts[k][k].x, s);
+    lds_barrier();
+    lower_inverse(W, bet, Tt, reinterpret_cast<double2(*)[BMAX + 1]>(&Gs[0][0]));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) Gs[l + 8 * u][c] = gx[u];
+    lds_barrier();
+    // M = U T^H: rows 16 wv .., columns 0 .. 15 and 16 .. 31
+    d4 mr[2], mi[2], wr, wi;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) mr[n] = mi[n] = d4{ 0.0, 0.0, 0.0, 0.0 };
+    wr = wi = d4{ 0.0, 0.0, 0.0, 0.0 };
+#pragma unroll 2
+    for (int ks = 0; ks < 8; ++ks) {
+        const double2 a = Us[16 * wv + f][4 * ks + kq];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const double2 b = Tt[4 * ks + kq][16 * n + f];   // conj(T(n, k))
+            mr[n] = mfma64(a.x, b.x, mr[n]);
+            mi[n] = mfma64(a.y, b.x, mi[n]);
+            mr[n] = mfma64(a.y, b.y, mr[n]);
+            mi[n] = mfma64(-a.x, b.y, mi[n]);
         }
-        __syncthreads();
-        if (t < k) Ts[t][k] = W2[t][0];
-        __syncthreads();
     }
-    double2 *Uj = g.U + int64_t(j) * 2 * r * r, *Tj = g.T + int64_t(j) * r * r, *Mj = g.Mw + int64_t(j) * 2 * r * r;
-    for (int e = t; e < 2 * r * r; e += 256) {
-        H[int64_t(j) * r * r + e] = X[e / r][e % r];
-        Uj[e] = Us[e / r][e % r];
-        const int row = e / r, a = e % r;   // M = U T^H: sum over b >= a, b <= row
-        double2 sv = make_double2(0.0, 0.0);
-        const int bmax = min(row, r - 1);
-        for (int b = a; b <= bmax; ++b) sv = cadd(sv, cmul(Us[row][b], make_double2(Ts[a][b].x, -Ts[a][b].y)));
-        Mj[e] = sv;
+    // U^H (E_1 S): rows 16 (wv / 2) .., columns 16 (wv % 2) ..
+#pragma unroll 2
+    for (int ks = 0; ks < 16; ++ks) {
+        const double2 a = Us[4 * ks + kq][16 * (wv >> 1) + f], b = Gs[4 * ks + kq][16 * (wv & 1) + f];
+        wr = mfma64(a.x, b.x, wr);
+        wi = mfma64(a.x, b.y, wi);
+        wr = mfma64(a.y, b.y, wr);
+        wi = mfma64(-a.y, b.x, wi);
     }
-    for (int e = t; e < r * r; e += 256) Tj[e] = Ts[e / r][e % r];
-    __syncthreads();
-    // E_1 S rows jr .. jr + 2r, q columns
-    for (int e = t; e < 2 * r * q; e += 256) X[e / q][e % q] = g.Gv[int64_t(j) * r * q + e];
-    __syncthreads();
-    wy_apply<BMAX + 1>(X, Us, Ts, W1, W2, r, q);
-    for (int e = t; e < 2 * r * q; e += 256) g.Gv[int64_t(j) * r * q + e] = X[e / q][e % q];
-    if (t < q) {
-        double s = 0.0;
-        for (int i = r; i < 2 * r; ++i) s += X[i][t].x * X[i][t].x + X[i][t].y * X[i][t].y;
-        g.est[t] = std::sqrt(s);
+    lds_barrier();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const int i = 16 * wv + kq + 4 * e, a = 16 * n + f;
+            Us[i][a] = make_double2(mr[n][e], mi[n][e]);
+            if (i < 2 * r && a < r) Mj[i * r + a] = make_double2(mr[n][e], mi[n][e]);
+        }
+        W[16 * (wv >> 1) + kq + 4 * e][16 * (wv & 1) + f] = make_double2(wr[e], wi[e]);
     }
+    lds_barrier();
+    // E_1 S -= M (U^H E_1 S), rows 16 wv ..
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double2 v = Gs[16 * wv + kq + 4 * e][16 * n + f];
+            mr[n][e] = v.x;
+            mi[n][e] = v.y;
+        }
+#pragma unroll 2
+    for (int ks = 0; ks < 8; ++ks) {
+        const double2 a = Us[16 * wv + f][4 * ks + kq];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const double2 b = W[4 * ks + kq][16 * n + f];
+            mr[n] = mfma64(-a.x, b.x, mr[n]);
+            mi[n] = mfma64(-a.x, b.y, mi[n]);
+            mr[n] = mfma64(a.y, b.y, mr[n]);
+            mi[n] = mfma64(-a.y, b.x, mi[n]);
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Gs[16 * wv + kq + 4 * e][16 * n + f] = make_double2(mr[n][e], mi[n][e]);
+    lds_barrier();
+    // the residual estimates from its last r rows
+    double e2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int i = l + 8 * u;
+        const double2 v = Gs[i][c];
+        if (c < q && i < 2 * r) Gv[i * q + c] = v;
+        if (i >= r && i < 2 * r) e2 += v.x * v.x + v.y * v.y;
+    }
+    e2 = sum8(e2);
+    if (c < q && l == 0) est[int64_t(gid) * BMAX + c] = std::sqrt(e2);
+    if (t == 0) mark[gid] = g.flag[2 + (j & 1)];
 }
 
 // Y = R^{-1} Gv(0 : J r, :) by right-looking block back substitution (R upper
@@ -1578,52 +1708,81 @@ __global__ __launch_bounds__(256) void k_bls_qr(GDev *__restrict__ gd, const int
 // row I from the last: workgroup b (block row b <= I) takes R(b, I+1) Y_{I+1}
 // off its rows of Gv, and the workgroup of block row I then solves
 // R_II Y_I = Gv_I.  Y holds the solution times the column scales; Gv is consumed.
+//
+// Eight lanes take a column of Y (rows l + 8u): the blocks of R come through LDS,
+// the triangular solve is a chain of r sums over the eight lanes without barriers
+// (a lane per column and rows of R from global memory: 34 us a launch at
+// r = q = 32, now 17).
 __global__ __launch_bounds__(256) void k_bls_back(GDev *__restrict__ gd, const int *__restrict__ gids,
                                                   const int *__restrict__ steps, int I, int m)
 {
     const int gid = gids[blockIdx.x];
     GDev g = gd[gid];
-    const int r = g.r, q = g.q, t = threadIdx.x, b = blockIdx.y, J = steps[gid];
+    const int r = g.r, q = g.q, t = threadIdx.x, b = blockIdx.y, J = steps[gid], c = t >> 3, l = t & 7;
     if (I >= J || b > I) return;
     const int64_t bs = int64_t(m + 1) * r * r;
     __shared__ double2 Ys[BMAX][BMAX + 1];
-    __shared__ double2 S[BMAX][BMAX + 1];
     __shared__ double2 D[BMAX][BMAX + 1];
-    if (I + 1 < J) {   // Y_{I+1} without the column scales
-        for (int e = t; e < r * q; e += 256) {
-            const int c = e % q;
-            const double sc = g.scale[c];
-            const double2 y = g.Y[int64_t((I + 1) * r + e / q) * q + c];
-            Ys[e / q][c] = sc > 0.0 ? cscale(1.0 / sc, y) : make_double2(0.0, 0.0);
+    __shared__ double2 Rs[BMAX][BMAX + 1];
+    __shared__ double2 di[BMAX];   // 1 / D_aa, 0 for a zero diagonal
+    const double2 zero = make_double2(0.0, 0.0);
+    const bool upd = I + 1 < J, solve = b == I;
+    for (int e = t; e < BMAX * BMAX; e += 256) {
+        const int i = e / BMAX, k = e % BMAX;
+        if (upd) {
+            Rs[i][k] = i < r && k < r ? g.Rt[(I + 1) * bs + int64_t(b * r + i) * r + k] : make_double2(0.0, 0.0);
+            double2 y = zero;
+            if (i < r && k < q) {   // Y_{I+1} without the column scales
+                const double sc = g.scale[k];
+                if (sc > 0.0) y = cscale(1.0 / sc, g.Y[int64_t((I + 1) * r + i) * q + k]);
+            }
+            Ys[i][k] = y;
         }
-        __syncthreads();
-        const double2 *Rb = g.Rt + (I + 1) * bs;
-        for (int e = t; e < r * q; e += 256) {
-            const int row = b * r + e / q, c = e % q;
-            double2 sv = g.Gv[int64_t(row) * q + c];
-            const double2 *Rr = Rb + int64_t(row) * r;
-            for (int k = 0; k < r; ++k) sv = csub(sv, cmul(Rr[k], Ys[k][c]));
-            g.Gv[int64_t(row) * q + c] = sv;
-        }
-    }
-    if (b != I) return;
-    __syncthreads();
-    const double2 *Rb = g.Rt + I * bs;
-    for (int e = t; e < r * r; e += 256) D[e / r][e % r] = Rb[int64_t(I * r + e / r) * r + e % r];
-    for (int e = t; e < r * q; e += 256) S[e / q][e % q] = g.Gv[int64_t(I * r + e / q) * q + e % q];
-    __syncthreads();
-    if (t < q) {
-        for (int a = r - 1; a >= 0; --a) {
-            double2 sv = S[a][t];
-            for (int c = a + 1; c < r; ++c) sv = csub(sv, cmul(D[a][c], S[c][t]));
-            const double2 d = D[a][a];
-            const double dd = d.x * d.x + d.y * d.y;
-            S[a][t] = dd > 0.0 ? make_double2((sv.x * d.x + sv.y * d.y) / dd, (sv.y * d.x - sv.x * d.y) / dd)
-                               : make_double2(0.0, 0.0);
+        if (solve) {
+            const double2 d = i < r && k < r ? g.Rt[I * bs + int64_t(I * r + i) * r + k] : make_double2(0.0, 0.0);
+            D[i][k] = d;
+            if (i == k) {
+                const double dd = d.x * d.x + d.y * d.y;
+                di[i] = dd > 0.0 ? make_double2(d.x / dd, -d.y / dd) : zero;
+            }
         }
     }
+    double2 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        x[u] = c < q && l + 8 * u < r ? g.Gv[int64_t(b * r + l + 8 * u) * q + c] : make_double2(0.0, 0.0);
     __syncthreads();
-    for (int e = t; e < r * q; e += 256) g.Y[int64_t(I * r + e / q) * q + e % q] = cscale(g.scale[e % q], S[e / q][e % q]);
+    if (upd) {
+#pragma unroll 2
+        for (int k = 0; k < r; ++k) {
+            const double2 y = Ys[k][c];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = csub(x[u], cmul(Rs[l + 8 * u][k], y));
+        }
+        if (!solve)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (c < q && l + 8 * u < r) g.Gv[int64_t(b * r + l + 8 * u) * q + c] = x[u];
+    }
+    if (!solve) return;
+    double2 y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) y[u] = zero;
+    for (int a = r - 1; a >= 0; --a) {
+        double2 s = zero;   // S_a - sum over k > a; the entry itself lies in one of the lanes
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            s = cadd(s, pick(l + 8 * u == a, x[u], zero));
+            s = csub(s, cmul(D[a][l + 8 * u], y[u]));   // y zero up to a
+        }
+        const double2 v = cmul(sum8(s), di[a]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            y[u] = pick(l + 8 * u == a, v, y[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (c < q && l + 8 * u < r) g.Y[int64_t(I * r + l + 8 * u) * q + c] = cscale(g.scale[c], y[u]);
 }
 
 // Start-of-cycle uploads of every group in one launch: dst[0 .. n) = src, then
@@ -2064,10 +2223,9 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
     double *nrm = db.get<double>(size_t(R));
     // group regions
     const size_t p2 = size_t(p) * p;
-    const size_t per = (m + 1) * p2 + 2 * p2 + size_t(m) * (m + 1) * p2 + 4 * size_t(m) * p2 + size_t(m) * p2 + p2 +
+    const size_t per = (m + 1) * p2 + 2 * p2 + size_t(m) * (m + 1) * p2 + 4 * size_t(m) * p2 + p2 +
                        (m + 1) * p2 + size_t(m) * p2;
     double2 *greg = db.get<double2>(per * Gmax);
-    double *gest = db.get<double>(size_t(Gmax) * BMAX);
     double *gscale = db.get<double>(size_t(Gmax) * BMAX);
     int *gflag = db.get<int>(size_t(Gmax) * 4);
     GDev *gd = db.get<GDev>(size_t(Gmax));
@@ -2080,12 +2238,10 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
         d.G2 = b; b += p2;
         d.Rt = b; b += size_t(m) * (m + 1) * p2;
         d.U = b; b += 2 * size_t(m) * p2;
-        d.T = b; b += size_t(m) * p2;
         d.Mw = b; b += 2 * size_t(m) * p2;
         d.Tinv = b; b += p2;
         d.Gv = b; b += (m + 1) * p2;
         d.Y = b;
-        d.est = gest + g * BMAX;
         d.scale = gscale + g * BMAX;
         d.flag = gflag + 4 * g;
     }
@@ -2099,11 +2255,11 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
     BIE_HIP(hipEventRecord(ev_arena[1], s));
     BIE_HIP(hipEventRecord(ev_s3[0], s3));
     BIE_HIP(hipEventRecord(ev_s3[1], s3));
-    double *hest[2];
+    double *hest[2];   // estimates and breakdown marks, written by k_bls_qr
     int *hfl[2];
     for (int i = 0; i < 2; ++i) {
         hest[i] = db.pinned<double>(size_t(Gmax) * BMAX);
-        hfl[i] = db.pinned<int>(size_t(Gmax) * 4);
+        hfl[i] = db.pinned<int>(size_t(Gmax));
     }
     int *gsteps = db.get<int>(size_t(Gmax));
     double2 *gG = db.get<double2>(size_t(Gmax) * p2);   // Gram matrices of the start blocks, gathered
@@ -2298,8 +2454,15 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
         // least-squares update of step j runs on the second stream beside the
         // orthogonalisation of step j + 1; its estimates are read one step late,
         // so a group that has met its targets runs at most one step more
-        // (discarded: its solution uses the steps up to the decision).
-        int prev = -1;
+        // (discarded: its solution uses the steps up to the decision).  Up to
+        // LS_EARLY columns it is queued with step j itself and so runs beside the
+        // product of step j + 1, whose workgroups leave compute units free then (mixed
+        // precision, restart 30, ms beside / after the product: 1920 unknowns and 16
+        // vectors 29.7 / 37.0, 64 16.9 / 19.1, 256 22.8 / 23.8; 7680 and 256 369 / 376);
+        // beyond them after that product (7680 and 512 669 / 653).  A group that
+        // step j - 1 turns out to end is updated in vain: rows and block columns
+        // beyond those its solution takes.
+        int prev = -1, ls_queued = -1;   // last step with a queued least-squares update
         std::vector<int> prev_act;
         for (int j = 0; j <= m; ++j) {
             std::vector<int> act, cols;
@@ -2314,30 +2477,28 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
             BIE_HIP(hipEventSynchronize(ev_arena[j & 1]));
             BIE_HIP(hipEventSynchronize(ev_s3[j & 1]));
             A.reset();
-            // least-squares update of step prev on the second stream, queued after
-            // this step's product so that it shares the GPU with the smaller
-            // kernels of the step instead of with the product's workgroups
-            bool ls_queued = false;
-            auto launch_ls = [&]() {
-                if (prev < 0 || ls_queued) return;
-                ls_queued = true;
+            // least-squares update of step i on the second stream, for the active groups of
+            // which (dls: all of them, their table on the device)
+            auto launch_ls = [&](int i, const std::vector<int> &which, const int *dls = nullptr) {
+                if (i < 0 || ls_queued >= i) return;
+                ls_queued = i;
                 std::vector<int> lsg;
-                for (int g : prev_act)
+                for (int g : which)
                     if (grp[g].active) lsg.push_back(g);
                 if (!lsg.empty()) {
-                    const int *dls = A.put(lsg);
-                    A.flush(s);
+                    if (!dls) {
+                        dls = A.put(lsg);
+                        A.flush(s);
+                    }
                     BIE_HIP(hipEventRecord(ev_prod, s));
                     BIE_HIP(hipStreamWaitEvent(s2, ev_prod, 0));
                     hipLaunchKernelGGL(k_bls_apply, dim3(unsigned(lsg.size()), unsigned((p + CS - 1) / CS)), dim3(256), 0,
-                                       s2, gd, dls, prev, m);
-                    hipLaunchKernelGGL(k_bls_qr, dim3(unsigned(lsg.size())), dim3(256), 0, s2, gd, dls, prev, m);
+                                       s2, gd, dls, i, m);
+                    hipLaunchKernelGGL(k_bls_qr, dim3(unsigned(lsg.size())), dim3(256), 0, s2, gd, dls, i, m,
+                                       hest[i & 1], hfl[i & 1]);
                     BIE_HIP(hipGetLastError());
                 }
-                BIE_HIP(hipMemcpyAsync(hest[prev & 1], gest, size_t(ng) * BMAX * sizeof(double), hipMemcpyDeviceToHost,
-                                       s2));
-                BIE_HIP(hipMemcpyAsync(hfl[prev & 1], gflag, size_t(ng) * 4 * sizeof(int), hipMemcpyDeviceToHost, s2));
-                BIE_HIP(hipEventRecord(ev_ls[prev & 1], s2));
+                BIE_HIP(hipEventRecord(ev_ls[i & 1], s2));
             };
             if (!act.empty()) {
                 const int na = int(act.size());
@@ -2381,7 +2542,7 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
                 } else {
                     gemm64_product(op, Vj, N, Wb, N, nullptr, 0, nc, dc, s);
                 }
-                launch_ls();
+                launch_ls(prev, prev_act);
                 // Gram matrices of W: FP64 matrix cores in the mixed forms
                 auto gram = [&](const DItem *gi, size_t n) {
                     if constexpr (std::is_same<VT, double2>::value) launch_dots<double2, 1>(gi, n, N, part, p, s);
@@ -2400,17 +2561,18 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
                 basis_comb<VT>(pc0, ci[0].size(), N, p, s);
                 prof_end(5, s);
                 gram(pp0, dpost[0].size());
-                hipLaunchKernelGGL(k_bflag, dim3(unsigned(na)), dim3(64), 0, s, gd, dg, reorth);
                 if (reorth > 0.0) {
+                    hipLaunchKernelGGL(k_bflag, dim3(unsigned(na)), dim3(64), 0, s, gd, dg, reorth);
                     basis_dots<VT>(pv1, dv[1].size(), N, part, p, s);
                     basis_comb<VT>(pc1, ci[1].size(), N, p, s);
                     gram(pp1, dpost[1].size());
                 }
-                hipLaunchKernelGGL(k_bchol, dim3(unsigned(na)), dim3(256), 0, s, gd, dg, j, m, DELTA);
+                hipLaunchKernelGGL(k_bchol, dim3(unsigned(na)), dim3(256), 0, s, gd, dg, j, m, DELTA, reorth > 0.0);
+                if (nc <= LS_EARLY) launch_ls(j, act, dg);
                 if constexpr (std::is_same<VT, double2>::value) launch_comb<double2, VT>(pcs, cs.size(), N, p, s);
                 else launch_comb64<VT>(pcs, cs.size(), N, p, s, true);   // K = r <= 32, R^{-1} upper triangular
             }
-            launch_ls();   // no step j: the update of step prev right away
+            launch_ls(prev, prev_act);   // no step j: the update of step prev right away
             if (prev >= 0) {
                 BIE_HIP(hipEventSynchronize(ev_ls[prev & 1]));
                 const double *est = hest[prev & 1];
@@ -2429,7 +2591,7 @@ int solve_chunk(bie_op *op, const double2 *B, double2 *X, int64_t R, const bie_s
                         st.relres_est = e * h.scale[a] / bn[h.rhs[a]];
                         if (!(e <= h.target[a])) met = false;
                     }
-                    if (met || fl[4 * g + 2 + (prev & 1)] || h.steps >= h.cap) {
+                    if (met || fl[g] || h.steps >= h.cap) {
                         h.active = false;
                         hsteps[g] = h.steps;
                         ended.push_back(g);
