@@ -94,6 +94,10 @@ typedef struct {
  * The matrix is complete when the call returns (it synchronises `stream`). */
 int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t nt,
                   double k, const bie_fill_opts *opts, void *stream, bie_op **out);
+/* The large blocks of an operator and of the set-ups are kept for the next one on the
+ * device: at most 4 GiB (or 1/64 of its memory, if that is less), released when they
+ * have not been used for two seconds, by the next call that makes or drops an
+ * operator, or when an allocation of the library fails. */
 void bie_op_destroy(bie_op *op);
 
 /* Fast operator (the paper's method, Sec. III-V): T x = N x + F x with no dense

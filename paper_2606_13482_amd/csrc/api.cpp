@@ -41,12 +41,10 @@ void destroy_op(bie_op *op)
     bie::free_block_cache(op);
     bie::packed_free(op->pk);
     bie::packed_free(op->pkv);
-    void *ptrs[] = { op->Z64, op->Z32, op->V64, op->V32, op->star_buf, op->Abf, op->Bbf,
-                     op->gemm_part, op->A64,
-                     op->d64_part, op->tri.cent, op->tri.loc, op->tri.vfree, op->tri.verts, op->tri.area, op->tri.rad, op->tri.sgn,
-                     op->tri.slot_m, op->tri.edges, op->flagged };
-    for (void *p : ptrs)
+    void *ptrs[] = { op->star_buf, op->Bbf, op->gemm_part, op->d64_part, op->tri.mem, op->flagged };
+    for (void *p : ptrs)   // hipFree waits for the device: what follows is out of use
         if (p) (void)hipFree(p);
+    for (void *p : { op->Z64, op->Z32, op->V64, op->V32, op->Abf, op->A64 }) bie::pool_put(p);
     delete op;
 }
 }  // namespace
@@ -81,16 +79,20 @@ int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t 
             hipStream_t s = as_stream(stream);
             bie::upload_triangles(op, s);
             bie::flag_pairs(op, o.near_factor, true, s);
-            bie::packed_setup(op->pk, op->mesh.N);
-            if (op->star) bie::packed_setup(op->pkv, op->mesh.F);
-            const size_t tile_elems = size_t(op->pk.ntiles) * bie::TB * bie::TB;
-            const size_t vtile_elems = op->star ? size_t(op->pkv.ntiles) * bie::TB * bie::TB : 0;
             const bool want64 = o.storage == BIE_C128 || o.storage == BIE_SPLIT_BF16 || o.keep_fp64;
             const bool want32 = o.storage == BIE_C64;
-            if (want64) BIE_HIP(hipMalloc(&op->Z64, tile_elems * 16));
-            if (want32) BIE_HIP(hipMalloc(&op->Z32, tile_elems * 8));
-            if (want64 && op->star) BIE_HIP(hipMalloc(&op->V64, vtile_elems * 16));
-            if (want32 && op->star) BIE_HIP(hipMalloc(&op->V32, vtile_elems * 8));
+            if (op->star) {
+                bie::packed_setup(op->pk, op->mesh.N);
+                bie::packed_setup(op->pkv, op->mesh.F);
+            } else {
+                bie::packed_setup_tuned(op->pk, op->mesh.N, want64);
+            }
+            const size_t tile_elems = size_t(op->pk.ntiles) * bie::TB * bie::TB;
+            const size_t vtile_elems = op->star ? size_t(op->pkv.ntiles) * bie::TB * bie::TB : 0;
+            if (want64) BIE_HIP(bie::pool_get(&op->Z64, tile_elems * 16));
+            if (want32) BIE_HIP(bie::pool_get(&op->Z32, tile_elems * 8));
+            if (want64 && op->star) BIE_HIP(bie::pool_get(&op->V64, vtile_elems * 16));
+            if (want32 && op->star) BIE_HIP(bie::pool_get(&op->V32, vtile_elems * 8));
             if (o.storage == BIE_C128) {
                 bie::fill_matrix(op, true, true, false, s);
             } else if (o.storage == BIE_SPLIT_BF16) {

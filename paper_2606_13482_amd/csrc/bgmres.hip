@@ -1811,7 +1811,7 @@ struct Arena {
     explicit Arena(size_t n) : cap(n)
     {
         BIE_HIP(hipHostMalloc(reinterpret_cast<void **>(&h), n));
-        BIE_HIP(hipMalloc(reinterpret_cast<void **>(&d), n));
+        BIE_HIP(device_malloc(reinterpret_cast<void **>(&d), n));
     }
     ~Arena()
     {
@@ -2147,7 +2147,7 @@ struct BlockCache {
         if (slot.second < bytes) {
             if (slot.first) (void)hipFree(slot.first);
             slot = { nullptr, 0 };
-            BIE_HIP(hipMalloc(&slot.first, bytes));
+            BIE_HIP(device_malloc(&slot.first, bytes));
             slot.second = bytes;
         }
         return static_cast<T *>(slot.first);

@@ -28,6 +28,36 @@ struct Error : std::runtime_error {
                                std::string(#expr) + ": " + hipGetErrorString(_e));      \
     } while (0)
 
+// Device memory (pool.cpp).  device_malloc is hipMalloc, tried again after a release
+// of the kept blocks where it fails.  pool_get's memory (its contents are any) goes
+// back with pool_put once its last use, on any stream, has completed; pool_put frees
+// what is not the pool's.  All are safe to call from several threads.
+bool pool_release();   // true if there was anything to release on the current device
+hipError_t pool_get(void **p, size_t bytes);
+void pool_put(void *p);
+template <typename T>
+hipError_t device_malloc(T **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory || !pool_release()) return e;
+    (void)hipGetLastError();
+    return hipMalloc(p, bytes);
+}
+// A block of the pool for work on stream s, returned at the end of the scope.
+struct PoolBlock {
+    void *p = nullptr;
+    hipStream_t s;
+    explicit PoolBlock(hipStream_t st) : s(st) {}
+    void get(size_t bytes) { BIE_HIP(pool_get(&p, bytes)); }
+    ~PoolBlock()
+    {
+        if (!p) return;
+        if (hipStreamSynchronize(s) == hipSuccess) pool_put(p);
+    }
+    PoolBlock(const PoolBlock &) = delete;
+    PoolBlock &operator=(const PoolBlock &) = delete;
+};
+
 // Host-side RWG table and pair list (mesh.cpp).
 struct Mesh {
     int64_t nv = 0, F = 0, N = 0;
@@ -55,6 +85,7 @@ std::vector<int64_t> rscc_rows(int64_t N, int64_t S, uint64_t seed);
 struct TriDev {
     std::vector<int32_t> rank;  // host: device position of triangle t (see upload_triangles); every table below is in
                                 // that order, and edges names triangles by it
+    void *mem = nullptr;        // one allocation that holds them all
     double *cent = nullptr;     // F x 3
     double *loc = nullptr;      // F x 7 x 3   quadrature points - centroid
     double *vfree = nullptr;    // F x 3 x 3   free vertex of slot a - centroid
@@ -235,7 +266,8 @@ void farfield(const bie_op *op, const void *X, int64_t R, const double *obs, int
               hipStream_t s);
 
 // blas.hip: products with the packed symmetric matrix.
-void packed_setup(Packed &pk, int64_t n);   // tables of the packed n x n tiles
+void packed_setup(Packed &pk, int64_t n);
+void packed_setup_tuned(Packed &pk, int64_t n, bool mat64);   // tables of the packed n x n tiles
 // work units of U tiles along each tile row, and the partial-vector slots
 void build_units(int64_t nT, int U, std::vector<int32_t> &units, std::vector<int32_t> &uptr,
                  std::vector<int64_t> &seg);

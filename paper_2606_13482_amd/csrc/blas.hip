@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 #include <utility>
 #include <mutex>
 #include <string>
@@ -1165,14 +1166,23 @@ static void packed_setup_units(Packed &pk, int64_t n, int U)
     pk.nunits = int64_t(units.size() / 3);
     pk.nruns = int64_t(rptr.size()) - 1;
     pk.nslots = seg[pk.nT];
-    BIE_HIP(hipMalloc(&pk.seg, seg.size() * sizeof(int64_t)));
-    BIE_HIP(hipMemcpy(pk.seg, seg.data(), seg.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-    BIE_HIP(hipMalloc(&pk.units, units.size() * sizeof(int32_t)));
-    BIE_HIP(hipMalloc(&pk.unit_ptr, uptr.size() * sizeof(int32_t)));
-    BIE_HIP(hipMalloc(&pk.run_ptr, rptr.size() * sizeof(int32_t)));
-    BIE_HIP(hipMemcpy(pk.units, units.data(), units.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(pk.unit_ptr, uptr.data(), uptr.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    BIE_HIP(hipMemcpy(pk.run_ptr, rptr.data(), rptr.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    // seg, units, unit_ptr and run_ptr side by side, copied at once
+    std::vector<char> image(seg.size() * sizeof(int64_t) + (units.size() + uptr.size() + rptr.size()) * sizeof(int32_t));
+    size_t bytes = 0;
+    auto put = [&](const auto &v) {
+        const size_t at = bytes, n = v.size() * sizeof(v[0]);
+        std::memcpy(image.data() + at, v.data(), n);
+        bytes += n;
+        return at;
+    };
+    const size_t o_seg = put(seg), o_units = put(units), o_uptr = put(uptr), o_rptr = put(rptr);
+    char *d = nullptr;
+    BIE_HIP(device_malloc(&d, bytes));
+    pk.seg = reinterpret_cast<int64_t *>(d + o_seg);
+    pk.units = reinterpret_cast<int32_t *>(d + o_units);
+    pk.unit_ptr = reinterpret_cast<int32_t *>(d + o_uptr);
+    pk.run_ptr = reinterpret_cast<int32_t *>(d + o_rptr);
+    BIE_HIP(hipMemcpy(d, image.data(), bytes, hipMemcpyHostToDevice));
     pk.h_units = std::move(units);
     pk.h_unit_ptr = std::move(uptr);
     pk.h_seg = std::move(seg);
@@ -1180,16 +1190,29 @@ static void packed_setup_units(Packed &pk, int64_t n, int U)
 
 void packed_setup(Packed &pk, int64_t n) { packed_setup_units(pk, n, unit_tiles()); }
 
+static std::string tune_key(int64_t N, bool mat64) { return "sym:" + std::to_string(N) + (mat64 ? ":f64" : ":f32"); }
+static bool tuned_unit(const std::string &key, int &unit)
+{
+    std::vector<int> v;
+    if (!tune_get(key, v) || v.size() != 1 || v[0] < 0 || v[0] > 64) return false;
+    unit = v[0];
+    return true;
+}
+
+// With the autotuner's units where it has met the size (tune_packed then has nothing to rebuild).
+void packed_setup_tuned(Packed &pk, int64_t n, bool mat64)
+{
+    int unit = unit_tiles();
+    if (!getenv("BIE_SYM_UNIT") && tune_enabled()) (void)tuned_unit(tune_key(n, mat64), unit);
+    packed_setup_units(pk, n, unit);
+}
+
 void packed_free(Packed &pk)
 {
-    if (pk.units) (void)hipFree(pk.units);
-    if (pk.unit_ptr) (void)hipFree(pk.unit_ptr);
-    if (pk.run_ptr) (void)hipFree(pk.run_ptr);
-    pk.run_ptr = nullptr;
-    if (pk.seg) (void)hipFree(pk.seg);
-    pk.seg = nullptr;
+    if (pk.seg) (void)hipFree(pk.seg);   // and the tables behind it
     if (pk.part) (void)hipFree(pk.part);
-    pk.units = pk.unit_ptr = nullptr;
+    pk.seg = nullptr;
+    pk.units = pk.unit_ptr = pk.run_ptr = nullptr;
     pk.part = nullptr;
     pk.part_R = 0;
 }
@@ -1216,7 +1239,7 @@ static void ensure_part(Packed &pk, int64_t R, hipStream_t s)
     if (pk.part) (void)hipFree(pk.part);
     pk.part = nullptr;
     pk.part_R = 0;
-    BIE_HIP(hipMalloc(&pk.part, size_t(R) * size_t(pk.nslots) * TB * 16));
+    BIE_HIP(device_malloc(&pk.part, size_t(R) * size_t(pk.nslots) * TB * 16));
     pk.part_R = R;
 }
 
@@ -1232,13 +1255,13 @@ void tune_packed(bie_op *op, hipStream_t s)
     const void *Z = mat64 ? op->Z64 : op->Z32;
     if (!Z) return;
     const int64_t N = op->mesh.N;
-    const std::string key = "sym:" + std::to_string(N) + (mat64 ? ":f64" : ":f32");
-    std::vector<int> v;
-    if (!tune_get(key, v) || v.size() != 1 || v[0] < 0 || v[0] > 64) {
+    const std::string key = tune_key(N, mat64);
+    std::vector<int> v(1);
+    if (!tuned_unit(key, v[0])) {
         void *x = nullptr, *y = nullptr;
-        BIE_HIP(hipMalloc(&x, size_t(N) * 16));
+        BIE_HIP(device_malloc(&x, size_t(N) * 16));
         try {
-            BIE_HIP(hipMalloc(&y, size_t(N) * 16));
+            BIE_HIP(device_malloc(&y, size_t(N) * 16));
             BIE_HIP(hipMemsetAsync(x, 0, size_t(N) * 16, s));
             float best = 0.f;
             v = { unit_tiles() };
@@ -1295,7 +1318,7 @@ static void star_product(bie_op *op, const void *Za, const void *Vm, const void 
         if (op->star_buf) (void)hipFree(op->star_buf);
         op->star_buf = nullptr;
         op->star_R = 0;
-        BIE_HIP(hipMalloc(&op->star_buf, 2 * size_t(R) * size_t(F) * 16));
+        BIE_HIP(device_malloc(&op->star_buf, 2 * size_t(R) * size_t(F) * 16));
         op->star_R = R;
     }
     T *U = static_cast<T *>(op->star_buf), *W = U + 2 * R * F;
@@ -1474,7 +1497,7 @@ void convert_c64_to_c128(const void *src, void *dst, int64_t n, hipStream_t s)
 bool has_nonfinite(const void *x, int64_t n_doubles, hipStream_t s)
 {
     int *flag = nullptr;
-    BIE_HIP(hipMalloc(&flag, sizeof(int)));
+    BIE_HIP(device_malloc(&flag, sizeof(int)));
     BIE_HIP(hipMemsetAsync(flag, 0, sizeof(int), s));
     hipLaunchKernelGGL(k_nonfinite, dim3(1024), dim3(256), 0, s, (const double *)x, n_doubles, flag);
     int h = 0;

@@ -26,11 +26,11 @@
 //     products read whole rows of 64 columns.
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 #include <chrono>
 #include <map>
 #include <memory>
 #include <mutex>
-#include <unordered_map>
 
 #include "bie_internal.hpp"
 #include "pairs.hpp"
@@ -65,9 +65,9 @@ struct CsrDev {
     void upload(const Csr &c)
     {
         rows = int64_t(c.ptr.size()) - 1;
-        BIE_HIP(hipMalloc(&ptr, c.ptr.size() * sizeof(int64_t)));
-        BIE_HIP(hipMalloc(&idx, std::max<size_t>(1, c.idx.size()) * sizeof(int32_t)));
-        BIE_HIP(hipMalloc(&val, std::max<size_t>(1, c.val.size()) * sizeof(double)));
+        BIE_HIP(device_malloc(&ptr, c.ptr.size() * sizeof(int64_t)));
+        BIE_HIP(device_malloc(&idx, std::max<size_t>(1, c.idx.size()) * sizeof(int32_t)));
+        BIE_HIP(device_malloc(&val, std::max<size_t>(1, c.val.size()) * sizeof(double)));
         BIE_HIP(hipMemcpy(ptr, c.ptr.data(), c.ptr.size() * sizeof(int64_t), hipMemcpyHostToDevice));
         BIE_HIP(hipMemcpy(idx, c.idx.data(), c.idx.size() * sizeof(int32_t), hipMemcpyHostToDevice));
         BIE_HIP(hipMemcpy(val, c.val.data(), c.val.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -438,40 +438,41 @@ void refine(const Mesh &M, std::vector<double> &Vb, std::vector<int32_t> &Tb)
 // matrix (CSR, N x N) and its transpose.
 void bc_and_gram(const Mesh &M, const Mesh &B, Csr &C, Csr &G, Csr &Gt)
 {
-    const int64_t nv = M.nv, N = M.N, nvb = B.nv;
-    std::unordered_map<uint64_t, int32_t> eid;
-    eid.reserve(size_t(B.N) * 2);
-    for (int64_t e = 0; e < B.N; ++e) eid[uint64_t(B.edges[4 * e]) * uint64_t(nvb) + uint64_t(B.edges[4 * e + 1])] = int32_t(e);
-    auto edge_of = [&](int32_t a, int32_t b) -> int32_t {
-        const auto it = eid.find(uint64_t(std::min(a, b)) * uint64_t(nvb) + uint64_t(std::max(a, b)));
-        if (it == eid.end()) throw Error(BIE_EMESH, "refined mesh lacks an expected edge");
-        return it->second;
+    const int64_t N = M.N;
+    // refined edge (v, mid) for the end v of m, or (mid, g) for v < 0, by triangle t's children at
+    // edge m = a-b, 2k: (a, mid, g) and 2k + 1: (mid, b, g)
+    auto child_edge = [&](int64_t m, int32_t t, int32_t v) {
+        int k = 0;
+        while (M.slot_m[3 * t + (k + 2) % 3] != m) ++k;
+        const int64_t c = 6 * int64_t(t) + 2 * k;
+        if (v < 0) return B.slot_m[3 * c];
+        return B.slot_m[3 * (M.T[3 * t + k] == v ? c : c + 1) + 2];
     };
     auto sigma = [&](int32_t e, int32_t t) { return B.edges[4 * e + 2] == t ? 1.0 : -1.0; };
     auto across = [&](int32_t e, int32_t t) { return B.edges[4 * e + 2] == t ? B.edges[4 * e + 3] : B.edges[4 * e + 2]; };
     auto Vb = [&](int32_t v) { return V3{ B.V[3 * v], B.V[3 * v + 1], B.V[3 * v + 2] }; };
     // the radial edge of child t (corner v) other than e
     auto other_radial = [&](int32_t t, int32_t v, int32_t e) {
-        int32_t x[2], n = 0;
+        int32_t out = -1;
         for (int k = 0; k < 3; ++k)
-            if (B.T[3 * t + k] != v) x[n++] = B.T[3 * t + k];
-        const int32_t e1 = edge_of(v, x[0]), e2 = edge_of(v, x[1]);
-        return e1 == e ? e2 : e1;
+            if (B.T[3 * t + k] != v && B.slot_m[3 * t + k] != e) out = B.slot_m[3 * t + k];
+        return out;
     };
 
     C.ptr.assign(1, 0);
     std::vector<std::pair<int32_t, double>> row;
+    std::vector<int32_t> ts, es;
     for (int64_t m = 0; m < N; ++m) {
         row.clear();
         const int32_t lo = M.edges[4 * m], hi = M.edges[4 * m + 1], cp = M.edges[4 * m + 2], cm = M.edges[4 * m + 3];
-        const int32_t mid = int32_t(nv + m);
-        const int32_t half_p = edge_of(mid, int32_t(nv + N + cp)), half_m = edge_of(mid, int32_t(nv + N + cm));
+        const int32_t half_p = child_edge(m, cp, -1), half_m = child_edge(m, cm, -1);
         for (int side = 0; side < 2; ++side) {
             const int32_t v = side == 0 ? hi : lo;
             const double charge = side == 0 ? 1.0 : -1.0;
-            const int32_t e0 = edge_of(v, mid);
+            const int32_t e0 = child_edge(m, cp, v);
             const int32_t t1 = B.edges[4 * e0 + 2] / 6 == cp ? B.edges[4 * e0 + 2] : B.edges[4 * e0 + 3];
-            std::vector<int32_t> ts, es;
+            ts.clear();
+            es.clear();
             int32_t t = t1, prev = e0;
             while (true) {
                 ts.push_back(t);
@@ -503,7 +504,35 @@ void bc_and_gram(const Mesh &M, const Mesh &B, Csr &C, Csr &G, Csr &Gt)
         C.ptr.push_back(int64_t(C.idx.size()));
     }
 
-    // G_mn = <n x b_m, f_n>
+    // G_mn = <n x b_m, f_n>: first the integrals of every child's three refined functions
+    // against its triangle's three
+    std::vector<double> part(9 * size_t(B.F));
+    for (int64_t T = 0; T < M.F; ++T) {
+        const V3 p[3] = { { M.V[3 * M.T[3 * T]], M.V[3 * M.T[3 * T] + 1], M.V[3 * M.T[3 * T] + 2] },
+                          { M.V[3 * M.T[3 * T + 1]], M.V[3 * M.T[3 * T + 1] + 1], M.V[3 * M.T[3 * T + 1] + 2] },
+                          { M.V[3 * M.T[3 * T + 2]], M.V[3 * M.T[3 * T + 2] + 1], M.V[3 * M.T[3 * T + 2] + 2] } };
+        V3 nrm = vcross(vsub(p[1], p[0]), vsub(p[2], p[0]));
+        nrm = vscale(nrm, 1.0 / std::sqrt(vdot(nrm, nrm)));
+        for (int64_t t = 6 * T; t < 6 * T + 6; ++t) {
+            const V3 x[3] = { Vb(B.T[3 * t]), Vb(B.T[3 * t + 1]), Vb(B.T[3 * t + 2]) };
+            const V3 xq[3] = { vmid(x[0], x[1]), vmid(x[1], x[2]), vmid(x[2], x[0]) };
+            V3 f[3][3];   // function of slot sl at point q
+            for (int sl = 0; sl < 3; ++sl) {
+                const double sf = double(M.slot_s[3 * T + sl]) / (2.0 * M.area[T]);
+                for (int q = 0; q < 3; ++q) f[sl][q] = vscale(vsub(xq[q], p[sl]), sf);
+            }
+            for (int a = 0; a < 3; ++a) {
+                const double sb = double(B.slot_s[3 * t + a]) / (2.0 * B.area[t]);
+                V3 rb[3];
+                for (int q = 0; q < 3; ++q) rb[q] = vcross(nrm, vscale(vsub(xq[q], x[a]), sb));
+                for (int sl = 0; sl < 3; ++sl) {
+                    double sum = 0.0;
+                    for (int q = 0; q < 3; ++q) sum += vdot(rb[q], f[sl][q]);
+                    part[9 * t + 3 * a + sl] = sum;
+                }
+            }
+        }
+    }
     G.ptr.assign(1, 0);
     std::vector<double> acc(N, 0.0);
     std::vector<char> seen(N, 0);
@@ -515,31 +544,14 @@ void bc_and_gram(const Mesh &M, const Mesh &B, Csr &C, Csr &G, Csr &Gt)
             const double ce = C.val[k];
             for (int side = 0; side < 2; ++side) {
                 const int32_t t = B.edges[4 * e + 2 + side], T = t / 6;
-                const V3 a = { M.V[3 * M.T[3 * T]], M.V[3 * M.T[3 * T] + 1], M.V[3 * M.T[3 * T] + 2] };
-                const V3 b = { M.V[3 * M.T[3 * T + 1]], M.V[3 * M.T[3 * T + 1] + 1], M.V[3 * M.T[3 * T + 1] + 2] };
-                const V3 c = { M.V[3 * M.T[3 * T + 2]], M.V[3 * M.T[3 * T + 2] + 1], M.V[3 * M.T[3 * T + 2] + 2] };
-                V3 nrm = vcross(vsub(b, a), vsub(c, a));
-                nrm = vscale(nrm, 1.0 / std::sqrt(vdot(nrm, nrm)));
-                int32_t fb = -1;
-                for (int q = 0; q < 3; ++q)
-                    if (B.T[3 * t + q] != B.edges[4 * e] && B.T[3 * t + q] != B.edges[4 * e + 1]) fb = B.T[3 * t + q];
-                const V3 p0 = Vb(B.T[3 * t]), p1 = Vb(B.T[3 * t + 1]), p2 = Vb(B.T[3 * t + 2]);
-                const V3 xq[3] = { vmid(p0, p1), vmid(p1, p2), vmid(p2, p0) };
-                const double sb = sigma(e, t) / (2.0 * B.area[t]);
+                const int a = B.slot_m[3 * t] == e ? 0 : B.slot_m[3 * t + 1] == e ? 1 : 2;
                 for (int sl = 0; sl < 3; ++sl) {
                     const int32_t n = M.slot_m[3 * T + sl];
-                    const V3 vf = { M.V[3 * M.T[3 * T + sl]], M.V[3 * M.T[3 * T + sl] + 1], M.V[3 * M.T[3 * T + sl] + 2] };
-                    const double sf = double(M.slot_s[3 * T + sl]) / (2.0 * M.area[T]);
-                    double s = 0.0;
-                    for (int q = 0; q < 3; ++q) {
-                        const V3 rb = vcross(nrm, vscale(vsub(xq[q], Vb(fb)), sb));
-                        s += vdot(rb, vscale(vsub(xq[q], vf), sf));
-                    }
                     if (!seen[n]) {
                         seen[n] = 1;
                         touched.push_back(n);
                     }
-                    acc[n] += ce * B.area[t] / 3.0 * s;
+                    acc[n] += ce * B.area[t] / 3.0 * part[9 * size_t(t) + 3 * a + sl];
                 }
             }
         }
@@ -653,9 +665,9 @@ struct SlicedDev {
                 }
             p.push_back(p.back() + int32_t(w));
         }
-        BIE_HIP(hipMalloc(&ptr, p.size() * sizeof(int32_t)));
-        BIE_HIP(hipMalloc(&idx, ix.size() * sizeof(uint16_t)));
-        BIE_HIP(hipMalloc(&val, vl.size() * sizeof(double)));
+        BIE_HIP(device_malloc(&ptr, p.size() * sizeof(int32_t)));
+        BIE_HIP(device_malloc(&idx, ix.size() * sizeof(uint16_t)));
+        BIE_HIP(device_malloc(&val, vl.size() * sizeof(double)));
         BIE_HIP(hipMemcpy(ptr, p.data(), p.size() * sizeof(int32_t), hipMemcpyHostToDevice));
         BIE_HIP(hipMemcpy(idx, ix.data(), ix.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
         BIE_HIP(hipMemcpy(val, vl.data(), vl.size() * sizeof(double), hipMemcpyHostToDevice));
@@ -801,7 +813,7 @@ bool gram_solve_cheb(const SlicedDev &G, int64_t n, const double2 *Bt, double2 *
     const int64_t nv = J <= 2 ? 8 : J <= 4 ? 4 : J <= 9 ? 2 : 1;
     const int64_t nblk = (2 * n + nv - 1) / nv;
     GramStat *ds = nullptr;
-    BIE_HIP(hipMalloc(&ds, size_t(nblk) * sizeof(GramStat)));
+    BIE_HIP(device_malloc(&ds, size_t(nblk) * sizeof(GramStat)));
     std::vector<GramStat> h(nblk);
     auto run = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(unsigned(nblk)), dim3(1024), 0, s, int(n), G.ptr, G.idx, G.val, (const double *)Bt,
@@ -865,8 +877,8 @@ void gram_solve_any(const SlicedDev &Gs, const Csr &G, const Csr &Gt, int64_t n,
                 if (q) (void)hipFree(q);
         }
     } wk;
-    for (int i = 0; i < 3; ++i) BIE_HIP(hipMalloc(&wk.p[i], nn * sizeof(double2)));
-    BIE_HIP(hipMalloc(&wk.p[3], size_t((5 + NSLICE) * n) * sizeof(double)));
+    for (int i = 0; i < 3; ++i) BIE_HIP(device_malloc(&wk.p[i], nn * sizeof(double2)));
+    BIE_HIP(device_malloc(&wk.p[3], size_t((5 + NSLICE) * n) * sizeof(double)));
     double2 *Rr = static_cast<double2 *>(wk.p[0]), *X = static_cast<double2 *>(wk.p[1]),
             *P = static_cast<double2 *>(wk.p[2]);
     int64_t it2 = 0;
@@ -879,90 +891,95 @@ void gram_solve_any(const SlicedDev &Gs, const Csr &G, const Csr &Gt, int64_t n,
 
 }  // namespace
 
-struct DualWork {   // the setup's largest array: D, later two n x n blocks
-    void *p = nullptr;
-    ~DualWork()
-    {
-        if (p) (void)hipFree(p);
-    }
-};
-
-// device copies of host tables, freed together
+// device copies of host tables, placed side by side and copied at once by send()
 struct Bufs {
-    std::vector<void *> p;
+    std::vector<char> image;
+    char *d = nullptr;
     ~Bufs()
     {
-        for (void *q : p) (void)hipFree(q);
+        if (d) (void)hipFree(d);
     }
     template <typename T>
-    T *up(const std::vector<T> &v)
+    size_t add(const std::vector<T> &v)
     {
-        void *q = nullptr;
-        BIE_HIP(hipMalloc(&q, std::max<size_t>(1, v.size()) * sizeof(T)));
-        p.push_back(q);
-        BIE_HIP(hipMemcpy(q, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
-        return static_cast<T *>(q);
+        const size_t at = (image.size() + 255) / 256 * 256;
+        image.resize(at + v.size() * sizeof(T));
+        if (!v.empty()) std::memcpy(image.data() + at, v.data(), v.size() * sizeof(T));
+        return at;
+    }
+    void send()
+    {
+        BIE_HIP(device_malloc(&d, std::max<size_t>(1, image.size())));
+        BIE_HIP(hipMemcpy(d, image.data(), image.size(), hipMemcpyHostToDevice));
+    }
+    template <typename T>
+    const T *at(size_t o) const
+    {
+        return reinterpret_cast<const T *>(d + o);
     }
 };
 
 // T_BC (row-major n x n) of the BC functions C on the refined mesh of opb.
-void dual_matrix(const Mesh &M, const bie_op *opb, const Csr &C, DualWork &work, double2 *T, hipStream_t s)
+void dual_matrix(const Mesh &M, const bie_op *opb, const Csr &C, PoolBlock &work, double2 *T, hipStream_t s)
 {
     const Mesh &B = opb->mesh;
     const TriDev &td = opb->tri;
     const int64_t N = M.N, Fb = B.F;
     const double near_factor = 2.0;   // the fill's default
     // edges of every vertex, and its children (the device order runs cell by cell)
-    std::vector<std::vector<int32_t>> inc(M.nv);
-    for (int64_t m = 0; m < N; ++m)
-        for (int e = 0; e < 2; ++e) inc[M.edges[4 * m + e]].push_back(int32_t(m));
-    size_t maxdeg = 1;
-    for (const auto &e : inc) maxdeg = std::max(maxdeg, e.size());
+    std::vector<int32_t> iptr(M.nv + 1, 0), inc(2 * N), place(2 * N);   // place: of edge m among its ends' edges
+    for (int64_t i = 0; i < 2 * N; ++i) ++iptr[M.edges[4 * (i / 2) + i % 2] + 1];
+    int32_t maxdeg = 1;
+    for (int64_t v = 0; v < M.nv; ++v) {
+        maxdeg = std::max(maxdeg, iptr[v + 1]);
+        iptr[v + 1] += iptr[v];
+    }
+    {
+        std::vector<int32_t> next(iptr.begin(), iptr.end() - 1);
+        for (int64_t i = 0; i < 2 * N; ++i) {
+            const int32_t v = M.edges[4 * (i / 2) + i % 2];
+            place[i] = next[v] - iptr[v];
+            inc[next[v]++] = int32_t(i / 2);
+        }
+    }
     const int ci = maxdeg <= 6 ? 6 : 8;
-    std::vector<int32_t> tri_at(Fb), cell_of(Fb), row_cell, group(1, 0), hptr(N + 1, 0), hrow;
+    std::vector<int32_t> tri_at(Fb), cell_of(Fb), cell_v, row_cell, row_m, group(1, 0), hptr(N + 1, 0);
     for (int64_t t = 0; t < Fb; ++t) tri_at[td.rank[t]] = int32_t(t);
     std::vector<Cell> cells;
-    std::vector<double> coef, longest(Fb);
+    std::vector<double> longest(Fb);
     std::vector<int64_t> rowoff;
-    std::vector<std::vector<int32_t>> rows_of(N);
+    int64_t ncoef = 0;
     int32_t r = 0, gchildren = 0;
     for (int64_t v = 0; v < M.nv; ++v) {
-        int32_t left = 2 * int32_t(inc[v].size());   // two children per triangle, a triangle per edge
+        const int32_t deg = iptr[v + 1] - iptr[v];
+        int32_t left = 2 * deg;   // two children per triangle, a triangle per edge
         while (left > 0) {
             Cell c;
             c.t0 = r;
             c.nt = std::min(left, int32_t(CB));
-            c.deg = int32_t(inc[v].size());
+            c.deg = deg;
             c.dp = (c.deg + ci - 1) / ci * ci;
             c.h0 = int64_t(row_cell.size());
-            c.cf = int64_t(coef.size());
+            c.cf = ncoef;
+            ncoef += int64_t(c.nt) * c.dp * 3;
             const int32_t id = int32_t(cells.size());
             if (gchildren + c.nt > CB) {
                 group.push_back(id);
                 gchildren = 0;
             }
             gchildren += c.nt;
-            coef.resize(coef.size() + size_t(c.nt) * c.dp * 3, 0.0);
             for (int32_t u = 0; u < c.nt; ++u) {
                 const int32_t t = tri_at[r + u];
                 if (B.T[3 * t] != v && B.T[3 * t + 1] != v) throw Error(BIE_EMESH, "refined triangles out of cell order");
                 cell_of[r + u] = id;
                 longest[r + u] = B.longest[t];
-                for (int i = 0; i < c.deg; ++i) {
-                    const int32_t m = inc[v][i];
-                    const int32_t *x0 = C.idx.data() + C.ptr[m], *x1 = C.idx.data() + C.ptr[m + 1];
-                    for (int a = 0; a < 3; ++a) {
-                        const int32_t e = B.slot_m[3 * t + a];
-                        const int32_t *x = std::lower_bound(x0, x1, e);
-                        if (x < x1 && *x == e) coef[c.cf + (size_t(u) * c.dp + i) * 3 + a] = C.val[x - C.idx.data()];
-                    }
-                }
             }
-            for (int i = 0; i < c.deg; ++i) {
-                rows_of[inc[v][i]].push_back(int32_t(row_cell.size()));
+            for (int32_t i = iptr[v]; i < iptr[v + 1]; ++i) {
+                row_m.push_back(inc[i]);
                 row_cell.push_back(id);
             }
             cells.push_back(c);
+            cell_v.push_back(int32_t(v));
             r += c.nt;
             left -= c.nt;
         }
@@ -977,11 +994,26 @@ void dual_matrix(const Mesh &M, const bie_op *opb, const Csr &C, DualWork &work,
         rowoff[h] = total - c0;
         total += H - c0;
     }
-    for (int64_t m = 0; m < N; ++m) {
-        hrow.insert(hrow.end(), rows_of[m].begin(), rows_of[m].end());
-        hptr[m + 1] = int32_t(hrow.size());
+    std::vector<int32_t> hrow(H);   // the rows of function m, in their order
+    for (int64_t h = 0; h < H; ++h) ++hptr[row_m[h] + 1];
+    for (int64_t m = 0; m < N; ++m) hptr[m + 1] += hptr[m];
+    {
+        std::vector<int32_t> next(hptr.begin(), hptr.end() - 1);
+        for (int64_t h = 0; h < H; ++h) hrow[next[row_m[h]]++] = int32_t(h);
     }
-    BIE_HIP(hipMalloc(&work.p, std::max(size_t(total), 2 * size_t(N) * size_t(N)) * sizeof(double2)));
+    // the BC coefficients child by child: an edge of function m lies on two children of m's cells
+    std::vector<double> coef(ncoef, 0.0);
+    for (int64_t m = 0; m < N; ++m)
+        for (int64_t k = C.ptr[m]; k < C.ptr[m + 1]; ++k)
+            for (int side = 0; side < 2; ++side) {
+                const int32_t e = C.idx[k], t = B.edges[4 * e + 2 + side], rt = td.rank[t], id = cell_of[rt];
+                const Cell &c = cells[id];
+                const int end = M.edges[4 * m] == cell_v[id] ? 0 : M.edges[4 * m + 1] == cell_v[id] ? 1 : -1;
+                if (end < 0) continue;
+                const int a = B.slot_m[3 * t] == e ? 0 : B.slot_m[3 * t + 1] == e ? 1 : 2;
+                coef[c.cf + (int64_t(rt - c.t0) * c.dp + place[2 * m + end]) * 3 + a] = C.val[k];
+            }
+    work.get(std::max(size_t(total), 2 * size_t(N) * size_t(N)) * sizeof(double2));
     double2 *D = static_cast<double2 *>(work.p);
     double qwh[QPTS];
     quad_weights(qwh);
@@ -989,21 +1021,31 @@ void dual_matrix(const Mesh &M, const bie_op *opb, const Csr &C, DualWork &work,
     NearDev nd;
     ranked_near(opb, near_factor, nd, s);
     Bufs bufs;
-    const Cell *dc = bufs.up(cells);
-    const int32_t *dg = bufs.up(group), *dco = bufs.up(cell_of), *drc = bufs.up(row_cell), *dhp = bufs.up(hptr),
-                  *dhr = bufs.up(hrow);
-    const double *dcf = bufs.up(coef), *dl = bufs.up(longest), *dqw = bufs.up(std::vector<double>(qwh, qwh + QPTS));
-    const int64_t *dro = bufs.up(rowoff);
-    int32_t *pairs = near_list(nd, Fb, s);
-    bufs.p.push_back(pairs);
-    void *fb = nullptr;
-    BIE_HIP(hipMalloc(&fb, std::max<int64_t>(1, nd.n) * 18 * sizeof(double)));
-    bufs.p.push_back(fb);
-    singular_blocks(opb, pairs, nd.n, static_cast<double *>(fb), s);
+    const size_t o_c = bufs.add(cells), o_g = bufs.add(group), o_co = bufs.add(cell_of), o_rc = bufs.add(row_cell),
+                 o_hp = bufs.add(hptr), o_hr = bufs.add(hrow), o_cf = bufs.add(coef), o_l = bufs.add(longest),
+                 o_qw = bufs.add(std::vector<double>(qwh, qwh + QPTS)), o_ro = bufs.add(rowoff);
+    bufs.send();
+    const Cell *dc = bufs.at<Cell>(o_c);
+    const int32_t *dg = bufs.at<int32_t>(o_g), *dco = bufs.at<int32_t>(o_co), *drc = bufs.at<int32_t>(o_rc),
+                  *dhp = bufs.at<int32_t>(o_hp), *dhr = bufs.at<int32_t>(o_hr);
+    const double *dcf = bufs.at<double>(o_cf), *dl = bufs.at<double>(o_l), *dqw = bufs.at<double>(o_qw);
+    const int64_t *dro = bufs.at<int64_t>(o_ro);
+    struct Pairs {
+        int32_t *p = nullptr;
+        ~Pairs()
+        {
+            if (p) (void)hipFree(p);
+        }
+    } pairs;
+    pairs.p = near_list(nd, Fb, s);
+    PoolBlock blocks(s);
+    blocks.get(std::max<int64_t>(1, nd.n) * 18 * sizeof(double));
+    double *fb = static_cast<double *>(blocks.p);
+    singular_blocks(opb, pairs.p, nd.n, fb, s);
     const dim3 grid(unsigned(group.size() - 1), unsigned(cells.size()), unsigned((maxdeg + ci - 1) / ci));
     auto run = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, dim3(CB), 0, s, dc, dg, dco, drc, dcf, dro, td.cent, td.loc, td.vfree, td.sgn,
-                           td.rad, dl, dqw, nd.ptr, nd.list, (const double *)fb, near_factor, opb->k, D);
+                           td.rad, dl, dqw, nd.ptr, nd.list, fb, near_factor, opb->k, D);
     };
     const bool wide = opb->k * 2.0 * td.max_rad > NARROW_PHASE;
     if (ci == 6) {
@@ -1067,8 +1109,8 @@ bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
     // T_BC, then A1^T = (G^{-1} T_BC)^T (T_BC symmetric: its columns are its rows),
     // A1, and M' = G^{-1} A1^T, transposed; M is symmetric, so either will do
     const int64_t nn = N * N;
-    DualWork work, tbc;
-    BIE_HIP(hipMalloc(&tbc.p, size_t(nn) * sizeof(double2)));
+    PoolBlock work(s), tbc(s);
+    tbc.get(size_t(nn) * sizeof(double2));
     double2 *T = static_cast<double2 *>(tbc.p);
     dual_matrix(M, opb, C, work, T, s);
     hold.reset();   // the refined mesh is no longer needed
@@ -1085,7 +1127,7 @@ bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
     v->storage = BIE_C128;
     v->mesh.N = N;
     packed_setup(v->pk, N);
-    BIE_HIP(hipMalloc(&v->Z64, size_t(v->pk.ntiles) * TB * TB * sizeof(double2)));
+    BIE_HIP(pool_get(&v->Z64, size_t(v->pk.ntiles) * TB * TB * sizeof(double2)));
     hipLaunchKernelGGL(k_pack_sym, dim3(unsigned(v->pk.nT), unsigned(v->pk.nT)), dim3(256), 0, s, N, v->pk.nT,
                        T, -1.0, (double2 *)v->Z64);
     BIE_HIP(hipGetLastError());
@@ -1102,18 +1144,11 @@ bie_op *calderon_tm(const bie_calderon *pcc, hipStream_t s)
     const bie_op *op = pc->op;
     if (!op->Z64) throw Error(BIE_EINVAL, "Calderon preconditioner: T M needs the FP64 matrix");
     const int64_t N = pc->info.N, ch = std::min<int64_t>(N, 512);
-    double2 *A = nullptr, *I = nullptr, *Mc = nullptr;
-    struct F3 {
-        double2 **p[3];
-        ~F3()
-        {
-            for (auto q : p)
-                if (*q) (void)hipFree(*q);
-        }
-    } guard{ { &A, &I, &Mc } };
-    BIE_HIP(hipMalloc(&A, size_t(N) * N * sizeof(double2)));
-    BIE_HIP(hipMalloc(&I, size_t(N) * ch * sizeof(double2)));
-    BIE_HIP(hipMalloc(&Mc, size_t(N) * ch * sizeof(double2)));
+    PoolBlock a(s), unit(s), prod(s);
+    a.get(size_t(N) * N * sizeof(double2));
+    unit.get(size_t(N) * ch * sizeof(double2));
+    prod.get(size_t(N) * ch * sizeof(double2));
+    double2 *A = static_cast<double2 *>(a.p), *I = static_cast<double2 *>(unit.p), *Mc = static_cast<double2 *>(prod.p);
     // column chunk of T M: unit vectors, M on the FP64 matrix cores, then T
     for (int64_t j0 = 0; j0 < N; j0 += ch) {
         const int64_t nc = std::min(ch, N - j0);
@@ -1160,7 +1195,7 @@ bie_op *calderon_view32(const bie_calderon *pc, hipStream_t s)
     if (!v->Z32) {
         const int64_t n = v->pk.ntiles * TB * TB;
         void *z = nullptr;
-        BIE_HIP(hipMalloc(&z, size_t(n) * sizeof(float2)));
+        BIE_HIP(device_malloc(&z, size_t(n) * sizeof(float2)));
         convert_c128_to_c64(v->Z64, z, n, s);
         BIE_HIP(hipStreamSynchronize(s));
         v->Z32 = z;
@@ -1177,7 +1212,7 @@ double2 *calderon_scratch(const bie_calderon *pcc, int64_t R, hipStream_t s)
         if (pc->tmp) (void)hipFree(pc->tmp);
         pc->tmp = nullptr;
         pc->tmp_R = 0;
-        BIE_HIP(hipMalloc(&pc->tmp, size_t(2 * R * pc->info.N) * sizeof(double2)));
+        BIE_HIP(device_malloc(&pc->tmp, size_t(2 * R * pc->info.N) * sizeof(double2)));
         pc->tmp_R = R;
     }
     return static_cast<double2 *>(pc->tmp);

@@ -171,7 +171,7 @@ template <typename T>
 T *up(const std::vector<T> &v)
 {
     void *d = nullptr;
-    BIE_HIP(hipMalloc(&d, std::max<size_t>(v.size(), 1) * sizeof(T)));
+    BIE_HIP(device_malloc(&d, std::max<size_t>(v.size(), 1) * sizeof(T)));
     if (!v.empty()) BIE_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
     return static_cast<T *>(d);
 }
@@ -228,9 +228,9 @@ void fast_setup(bie_op *op, double near_factor, double box, int levels, int s, i
     f->rowptr = up(rowptr);
     f->colptr = up(colptr);
     f->cols = up(cols);
-    BIE_HIP(hipMalloc(&f->fblk, std::max<int64_t>(nflag, 1) * 18 * sizeof(double)));
-    BIE_HIP(hipMalloc(&f->vals, std::max<int64_t>(f->nnz, 1) * sizeof(double2)));
-    BIE_HIP(hipMalloc(&f->tmp, std::max<int64_t>(N, 1) * sizeof(double2)));
+    BIE_HIP(device_malloc(&f->fblk, std::max<int64_t>(nflag, 1) * 18 * sizeof(double)));
+    BIE_HIP(device_malloc(&f->vals, std::max<int64_t>(f->nnz, 1) * sizeof(double2)));
+    BIE_HIP(device_malloc(&f->tmp, std::max<int64_t>(N, 1) * sizeof(double2)));
     singular_blocks(op, dpairs, nflag, f->fblk, st);
     const TriDev &D = op->tri;
     hipLaunchKernelGGL(k_near_entries, dim3(unsigned(N)), dim3(256), 0, st, N, f->rowptr, f->colptr, f->cols,

@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "bie_internal.hpp"
@@ -66,7 +67,9 @@ Rule make_rule()
     return r;
 }
 
-__constant__ double c_w[NQ];
+// the rule's weights: 9/40, three times (155 - sqrt 15)/1200, three times (155 + sqrt 15)/1200
+__constant__ double c_w[NQ] = { 0.225, 0x1.01ec66adccf2ap-3, 0x1.01ec66adccf2ap-3, 0x1.01ec66adccf2ap-3,
+                                0x1.0f24aa63441e7p-3, 0x1.0f24aa63441e7p-3, 0x1.0f24aa63441e7p-3 };
 
 // Scratch of the local blocks: triangles in the device order, in bands of TT
 // rows p; band I holds the columns q >= TT I up to Fp (F rounded up to TT) and
@@ -668,17 +671,6 @@ __global__ __launch_bounds__(256) void k_far_out(int64_t nm, int64_t ld, int64_t
     }
 }
 
-template <typename T>
-T *dev_upload(const std::vector<T> &v)
-{
-    void *p = nullptr;
-    BIE_HIP(hipMalloc(&p, v.size() * sizeof(T)));
-    const hipError_t e = hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
-    if (e != hipSuccess) (void)hipFree(p);
-    BIE_HIP(e);
-    return static_cast<T *>(p);
-}
-
 }  // namespace
 
 // Weights of the triangle rule (relative to the area), for other kernels that
@@ -712,7 +704,6 @@ void upload_triangles(bie_op *op, hipStream_t s, const std::vector<int32_t> *giv
     const Mesh &M = op->mesh;
     const int64_t F = M.F;
     const Rule rule = make_rule();
-    BIE_HIP(hipMemcpyToSymbol(HIP_SYMBOL(c_w), rule.w, sizeof(rule.w)));
     TriDev &D = op->tri;
     D.rank.assign(F, -1);
     std::vector<int32_t> order;
@@ -728,14 +719,30 @@ void upload_triangles(bie_op *op, hipStream_t s, const std::vector<int32_t> *giv
             D.rank[t] = int32_t(order.size());
             order.push_back(t);
         }
-    std::vector<double> cent(F * 3), loc(F * NQ * 3), vf(F * 9), vt(F * 9), area(F), rad(F, 0.0);
-    std::vector<int8_t> sgn(F * 3);
-    std::vector<int32_t> slot(F * 3);
+    // one host image of the tables, copied at once
+    size_t bytes = 0;
+    auto place = [&](size_t n, size_t size) {
+        const size_t at = bytes;
+        bytes += (n * size + 255) / 256 * 256;
+        return at;
+    };
+    const size_t d = sizeof(double), i4 = sizeof(int32_t);
+    const size_t o_cent = place(3 * F, d), o_loc = place(3 * NQ * F, d), o_vf = place(9 * F, d), o_vt = place(9 * F, d),
+                 o_area = place(F, d), o_rad = place(F, d), o_sgn = place(3 * F, 1), o_slot = place(3 * F, i4),
+                 o_edges = place(4 * M.N, i4);
+    std::vector<char> image(bytes);
+    auto doubles = [&](size_t o) { return reinterpret_cast<double *>(image.data() + o); };
+    auto ints = [&](size_t o) { return reinterpret_cast<int32_t *>(image.data() + o); };
+    double *cent = doubles(o_cent), *loc = doubles(o_loc), *vf = doubles(o_vf), *vt = doubles(o_vt),
+           *area = doubles(o_area), *rad = doubles(o_rad);
+    int8_t *sgn = reinterpret_cast<int8_t *>(image.data() + o_sgn);
+    int32_t *slot = ints(o_slot), *r4 = ints(o_edges);   // r4: (c+, c-, slot of m in c+, slot of m in c-)
     for (int64_t r = 0; r < F; ++r) {
         const int64_t t = order[r];
         const double *v[3] = { &M.V[3 * M.T[3 * t]], &M.V[3 * M.T[3 * t + 1]], &M.V[3 * M.T[3 * t + 2]] };
         const double *c = &M.cent[3 * t];
         area[r] = M.area[t];
+        rad[r] = 0.0;
         for (int i = 0; i < NQ; ++i) {
             double d2 = 0.0;
             for (int d = 0; d < 3; ++d) {
@@ -756,8 +763,6 @@ void upload_triangles(bie_op *op, hipStream_t s, const std::vector<int32_t> *giv
             }
         }
     }
-    // rwg4: (c+, c-, slot of m in c+, slot of m in c-)
-    std::vector<int32_t> r4(M.N * 4);
     for (int64_t m = 0; m < M.N; ++m) {
         const int32_t tp = M.edges[4 * m + 2], tm = M.edges[4 * m + 3];
         int sp = -1, sm = -1;
@@ -767,15 +772,18 @@ void upload_triangles(bie_op *op, hipStream_t s, const std::vector<int32_t> *giv
         }
         r4[4 * m + 0] = D.rank[tp]; r4[4 * m + 1] = D.rank[tm]; r4[4 * m + 2] = sp; r4[4 * m + 3] = sm;
     }
-    D.cent = dev_upload(cent);
-    D.loc = dev_upload(loc);
-    D.vfree = dev_upload(vf);
-    D.verts = dev_upload(vt);
-    D.area = dev_upload(area);
-    D.rad = dev_upload(rad);
-    D.sgn = dev_upload(sgn);
-    D.slot_m = dev_upload(slot);
-    D.edges = dev_upload(r4);
+    BIE_HIP(device_malloc(&D.mem, bytes));
+    BIE_HIP(hipMemcpy(D.mem, image.data(), bytes, hipMemcpyHostToDevice));
+    auto dev = [&](auto *&p, size_t o) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(static_cast<char *>(D.mem) + o); };
+    dev(D.cent, o_cent);
+    dev(D.loc, o_loc);
+    dev(D.vfree, o_vf);
+    dev(D.verts, o_vt);
+    dev(D.area, o_area);
+    dev(D.rad, o_rad);
+    dev(D.sgn, o_sgn);
+    dev(D.slot_m, o_slot);
+    dev(D.edges, o_edges);
     (void)s;
 }
 
@@ -830,29 +838,20 @@ void fill_matrix(bie_op *op, bool fp64_regular, bool want64, bool want32, hipStr
     const int64_t F = M.F;
     const Bands bd{ (F + TT - 1) / TT * TT };
     const size_t elem = fp64_regular ? sizeof(double) : sizeof(float);
-    void *LB = nullptr, *VS = nullptr;
+    PoolBlock lb(s), vs(s);
     const int32_t *pairs = op->flagged;
     const int64_t npairs = int64_t(M.near.size() / 2);
-    try {
-        const size_t lb_bytes = size_t(bd.total()) * 9 * 2 * elem;
-        BIE_HIP(hipMalloc(&LB, lb_bytes));
-        if (op->star) BIE_HIP(hipMalloc(&VS, size_t(bd.total()) * 2 * elem));
-        if (fp64_regular) {
-            if (op->star) fill_launch<double, true>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
-            else fill_launch<double, false>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
-        } else {
-            if (op->star) fill_launch<float, true>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
-            else fill_launch<float, false>(op, bd, pairs, npairs, LB, VS, want64, want32, s);
-        }
-        BIE_HIP(hipGetLastError());
-        BIE_HIP(hipStreamSynchronize(s));
-    } catch (...) {
-        if (LB) hipFree(LB);
-        if (VS) hipFree(VS);
-        throw;
+    lb.get(size_t(bd.total()) * 9 * 2 * elem);
+    if (op->star) vs.get(size_t(bd.total()) * 2 * elem);
+    if (fp64_regular) {
+        if (op->star) fill_launch<double, true>(op, bd, pairs, npairs, lb.p, vs.p, want64, want32, s);
+        else fill_launch<double, false>(op, bd, pairs, npairs, lb.p, vs.p, want64, want32, s);
+    } else {
+        if (op->star) fill_launch<float, true>(op, bd, pairs, npairs, lb.p, vs.p, want64, want32, s);
+        else fill_launch<float, false>(op, bd, pairs, npairs, lb.p, vs.p, want64, want32, s);
     }
-    hipFree(LB);
-    if (VS) hipFree(VS);
+    BIE_HIP(hipGetLastError());
+    BIE_HIP(hipStreamSynchronize(s));
     (void)hipFree(op->flagged);   // not read again
     op->flagged = nullptr;
 }
@@ -861,7 +860,7 @@ void rhs_planewave(const bie_op *op, const double *dirs, const double *pols, int
 {
     const int64_t N = op->mesh.N;
     double *dd = nullptr;
-    BIE_HIP(hipMalloc(&dd, 6 * R * sizeof(double)));
+    BIE_HIP(device_malloc(&dd, 6 * R * sizeof(double)));
     BIE_HIP(hipMemcpy(dd, dirs, 3 * R * sizeof(double), hipMemcpyHostToDevice));
     BIE_HIP(hipMemcpy(dd + 3 * R, pols, 3 * R * sizeof(double), hipMemcpyHostToDevice));
     const TriDev &D = op->tri;
@@ -913,7 +912,7 @@ void farfield(const bie_op *op, const void *X, int64_t R, const double *obs, int
     hipError_t e = hipErrorOutOfMemory;
     for (int64_t limit : { int64_t(1) << 23, int64_t(1) << 19, int64_t(0) }) {
         p = plan(limit);
-        e = hipMalloc(&w, (nobs + p.coef + p.part) * sizeof(double));
+        e = device_malloc(&w, (nobs + p.coef + p.part) * sizeof(double));
         if (e != hipErrorOutOfMemory) break;
         (void)hipGetLastError();
     }

@@ -639,7 +639,7 @@ void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s,
             if (op->gemm_part) (void)hipFree(op->gemm_part);
             op->gemm_part = nullptr;
             op->gemm_part_elems = 0;
-            BIE_HIP(hipMalloc(&op->gemm_part, pelems * sizeof(float)));
+            BIE_HIP(device_malloc(&op->gemm_part, pelems * sizeof(float)));
             op->gemm_part_elems = pelems;
         }
         float *P = static_cast<float *>(op->gemm_part);
@@ -678,7 +678,7 @@ void split_matrix(bie_op *op, hipStream_t s)
 {
     const int64_t N = op->mesh.N, Mp = gemm_pad_rows(N), Kp = gemm_pad_k(N);
     const size_t plane = size_t(Mp) * size_t(Kp);
-    BIE_HIP(hipMalloc(&op->Abf, 2 * plane * sizeof(__bf16)));
+    BIE_HIP(pool_get(&op->Abf, 2 * plane * sizeof(__bf16)));
     op->gemm_Mp = Mp;
     op->gemm_Kp = Kp;
     __bf16 *Ah = static_cast<__bf16 *>(op->Abf), *Al = Ah + plane;
@@ -710,7 +710,7 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
         op->Bbf = nullptr;
         op->bstage_cols = 0;
         const int64_t cap = wide_cols(R);
-        BIE_HIP(hipMalloc(&op->Bbf, 2 * size_t(cap) * size_t(Kp) * sizeof(__bf16)));
+        BIE_HIP(device_malloc(&op->Bbf, 2 * size_t(cap) * size_t(Kp) * sizeof(__bf16)));
         op->bstage_cols = cap;
     }
     __bf16 *Bh = static_cast<__bf16 *>(op->Bbf), *Bl = Bh + plane;
@@ -739,7 +739,7 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
         op->gemm_part = nullptr;
         op->gemm_part_elems = 0;
         const size_t cap = size_t(KS) * size_t(Mp) * size_t(wide_cols(R));
-        BIE_HIP(hipMalloc(&op->gemm_part, cap * sizeof(float)));
+        BIE_HIP(device_malloc(&op->gemm_part, cap * sizeof(float)));
         op->gemm_part_elems = cap;
     }
     float *P = static_cast<float *>(op->gemm_part);
@@ -757,7 +757,7 @@ void split_dense(bie_op *op, const void *A, hipStream_t s)
 {
     const int64_t N = op->mesh.N, Mp = gemm_pad_rows(N), Kp = gemm_pad_k(N);
     const size_t plane = size_t(Mp) * size_t(Kp);
-    BIE_HIP(hipMalloc(&op->Abf, 2 * plane * sizeof(__bf16)));
+    BIE_HIP(pool_get(&op->Abf, 2 * plane * sizeof(__bf16)));
     op->gemm_Mp = Mp;
     op->gemm_Kp = Kp;
     __bf16 *Ah = static_cast<__bf16 *>(op->Abf), *Al = Ah + plane;
@@ -773,7 +773,7 @@ void dense64_setup(bie_op *op, hipStream_t s)
 {
     if (op->A64) return;
     const int64_t N = op->mesh.N, Mp = (N + DBM - 1) / DBM * DBM, Kp = (2 * N + DBK - 1) / DBK * DBK;
-    BIE_HIP(hipMalloc(&op->A64, size_t(Mp) * size_t(Kp) * sizeof(double)));
+    BIE_HIP(pool_get(&op->A64, size_t(Mp) * size_t(Kp) * sizeof(double)));
     op->d64_Mp = Mp;
     op->d64_Kp = Kp;
     const dim3 grid(unsigned(std::min<int64_t>((Kp / 2 + 255) / 256, 64)), unsigned(Mp));
@@ -812,7 +812,7 @@ void gemm64_product(const bie_op *opc, const void *X, int64_t ldx, void *Y, int6
                 if (op->d64_part) (void)hipFree(op->d64_part);
                 op->d64_part = nullptr;
                 op->d64_part_elems = 0;
-                BIE_HIP(hipMalloc(&op->d64_part, pmax * sizeof(double)));
+                BIE_HIP(device_malloc(&op->d64_part, pmax * sizeof(double)));
                 op->d64_part_elems = pmax;
             }
             double *Pt = static_cast<double *>(op->d64_part);
@@ -839,7 +839,7 @@ void gemm64_product(const bie_op *opc, const void *X, int64_t ldx, void *Y, int6
         if (op->d64_part) (void)hipFree(op->d64_part);
         op->d64_part = nullptr;
         op->d64_part_elems = 0;
-        BIE_HIP(hipMalloc(&op->d64_part, pelems * sizeof(double)));
+        BIE_HIP(device_malloc(&op->d64_part, pelems * sizeof(double)));
         op->d64_part_elems = pelems;
     }
     double *P = static_cast<double *>(op->d64_part);

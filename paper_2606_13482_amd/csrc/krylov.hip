@@ -900,7 +900,7 @@ struct Workspace {
     T *alloc(size_t n)
     {
         void *p = nullptr;
-        BIE_HIP(hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)));
+        BIE_HIP(device_malloc(&p, std::max<size_t>(n, 1) * sizeof(T)));
         all.push_back(p);
         return static_cast<T *>(p);
     }
@@ -1426,7 +1426,7 @@ struct DevBufs {
     T *get(size_t n)
     {
         void *p = nullptr;
-        BIE_HIP(hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)));
+        BIE_HIP(device_malloc(&p, std::max<size_t>(n, 1) * sizeof(T)));
         all.push_back(p);
         return static_cast<T *>(p);
     }

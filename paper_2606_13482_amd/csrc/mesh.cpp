@@ -59,25 +59,32 @@ Mesh build_mesh(const double *verts, int64_t nv, const int32_t *tris, int64_t nt
     // Half-edges sorted by undirected key, then direction; a closed,
     // consistently oriented 2-manifold has exactly one forward and one
     // backward half-edge per key.
-    std::vector<HalfEdge> he;
-    he.reserve(3 * F);
+    // Buckets by the lower vertex, a few half-edges each.
+    std::vector<int64_t> bucket(nv + 1, 0);
     for (int64_t t = 0; t < F; ++t)
         for (int k = 0; k < 3; ++k) {
-            int32_t i = M.T[3 * t + k], j = M.T[3 * t + (k + 1) % 3];
+            const int32_t i = M.T[3 * t + k], j = M.T[3 * t + (k + 1) % 3];
             if (i == j) throw Error(BIE_EMESH, "degenerate triangle");
-            HalfEdge h;
+            ++bucket[std::min(i, j) + 1];
+        }
+    for (int64_t v = 0; v < nv; ++v) bucket[v + 1] += bucket[v];
+    std::vector<HalfEdge> he(3 * F);
+    std::vector<int64_t> next(bucket.begin(), bucket.end() - 1);
+    for (int64_t t = 0; t < F; ++t)
+        for (int k = 0; k < 3; ++k) {
+            const int32_t i = M.T[3 * t + k], j = M.T[3 * t + (k + 1) % 3];
+            HalfEdge &h = he[next[std::min(i, j)]++];
             h.lo = std::min(i, j);
             h.hi = std::max(i, j);
             h.tri = int32_t(t);
             h.slot = int8_t((k + 2) % 3);
             h.forward = i < j ? 1 : 0;
-            he.push_back(h);
         }
-    std::sort(he.begin(), he.end(), [](const HalfEdge &x, const HalfEdge &y) {
-        if (x.lo != y.lo) return x.lo < y.lo;
-        if (x.hi != y.hi) return x.hi < y.hi;
-        return x.forward > y.forward;
-    });
+    for (int64_t v = 0; v < nv; ++v)
+        std::sort(he.begin() + bucket[v], he.begin() + bucket[v + 1], [](const HalfEdge &x, const HalfEdge &y) {
+            if (x.hi != y.hi) return x.hi < y.hi;
+            return x.forward > y.forward;
+        });
     if (he.size() % 2) throw Error(BIE_EMESH, "open mesh");
     const int64_t N = int64_t(he.size() / 2);
     M.N = N;

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void k_pairs_of(int64_t F, const int64_t *__re
 int32_t *pairs_of(const NearDev &nd, int64_t F, const int32_t *rank, hipStream_t s)
 {
     int32_t *out = nullptr;
-    BIE_HIP(hipMalloc(&out, std::max<int64_t>(nd.n, 1) * 2 * sizeof(int32_t)));
+    BIE_HIP(device_malloc(&out, std::max<int64_t>(nd.n, 1) * 2 * sizeof(int32_t)));
     hipLaunchKernelGGL(k_pairs_of, dim3(unsigned((F + 3) / 4)), dim3(256), 0, s, F, nd.ptr, nd.list, rank, out);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) (void)hipFree(out);
@@ -155,7 +155,7 @@ int32_t *pairs_of(const NearDev &nd, int64_t F, const int32_t *rank, hipStream_t
 // device memory that is freed with the scope
 struct Temp {
     void *p = nullptr;
-    explicit Temp(size_t bytes) { BIE_HIP(hipMalloc(&p, std::max<size_t>(bytes, 1))); }
+    explicit Temp(size_t bytes) { BIE_HIP(device_malloc(&p, std::max<size_t>(bytes, 1))); }
     ~Temp() { (void)hipFree(p); }
     Temp(const Temp &) = delete;
     Temp &operator=(const Temp &) = delete;
@@ -178,14 +178,14 @@ void near_search(const Mesh &M, double near_factor, const std::vector<int32_t> *
     }
     Temp tri(size_t(F) * sizeof(Tri));
     BIE_HIP(hipMemcpyAsync(tri.p, h.data(), size_t(F) * sizeof(Tri), hipMemcpyHostToDevice, s));
-    BIE_HIP(hipMalloc(&out.ptr, size_t(F + 1) * sizeof(int64_t)));
+    BIE_HIP(device_malloc(&out.ptr, size_t(F + 1) * sizeof(int64_t)));
     const dim3 grid(unsigned((F + PR - 1) / PR));
     hipLaunchKernelGGL(k_near<false>, grid, dim3(64 * PW), 0, s, F, (const Tri *)tri.p, near_factor, out.ptr, nullptr);
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, F, out.ptr);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipMemcpyAsync(&out.n, out.ptr + F, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     BIE_HIP(hipStreamSynchronize(s));
-    BIE_HIP(hipMalloc(&out.list, std::max<int64_t>(out.n, 1) * sizeof(int32_t)));
+    BIE_HIP(device_malloc(&out.list, std::max<int64_t>(out.n, 1) * sizeof(int32_t)));
     hipLaunchKernelGGL(k_near<true>, grid, dim3(64 * PW), 0, s, F, (const Tri *)tri.p, near_factor, out.ptr, out.list);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipStreamSynchronize(s));   // the triangles' copy ends with the call
@@ -222,7 +222,7 @@ void flag_pairs(bie_op *op, double near_factor, bool device_list, hipStream_t s)
             h[i] = std::min(p, q);
             h[i + 1] = std::max(p, q);
         }
-        BIE_HIP(hipMalloc(&op->flagged, std::max<size_t>(h.size(), 1) * sizeof(int32_t)));
+        BIE_HIP(device_malloc(&op->flagged, std::max<size_t>(h.size(), 1) * sizeof(int32_t)));
         BIE_HIP(hipMemcpy(op->flagged, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     }
 }
@@ -251,8 +251,8 @@ void ranked_near(const bie_op *op, double near_factor, NearDev &out, hipStream_t
         list[i] = fl[i].second;
     }
     for (int64_t t = 0; t < M.F; ++t) ptr[t + 1] += ptr[t];
-    BIE_HIP(hipMalloc(&out.ptr, ptr.size() * sizeof(int64_t)));
-    BIE_HIP(hipMalloc(&out.list, std::max<size_t>(list.size(), 1) * sizeof(int32_t)));
+    BIE_HIP(device_malloc(&out.ptr, ptr.size() * sizeof(int64_t)));
+    BIE_HIP(device_malloc(&out.list, std::max<size_t>(list.size(), 1) * sizeof(int32_t)));
     BIE_HIP(hipMemcpy(out.ptr, ptr.data(), ptr.size() * sizeof(int64_t), hipMemcpyHostToDevice));
     BIE_HIP(hipMemcpy(out.list, list.data(), list.size() * sizeof(int32_t), hipMemcpyHostToDevice));
 }

@@ -342,7 +342,7 @@ template <typename T>
 T *dmalloc(size_t n)
 {
     void *p = nullptr;
-    BIE_HIP(hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)));
+    BIE_HIP(device_malloc(&p, std::max<size_t>(n, 1) * sizeof(T)));
     return static_cast<T *>(p);
 }
 
