@@ -285,7 +285,8 @@ void packed_free(Packed &pk);
 // (mat64) or FP32 matrix; vectors complex128 (vec64, FP64 accumulation) or
 // complex64 (FP32 matrix only).
 // mat: MAT64 (packed FP64), MAT32 (packed FP32), MATBF16 (split-BF16 block product,
-// complex128 vectors only, no conj).
+// complex128 vectors only, no conj).  Y null (packed matrices of assembled
+// operators): the tile pass alone; its partial sums are left in op->pk.part.
 enum { MAT64 = 0, MAT32 = 1, MATBF16 = 2 };
 void product(const bie_op *op, int mat, bool vec64, const void *X, int64_t ldx, void *Y, int64_t ldy,
              const void *B, int64_t ldb, int64_t R, const int *skip, int64_t sks, bool conj, hipStream_t s);

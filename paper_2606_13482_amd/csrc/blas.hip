@@ -93,18 +93,24 @@ void prof_read(int kernel, int64_t *launches, double *total_ms, int64_t *columns
 
 namespace {
 
-// Work of the single-operator tile pass: units of 8 tiles, one per block
-// (default); BIE_SYM_UNIT = 1..64 selects another unit length, 0 balanced runs
-// (measurement: at N = 7680 both take the same time, and on the small
-// matrices of the uneven batch the runs were slower).
-int unit_tiles()
+// Tiles per unit of the single-operator tile pass, one unit per block: 8, and fewer
+// where that would leave less than 1.5 blocks per CU, for a small matrix is bound
+// by how many CUs read it (product of one FP64 vector, units of 1 / 2 / 4 / 8 / 16
+// tiles and balanced runs: 450 unknowns 7.0 / 7.9 / 9.4 / 12.5 / 12.6 / 19.7 us, 1152
+// 8.6 / 9.8 / 12.6 / 18.1 / 29.2 / 25.7, 2592 17.3 / 14.7 / 15.5 / 20.6 / 32.2 / 27.9, 3528
+// 27.6 / 25.2 / 22.5 / 23.9 / 34.3 / 29.9, 5202 51.0 / 44.8 / 43.2 / 43.2 / 42.5 / 45.9).
+// BIE_SYM_UNIT = 1..64 fixes the length, 0 balanced runs (measurement).
+int unit_tiles(int64_t nT)
 {
-    static int v = [] {
+    static const int env = [] {
         const char *e = getenv("BIE_SYM_UNIT");
-        const int u = e ? atoi(e) : 8;
-        return u >= 0 && u <= 64 ? u : 8;
+        const int u = e ? atoi(e) : -1;
+        return e ? (u >= 0 && u <= 64 ? u : 8) : -1;
     }();
-    return v;
+    if (env >= 0) return env;
+    int u = 8;
+    while (u > 1 && nT * (nT + 1) / 2 < 384 * u) u /= 2;
+    return u;
 }
 
 typedef double nd2 __attribute__((ext_vector_type(2)));
@@ -1074,10 +1080,12 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
         hipLaunchKernelGGL((k_sym_tiles<M, T, CONJ, false, NT>), grid, dim3(256), 0, s, (const M *)Z, pk.N, pk.nT,
                            pk.units, pk.unit_ptr, pk.run_ptr, pk.seg, pk.nslots, (const T *)X, ldx, (T *)part,
                            skip, sks);
-    if (profile) {
-        prof::end(0, s);
-        prof::begin(3, s, R);
+    if (profile) prof::end(0, s);
+    if (!Y) {   // the caller adds the partial sums
+        BIE_HIP(hipGetLastError());
+        return;
     }
+    if (profile) prof::begin(3, s, R);
     hipLaunchKernelGGL((k_sym_reduce<T, SUB>), dim3(unsigned(pk.nT), unsigned(R)), dim3(512), 0, s, pk.N, pk.seg,
                        pk.nslots, (const T *)part, (T *)Y, ldy, (const T *)B, ldb, skip, sks);
     BIE_HIP(hipGetLastError());
@@ -1188,7 +1196,7 @@ static void packed_setup_units(Packed &pk, int64_t n, int U)
     pk.h_seg = std::move(seg);
 }
 
-void packed_setup(Packed &pk, int64_t n) { packed_setup_units(pk, n, unit_tiles()); }
+void packed_setup(Packed &pk, int64_t n) { packed_setup_units(pk, n, unit_tiles((n + TB - 1) / TB)); }
 
 static std::string tune_key(int64_t N, bool mat64) { return "sym:" + std::to_string(N) + (mat64 ? ":f64" : ":f32"); }
 static bool tuned_unit(const std::string &key, int &unit)
@@ -1202,7 +1210,7 @@ static bool tuned_unit(const std::string &key, int &unit)
 // With the autotuner's units where it has met the size (tune_packed then has nothing to rebuild).
 void packed_setup_tuned(Packed &pk, int64_t n, bool mat64)
 {
-    int unit = unit_tiles();
+    int unit = unit_tiles((n + TB - 1) / TB);
     if (!getenv("BIE_SYM_UNIT") && tune_enabled()) (void)tuned_unit(tune_key(n, mat64), unit);
     packed_setup_units(pk, n, unit);
 }
@@ -1264,13 +1272,17 @@ void tune_packed(bie_op *op, hipStream_t s)
             BIE_HIP(device_malloc(&y, size_t(N) * 16));
             BIE_HIP(hipMemsetAsync(x, 0, size_t(N) * 16, s));
             float best = 0.f;
-            v = { unit_tiles() };
-            for (int U : { 8, 0, 4, 16 }) {
+            const int def = unit_tiles((N + TB - 1) / TB);
+            v = { def };
+            // below the rule's 8 tiles a launch is some microseconds: its neighbours, and more launches
+            const std::vector<int> cand = def == 8 ? std::vector<int>{ 8, 0, 4, 16 }
+                                                   : std::vector<int>{ def, 2 * def, std::max(1, def / 2) };
+            for (int U : cand) {
                 Packed c;
                 try {
                     packed_setup_units(c, N, U);
                     ensure_part(c, 1, s);
-                    const float ms = time_launches(s, 3, [&]() {
+                    const float ms = time_launches(s, def == 8 ? 3 : 20, [&]() {
                         if (mat64)
                             launch_product<double, double, false, false>(c, c.part, Z, x, N, y, N, nullptr, 0, 1,
                                                                          nullptr, 1, s, false);
@@ -1400,7 +1412,15 @@ void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64
 {
     if (op->star) throw Error(BIE_EINVAL, "the allocation-free product takes an assembled operator");
     const Packed &pk = op->pk;
-    const size_t need = size_t(R) * size_t(pk.nslots) * TB * (vec64 ? 16 : 8);
+    // The short units of a small matrix take up to twice the partial slots of long ones: such
+    // a call is judged by units of 16 tiles and, where its own do not fit, made in several passes.
+    int64_t slots = pk.nslots;
+    if (unit_tiles(pk.nT) < 8) {
+        int64_t most = pk.nT * (pk.nT - 1) / 2;
+        for (int64_t I = 0; I < pk.nT; ++I) most += (pk.nT - I + 15) / 16;
+        slots = std::min(slots, most);
+    }
+    const size_t per = TB * (vec64 ? 16 : 8), need = size_t(R) * size_t(slots) * per;
     if (need > NOALLOC_SCRATCH_BYTES)
         throw Error(BIE_EINVAL, "partial sums of " + std::to_string(need) + " bytes exceed the " +
                                     std::to_string(NOALLOC_SCRATCH_BYTES) + "-byte scratch of the allocation-free "
@@ -1408,14 +1428,18 @@ void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64
     int dev = -1;
     BIE_HIP(hipGetDevice(&dev));
     if (dev != op->device) throw Error(BIE_EINVAL, "the operator's device must be current");
+    if (vec64 ? !op->Z64 && !op->Z32 : !op->Z32)
+        throw Error(BIE_EINVAL, vec64 ? "no packed matrix stored" : "complex64 vectors need the FP32 matrix");
     void *part = noalloc_scratch(dev);
-    if (vec64) {
-        if (op->Z64) dispatch<double, double>(pk, op->Z64, X, pk.N, Y, pk.N, nullptr, 0, R, nullptr, 1, conj, s, part);
-        else if (op->Z32) dispatch<float, double>(pk, op->Z32, X, pk.N, Y, pk.N, nullptr, 0, R, nullptr, 1, conj, s, part);
-        else throw Error(BIE_EINVAL, "no packed matrix stored");
-    } else {
-        if (!op->Z32) throw Error(BIE_EINVAL, "complex64 vectors need the FP32 matrix");
-        dispatch<float, float>(pk, op->Z32, X, pk.N, Y, pk.N, nullptr, 0, R, nullptr, 1, conj, s, part);
+    const int64_t pass = std::max<int64_t>(1, int64_t(NOALLOC_SCRATCH_BYTES / (size_t(pk.nslots) * per)));
+    const size_t vec = size_t(pk.N) * (vec64 ? 16 : 8);
+    for (int64_t r0 = 0; r0 < R; r0 += pass) {
+        const int64_t n = std::min(pass, R - r0);
+        const void *x = static_cast<const char *>(X) + size_t(r0) * vec;
+        void *y = static_cast<char *>(Y) + size_t(r0) * vec;
+        if (!vec64) dispatch<float, float>(pk, op->Z32, x, pk.N, y, pk.N, nullptr, 0, n, nullptr, 1, conj, s, part);
+        else if (op->Z64) dispatch<double, double>(pk, op->Z64, x, pk.N, y, pk.N, nullptr, 0, n, nullptr, 1, conj, s, part);
+        else dispatch<float, double>(pk, op->Z32, x, pk.N, y, pk.N, nullptr, 0, n, nullptr, 1, conj, s, part);
     }
 }
 

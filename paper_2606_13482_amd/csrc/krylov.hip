@@ -110,11 +110,43 @@ template <> __device__ inline double2 st2<double2>(double2 v) { return v; }
 template <> __device__ inline float2 st2<float2>(double2 v) { return make_float2(float(v.x), float(v.y)); }
 template <> __device__ inline c32h st2<c32h>(double2 v) { return c32h{ (_Float16)v.x, (_Float16)v.y }; }
 
+// Exchanges between lanes in registers (a permute through LDS takes its latency and
+// its bandwidth for every 4 bytes).  xor_add<O>(v): v + the value of lane ^ O.
+template <int CTRL, int BANKS = 0xf> __device__ inline int2 dpp2(int2 old, int2 v)
+{
+    return make_int2(__builtin_amdgcn_update_dpp(old.x, v.x, CTRL, 0xf, BANKS, false),
+                     __builtin_amdgcn_update_dpp(old.y, v.y, CTRL, 0xf, BANKS, false));
+}
+// a of lane and lane ^ O in the lanes whose bit O is clear, b in the others, added
+template <int O> __device__ inline double pair_add(double a, double b)
+{
+    const int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
+    const auto lo = O == 32 ? __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false)
+                            : __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+    const auto hi = O == 32 ? __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false)
+                            : __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    return __builtin_bit_cast(double, make_int2(int(lo[0]), int(hi[0]))) +
+           __builtin_bit_cast(double, make_int2(int(lo[1]), int(hi[1])));
+}
+template <int O> __device__ inline double lane_xor(double v)
+{
+    const int2 w = __builtin_bit_cast(int2, v), z = make_int2(0, 0);
+    int2 r;
+    if (O == 8) r = dpp2<0x128>(z, w);                                   // rotation of 16 lanes by 8
+    else if (O == 4) r = dpp2<0x114, 0xa>(dpp2<0x104, 0x5>(z, w), w);    // shifts of 16 lanes by 4, for every other quad
+    else if (O == 2) r = dpp2<0x4e>(z, w);
+    else r = dpp2<0xb1>(z, w);
+    return __builtin_bit_cast(double, r);
+}
+
 __device__ inline double wsum(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v = pair_add<32>(v, v);
+    v = pair_add<16>(v, v);
+    v += lane_xor<8>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    return v + lane_xor<1>(v);
 }
 
 // Sums 8 complex values p[0..7] over the 64 lanes of a wave at once.  Each
@@ -123,36 +155,21 @@ __device__ inline double wsum(double v)
 // 8x6.  On return p[0] of lane L holds the total of value (L >> 3) & 7.
 __device__ inline void wave_sum8(double2 p[8])
 {
-    const int lane = threadIdx.x & 63;
-    {
-        const bool b = lane & 32;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const double2 snd = b ? p[i] : p[i + 4];
-            const double2 kp = b ? p[i + 4] : p[i];
-            p[i] = make_double2(kp.x + __shfl_xor(snd.x, 32, 64), kp.y + __shfl_xor(snd.y, 32, 64));
-        }
-    }
-    {
-        const bool b = lane & 16;
+    for (int i = 0; i < 4; ++i)
+        p[i] = make_double2(pair_add<32>(p[i].x, p[i + 4].x), pair_add<32>(p[i].y, p[i + 4].y));
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const double2 snd = b ? p[i] : p[i + 2];
-            const double2 kp = b ? p[i + 2] : p[i];
-            p[i] = make_double2(kp.x + __shfl_xor(snd.x, 16, 64), kp.y + __shfl_xor(snd.y, 16, 64));
-        }
-    }
+    for (int i = 0; i < 2; ++i)
+        p[i] = make_double2(pair_add<16>(p[i].x, p[i + 2].x), pair_add<16>(p[i].y, p[i + 2].y));
     {
-        const bool b = lane & 8;
-        const double2 snd = b ? p[0] : p[1];
-        const double2 kp = b ? p[1] : p[0];
-        p[0] = make_double2(kp.x + __shfl_xor(snd.x, 8, 64), kp.y + __shfl_xor(snd.y, 8, 64));
+        const bool b = threadIdx.x & 8;
+        const double sx = b ? p[0].x : p[1].x, sy = b ? p[0].y : p[1].y;
+        const double kx = b ? p[1].x : p[0].x, ky = b ? p[1].y : p[0].y;
+        p[0] = make_double2(kx + lane_xor<8>(sx), ky + lane_xor<8>(sy));
     }
-#pragma unroll
-    for (int o = 4; o > 0; o >>= 1) {
-        p[0].x += __shfl_xor(p[0].x, o, 64);
-        p[0].y += __shfl_xor(p[0].y, o, 64);
-    }
+    p[0] = make_double2(p[0].x + lane_xor<4>(p[0].x), p[0].y + lane_xor<4>(p[0].y));
+    p[0] = make_double2(p[0].x + lane_xor<2>(p[0].x), p[0].y + lane_xor<2>(p[0].y));
+    p[0] = make_double2(p[0].x + lane_xor<1>(p[0].x), p[0].y + lane_xor<1>(p[0].y));
 }
 
 // Chunk partials of conj(V[k][e]) * w[e] for k = 0..nk-1: element q of this
@@ -548,6 +565,47 @@ __device__ inline void givens(double2 a, double2 b, double &c, double2 &s)
     s = make_double2((ph.x * b.x + ph.y * b.y) / t, (ph.y * b.x - ph.x * b.y) / t);   // (a/|a|) conj(b) / t
 }
 
+// Column j of Hbar (Hc, its first j + 1 entries) through the earlier rotations, the new
+// rotation and the cycle test; one thread.
+__device__ inline void givens_update(int m, int j, double tol, double hn, double w2, int r, double2 *Hc, const double *cs,
+                                     const double2 *sn, double2 *__restrict__ Hall, double *__restrict__ csall,
+                                     double2 *__restrict__ snall, double2 *__restrict__ gall, ColStat &S)
+{
+    S.hn = hn;
+    S.wnorm0 = sqrt(w2);
+    Hc[j + 1] = make_double2(hn, 0.0);
+    double2 a = Hc[0];
+#pragma unroll 4
+    for (int i = 0; i < j; ++i) {
+        const double2 b = Hc[i + 1];
+        const double2 sb = cmul(sn[i], b);
+        const double2 csa = cmul(make_double2(sn[i].x, -sn[i].y), a);
+        Hc[i] = make_double2(cs[i] * a.x + sb.x, cs[i] * a.y + sb.y);
+        a = make_double2(-csa.x + cs[i] * b.x, -csa.y + cs[i] * b.y);
+    }
+    Hc[j] = a;
+    double c;
+    double2 s;
+    givens(Hc[j], Hc[j + 1], c, s);
+    const double2 sb = cmul(s, Hc[j + 1]);
+    Hc[j] = make_double2(c * Hc[j].x + sb.x, c * Hc[j].y + sb.y);
+    Hc[j + 1] = make_double2(0.0, 0.0);
+    double2 *H = Hall + (int64_t(r) * m + j) * (m + 1);
+    for (int i = 0; i <= j + 1; ++i) H[i] = Hc[i];
+    csall[int64_t(r) * m + j] = c;
+    snall[int64_t(r) * m + j] = s;
+    double2 *g = gall + int64_t(r) * (m + 1);
+    const double2 gj = g[j];
+    const double2 t = cmul(make_double2(s.x, -s.y), gj);
+    g[j + 1] = make_double2(-t.x, -t.y);
+    g[j] = make_double2(c * gj.x, c * gj.y);
+    S.est = hypot(t.x, t.y) / S.bnorm;
+    const bool brk = hn <= 64.0 * 2.220446049250313e-16 * S.wnorm0;
+    S.jend = j + 1;
+    if (brk) S.brk = 1;
+    if (S.est <= tol || brk || j + 1 >= S.jcap) S.done = 1;
+}
+
 template <typename VT, int EPT>
 __global__ __launch_bounds__(AB) void k_cgs_finish(Cols cl, int m, int j, double tol, VT *__restrict__ Vall,
                                                    const double2 *__restrict__ Wall, const double *__restrict__ PNall,
@@ -592,37 +650,161 @@ __global__ __launch_bounds__(AB) void k_cgs_finish(Cols cl, int m, int j, double
         }
     }
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    ColStat &S = st[r];
-    S.hn = hn;
-    S.wnorm0 = sqrt(s_w2);
-    Hc[j + 1] = make_double2(hn, 0.0);
-    for (int i = 0; i < j; ++i) {
-        const double2 a = Hc[i], b = Hc[i + 1];
-        const double2 sb = cmul(sn[i], b);
-        const double2 csa = cmul(make_double2(sn[i].x, -sn[i].y), a);
-        Hc[i] = make_double2(cs[i] * a.x + sb.x, cs[i] * a.y + sb.y);
-        Hc[i + 1] = make_double2(-csa.x + cs[i] * b.x, -csa.y + cs[i] * b.y);
+    givens_update(m, j, tol, hn, s_w2, r, Hc, cs, sn, Hall, csall, snall, gall, st[r]);
+}
+
+// The whole step of a column of at most SMALL unknowns in one block, a thread per
+// element: the sums of the four launches above in the same order, so the results are
+// bitwise theirs.  Such a step is latency: four launches of two blocks took
+// 20.5 us at 480 unknowns and the reduction before them 3.9, one takes 13.
+// A product that left its partial sums (the packed tile pass) is added up here too, as
+// its reduction does it: eight running sums over every eighth slot, added in order.
+constexpr int SMALL = 1024;
+struct Partials {
+    const double2 *part = nullptr;   // null: the product lies in W
+    const int64_t *seg = nullptr;
+    int64_t nslots = 0;
+};
+template <typename VT>
+__global__ __launch_bounds__(SMALL) void k_cgs_step(Cols cl, int m, int j, double tol, VT *__restrict__ Vall,
+                                                    const double2 *__restrict__ Wall, Partials pp,
+                                                    double2 *__restrict__ Hall,
+                                                    double *__restrict__ csall, double2 *__restrict__ snall,
+                                                    double2 *__restrict__ gall, ColStat *__restrict__ st)
+{
+    const int r = blockIdx.x;
+    if (st[r].done) return;
+    const int64_t N = cl.len(r), e = threadIdx.x;
+    const int nc = int((N + AB - 1) / AB), t = threadIdx.x, c = t / AB, lane = t & 63, wave = (t >> 6) & 3;
+    VT *V = Vall + cl.vo(r);
+    constexpr int NCH = SMALL / AB;
+    __shared__ double2 red[NCH][MAXM + 8][AB / 64];
+    __shared__ double2 h[MAXM + 1], Hc[MAXM + 2], sn[MAXM];
+    __shared__ double rn[NCH][AB / 64], cs[MAXM], s_sum[2];
+    __shared__ int s_reorth;
+    for (int k = t; k < j; k += blockDim.x) {
+        cs[k] = csall[int64_t(r) * m + k];
+        sn[k] = snall[int64_t(r) * m + k];
     }
-    double c;
-    double2 s;
-    givens(Hc[j], Hc[j + 1], c, s);
-    const double2 sb = cmul(s, Hc[j + 1]);
-    Hc[j] = make_double2(c * Hc[j].x + sb.x, c * Hc[j].y + sb.y);
-    Hc[j + 1] = make_double2(0.0, 0.0);
-    double2 *H = Hall + (int64_t(r) * m + j) * (m + 1);
-    for (int i = 0; i <= j + 1; ++i) H[i] = Hc[i];
-    csall[int64_t(r) * m + j] = c;
-    snall[int64_t(r) * m + j] = s;
-    double2 *g = gall + int64_t(r) * (m + 1);
-    const double2 gj = g[j];
-    const double2 t = cmul(make_double2(s.x, -s.y), gj);
-    g[j + 1] = make_double2(-t.x, -t.y);
-    g[j] = make_double2(c * gj.x, c * gj.y);
-    S.est = hypot(t.x, t.y) / S.bnorm;
-    const bool brk = hn <= 64.0 * 2.220446049250313e-16 * S.wnorm0;
-    S.jend = j + 1;
-    if (brk) S.brk = 1;
-    if (S.est <= tol || brk || j + 1 >= S.jcap) S.done = 1;
+    double2 w = make_double2(0.0, 0.0);
+    if (e < N && pp.part) {
+        const int64_t s0 = pp.seg[e / TB], K = pp.seg[e / TB + 1] - s0;
+        const double2 *pv = pp.part + (int64_t(r) * pp.nslots + s0) * TB + e % TB;
+        double2 a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = make_double2(0.0, 0.0);
+        for (int64_t q = 0; q < K; q += 8) {
+            double2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = q + u < K ? pv[(q + u) * TB] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                a[u].x += v[u].x;
+                a[u].y += v[u].y;
+            }
+        }
+        w = a[0];
+#pragma unroll
+        for (int u = 1; u < 8; ++u) {
+            w.x += a[u].x;
+            w.y += a[u].y;
+        }
+    } else if (e < N) {
+        w = Wall[cl.wo(r) + e];
+    }
+    auto norm = [&]() {   // chunk partials of ||w||^2
+        const double nn = wsum(w.x * w.x + w.y * w.y);
+        if (lane == 0) rn[c][wave] = nn;
+    };
+    auto norm_sum = [&](double *out) {   // their sum, by the first wave
+        if (t < 64) {
+            double a = 0.0;
+            if (t < nc) a += rn[t][0] + rn[t][1] + rn[t][2] + rn[t][3];
+            a = wsum(a);
+            if (t == 0) *out = a;
+        }
+    };
+    auto dots = [&]() {   // h = V_{0..j}^H w, to be read after a barrier
+        constexpr int NG = 2;
+        for (int k0 = 0; k0 <= j; k0 += 8 * NG) {
+            VT vv[NG][8];
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int k = k0 + 8 * g + i;
+                    vv[g][i] = (e < N && k <= j) ? V[int64_t(k) * N + e] : VT{};
+                }
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (k0 + 8 * g > j) break;
+                double2 p[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) p[i] = cmulc(ld2(vv[g][i]), w);
+                wave_sum8(p);
+                if ((lane & 7) == 0) red[c][k0 + 8 * g + (lane >> 3)][wave] = p[0];
+            }
+        }
+        __syncthreads();
+        for (int k = t; k <= j; k += blockDim.x) {
+            double ar = 0.0, ai = 0.0;
+            for (int b = 0; b < nc; ++b) {
+                double2 a = red[b][k][0];
+                for (int u = 1; u < AB / 64; ++u) { a.x += red[b][k][u].x; a.y += red[b][k][u].y; }
+                ar += a.x;
+                ai += a.y;
+            }
+            h[k] = make_double2(ar, ai);
+        }
+    };
+    auto update = [&]() {   // w -= V_{0..j} h, in ascending k
+        constexpr int KB = 16;
+        for (int k0 = 0; k0 <= j; k0 += KB) {
+            VT vv[KB];
+#pragma unroll
+            for (int i = 0; i < KB; ++i) vv[i] = (e < N && k0 + i <= j) ? V[int64_t(k0 + i) * N + e] : VT{};
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                if (k0 + i > j) break;
+                const double2 p = cmul(ld2(vv[i]), h[k0 + i]);
+                w.x -= p.x;
+                w.y -= p.y;
+            }
+        }
+    };
+    norm();
+    dots();
+    norm_sum(&s_sum[0]);
+    __syncthreads();
+    const double w2 = s_sum[0];
+    if (t == 0) {
+        double h2 = 0.0;
+        for (int k = 0; k <= j; ++k) h2 += h[k].x * h[k].x + h[k].y * h[k].y;
+        s_reorth = (w2 - h2) < 0.5 * w2;
+    }
+    for (int k = t; k <= j; k += blockDim.x) Hc[k] = h[k];
+    update();
+    norm();
+    __syncthreads();
+    const bool reorth = s_reorth != 0;
+    if (reorth) {   // the second pass (the barriers inside order h, Hc and rn)
+        dots();
+        __syncthreads();
+        for (int k = t; k <= j; k += blockDim.x) Hc[k] = make_double2(Hc[k].x + h[k].x, Hc[k].y + h[k].y);
+        update();
+        norm();
+        __syncthreads();
+    }
+    norm_sum(&s_sum[1]);
+    __syncthreads();
+    const double hn = sqrt(s_sum[1]);
+    if (hn > 0.0 && e < N) {
+        const double inv = 1.0 / hn;
+        V[int64_t(j + 1) * N + e] = st2<VT>(make_double2(w.x * inv, w.y * inv));
+    }
+    if (t != 0) return;
+    st[r].reorth = reorth;
+    givens_update(m, j, tol, hn, w2, r, Hc, cs, sn, Hall, csall, snall, gall, st[r]);
 }
 
 // Upper-triangular solve H y = g for the iterations of the cycle: one block
@@ -947,8 +1129,16 @@ static void arnoldi_launch(Workspace *w, const Cols &cl, int64_t Nmax, VT *V, in
 }
 template <typename VT>
 static void arnoldi_step(Workspace *w, const Cols &cl, int64_t Nmax, VT *V, int m, int j, double tol, int64_t R,
-                         hipStream_t s)
+                         hipStream_t s, const Partials &pp = Partials())
 {
+    if (Nmax <= SMALL) {   // faster for one column and for many (ms a solve, four launches / one: 648 unknowns,
+                           // 1 column 14.2 / 12.1, 512 columns 168 / 160; 162: 4.2 / 3.2 and 14.3 / 12.1)
+        const unsigned threads = unsigned((Nmax + AB - 1) / AB * AB);
+        hipLaunchKernelGGL(k_cgs_step<VT>, dim3(unsigned(R)), dim3(threads), 0, s, cl, m, j, tol, V, w->W, pp, w->H,
+                           w->cs, w->sn, w->g, w->st);
+        BIE_HIP(hipGetLastError());
+        return;
+    }
     arnoldi_launch<VT, 1>(w, cl, Nmax, V, m, j, tol, R, s);
 }
 
@@ -1232,16 +1422,21 @@ static int solve_impl(const bie_op *opc, const void *Bv, void *Xv, int64_t R, co
             int jmax = 0;
             for (int64_t r = 0; r < R; ++r)
                 if (active[r]) jmax = std::max(jmax, st[r].jcap);
+            // small columns: the step adds up the product's partial sums itself
+            const bool direct = N <= SMALL && !op->fast && !op->star && fp64 != MATBF16;
+            double2 *const Wy = direct ? nullptr : w->W;
             for (int j = 0; j < jmax; ++j) {
                 const double2 *vj = w->V + int64_t(j) * N;
                 if (pcd) {   // right preconditioning: w = T (M v_j)
                     calderon_apply(pcd, vj, int64_t(m + 1) * N, pcw, N, R, done_flags, done_stride, s);
-                    product(op, fp64, true, pcw, N, w->W, N, nullptr, 0, R, done_flags, done_stride, false, s);
+                    product(op, fp64, true, pcw, N, Wy, N, nullptr, 0, R, done_flags, done_stride, false, s);
                 } else {
-                    product(op, fp64, true, vj, int64_t(m + 1) * N, w->W, N, nullptr, 0, R, done_flags, done_stride,
+                    product(op, fp64, true, vj, int64_t(m + 1) * N, Wy, N, nullptr, 0, R, done_flags, done_stride,
                             false, s);
                 }
-                arnoldi_step<double2>(w, ucols, N, w->V, m, j, o.tol, R, s);
+                Partials pp;
+                if (direct) pp = Partials{ static_cast<const double2 *>(op->pk.part), op->pk.seg, op->pk.nslots };
+                arnoldi_step<double2>(w, ucols, N, w->V, m, j, o.tol, R, s, pp);
             }
             hipLaunchKernelGGL(k_lsq, dim3(unsigned(R)), dim3(64), size_t(m) * m * sizeof(double2), s, m, w->H, w->g,
                                w->y, w->st);
