@@ -134,17 +134,38 @@ __global__ __launch_bounds__(256) void k_inner(int64_t P, int64_t S, int64_t N, 
 // EPI_BIAS C = acc + bias[n]; EPI_TANH_BACK C = acc (1 - X[m][n]^2) with X the
 // stored tanh output of the layer (the backward step through tanh).
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-enum { EPI_STORE = 0, EPI_BIAS_TANH = 1, EPI_BIAS = 2, EPI_TANH_BACK = 3 };
+// EPI_MSE (last layer of a training step): with the output y = acc + bias[n] and the
+// target X[m][n], C = dL/dy = 2 (y - X) inv, and the block's part of the squared error to
+// loss[its tile].
+enum { EPI_STORE = 0, EPI_BIAS_TANH = 1, EPI_BIAS = 2, EPI_TANH_BACK = 3, EPI_MSE = 4 };
+
+struct Gemm {
+    int M, N, K;
+    const float *A;
+    int lda;
+    const float *B;
+    int ldb;
+    float *C;
+    int ldc;
+    int epi;
+    const float *bias, *X;
+    float inv;
+    double *loss;
+    __host__ __device__ int tx() const { return (N + 31) / 32; }
+    __host__ __device__ int tiles() const { return tx() * ((M + 31) / 32); }
+};
+struct GemmLds {
+    float A[4][32][33];    // per wave: [k][m] of its K chunk
+    float B[4][32][33];    // per wave: [k][n]
+    float red[3][16][64];  // partial tiles of waves 1..3
+};
 
 template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void k_sgemm_mf(int M, int N, int K, const float *__restrict__ A, int lda,
-                                                  const float *__restrict__ Bm, int ldb, float *__restrict__ C, int ldc,
-                                                  int epi, const float *__restrict__ bias, const float *__restrict__ X)
+__device__ __forceinline__ void sgemm_tile(const Gemm &g, int bx, int by, GemmLds &L)
 {
-    __shared__ float As[4][32][33];   // per wave: [k][m] of its K chunk
-    __shared__ float Bs[4][32][33];   // per wave: [k][n]
-    __shared__ float red[3][16][64];  // partial tiles of waves 1..3
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+    const int M = g.M, N = g.N, K = g.K, lda = g.lda, ldb = g.ldb;
+    const float *__restrict__ A = g.A, *__restrict__ Bm = g.B;
+    const int m0 = by * 32, n0 = bx * 32;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     f32x16 acc;
 #pragma unroll
@@ -171,37 +192,104 @@ __global__ __launch_bounds__(256) void k_sgemm_mf(int M, int N, int K, const flo
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int e = lane + 64 * j, hi = e >> 5, lo = e & 31;
-            if (TA) As[w][hi][lo] = ra[j];
-            else As[w][lo][hi] = ra[j];
-            if (TB) Bs[w][lo][hi] = rb[j];
-            else Bs[w][hi][lo] = rb[j];
+            if (TA) L.A[w][hi][lo] = ra[j];
+            else L.A[w][lo][hi] = ra[j];
+            if (TB) L.B[w][lo][hi] = rb[j];
+            else L.B[w][hi][lo] = rb[j];
         }
         __syncthreads();
         if (it + 1 < nit) load(it + 1);
         const int i = lane & 31, h = lane >> 5;
 #pragma unroll
         for (int kk = 0; kk < 32; kk += 2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[w][kk + h][i], Bs[w][kk + h][i], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(L.A[w][kk + h][i], L.B[w][kk + h][i], acc, 0, 0, 0);
         __syncthreads();
     }
     if (w > 0)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) red[w - 1][q][lane] = acc[q];
+        for (int q = 0; q < 16; ++q) L.red[w - 1][q][lane] = acc[q];
     __syncthreads();
     if (w != 0) return;
+    double se = 0.0;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-        const float v = ((acc[q] + red[0][q][lane]) + red[1][q][lane]) + red[2][q][lane];
+        const float v = ((acc[q] + L.red[0][q][lane]) + L.red[1][q][lane]) + L.red[2][q][lane];
         const int m = m0 + 8 * (q / 4) + 4 * (lane / 32) + q % 4, n = n0 + (lane & 31);
         if (m >= M || n >= N) continue;
+        const int64_t at = int64_t(m) * g.ldc + n;
         float o = v;
-        if (epi == EPI_BIAS_TANH) o = tanhf(v + bias[n]);
-        else if (epi == EPI_BIAS) o = v + bias[n];
-        else if (epi == EPI_TANH_BACK) {
-            const float a = X[int64_t(m) * ldc + n];
+        if (g.epi == EPI_BIAS_TANH) o = tanhf(v + g.bias[n]);
+        else if (g.epi == EPI_BIAS) o = v + g.bias[n];
+        else if (g.epi == EPI_TANH_BACK) {
+            const float a = g.X[at];
             o = v * (1.f - a * a);
+        } else if (g.epi == EPI_MSE) {
+            const float d = (v + g.bias[n]) - g.X[at];
+            o = 2.f * d * g.inv;
+            se += double(d) * double(d);
         }
-        C[int64_t(m) * ldc + n] = o;
+        g.C[at] = o;
+    }
+    if (g.epi == EPI_MSE) {
+        for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
+        if (lane == 0) g.loss[by * g.tx() + bx] = se;
+    }
+}
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void k_sgemm_mf(Gemm g)
+{
+    __shared__ GemmLds L;
+    sgemm_tile<TA, TB>(g, blockIdx.x, blockIdx.y, L);
+}
+
+// The three products that a layer's dZ enters, in one launch (each of a few
+// microseconds and a hundred or two blocks: launched one after the other they left
+// the GPU idle between and within them; 256 x 512 x 512: 27 us in three launches,
+// 15 in one): dX = (dZ W) (1 - X^2) of the layer below, dW = dZ^T X, and db,
+// the column sums of dZ (64 columns per block, its wave v summing rows v', v' + 16, ..
+// for the four v' = v + 4 i, the 16 partial sums added in order).
+__global__ __launch_bounds__(256) void k_mlp_back(Gemm dx, Gemm dw, int ndx, int Bn, int O, const float *__restrict__ dZ,
+                                                  float *__restrict__ db)
+{
+    __shared__ GemmLds L;
+    int b = int(blockIdx.x);
+    if (b < ndx) {
+        sgemm_tile<false, false>(dx, b % dx.tx(), b / dx.tx(), L);
+        return;
+    }
+    b -= ndx;
+    if (b < dw.tiles()) {
+        sgemm_tile<true, false>(dw, b % dw.tx(), b / dw.tx(), L);
+        return;
+    }
+    b -= dw.tiles();
+    float(*red)[64] = reinterpret_cast<float(*)[64]>(&L.A[0][0][0]);
+    const int lane = threadIdx.x & 63, o = b * 64 + lane;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int v = int(threadIdx.x >> 6) + 4 * u;
+        float s = 0.f;
+        if (o < O) {
+            float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
+            int r = v;
+            for (; r + 48 < Bn; r += 64) {
+                p0 += dZ[int64_t(r) * O + o];
+                p1 += dZ[int64_t(r + 16) * O + o];
+                p2 += dZ[int64_t(r + 32) * O + o];
+                p3 += dZ[int64_t(r + 48) * O + o];
+            }
+            for (; r < Bn; r += 16) p0 += dZ[int64_t(r) * O + o];
+            s = (p0 + p1) + (p2 + p3);
+        }
+        red[v][lane] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64 && o < O) {
+        float a = 0.f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) a += red[u][lane];
+        db[o] = a;
     }
 }
 
@@ -223,37 +311,6 @@ __global__ void k_mse(int n, const float *__restrict__ y, const float *__restric
         __syncthreads();
     }
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-// db[o] = sum_b dZ[b][o]: 64 columns per block of 16 waves, wave v summing the
-// rows b = v, v + 16, ... (all its loads issued together), the 16 partial sums
-// of a column then added in a fixed order
-__global__ __launch_bounds__(1024) void k_colsum(int Bn, int O, const float *__restrict__ dZ, float *__restrict__ db)
-{
-    __shared__ float red[16][64];
-    const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
-    const int o = blockIdx.x * 64 + lane;
-    float s = 0.f;
-    if (o < O) {
-        float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
-        int b = v;
-        for (; b + 48 < Bn; b += 64) {
-            p0 += dZ[int64_t(b) * O + o];
-            p1 += dZ[int64_t(b + 16) * O + o];
-            p2 += dZ[int64_t(b + 32) * O + o];
-            p3 += dZ[int64_t(b + 48) * O + o];
-        }
-        for (; b < Bn; b += 16) p0 += dZ[int64_t(b) * O + o];
-        s = (p0 + p1) + (p2 + p3);
-    }
-    red[v][lane] = s;
-    __syncthreads();
-    if (v == 0 && o < O) {
-        float a = 0.f;
-#pragma unroll
-        for (int u = 0; u < 16; ++u) a += red[u][lane];
-        db[o] = a;
-    }
 }
 
 __global__ void k_adam(int n, float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
@@ -360,12 +417,25 @@ void inner(int64_t P, int64_t S, int64_t N, const double2 *A, const double2 *B, 
     BIE_HIP(hipGetLastError());
 }
 
-template <bool TA, bool TB>
-void sgemm(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc, hipStream_t s,
-           int epi = EPI_STORE, const float *bias = nullptr, const float *X = nullptr)
+// C = opA(A) opB(B) with the epilogue epi (see k_sgemm_mf)
+Gemm gemm_of(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
+             int epi = EPI_STORE, const float *bias = nullptr, const float *X = nullptr)
 {
-    const dim3 grid(unsigned((N + 31) / 32), unsigned((M + 31) / 32));
-    hipLaunchKernelGGL((k_sgemm_mf<TA, TB>), grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, C, ldc, epi, bias, X);
+    return Gemm{ M, N, K, A, lda, B, ldb, C, ldc, epi, bias, X, 0.f, nullptr };
+}
+
+template <bool TA, bool TB>
+void sgemm(const Gemm &g, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_sgemm_mf<TA, TB>), dim3(unsigned(g.tx()), unsigned((g.M + 31) / 32)), dim3(256), 0, s, g);
+    BIE_HIP(hipGetLastError());
+}
+
+// dw, db and (unless dx has no rows) dx from dZ (Bn x O)
+void mlp_back_layer(const Gemm &dx, const Gemm &dw, int Bn, int O, const float *dZ, float *db, hipStream_t s)
+{
+    const int ndx = dx.M > 0 ? dx.tiles() : 0, nb = ndx + dw.tiles() + (O + 63) / 64;
+    hipLaunchKernelGGL(k_mlp_back, dim3(unsigned(nb)), dim3(256), 0, s, dx, dw, ndx, Bn, O, dZ, db);
     BIE_HIP(hipGetLastError());
 }
 
@@ -542,49 +612,54 @@ void ws_batch_scratch(bie_ws *w, int B)
     w->cap_batch = B;
 }
 
-// forward for B inputs already in w->in; output in w->y
-void mlp_forward(bie_ws *w, int B, hipStream_t s)
+// forward for B inputs already in w->in; output in w->y, or with loss the
+// parts of the squared error against w->tgt there (one per tile of the output) and
+// its gradient in w->dy
+int loss_parts(const bie_ws *w, int B) { return (w->O + 31) / 32 * ((B + 31) / 32); }
+void mlp_forward(bie_ws *w, int B, hipStream_t s, double *loss = nullptr)
 {
     const int H = w->H, O = w->O;
     float *P = w->params;
-    sgemm<false, true>(B, H, 4, w->in, 4, P + w->off[0], 4, w->a1, H, s, EPI_BIAS_TANH, P + w->off[1]);
-    sgemm<false, true>(B, H, H, w->a1, H, P + w->off[2], H, w->a2, H, s, EPI_BIAS_TANH, P + w->off[3]);
-    sgemm<false, true>(B, O, H, w->a2, H, P + w->off[4], H, w->y, O, s, EPI_BIAS, P + w->off[5]);
+    sgemm<false, true>(gemm_of(B, H, 4, w->in, 4, P + w->off[0], 4, w->a1, H, EPI_BIAS_TANH, P + w->off[1]), s);
+    sgemm<false, true>(gemm_of(B, H, H, w->a1, H, P + w->off[2], H, w->a2, H, EPI_BIAS_TANH, P + w->off[3]), s);
+    Gemm g = gemm_of(B, O, H, w->a2, H, P + w->off[4], H, loss ? w->dy : w->y, O, loss ? EPI_MSE : EPI_BIAS,
+                     P + w->off[5], w->tgt);
+    g.inv = 1.f / float(B * O);
+    g.loss = loss;
+    sgemm<false, true>(g, s);
 }
 
-// loss partials (w->lpart[0..nb)) and gradient of the mean squared error into
-// w->grad.  combine: the loss is on y = sum_c e_c f_c against 2K targets
+// loss partials (w->lpart[0..nb)) and gradient dL/dy of the mean squared error
+// from w->y into w->dy.  combine: the loss is on y = sum_c e_c f_c against 2K targets
 // (linear-in-polarisation model); otherwise on the raw outputs.
-int mlp_backward(bie_ws *w, int B, hipStream_t s, bool combine = false)
+int mlp_loss(bie_ws *w, int B, double *loss, hipStream_t s, bool combine)
 {
-    const int H = w->H, O = w->O;
-    float *P = w->params, *G = w->grad;
+    const int O = w->O;
     const int nb = 32;
     if (combine) {
         const int K2 = 2 * w->K;
         hipLaunchKernelGGL(k_pol_combine, dim3((B * K2 + 255) / 256), dim3(256), 0, s, B, K2, w->y, w->pol, w->yc);
-        hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, B * K2, w->yc, w->tgt, w->dyc, 1.f / float(B * K2),
-                           w->lpart);
+        hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, B * K2, w->yc, w->tgt, w->dyc, 1.f / float(B * K2), loss);
         hipLaunchKernelGGL(k_pol_combine_back, dim3((B * O + 255) / 256), dim3(256), 0, s, B, K2, w->dyc, w->pol,
                            w->dy);
     } else {
-        hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, B * O, w->y, w->tgt, w->dy, 1.f / float(B * O),
-                           w->lpart);
+        hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, B * O, w->y, w->tgt, w->dy, 1.f / float(B * O), loss);
     }
-    // layer 3
-    sgemm<true, false>(O, H, B, w->dy, O, w->a2, H, G + w->off[4], H, s);   // dW3 = dy^T a2
-    hipLaunchKernelGGL(k_colsum, dim3((O + 63) / 64), dim3(1024), 0, s, B, O, w->dy, G + w->off[5]);
-    // dZ2 = (dy W3) (1 - a2^2)
-    sgemm<false, false>(B, H, O, w->dy, O, P + w->off[4], H, w->d2, H, s, EPI_TANH_BACK, nullptr, w->a2);
-    // layer 2
-    sgemm<true, false>(H, H, B, w->d2, H, w->a1, H, G + w->off[2], H, s);
-    hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64), dim3(1024), 0, s, B, H, w->d2, G + w->off[3]);
-    sgemm<false, false>(B, H, H, w->d2, H, P + w->off[2], H, w->d1, H, s, EPI_TANH_BACK, nullptr, w->a1);
-    // layer 1
-    sgemm<true, false>(H, 4, B, w->d1, H, w->in, 4, G + w->off[0], 4, s);
-    hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64), dim3(1024), 0, s, B, H, w->d1, G + w->off[1]);
     BIE_HIP(hipGetLastError());
     return nb;
+}
+
+// gradient of the loss into w->grad from dL/dy in w->dy
+void mlp_backward(bie_ws *w, int B, hipStream_t s)
+{
+    const int H = w->H, O = w->O;
+    float *P = w->params, *G = w->grad;
+    // layer 3: dZ2 = (dy W3) (1 - a2^2), dW3 = dy^T a2
+    mlp_back_layer(gemm_of(B, H, O, w->dy, O, P + w->off[4], H, w->d2, H, EPI_TANH_BACK, nullptr, w->a2),
+                   gemm_of(O, H, B, w->dy, O, w->a2, H, G + w->off[4], H), B, O, w->dy, G + w->off[5], s);
+    mlp_back_layer(gemm_of(B, H, H, w->d2, H, P + w->off[2], H, w->d1, H, EPI_TANH_BACK, nullptr, w->a1),
+                   gemm_of(H, H, B, w->d2, H, w->a1, H, G + w->off[2], H), B, H, w->d2, G + w->off[3], s);
+    mlp_back_layer(Gemm{}, gemm_of(H, 4, B, w->d1, H, w->in, 4, G + w->off[0], 4), B, H, w->d1, G + w->off[1], s);
 }
 
 void glorot(bie_ws *w, uint64_t seed)
@@ -645,10 +720,16 @@ static double ws_fit_dev(bie_ws *w, const float *F, const float *T, const float 
     int64_t step = 0;
     std::vector<int64_t> perm(S);
     int64_t *dperm = dmalloc<int64_t>(size_t(S));
-    std::vector<double> lp(64);
-    double last = NAN;
+    // loss parts of the last epoch's steps, read when the buffer is full or the epoch ends
+    const bool combine = w->pmodel == 1;
+    const int parts = combine ? 32 : loss_parts(w, Bsz);
+    const int64_t room = std::max<int64_t>(1, std::min<int64_t>(nbatch, (int64_t(1) << 17) / parts));
+    std::vector<double> lp(size_t(room) * parts);
+    std::vector<int> lrows;
+    double last = NAN, *dloss = nullptr;
     const double PI = 3.14159265358979323846;
     try {
+        dloss = dmalloc<double>(lp.size());
         for (int ep = 0; ep < epochs; ++ep) {
             for (int64_t i = 0; i < S; ++i) perm[i] = i;
             SM64 g(seed + 1 + uint64_t(ep));
@@ -660,8 +741,10 @@ static double ws_fit_dev(bie_ws *w, const float *F, const float *T, const float 
                 const int B = int(std::min<int64_t>(Bsz, S - b0));
                 hipLaunchKernelGGL(k_gather, dim3(unsigned(B)), dim3(256), 0, s, B, TW, dperm, b0, F, T, E, w->in,
                                    w->tgt, w->pol);
-                mlp_forward(w, B, s);
-                const int nb = mlp_backward(w, B, s, w->pmodel == 1);
+                double *lo = dloss + int64_t(lrows.size()) * parts;
+                mlp_forward(w, B, s, combine ? nullptr : lo);
+                if (combine) (void)mlp_loss(w, B, lo, s, true);
+                mlp_backward(w, B, s);
                 ++step;
                 const double lr = lr_min + 0.5 * (lr_max - lr_min) *
                                                (1.0 + std::cos(PI * double(step - 1) /
@@ -672,13 +755,19 @@ static double ws_fit_dev(bie_ws *w, const float *F, const float *T, const float 
                                    int(w->nparams), w->params, w->grad, w->am, w->av, float(lr), 0.9f, 0.999f, 1e-8f,
                                    c1, c2);
                 BIE_HIP(hipGetLastError());
-                if (ep == epochs - 1) {
-                    BIE_HIP(hipMemcpyAsync(lp.data(), w->lpart, nb * sizeof(double), hipMemcpyDeviceToHost, s));
-                    BIE_HIP(hipStreamSynchronize(s));
+                if (ep != epochs - 1) continue;
+                lrows.push_back(B);
+                if (int64_t(lrows.size()) < room && bi + 1 < nbatch) continue;
+                BIE_HIP(hipMemcpyAsync(lp.data(), dloss, lrows.size() * parts * sizeof(double), hipMemcpyDeviceToHost,
+                                       s));
+                BIE_HIP(hipStreamSynchronize(s));
+                for (size_t r = 0; r < lrows.size(); ++r) {
+                    const int nb = combine ? 32 : loss_parts(w, lrows[r]);
                     double a = 0.0;
-                    for (int q = 0; q < nb; ++q) a += lp[q];
-                    eloss += a / double(B * TW) * B;
+                    for (int q = 0; q < nb; ++q) a += lp[r * parts + q];
+                    eloss += a / double(lrows[r] * TW) * lrows[r];
                 }
+                lrows.clear();
             }
             if (ep == epochs - 1) last = eloss / double(S);
             // the host permutation is rewritten next epoch: wait for its upload
@@ -686,9 +775,11 @@ static double ws_fit_dev(bie_ws *w, const float *F, const float *T, const float 
         }
     } catch (...) {
         (void)hipFree(dperm);
+        if (dloss) (void)hipFree(dloss);
         throw;
     }
     (void)hipFree(dperm);
+    (void)hipFree(dloss);
     BIE_HIP(hipStreamSynchronize(s));
     return last;
 }
@@ -912,7 +1003,8 @@ double ws_loss_grad(bie_ws *w, const double *feats, const double *pols, const fl
         for (size_t i = 0; i < eh.size(); ++i) eh[i] = float(pols[i]);
         BIE_HIP(hipMemcpyAsync(w->pol, eh.data(), eh.size() * sizeof(float), hipMemcpyHostToDevice, s));
     }
-    const int nb = mlp_backward(w, int(R), s, w->pmodel == 1);
+    const int nb = mlp_loss(w, int(R), w->lpart, s, w->pmodel == 1);
+    mlp_backward(w, int(R), s);
     std::vector<double> lp(nb);
     BIE_HIP(hipMemcpyAsync(lp.data(), w->lpart, nb * sizeof(double), hipMemcpyDeviceToHost, s));
     if (grad_host) BIE_HIP(hipMemcpyAsync(grad_host, w->grad, w->nparams * sizeof(float), hipMemcpyDeviceToHost, s));
