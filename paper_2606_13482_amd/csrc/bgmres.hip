@@ -2102,7 +2102,9 @@ struct Aux {
     {
         BIE_HIP(hipStreamCreateWithFlags(&s2, hipStreamNonBlocking));
         BIE_HIP(hipStreamCreateWithFlags(&s3, hipStreamNonBlocking));
-        for (auto &e : ev) BIE_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        // ev[0] orders two streams of the device only: no fence to the host with it
+        for (int i = 0; i < 7; ++i)
+            BIE_HIP(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming | (i ? 0 : hipEventDisableSystemFence)));
     }
     ~Aux()
     {

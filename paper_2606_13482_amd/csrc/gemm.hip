@@ -359,12 +359,12 @@ __global__ __launch_bounds__(64 * (GBM / WM) * (BN / WN)) void k_gemm_split(
 }
 
 // Y[v][m] = sum_z (P[z][m][2r], P[z][m][2r+1]) (or Bsub[v][m] - that), v = cols ?
-// cols[r] : r, for a tile of RM = 16 rows x 32 right-hand sides; the slices are
+// cols[r] : r, for a tile of RM = 8 rows x 32 right-hand sides; the slices are
 // summed in FP64 in their order.  A read of the partial tiles from the last-level
-// cache: each thread asks for eight slices of its four entries at a time, and 16
-// rows make 1.7 blocks per CU at 3528 x 64 (18 slices: 21 us; 64 rows and one
-// slice after the other 76).
-constexpr int RM = 16;
+// cache: each thread asks for eight slices of its two entries at a time, and 8 rows
+// make 3.5 blocks per CU at 3528 x 64 (18 slices: 7.6 us, 4.3 TB/s; 16 rows 21; 64 rows and
+// one slice after the other 76).
+constexpr int RM = 8;
 template <typename PT>
 __global__ __launch_bounds__(256) void k_gemm_reduce(const PT *__restrict__ P, int KS, int64_t Mp, int64_t NCp,
                                                      int64_t N, int64_t R, const int *__restrict__ cols,
