@@ -568,7 +568,7 @@ __device__ inline void givens(double2 a, double2 b, double &c, double2 &s)
 // Column j of Hbar (Hc, its first j + 1 entries) through the earlier rotations, the new
 // rotation and the cycle test; one thread.
 __device__ inline void givens_update(int m, int j, double tol, double hn, double w2, int r, double2 *Hc, const double *cs,
-                                     const double2 *sn, double2 *__restrict__ Hall, double *__restrict__ csall,
+                                     const double2 *sn, double *__restrict__ csall,
                                      double2 *__restrict__ snall, double2 *__restrict__ gall, ColStat &S)
 {
     S.hn = hn;
@@ -590,8 +590,6 @@ __device__ inline void givens_update(int m, int j, double tol, double hn, double
     const double2 sb = cmul(s, Hc[j + 1]);
     Hc[j] = make_double2(c * Hc[j].x + sb.x, c * Hc[j].y + sb.y);
     Hc[j + 1] = make_double2(0.0, 0.0);
-    double2 *H = Hall + (int64_t(r) * m + j) * (m + 1);
-    for (int i = 0; i <= j + 1; ++i) H[i] = Hc[i];
     csall[int64_t(r) * m + j] = c;
     snall[int64_t(r) * m + j] = s;
     double2 *g = gall + int64_t(r) * (m + 1);
@@ -650,13 +648,14 @@ __global__ __launch_bounds__(AB) void k_cgs_finish(Cols cl, int m, int j, double
         }
     }
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    givens_update(m, j, tol, hn, s_w2, r, Hc, cs, sn, Hall, csall, snall, gall, st[r]);
+    givens_update(m, j, tol, hn, s_w2, r, Hc, cs, sn, csall, snall, gall, st[r]);
+    for (int i = 0; i <= j + 1; ++i) Hall[(int64_t(r) * m + j) * (m + 1) + i] = Hc[i];
 }
 
 // The whole step of a column of at most SMALL unknowns in one block, a thread per
 // element: the sums of the four launches above in the same order, so the results are
 // bitwise theirs.  Such a step is latency: four launches of two blocks took
-// 20.5 us at 480 unknowns and the reduction before them 3.9, one takes 13.
+// 20.5 us at 480 unknowns and the reduction before them 3.9, one takes 10.5.
 // A product that left its partial sums (the packed tile pass) is added up here too, as
 // its reduction does it: eight running sums over every eighth slot, added in order.
 constexpr int SMALL = 1024;
@@ -665,19 +664,31 @@ struct Partials {
     const int64_t *seg = nullptr;
     int64_t nslots = 0;
 };
-template <typename VT>
-__global__ __launch_bounds__(SMALL) void k_cgs_step(Cols cl, int m, int j, double tol, VT *__restrict__ Vall,
+// Basis entries of the thread's element stay in registers from the first dots to the
+// second update, KR of them; their loads go out before anything is waited for.
+template <typename VT, int BS>
+__global__ __launch_bounds__(BS) void k_cgs_step(Cols cl, int m, int j, double tol, VT *__restrict__ Vall,
                                                     const double2 *__restrict__ Wall, Partials pp,
                                                     double2 *__restrict__ Hall,
                                                     double *__restrict__ csall, double2 *__restrict__ snall,
                                                     double2 *__restrict__ gall, ColStat *__restrict__ st)
 {
-    const int r = blockIdx.x;
-    if (st[r].done) return;
+    constexpr int KR = BS <= 512 ? 32 : 8;
+    const int r = blockIdx.x, done = st[r].done;
     const int64_t N = cl.len(r), e = threadIdx.x;
     const int nc = int((N + AB - 1) / AB), t = threadIdx.x, c = t / AB, lane = t & 63, wave = (t >> 6) & 3;
     VT *V = Vall + cl.vo(r);
-    constexpr int NCH = SMALL / AB;
+    VT vr[KR];
+#pragma unroll
+    for (int i = 0; i < KR; ++i) vr[i] = VT{};
+    if (e < N)
+#pragma unroll
+        for (int g = 0; g < KR; g += 8)
+            if (g <= j)   // entries beyond j are read as j's and not used
+#pragma unroll
+                for (int i = g; i < g + 8; ++i) vr[i] = V[int64_t(min(i, j)) * N + e];
+    if (done) return;
+    constexpr int NCH = BS / AB;
     __shared__ double2 red[NCH][MAXM + 8][AB / 64];
     __shared__ double2 h[MAXM + 1], Hc[MAXM + 2], sn[MAXM];
     __shared__ double rn[NCH][AB / 64], cs[MAXM], s_sum[2];
@@ -725,25 +736,21 @@ __global__ __launch_bounds__(SMALL) void k_cgs_step(Cols cl, int m, int j, doubl
         }
     };
     auto dots = [&]() {   // h = V_{0..j}^H w, to be read after a barrier
-        constexpr int NG = 2;
-        for (int k0 = 0; k0 <= j; k0 += 8 * NG) {
-            VT vv[NG][8];
+        auto group = [&](const VT *v, int k0) {
+            double2 p[8];
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
+            for (int i = 0; i < 8; ++i) p[i] = cmulc(ld2(v[i]), w);
+            wave_sum8(p);
+            if ((lane & 7) == 0) red[c][k0 + (lane >> 3)][wave] = p[0];
+        };
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int k = k0 + 8 * g + i;
-                    vv[g][i] = (e < N && k <= j) ? V[int64_t(k) * N + e] : VT{};
-                }
+        for (int k0 = 0; k0 < KR; k0 += 8)
+            if (k0 <= j) group(vr + k0, k0);
+        for (int k0 = KR; k0 <= j; k0 += 8) {
+            VT v[8];
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                if (k0 + 8 * g > j) break;
-                double2 p[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) p[i] = cmulc(ld2(vv[g][i]), w);
-                wave_sum8(p);
-                if ((lane & 7) == 0) red[c][k0 + 8 * g + (lane >> 3)][wave] = p[0];
-            }
+            for (int i = 0; i < 8; ++i) v[i] = (e < N && k0 + i <= j) ? V[int64_t(k0 + i) * N + e] : VT{};
+            group(v, k0);
         }
         __syncthreads();
         for (int k = t; k <= j; k += blockDim.x) {
@@ -758,18 +765,28 @@ __global__ __launch_bounds__(SMALL) void k_cgs_step(Cols cl, int m, int j, doubl
         }
     };
     auto update = [&]() {   // w -= V_{0..j} h, in ascending k
-        constexpr int KB = 16;
-        for (int k0 = 0; k0 <= j; k0 += KB) {
-            VT vv[KB];
+        auto term = [&](const VT &v, int k) {
+            const double2 p = cmul(ld2(v), h[k]);
+            w.x -= p.x;
+            w.y -= p.y;
+        };
 #pragma unroll
-            for (int i = 0; i < KB; ++i) vv[i] = (e < N && k0 + i <= j) ? V[int64_t(k0 + i) * N + e] : VT{};
+        for (int k0 = 0; k0 < KR; k0 += 8) {   // no branch within a group: its reads of h go out together
+            if (k0 > j) break;
 #pragma unroll
-            for (int i = 0; i < KB; ++i) {
-                if (k0 + i > j) break;
-                const double2 p = cmul(ld2(vv[i]), h[k0 + i]);
-                w.x -= p.x;
-                w.y -= p.y;
+            for (int k = k0; k < k0 + 8; ++k) {
+                const double2 p = cmul(ld2(vr[k]), h[k]);
+                w.x = k <= j ? w.x - p.x : w.x;
+                w.y = k <= j ? w.y - p.y : w.y;
             }
+        }
+        for (int k0 = KR; k0 <= j; k0 += 8) {
+            VT v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = (e < N && k0 + i <= j) ? V[int64_t(k0 + i) * N + e] : VT{};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (k0 + i <= j) term(v[i], k0 + i);
         }
     };
     norm();
@@ -779,6 +796,7 @@ __global__ __launch_bounds__(SMALL) void k_cgs_step(Cols cl, int m, int j, doubl
     const double w2 = s_sum[0];
     if (t == 0) {
         double h2 = 0.0;
+#pragma unroll 8
         for (int k = 0; k <= j; ++k) h2 += h[k].x * h[k].x + h[k].y * h[k].y;
         s_reorth = (w2 - h2) < 0.5 * w2;
     }
@@ -802,9 +820,13 @@ __global__ __launch_bounds__(SMALL) void k_cgs_step(Cols cl, int m, int j, doubl
         const double inv = 1.0 / hn;
         V[int64_t(j + 1) * N + e] = st2<VT>(make_double2(w.x * inv, w.y * inv));
     }
-    if (t != 0) return;
-    st[r].reorth = reorth;
-    givens_update(m, j, tol, hn, w2, r, Hc, cs, sn, Hall, csall, snall, gall, st[r]);
+    if (t >= 64) return;
+    if (t == 0) {
+        st[r].reorth = reorth;
+        givens_update(m, j, tol, hn, w2, r, Hc, cs, sn, csall, snall, gall, st[r]);
+    }
+    __threadfence_block();   // the first wave's own LDS writes
+    for (int i = t; i <= j + 1; i += 64) Hall[(int64_t(r) * m + j) * (m + 1) + i] = Hc[i];
 }
 
 // Upper-triangular solve H y = g for the iterations of the cycle: one block
@@ -1134,8 +1156,12 @@ static void arnoldi_step(Workspace *w, const Cols &cl, int64_t Nmax, VT *V, int 
     if (Nmax <= SMALL) {   // faster for one column and for many (ms a solve, four launches / one: 648 unknowns,
                            // 1 column 14.2 / 12.1, 512 columns 168 / 160; 162: 4.2 / 3.2 and 14.3 / 12.1)
         const unsigned threads = unsigned((Nmax + AB - 1) / AB * AB);
-        hipLaunchKernelGGL(k_cgs_step<VT>, dim3(unsigned(R)), dim3(threads), 0, s, cl, m, j, tol, V, w->W, pp, w->H,
-                           w->cs, w->sn, w->g, w->st);
+        auto step = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(unsigned(R)), dim3(threads), 0, s, cl, m, j, tol, V, w->W, pp, w->H, w->cs,
+                               w->sn, w->g, w->st);
+        };
+        if (threads <= 512) step(k_cgs_step<VT, 512>);
+        else step(k_cgs_step<VT, SMALL>);
         BIE_HIP(hipGetLastError());
         return;
     }
