@@ -93,9 +93,10 @@ void prof_read(int kernel, int64_t *launches, double *total_ms, int64_t *columns
 
 namespace {
 
-// Tiles per unit of the single-operator tile pass, one unit per block: 8, and fewer
-// where that would leave less than 1.5 blocks per CU, for a small matrix is bound
-// by how many CUs read it (product of one FP64 vector, units of 1 / 2 / 4 / 8 / 16
+// Tiles per unit of the single-operator tile pass, one unit per block: 16 from 208
+// blocks of them on (5202 unknowns, six vectors with units of 8 / 16 / 32: 92 / 83 / 87 us),
+// else 8, and fewer where that would leave less than 1.5 blocks per CU, for a small matrix
+// is bound by how many CUs read it (product of one FP64 vector, units of 1 / 2 / 4 / 8 / 16
 // tiles and balanced runs: 450 unknowns 7.0 / 7.9 / 9.4 / 12.5 / 12.6 / 19.7 us, 1152
 // 8.6 / 9.8 / 12.6 / 18.1 / 29.2 / 25.7, 2592 17.3 / 14.7 / 15.5 / 20.6 / 32.2 / 27.9, 3528
 // 27.6 / 25.2 / 22.5 / 23.9 / 34.3 / 29.9, 5202 51.0 / 44.8 / 43.2 / 43.2 / 42.5 / 45.9).
@@ -108,8 +109,10 @@ int unit_tiles(int64_t nT)
         return e ? (u >= 0 && u <= 64 ? u : 8) : -1;
     }();
     if (env >= 0) return env;
+    const int64_t tiles = nT * (nT + 1) / 2;
+    if (tiles >= 208 * 16) return 16;
     int u = 8;
-    while (u > 1 && nT * (nT + 1) / 2 < 384 * u) u /= 2;
+    while (u > 1 && tiles < 384 * u) u /= 2;
     return u;
 }
 
@@ -1275,14 +1278,14 @@ void tune_packed(bie_op *op, hipStream_t s)
             const int def = unit_tiles((N + TB - 1) / TB);
             v = { def };
             // below the rule's 8 tiles a launch is some microseconds: its neighbours, and more launches
-            const std::vector<int> cand = def == 8 ? std::vector<int>{ 8, 0, 4, 16 }
+            const std::vector<int> cand = def >= 8 ? std::vector<int>{ def, 24 - def, 0, 4 }
                                                    : std::vector<int>{ def, 2 * def, std::max(1, def / 2) };
             for (int U : cand) {
                 Packed c;
                 try {
                     packed_setup_units(c, N, U);
                     ensure_part(c, 1, s);
-                    const float ms = time_launches(s, def == 8 ? 3 : 20, [&]() {
+                    const float ms = time_launches(s, def >= 8 ? 10 : 20, [&]() {
                         if (mat64)
                             launch_product<double, double, false, false>(c, c.part, Z, x, N, y, N, nullptr, 0, 1,
                                                                          nullptr, 1, s, false);
@@ -1290,7 +1293,7 @@ void tune_packed(bie_op *op, hipStream_t s)
                             launch_product<float, double, false, false>(c, c.part, Z, x, N, y, N, nullptr, 0, 1,
                                                                         nullptr, 1, s, false);
                     });
-                    if (best == 0.f || ms < best) {
+                    if (best == 0.f || ms < 0.97f * best) {   // the rule's unless clearly slower
                         best = ms;
                         v = { U };
                     }
