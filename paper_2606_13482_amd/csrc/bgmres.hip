@@ -1003,17 +1003,29 @@ __global__ __launch_bounds__(256, BasisRaw<AT>::MINB) void k_bcomb_bd(const CIte
             oi = mfma_bf(ail, fh[ks], oi);
         }
     }
-    if (!nlive) return;
+    // The outputs' old values from clamped places without a condition (a load under one is
+    // waited for on the spot), two at a time: more spill at four waves per SIMD.
     double2 *out = static_cast<double2 *>(it.out);
+    const int64_t nc = nlive ? nn : N - 1;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int b = 8 * (q >> 2) + 4 * h + (q & 3);
-        if (b < it.nb) {
-            const int64_t ob = int64_t(it.ocol ? it.ocol[b] : b) * N;
-            double2 y = make_double2(it.alpha * double(orr[q]), it.alpha * double(oi[q]));
-            if (it.beta != 0.0) y = cadd(y, cscale(it.beta, out[ob + nn]));
-            out[ob + nn] = y;
+    for (int q0 = 0; q0 < 16; q0 += 2) {
+        int64_t ob[2];
+        double2 y[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int b = min(8 * (q0 >> 2) + 4 * h + (q0 & 3) + u, it.nb - 1);
+            ob[u] = int64_t(it.ocol ? it.ocol[b] : b) * N + nc;
         }
+        if (it.beta != 0.0)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) y[u] = ld_global(out, ob[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (nlive && 8 * (q0 >> 2) + 4 * h + (q0 & 3) + u < it.nb) {
+                double2 v = make_double2(it.alpha * double(orr[q0 + u]), it.alpha * double(oi[q0 + u]));
+                if (it.beta != 0.0) v = cadd(v, cscale(it.beta, y[u]));
+                out[ob[u]] = v;
+            }
     }
 }
 
@@ -1043,30 +1055,31 @@ __global__ __launch_bounds__(256) void k_bcomb64(const CItem *__restrict__ items
     for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int q = 0; q < 4; ++q) orr[c][q] = oi[c][q] = 0.0;
+    // all operands of the item's K <= 32 issued first, without conditions (see k_bcomb_bd)
     double2 a[8], b[8][2];
+    const int64_t nc = min(nrow, N - 1);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {   // all operands of the item's K <= 32 issued first
-        const int k = 4 * ks + lk;
-        const bool kl = k < it.K;
-        a[ks] = (kl && nrow < N) ? ld_global(A, (int64_t(k / it.ar) * it.astride + k % it.ar) * N + nrow)
-                                 : make_double2(0.0, 0.0);
+    for (int ks = 0; ks < 8; ++ks) {
+        const int k = min(4 * ks + lk, it.K - 1);
+        a[ks] = ld_global(A, (int64_t(k / it.ar) * it.astride + k % it.ar) * N + nc);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int col = 16 * c + li;
-            b[ks][c] = (kl && col < it.nb && !(UPPER && c == 0 && ks >= 4)) ? ld_global(it.C, int64_t(k) * it.ldc + col)
-                                                                             : make_double2(0.0, 0.0);
-        }
+        for (int c = 0; c < 2; ++c)
+            if (!(UPPER && c == 0 && ks >= 4)) b[ks][c] = ld_global(it.C, int64_t(k) * it.ldc + min(16 * c + li, it.nb - 1));
     }
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
+    for (int ks = 0; ks < 8; ++ks) {
+        const bool kl = 4 * ks + lk < it.K;   // zeros beyond K; rows and columns beyond N, nb are not stored
+        const double ax = kl ? a[ks].x : 0.0, ay = kl ? a[ks].y : 0.0;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             if (UPPER && c == 0 && ks >= 4) continue;
-            orr[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks].x, b[ks][c].x, orr[c], 0, 0, 0);
-            orr[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[ks].y, b[ks][c].y, orr[c], 0, 0, 0);
-            oi[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks].x, b[ks][c].y, oi[c], 0, 0, 0);
-            oi[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks].y, b[ks][c].x, oi[c], 0, 0, 0);
+            const double bx = kl ? b[ks][c].x : 0.0, by = kl ? b[ks][c].y : 0.0;
+            orr[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ax, bx, orr[c], 0, 0, 0);
+            orr[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ay, by, orr[c], 0, 0, 0);
+            oi[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ax, by, oi[c], 0, 0, 0);
+            oi[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ay, bx, oi[c], 0, 0, 0);
         }
+    }
     OT *out = static_cast<OT *>(it.out);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {

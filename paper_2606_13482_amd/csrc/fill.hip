@@ -643,11 +643,19 @@ __global__ __launch_bounds__(256) void k_far_out(int64_t nm, int64_t ld, int64_t
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;   // each wave a quarter of the splits
     const int64_t mo = int64_t(blockIdx.x) * 64 + lane, r = blockIdx.y, R = gridDim.y, q = (splits + 3) / 4;
     double f[6] = { 0, 0, 0, 0, 0, 0 };
-    if (mo < nm)
-#pragma unroll 4
-        for (int64_t z = w * q; z < min(splits, (w + 1) * q); ++z)
+    const double *p = part + r * 6 * nm + min(mo, nm - 1);
+    const int64_t z1 = min(splits, (w + 1) * q);
+    for (int64_t z = w * q; z < z1; z += 4) {   // four splits' loads at a time, beyond the last from the last
+        double v[4][6];
 #pragma unroll
-            for (int c = 0; c < 6; ++c) f[c] += part[((z * R + r) * 6 + c) * nm + mo];
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) v[u][c] = p[(min(z + u, z1 - 1) * R * 6 + c) * nm];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) f[c] += z + u < z1 ? v[u][c] : 0.0;
+    }
     if (w)
         for (int c = 0; c < 6; ++c) red[w - 1][c][lane] = f[c];
     __syncthreads();

@@ -162,14 +162,17 @@ __global__ __launch_bounds__(256) void k_split_vectors(const XT *__restrict__ X,
     slot_owner(threadIdx.x & 63, r, h);
     const int64_t c = (tile / nst) * 32 + r, n0 = (tile % nst) * 8 + h * 4;
     const bool live = c < 2 * R;
-    const int64_t v = live ? (cols ? int64_t(cols[c >> 1]) : (c >> 1)) : 0;
+    const int64_t cv = min(c >> 1, R - 1), v = cols ? int64_t(cols[cv]) : cv;
+    XT xs[4];   // all four loads go out before any is used
+#pragma unroll
+    for (int e = 0; e < 4; ++e) xs[e] = X[v * ldx + min(n0 + e, N - 1)];
     bf16x8 hi, lw;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int64_t n = n0 + e;
         float a = 0.f, b = 0.f;
+        const XT x = xs[e];
         if (live && n < N) {
-            const XT x = X[v * ldx + n];
             if (!(c & 1)) { a = float(x.x); b = float(-x.y); }
             else { a = float(x.y); b = float(x.x); }
         }
@@ -469,12 +472,15 @@ __global__ __launch_bounds__(256) void k_gemm64(const double *__restrict__ A, in
     // staging: A 128 x 16 doubles = 1024 double2 (4 per thread); X 64 rhs x 8
     // complex = 512 double2 (2 per thread)
     double2 ra[4], rx[2];
-    int64_t xv[2];   // vector index of the two right-hand sides this thread stages (-1: padding)
+    const double2 *xp[2];   // the two right-hand sides this thread stages (the last one beyond R)
+    bool live[2];           // what rx holds is an entry, not padding
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const int64_t r = r0 + (tid + 256 * q) / 8;
-        xv[q] = r < R ? (cols ? int64_t(cols[r]) : r) : -1;
+        const int64_t r = min(r0 + (tid + 256 * q) / 8, R - 1);
+        xp[q] = X + (cols ? int64_t(cols[r]) : r) * ldx;
     }
+    // every load is made, from a clamped place where there is nothing to load: a load under a
+    // condition is waited for on the spot, twice a stage
     auto gload = [&](int64_t k0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -484,7 +490,8 @@ __global__ __launch_bounds__(256) void k_gemm64(const double *__restrict__ A, in
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int64_t n = k0 / 2 + (tid + 256 * q) % 8;
-            rx[q] = (xv[q] >= 0 && n < N) ? X[xv[q] * ldx + n] : make_double2(0.0, 0.0);
+            rx[q] = xp[q][min(n, N - 1)];
+            live[q] = n < N && r0 + (tid + 256 * q) / 8 < R;
         }
     };
     auto lstore = [&](int buf) {
@@ -497,10 +504,11 @@ __global__ __launch_bounds__(256) void k_gemm64(const double *__restrict__ A, in
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int c = tid + 256 * q, rl = c / 8, nl = c % 8;
-            sB[buf][2 * rl][2 * nl] = rx[q].x;
-            sB[buf][2 * rl][2 * nl + 1] = -rx[q].y;
-            sB[buf][2 * rl + 1][2 * nl] = rx[q].y;
-            sB[buf][2 * rl + 1][2 * nl + 1] = rx[q].x;
+            const double re = live[q] ? rx[q].x : 0.0, im = live[q] ? rx[q].y : 0.0;
+            sB[buf][2 * rl][2 * nl] = re;
+            sB[buf][2 * rl][2 * nl + 1] = -im;
+            sB[buf][2 * rl + 1][2 * nl] = im;
+            sB[buf][2 * rl + 1][2 * nl + 1] = re;
         }
     };
 

@@ -181,10 +181,10 @@ __device__ __forceinline__ void sgemm_tile(const Gemm &g, int bx, int by, GemmLd
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int e = lane + 64 * j, hi = e >> 5, lo = e & 31;
-            if (TA) ra[j] = (m0 + lo < M && kc + hi < K) ? A[int64_t(kc + hi) * lda + m0 + lo] : 0.f;
-            else ra[j] = (m0 + hi < M && kc + lo < K) ? A[int64_t(m0 + hi) * lda + kc + lo] : 0.f;
-            if (TB) rb[j] = (n0 + hi < N && kc + lo < K) ? Bm[int64_t(n0 + hi) * ldb + kc + lo] : 0.f;
-            else rb[j] = (n0 + lo < N && kc + hi < K) ? Bm[int64_t(kc + hi) * ldb + n0 + lo] : 0.f;
+            // unconditional, from clamped places: a load under a condition is waited for on the spot
+            const int kh = min(kc + hi, K - 1), kl = min(kc + lo, K - 1);
+            ra[j] = TA ? A[int64_t(kh) * lda + min(m0 + lo, M - 1)] : A[int64_t(min(m0 + hi, M - 1)) * lda + kl];
+            rb[j] = TB ? Bm[int64_t(min(n0 + hi, N - 1)) * ldb + kl] : Bm[int64_t(kh) * ldb + min(n0 + lo, N - 1)];
         }
     };
     load(0);
@@ -192,10 +192,12 @@ __device__ __forceinline__ void sgemm_tile(const Gemm &g, int bx, int by, GemmLd
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int e = lane + 64 * j, hi = e >> 5, lo = e & 31;
-            if (TA) L.A[w][hi][lo] = ra[j];
-            else L.A[w][lo][hi] = ra[j];
-            if (TB) L.B[w][lo][hi] = rb[j];
-            else L.B[w][hi][lo] = rb[j];
+            const int kc = it * 128 + w * 32;   // zeros beyond K (rows beyond M, N only reach outputs not stored)
+            const float a = kc + (TA ? hi : lo) < K ? ra[j] : 0.f, b = kc + (TB ? lo : hi) < K ? rb[j] : 0.f;
+            if (TA) L.A[w][hi][lo] = a;
+            else L.A[w][lo][hi] = a;
+            if (TB) L.B[w][lo][hi] = b;
+            else L.B[w][hi][lo] = b;
         }
         __syncthreads();
         if (it + 1 < nit) load(it + 1);
@@ -210,25 +212,31 @@ __device__ __forceinline__ void sgemm_tile(const Gemm &g, int bx, int by, GemmLd
         for (int q = 0; q < 16; ++q) L.red[w - 1][q][lane] = acc[q];
     __syncthreads();
     if (w != 0) return;
+    // the epilogue's operands first, all at once
+    const int n = n0 + (lane & 31), nc = min(n, N - 1);
+    const bool with_bias = g.epi == EPI_BIAS_TANH || g.epi == EPI_BIAS || g.epi == EPI_MSE;
+    const float bias = with_bias ? g.bias[nc] : 0.f;
+    float x[16];
+    if (g.epi == EPI_TANH_BACK || g.epi == EPI_MSE)
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            x[q] = g.X[int64_t(min(m0 + 8 * (q / 4) + 4 * (lane / 32) + q % 4, M - 1)) * g.ldc + nc];
     double se = 0.0;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const float v = ((acc[q] + L.red[0][q][lane]) + L.red[1][q][lane]) + L.red[2][q][lane];
-        const int m = m0 + 8 * (q / 4) + 4 * (lane / 32) + q % 4, n = n0 + (lane & 31);
-        if (m >= M || n >= N) continue;
-        const int64_t at = int64_t(m) * g.ldc + n;
+        const int m = m0 + 8 * (q / 4) + 4 * (lane / 32) + q % 4;
+        const bool in = m < M && n < N;
         float o = v;
-        if (g.epi == EPI_BIAS_TANH) o = tanhf(v + g.bias[n]);
-        else if (g.epi == EPI_BIAS) o = v + g.bias[n];
-        else if (g.epi == EPI_TANH_BACK) {
-            const float a = g.X[at];
-            o = v * (1.f - a * a);
-        } else if (g.epi == EPI_MSE) {
-            const float d = (v + g.bias[n]) - g.X[at];
+        if (g.epi == EPI_BIAS_TANH) o = tanhf(v + bias);
+        else if (g.epi == EPI_BIAS) o = v + bias;
+        else if (g.epi == EPI_TANH_BACK) o = v * (1.f - x[q] * x[q]);
+        else if (g.epi == EPI_MSE) {
+            const float d = (v + bias) - x[q];
             o = 2.f * d * g.inv;
-            se += double(d) * double(d);
+            if (in) se += double(d) * double(d);
         }
-        g.C[at] = o;
+        if (in) g.C[int64_t(m) * g.ldc + n] = o;
     }
     if (g.epi == EPI_MSE) {
         for (int o = 32; o > 0; o >>= 1) se += __shfl_xor(se, o);
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(256) void k_sgemm_mf(Gemm g)
 // The three products that a layer's dZ enters, in one launch (each of a few
 // microseconds and a hundred or two blocks: launched one after the other they left
 // the GPU idle between and within them; 256 x 512 x 512: 27 us in three launches,
-// 15 in one): dX = (dZ W) (1 - X^2) of the layer below, dW = dZ^T X, and db,
+// 12 in one): dX = (dZ W) (1 - X^2) of the layer below, dW = dZ^T X, and db,
 // the column sums of dZ (64 columns per block, its wave v summing rows v', v' + 16, ..
 // for the four v' = v + 4 i, the 16 partial sums added in order).
 __global__ __launch_bounds__(256) void k_mlp_back(Gemm dx, Gemm dw, int ndx, int Bn, int O, const float *__restrict__ dZ,
