@@ -727,6 +727,7 @@ __global__ __launch_bounds__(256) void k_ml_map(int nin, int nout, const typenam
     for (int32_t t = t0; t < t1; ++t) {
         const int64_t ib = ptr ? box[t] : ob;
         const int bt = bits ? bits[t] : 0;
+        const bool add = acc || t > t0;
         const El *Px = (bt & 4) ? m1 : m0, *Py = (bt & 2) ? m1 : m0, *Pz = (bt & 1) ? m1 : m0;
         const double2 *src = in + (ib * 4 + d) * int64_t(n2) * nin;
         __syncthreads();   // the previous entry's planes are read
@@ -763,7 +764,14 @@ __global__ __launch_bounds__(256) void k_ml_map(int nin, int nout, const typenam
         __syncthreads();
         for (int c0 = w * BG; c0 < nout; c0 += 4 * BG)   // along z: lanes (plane, y)
             for (int e = lane; e < na * nout; e += 64) {
-                double2 s[BG];
+                // what an earlier entry or pass left, asked for before the sums (the entry's own
+                // lane wrote it): the loads pass during the sums instead of one by one behind them
+                // (maps with real matrices, 30720 functions: 64.8 -> 60.4 us, the same bits)
+                double2 s[BG], o[BG];
+                double2 *to = dst + int64_t(e) * nout;
+                if (add)
+#pragma unroll
+                    for (int g = 0; g < BG; ++g) o[g] = to[min(c0 + g, nout - 1)];
 #pragma unroll
                 for (int g = 0; g < BG; ++g) s[g] = make_double2(0.0, 0.0);
 #pragma unroll 4
@@ -774,14 +782,8 @@ __global__ __launch_bounds__(256) void k_ml_map(int nin, int nout, const typenam
                 }
 #pragma unroll
                 for (int g = 0; g < BG; ++g)
-                    if (c0 + g < nout) {   // the entry's own lane: the next t adds to it
-                        double2 *o = dst + int64_t(e) * nout + c0 + g;
-                        if (acc || t > t0) {
-                            s[g].x += o->x;
-                            s[g].y += o->y;
-                        }
-                        *o = s[g];
-                    }
+                    if (c0 + g < nout)
+                        to[c0 + g] = add ? make_double2(s[g].x + o[g].x, s[g].y + o[g].y) : s[g];
             }
     }
 }
