@@ -1416,14 +1416,16 @@ void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64
     if (op->star) throw Error(BIE_EINVAL, "the allocation-free product takes an assembled operator");
     const Packed &pk = op->pk;
     // The short units of a small matrix take up to twice the partial slots of long ones: such
-    // a call is judged by units of 16 tiles and, where its own do not fit, made in several passes.
+    // a call is judged by units of 16 tiles and, where its own do not fit, made in several passes,
+    // each of one vector at least: units fixed too short for a large matrix are refused.
     int64_t slots = pk.nslots;
     if (unit_tiles(pk.nT) < 8) {
         int64_t most = pk.nT * (pk.nT - 1) / 2;
         for (int64_t I = 0; I < pk.nT; ++I) most += (pk.nT - I + 15) / 16;
         slots = std::min(slots, most);
     }
-    const size_t per = TB * (vec64 ? 16 : 8), need = size_t(R) * size_t(slots) * per;
+    const size_t per = TB * (vec64 ? 16 : 8), one = size_t(pk.nslots) * per,
+                 need = std::max(size_t(R) * size_t(slots) * per, one);
     if (need > NOALLOC_SCRATCH_BYTES)
         throw Error(BIE_EINVAL, "partial sums of " + std::to_string(need) + " bytes exceed the " +
                                     std::to_string(NOALLOC_SCRATCH_BYTES) + "-byte scratch of the allocation-free "
@@ -1434,7 +1436,7 @@ void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64
     if (vec64 ? !op->Z64 && !op->Z32 : !op->Z32)
         throw Error(BIE_EINVAL, vec64 ? "no packed matrix stored" : "complex64 vectors need the FP32 matrix");
     void *part = noalloc_scratch(dev);
-    const int64_t pass = std::max<int64_t>(1, int64_t(NOALLOC_SCRATCH_BYTES / (size_t(pk.nslots) * per)));
+    const int64_t pass = int64_t(NOALLOC_SCRATCH_BYTES / one);
     const size_t vec = size_t(pk.N) * (vec64 ? 16 : 8);
     for (int64_t r0 = 0; r0 < R; r0 += pass) {
         const int64_t n = std::min(pass, R - r0);
