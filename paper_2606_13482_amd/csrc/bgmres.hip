@@ -2115,9 +2115,8 @@ struct Aux {
     {
         BIE_HIP(hipStreamCreateWithFlags(&s2, hipStreamNonBlocking));
         BIE_HIP(hipStreamCreateWithFlags(&s3, hipStreamNonBlocking));
-        // ev[0] orders two streams of the device only: no fence to the host with it
-        for (int i = 0; i < 7; ++i)
-            BIE_HIP(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming | (i ? 0 : hipEventDisableSystemFence)));
+        // with their fences: ev[0] also orders table copies from the host before the second stream's reads
+        for (auto &e : ev) BIE_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
     ~Aux()
     {
