@@ -28,6 +28,7 @@ struct Block {
     void *p;
     size_t bytes;
     int device;
+    size_t limit;   // of the kept blocks on its device
     Clock::time_point since;
 };
 struct State {
@@ -42,12 +43,14 @@ State &state()   // never destroyed: blocks may outlive static objects
     return *s;
 }
 
+// the limit of device, which is current: asked when a block is taken, for it may be
+// given up while another device is
 size_t limit_of(State &st, int device)
 {
     const auto it = st.limit.find(device);
     if (it != st.limit.end()) return it->second;
     size_t free = 0, total = 0;
-    if (hipMemGetInfo(&free, &total) != hipSuccess) total = 0;
+    if (hipMemGetInfo(&free, &total) != hipSuccess) return 0;
     return st.limit[device] = std::min(LARGEST, total / 64);
 }
 
@@ -114,7 +117,7 @@ hipError_t pool_get(void **p, size_t bytes)
     const hipError_t e2 = device_malloc(p, bytes);
     if (e2 != hipSuccess) return e2;
     std::lock_guard<std::mutex> lk(st.mu);
-    st.used[*p] = Block{ *p, bytes, device, Clock::now() };
+    st.used[*p] = Block{ *p, bytes, device, limit_of(st, device), Clock::now() };
     return hipSuccess;
 }
 
@@ -127,19 +130,18 @@ void pool_put(void *p)
         std::lock_guard<std::mutex> lk(st.mu);
         const auto it = st.used.find(p);
         if (it == st.used.end()) {
-            out.push_back(Block{ p, 0, 0, {} });
+            out.push_back(Block{ p, 0, 0, 0, {} });
         } else {
             Block b = it->second;
             st.used.erase(it);
             b.since = Clock::now();
-            const size_t limit = limit_of(st, b.device);
-            if (b.bytes > limit) {
+            if (b.bytes > b.limit) {
                 out.push_back(b);
             } else {
                 st.kept.push_back(b);
                 size_t sum = 0;
                 for (const Block &k : st.kept) sum += k.device == b.device ? k.bytes : 0;
-                for (size_t i = 0; i < st.kept.size() && sum > limit;) {
+                for (size_t i = 0; i < st.kept.size() && sum > b.limit;) {
                     if (st.kept[i].device != b.device) {
                         ++i;
                         continue;

@@ -1,0 +1,99 @@
+"""The kept device blocks (pool.cpp) on the CPU: the file is built with a driver that stands
+in for the HIP runtime's allocator, two devices of different size, and counts what is
+allocated on each."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+DRIVER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <new>
+#include <thread>
+#include <chrono>
+#include "bie_internal.hpp"
+
+static const size_t MiB = size_t(1) << 20, GiB = size_t(1) << 30;
+static int current = 0;
+static const size_t total[2] = { 64 * GiB, 640 * GiB };   // 1/64 of them: 1 and 10 GiB
+static std::map<void *, std::pair<int, size_t>> live;
+static size_t held[2] = { 0, 0 };
+static size_t next = size_t(1) << 40;
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = current; return hipSuccess; }
+hipError_t hipMemGetInfo(size_t *f, size_t *t) { *t = total[current]; *f = *t - held[current]; return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n)
+{
+    if (held[current] + n > total[current]) return hipErrorOutOfMemory;
+    *p = reinterpret_cast<void *>(next);   // an address that nothing dereferences
+    next += n;
+    live[*p] = { current, n };
+    held[current] += n;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    const auto it = live.find(p);
+    if (it == live.end()) { std::printf("free of what is not allocated\n"); std::exit(3); }
+    held[it->second.first] -= it->second.second;
+    live.erase(it);
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return ""; }
+}
+
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); std::exit(1); } } while (0)
+static void *get(size_t n) { void *p = nullptr; CHECK(bie::pool_get(&p, n) == hipSuccess && p); return p; }
+
+// a block given up while another device is current: judged by its own device's limit
+static void other_device()
+{
+    current = 1;
+    void *a = get(3 * GiB);
+    current = 0;
+    bie::pool_put(a);
+    CHECK(held[1] == 3 * GiB);          // 4 GiB on the large device
+    void *b = get(2 * GiB);
+    current = 1;
+    bie::pool_put(b);
+    CHECK(held[0] == 0);                // 1 GiB on the small one
+}
+
+int main(int, char **argv)
+{
+    const std::string what = argv[1];
+    if (what == "other_device") other_device();
+    else return 2;
+    std::printf("ok\n");
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not os.path.exists(CLANG):
+        pytest.skip("ROCm clang++ not available")
+    d = tmp_path_factory.mktemp("pool")
+    src, exe = d / "drv.cpp", d / "drv"
+    src.write_text(DRIVER)
+    csrc = os.path.join(ROOT, "paper_2606_13482_amd", "csrc")
+    subprocess.run([CLANG, "-std=c++17", "-O1", "-g", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + csrc, str(src), os.path.join(csrc, "pool.cpp"), "-o",
+                    str(exe)], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("what", ["other_device"])
+def test_kept_blocks(driver, what):
+    p = subprocess.run([str(driver), what], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout + p.stderr
