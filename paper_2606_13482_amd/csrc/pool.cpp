@@ -10,9 +10,9 @@
 // seconds are released at the next request or return, and all are released when an
 // allocation of the library fails, before it is tried again.
 #include <chrono>
+#include <list>
 #include <mutex>
 #include <unordered_map>
-#include <vector>
 
 #include "bie_internal.hpp"
 
@@ -31,10 +31,13 @@ struct Block {
     size_t limit;   // of the kept blocks on its device
     Clock::time_point since;
 };
+typedef std::list<Block> Blocks;
+// A block stays in the list node that was made for it: giving one up moves nodes and
+// takes no host memory.
 struct State {
     std::mutex mu;
-    std::unordered_map<void *, Block> used;
-    std::vector<Block> kept;   // oldest first
+    Blocks used, kept;   // kept: oldest first
+    std::unordered_map<void *, Blocks::iterator> at;   // the used ones
     std::unordered_map<int, size_t> limit;
 };
 State &state()   // never destroyed: blocks may outlive static objects
@@ -54,18 +57,25 @@ size_t limit_of(State &st, int device)
     return st.limit[device] = std::min(LARGEST, total / 64);
 }
 
-void release(const std::vector<Block> &bs)
+void release(const Blocks &bs)
 {
     for (const Block &b : bs) (void)hipFree(b.p);
 }
 
-// takes out of kept what has been idle too long
-void take_idle(State &st, std::vector<Block> &out)
+// moves the kept blocks that f names to out
+template <typename F>
+void take(State &st, Blocks &out, F f)
+{
+    for (auto it = st.kept.begin(); it != st.kept.end();) {
+        const auto b = it++;
+        if (f(*b)) out.splice(out.end(), st.kept, b);
+    }
+}
+
+void take_idle(State &st, Blocks &out)
 {
     const Clock::time_point now = Clock::now();
-    std::vector<Block> left;
-    for (const Block &b : st.kept) (now - b.since > IDLE ? out : left).push_back(b);
-    st.kept.swap(left);
+    take(st, out, [&](const Block &b) { return now - b.since > IDLE; });
 }
 
 }  // namespace
@@ -75,11 +85,10 @@ bool pool_release()
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return false;
     State &st = state();
-    std::vector<Block> out, left;
+    Blocks out;
     {
         std::lock_guard<std::mutex> lk(st.mu);
-        for (const Block &b : st.kept) (b.device == device ? out : left).push_back(b);
-        st.kept.swap(left);
+        take(st, out, [&](const Block &b) { return b.device == device; });
     }
     release(out);
     return !out.empty();
@@ -93,22 +102,19 @@ hipError_t pool_get(void **p, size_t bytes)
     const hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return e;
     State &st = state();
-    std::vector<Block> idle;
+    Blocks idle;
     *p = nullptr;
     {
         std::lock_guard<std::mutex> lk(st.mu);
-        size_t best = st.kept.size();
-        for (size_t i = 0; i < st.kept.size(); ++i) {
-            const Block &b = st.kept[i];
-            if (b.device == device && b.bytes >= bytes && b.bytes - bytes <= bytes / 4 &&
-                (best == st.kept.size() || b.bytes < st.kept[best].bytes))
-                best = i;
-        }
-        if (best < st.kept.size()) {
-            const Block b = st.kept[best];
-            st.used[b.p] = b;
-            st.kept.erase(st.kept.begin() + int64_t(best));
-            *p = b.p;
+        auto best = st.kept.end();
+        for (auto b = st.kept.begin(); b != st.kept.end(); ++b)
+            if (b->device == device && b->bytes >= bytes && b->bytes - bytes <= bytes / 4 &&
+                (best == st.kept.end() || b->bytes < best->bytes))
+                best = b;
+        if (best != st.kept.end()) {
+            st.at.emplace(best->p, best);
+            st.used.splice(st.used.end(), st.kept, best);
+            *p = best->p;
         }
         take_idle(st, idle);
     }
@@ -117,7 +123,9 @@ hipError_t pool_get(void **p, size_t bytes)
     const hipError_t e2 = device_malloc(p, bytes);
     if (e2 != hipSuccess) return e2;
     std::lock_guard<std::mutex> lk(st.mu);
-    st.used[*p] = Block{ *p, bytes, device, limit_of(st, device), Clock::now() };
+    Blocks one(1, Block{ *p, bytes, device, limit_of(st, device), Clock::now() });
+    st.at.emplace(*p, one.begin());
+    st.used.splice(st.used.end(), one);
     return hipSuccess;
 }
 
@@ -125,35 +133,35 @@ void pool_put(void *p)
 {
     if (!p) return;
     State &st = state();
-    std::vector<Block> out;
+    Blocks out;
+    bool foreign = false;
     {
         std::lock_guard<std::mutex> lk(st.mu);
-        const auto it = st.used.find(p);
-        if (it == st.used.end()) {
-            out.push_back(Block{ p, 0, 0, 0, {} });
+        const auto it = st.at.find(p);
+        if (it == st.at.end()) {
+            foreign = true;
         } else {
-            Block b = it->second;
-            st.used.erase(it);
-            b.since = Clock::now();
-            if (b.bytes > b.limit) {
-                out.push_back(b);
+            const auto b = it->second;
+            st.at.erase(it);
+            b->since = Clock::now();
+            st.kept.splice(st.kept.end(), st.used, b);
+            const int device = b->device;
+            const size_t limit = b->limit;
+            size_t sum = 0;
+            if (b->bytes > limit) {
+                out.splice(out.end(), st.kept, b);
             } else {
-                st.kept.push_back(b);
-                size_t sum = 0;
-                for (const Block &k : st.kept) sum += k.device == b.device ? k.bytes : 0;
-                for (size_t i = 0; i < st.kept.size() && sum > b.limit;) {
-                    if (st.kept[i].device != b.device) {
-                        ++i;
-                        continue;
-                    }
-                    sum -= st.kept[i].bytes;
-                    out.push_back(st.kept[i]);
-                    st.kept.erase(st.kept.begin() + int64_t(i));
-                }
+                for (const Block &k : st.kept) sum += k.device == device ? k.bytes : 0;
+                take(st, out, [&](const Block &k) {
+                    if (k.device != device || sum <= limit) return false;
+                    sum -= k.bytes;
+                    return true;
+                });
             }
         }
         take_idle(st, out);
     }
+    if (foreign) (void)hipFree(p);
     release(out);
 }
 

@@ -20,6 +20,16 @@ DRIVER = r"""
 #include "bie_internal.hpp"
 
 static const size_t MiB = size_t(1) << 20, GiB = size_t(1) << 30;
+static bool full = false;   // no host memory
+void *operator new(size_t n)
+{
+    void *p = full ? nullptr : std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 static int current = 0;
 static const size_t total[2] = { 64 * GiB, 640 * GiB };   // 1/64 of them: 1 and 10 GiB
 static std::map<void *, std::pair<int, size_t>> live;
@@ -68,10 +78,33 @@ static void other_device()
     CHECK(held[0] == 0);                // 1 GiB on the small one
 }
 
+// giving a block up takes no host memory (operators are destroyed where nothing can
+// be thrown): one that is kept, one that goes over the limit, one of another allocator's
+static void no_host_memory()
+{
+    void *a = get(600 * MiB), *b = get(600 * MiB), *c = nullptr;
+    bie::pool_put(get(4 * MiB));
+    CHECK(hipMalloc(&c, MiB) == hipSuccess);
+    full = true;
+    try {
+        bie::pool_put(a);
+        bie::pool_put(b);
+        bie::pool_put(c);
+    } catch (...) {
+        full = false;
+        CHECK(!"thrown");
+    }
+    full = false;
+    CHECK(held[0] == 600 * MiB);   // the oldest went
+    bie::pool_release();
+    CHECK(held[0] == 0);
+}
+
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     if (what == "other_device") other_device();
+    else if (what == "no_host_memory") no_host_memory();
     else return 2;
     std::printf("ok\n");
     return 0;
@@ -93,7 +126,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["other_device"])
+@pytest.mark.parametrize("what", ["other_device", "no_host_memory"])
 def test_kept_blocks(driver, what):
     p = subprocess.run([str(driver), what], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
