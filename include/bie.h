@@ -97,8 +97,13 @@ int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t 
 /* The large blocks of an operator and of the set-ups are kept for the next one on the
  * device: at most 4 GiB (or 1/64 of its memory, if that is less), released when they
  * have not been used for two seconds, by the next call that makes or drops an
- * operator, or when an allocation of the library fails. */
+ * operator, or when an allocation of the library fails.  No call, no release: a
+ * program that has dropped its operators and gives the device to another allocator
+ * calls bie_release_memory. */
 void bie_op_destroy(bie_op *op);
+/* Releases the kept blocks of every device now; returns their bytes.  What operators and
+ * preconditioners hold stays.  It frees device memory (not for a stream capture). */
+int64_t bie_release_memory(void);
 
 /* Fast operator (the paper's method, Sec. III-V): T x = N x + F x with no dense
  * matrix.  F is the multilevel B-spline far field of bie_farml_create (leaf

@@ -98,6 +98,7 @@ _I64 = ctypes.c_int64
 SYMBOLS = [
     ("bie_op_create", ctypes.c_int, [_P, _I64, _P, _I64, ctypes.c_double, _P, _P, ctypes.POINTER(_P)]),
     ("bie_op_destroy", None, [_P]),
+    ("bie_release_memory", _I64, []),
     ("bie_op_create_fast", ctypes.c_int, [_P, _I64, _P, _I64, ctypes.c_double, _P, _P, ctypes.POINTER(_P)]),
     ("bie_op_fast_info", ctypes.c_int, [_P, _P]),
     ("bie_op_n", _I64, [_P]),
@@ -189,6 +190,30 @@ def _dev(t: torch.Tensor, dtype, shape=None):
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"need shape {shape}, got {tuple(t.shape)}")
     return ctypes.c_void_p(t.data_ptr())
+
+
+def release_memory() -> int:
+    """Releases the device blocks that the library keeps of closed operators and
+    preconditioners (at most 4 GiB a device); returns their bytes."""
+    return int(_lib.bie_release_memory())
+
+
+def _result(make):
+    """make(): a device tensor for a result; tried again without the library's kept blocks."""
+    try:
+        return make()
+    except torch.OutOfMemoryError:
+        if not release_memory():
+            raise
+        return make()
+
+
+def _empty(shape, dtype) -> torch.Tensor:
+    return _result(lambda: torch.empty(shape, dtype=dtype, device="cuda"))
+
+
+def _empty_like(x: torch.Tensor) -> torch.Tensor:
+    return _result(lambda: torch.empty_like(x))
 
 
 def rscc_rows(n: int, s: int, seed: int) -> np.ndarray:
@@ -298,7 +323,7 @@ class Operator:
         return out
 
     def matrix(self, dtype=torch.complex128, stream=None) -> torch.Tensor:
-        out = torch.empty((self.N, self.N), dtype=dtype, device="cuda")
+        out = _empty((self.N, self.N), dtype)
         code = BIE_C128 if dtype == torch.complex128 else BIE_C64
         _check(_lib.bie_op_matrix(self._h, _dev(out, dtype), code, _stream(stream)))
         return out
@@ -307,7 +332,7 @@ class Operator:
         d, pd = _host(np.atleast_2d(dirs), np.float64)
         p, pp = _host(np.atleast_2d(pols), np.float64)
         R = d.shape[0]
-        B = torch.empty((R, self.N), dtype=torch.complex128, device="cuda")
+        B = _empty((R, self.N), torch.complex128)
         _check(_lib.bie_rhs_planewave(self._h, pd, pp, R, _dev(B, torch.complex128), _stream(stream)))
         return B
 
@@ -317,7 +342,7 @@ class Operator:
         split-BF16 block product on the matrix cores (storage "split_bf16");
         block="fp64": the FP64 block product on the matrix cores."""
         X2 = X.reshape(-1, self.N)
-        Y = torch.empty_like(X2) if out is None else out
+        Y = _empty_like(X2) if out is None else out
         if block == "fp64":
             code = BIE_APPLY_F64_BLOCK
         elif block:
@@ -340,7 +365,7 @@ class Operator:
         elif x0 is not None:
             X = x0.reshape(-1, self.N).clone()
         else:
-            X = torch.empty_like(B2)
+            X = _empty_like(B2)
         if x0 is not None and out is not None:
             X.copy_(x0.reshape(-1, self.N))
         st = (SolveStat * R)()
@@ -353,7 +378,7 @@ class Operator:
     def farfield(self, X: torch.Tensor, obs, stream=None) -> torch.Tensor:
         X2 = X.reshape(-1, self.N)
         o, po = _host(np.atleast_2d(obs), np.float64)
-        F = torch.empty((X2.shape[0], o.shape[0], 3), dtype=torch.complex128, device="cuda")
+        F = _empty((X2.shape[0], o.shape[0], 3), torch.complex128)
         _check(_lib.bie_farfield(self._h, _dev(X2, torch.complex128), X2.shape[0], po, o.shape[0],
                                  _dev(F, torch.complex128), _stream(stream)))
         return F
@@ -362,7 +387,7 @@ class Operator:
         """Bistatic RCS (m^2) for unit-amplitude incidence (bie_rcs): R x M, device."""
         X2 = X.reshape(-1, self.N)
         o, po = _host(np.atleast_2d(obs), np.float64)
-        S = torch.empty((X2.shape[0], o.shape[0]), dtype=torch.float64, device="cuda")
+        S = _empty((X2.shape[0], o.shape[0]), torch.float64)
         _check(_lib.bie_rcs(self._h, _dev(X2, torch.complex128), X2.shape[0], po, o.shape[0],
                             _dev(S, torch.float64), _stream(stream)))
         return S
@@ -383,7 +408,7 @@ class Calderon:
     def apply(self, X: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
         """Y = M X for complex128 vectors (rows of X)."""
         X2 = X.reshape(-1, self.N)
-        Y = torch.empty_like(X2) if out is None else out
+        Y = _empty_like(X2) if out is None else out
         _check(_lib.bie_calderon_apply(self._h, _dev(X2, torch.complex128), _dev(Y, torch.complex128, X2.shape),
                                        X2.shape[0], _stream(stream)))
         return Y.reshape(X.shape)
@@ -448,7 +473,7 @@ class FarFieldML:
 
     def apply(self, X: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
         X2 = X.reshape(-1, self.N)
-        Y = torch.empty_like(X2) if out is None else out
+        Y = _empty_like(X2) if out is None else out
         _check(_lib.bie_farml_apply(self._h, _dev(X2, torch.complex128), _dev(Y, torch.complex128, X2.shape),
                                     X2.shape[0], _stream(stream)))
         return Y.reshape(X.shape)
@@ -485,7 +510,7 @@ class FarField:
 
     def apply(self, X: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
         X2 = X.reshape(-1, self.N)
-        Y = torch.empty_like(X2) if out is None else out
+        Y = _empty_like(X2) if out is None else out
         _check(_lib.bie_far_apply(self._h, _dev(X2, torch.complex128), _dev(Y, torch.complex128, X2.shape),
                                   X2.shape[0], _stream(stream)))
         return Y.reshape(X.shape)
@@ -528,7 +553,7 @@ def batch_solve(ops, Bs, opts: Solve | None = None, x0s=None, x0_fallback: bool 
     if x0s is not None:
         Xs = [x.reshape(-1, op.N).clone() for x, op in zip(x0s, ops)]
     else:
-        Xs = [torch.empty_like(b) for b in Bs]
+        Xs = [_empty_like(b) for b in Bs]
     oph = (ctypes.c_void_p * P)(*[op._h.value for op in ops])
     bp = (ctypes.c_void_p * P)(*[_dev(b, torch.complex128).value for b in Bs])
     xp = (ctypes.c_void_p * P)(*[_dev(x, torch.complex128, b.shape).value for x, b in zip(Xs, Bs)])
@@ -566,7 +591,7 @@ def batch_apply(ops, Xs, mat: str = "fp64", unit_tiles: int = 0, cols_per_item: 
     P = len(ops)
     Xs = [x.reshape(-1, op.N) for x, op in zip(Xs, ops)]
     R = np.array([x.shape[0] for x in Xs], np.int64)
-    Ys = [torch.empty_like(x) for x in Xs]
+    Ys = [_empty_like(x) for x in Xs]
     oph = (ctypes.c_void_p * P)(*[op._h.value for op in ops])
     xp = (ctypes.c_void_p * P)(*[_dev(x, torch.complex128).value for x in Xs])
     yp = (ctypes.c_void_p * P)(*[_dev(y, torch.complex128, x.shape).value for y, x in zip(Ys, Xs)])
@@ -657,7 +682,7 @@ class WarmStart:
         return out
 
     def basis(self, stream=None) -> torch.Tensor:
-        U = torch.empty((self.K, self.op.N), dtype=torch.complex128, device="cuda")
+        U = _empty((self.K, self.op.N), torch.complex128)
         _check(_lib.bie_ws_basis(self._h, _dev(U, torch.complex128), _stream(stream)))
         return U
 
@@ -716,7 +741,7 @@ class WarmStart:
         if pols is not None:
             e, pp = _host(pols, np.float64)
         R = f.shape[0]
-        X0 = torch.empty((R, self.op.N), dtype=torch.complex128, device="cuda")
+        X0 = _empty((R, self.op.N), torch.complex128)
         used = np.zeros(R, np.int32)
         pb = None if B is None else _dev(B.reshape(R, self.op.N), torch.complex128)
         _check(_lib.bie_ws_predict(self._h, pf, pp, R, pb, _dev(X0, torch.complex128),

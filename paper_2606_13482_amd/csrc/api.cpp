@@ -156,6 +156,8 @@ int bie_op_fast_info(const bie_op *op, bie_fast_info *info)
 
 void bie_op_destroy(bie_op *op) { destroy_op(op); }
 
+int64_t bie_release_memory(void) { return int64_t(bie::pool_release_all()); }
+
 int64_t bie_op_n(const bie_op *op) { return op ? op->mesh.N : int64_t(BIE_EINVAL); }
 
 int bie_op_edges(const bie_op *op, int32_t *out)

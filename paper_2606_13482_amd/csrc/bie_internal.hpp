@@ -33,6 +33,7 @@ struct Error : std::runtime_error {
 // back with pool_put once its last use, on any stream, has completed; pool_put frees
 // what is not the pool's.  All are safe to call from several threads.
 bool pool_release();   // true if there was anything to release on the current device
+size_t pool_release_all();   // on every device: the bytes given back
 hipError_t pool_get(void **p, size_t bytes);
 void pool_put(void *p);
 template <typename T>

@@ -8,7 +8,8 @@
 // size (up to a quarter less) on its device.  The kept blocks are bounded (4 GiB, or
 // 1/64 of the device's memory if that is less; the oldest go first), those unused for two
 // seconds are released at the next request or return, and all are released when an
-// allocation of the library fails, before it is tried again.
+// allocation of the library fails, before it is tried again, or when the caller asks
+// for it (bie_release_memory).
 #include <chrono>
 #include <list>
 #include <mutex>
@@ -92,6 +93,20 @@ bool pool_release()
     }
     release(out);
     return !out.empty();
+}
+
+size_t pool_release_all()
+{
+    State &st = state();
+    Blocks out;
+    {
+        std::lock_guard<std::mutex> lk(st.mu);
+        out.swap(st.kept);
+    }
+    release(out);
+    size_t bytes = 0;
+    for (const Block &b : out) bytes += b.bytes;
+    return bytes;
 }
 
 hipError_t pool_get(void **p, size_t bytes)

@@ -100,11 +100,56 @@ static void no_host_memory()
     CHECK(held[0] == 0);
 }
 
+// a caller gets all kept blocks back, of both devices; what is in use stays
+static void release_all()
+{
+    void *a = get(100 * MiB), *b = get(8 * MiB);
+    bie::pool_put(get(200 * MiB));
+    bie::pool_put(a);
+    current = 1;
+    void *c = get(3 * GiB);
+    bie::pool_put(c);
+    CHECK(held[0] == 308 * MiB && held[1] == 3 * GiB);
+    CHECK(bie::pool_release_all() == 300 * MiB + 3 * GiB);
+    CHECK(held[0] == 8 * MiB && held[1] == 0);
+    CHECK(bie::pool_release_all() == 0);
+    bie::pool_put(b);
+    CHECK(held[0] == 8 * MiB && bie::pool_release_all() == 8 * MiB && held[0] == 0);
+}
+
+// kept blocks stay within the limit of their device, the oldest going first, also where
+// they differ in size by so much that none serves another's request
+static void bounded()
+{
+    const size_t sizes[] = { 300 * MiB, 200 * MiB, 450 * MiB, 120 * MiB, 700 * MiB, 64 * MiB };
+    size_t kept = 0;
+    for (size_t n : sizes) {
+        bie::pool_put(get(n));
+        CHECK(held[0] <= GiB && held[0] >= n);
+        kept = std::max(kept, held[0]);
+    }
+    CHECK(kept > 900 * MiB);
+    CHECK(held[0] == 884 * MiB);   // the last three
+    void *a = get(96 * MiB);       // 120 MiB serve it: a quarter more
+    CHECK(held[0] == 884 * MiB);
+    void *b = get(94 * MiB);       // nothing left of up to a quarter more
+    CHECK(held[0] == 978 * MiB);
+    bie::pool_put(get(2 * GiB));   // beyond the limit: not kept
+    CHECK(held[0] == 978 * MiB);
+    bie::pool_put(a);
+    bie::pool_put(b);
+    std::this_thread::sleep_for(std::chrono::milliseconds(2100));
+    bie::pool_put(get(2 * MiB));   // what was idle goes
+    CHECK(held[0] == 2 * MiB);
+}
+
 int main(int, char **argv)
 {
     const std::string what = argv[1];
     if (what == "other_device") other_device();
     else if (what == "no_host_memory") no_host_memory();
+    else if (what == "release_all") release_all();
+    else if (what == "bounded") bounded();
     else return 2;
     std::printf("ok\n");
     return 0;
@@ -126,7 +171,28 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["other_device", "no_host_memory"])
+@pytest.mark.parametrize("what", ["other_device", "no_host_memory", "release_all", "bounded"])
 def test_kept_blocks(driver, what):
     p = subprocess.run([str(driver), what], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
+
+
+def test_results_are_tried_again_without_the_kept_blocks(monkeypatch):
+    import torch
+
+    from paper_2606_13482_amd import bie
+    asked, kept = [], [1 << 20]
+
+    def empty(shape, dtype=None, device=None):
+        asked.append(device)
+        if kept[0]:
+            raise torch.OutOfMemoryError("no room")
+        return "tensor"
+
+    monkeypatch.setattr(bie.torch, "empty", empty)
+    monkeypatch.setattr(bie, "release_memory", lambda: kept.__setitem__(0, 0) or 1 << 20)
+    assert bie._empty((2, 3), torch.float64) == "tensor" and asked == ["cuda", "cuda"]
+    kept[0] = 1
+    monkeypatch.setattr(bie, "release_memory", lambda: 0)
+    with pytest.raises(torch.OutOfMemoryError):
+        bie._empty((2, 3), torch.float64)
