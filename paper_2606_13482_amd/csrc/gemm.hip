@@ -615,6 +615,15 @@ int split_cfg_env()
     return v >= 0 && v < kSplitCfgs ? v : -1;
 }
 
+// The most K slices that a product of one column of blocks, of any width, takes: twice
+// the default where the autotuner chooses.
+int split_most(int64_t Mp, int64_t Kp)
+{
+    const int64_t blocks = Mp / GBM, nst = Kp / GBK;
+    const int ks = gemm_splitk(blocks, nst);
+    return split_cfg_env() >= 0 || env_int("BIE_GEMM_SPLITK", 0) > 0 ? ks : gemm_splitk(blocks, nst, 2 * ks);
+}
+
 // Wave-tile form and K slices of a split-BF16 product of this shape: the
 // environment's if set; else the autotuner's choice for (Mp, Kp, NCp, terms),
 // timing every form with the default, half and twice the default K slices on
@@ -676,8 +685,9 @@ void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s,
 
 int64_t gemm_pad_rows(int64_t N) { return (N + GBM - 1) / GBM * GBM; }
 int64_t gemm_pad_k(int64_t N) { return (2 * N + GBK - 1) / GBK * GBK; }
-// The vectors' staging and the partial sums are allocated for whole 256-column blocks, so
-// that growing the number of vectors within one asks for no new memory (under capture).
+// The vectors' staging and the partial sums are allocated for whole 256-column blocks, the
+// latter with the slices of every narrower width, so that another number of vectors within
+// one block asks for no new memory (under capture).
 static int64_t wide_cols(int64_t R) { return (2 * R + GBN - 1) / GBN * GBN; }
 int64_t gemm_pad_cols(int64_t R) { return R <= 32 ? 64 : R <= 64 ? 128 : wide_cols(R); }
 
@@ -736,8 +746,9 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
                            Kp, Bh, Bl, terms == 3);
     int cfg = 0, KS = 1;
     split_choice(Mp, Kp, NCp, terms, s, Ah, Al, Bh, Bl, op, cfg, KS);
-    const size_t pelems = size_t(KS) * size_t(Mp) * size_t(NCp);
-    if (op->gemm_part_elems < pelems) {
+    const size_t pelems = size_t(KS) * size_t(Mp) * size_t(NCp), wide = size_t(Mp) * size_t(wide_cols(R));
+    const size_t cap = wide_cols(R) == GBN ? size_t(std::max(KS, split_most(Mp, Kp))) * wide : size_t(KS) * wide;
+    if (op->gemm_part_elems < cap && (op->gemm_part_elems < pelems || !stream_capturing(s))) {
         if (stream_capturing(s))
             throw Error(BIE_EINVAL, "split-BF16 product: partial sums of " + std::to_string(pelems) + " (have " +
                                         std::to_string(op->gemm_part_elems) + ", K slices " + std::to_string(KS) +
@@ -746,7 +757,6 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
         if (op->gemm_part) (void)hipFree(op->gemm_part);
         op->gemm_part = nullptr;
         op->gemm_part_elems = 0;
-        const size_t cap = size_t(KS) * size_t(Mp) * size_t(wide_cols(R));
         BIE_HIP(device_malloc(&op->gemm_part, cap * sizeof(float)));
         op->gemm_part_elems = cap;
     }
