@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
+#include <cmath>
 #include <utility>
 #include <vector>
 
@@ -39,7 +41,8 @@ struct Tri {   // one triangle of the search, read by its position
 
 template <bool WRITE>
 __global__ __launch_bounds__(64 * PW) void k_near(int64_t F, const Tri *__restrict__ tri, double near_factor,
-                                                  int64_t *__restrict__ ptr, int32_t *__restrict__ list)
+                                                  double slack, int64_t *__restrict__ ptr,
+                                                  int32_t *__restrict__ list)
 {
     __shared__ int32_t cnt[PW][PR];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -62,8 +65,10 @@ __global__ __launch_bounds__(64 * PW) void k_near(int64_t F, const Tri *__restri
                 const double thr = near_factor * L;
                 const bool in = q < qb && q >= p;
                 bool hit = in && dd < thr * thr;
-                // triangles that share a vertex lie within 4/3 of the longest edge
-                if (__any(in && !hit && dd < 2.25 * L * L)) {
+                // triangles that share a vertex lie within 4/3 of the longest edge, the rounding
+                // of their centroids (slack) apart
+                const double reach = 1.5 * L + slack;
+                if (__any(in && !hit && dd < reach * reach)) {
                     bool touch = false;
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
@@ -176,17 +181,21 @@ void near_search(const Mesh &M, double near_factor, const std::vector<int32_t> *
         h[r].longest = M.longest[t];
         h[r].pad = 0;
     }
+    // a centroid is off by up to 4/3 eps of the largest coordinate on each axis
+    double most = 0.0;
+    for (double x : M.V) most = std::max(most, std::fabs(x));
+    const double slack = 8.0 * DBL_EPSILON * most;
     Temp tri(size_t(F) * sizeof(Tri));
     BIE_HIP(hipMemcpyAsync(tri.p, h.data(), size_t(F) * sizeof(Tri), hipMemcpyHostToDevice, s));
     BIE_HIP(device_malloc(&out.ptr, size_t(F + 1) * sizeof(int64_t)));
     const dim3 grid(unsigned((F + PR - 1) / PR));
-    hipLaunchKernelGGL(k_near<false>, grid, dim3(64 * PW), 0, s, F, (const Tri *)tri.p, near_factor, out.ptr, nullptr);
+    hipLaunchKernelGGL(k_near<false>, grid, dim3(64 * PW), 0, s, F, (const Tri *)tri.p, near_factor, slack, out.ptr, nullptr);
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, F, out.ptr);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipMemcpyAsync(&out.n, out.ptr + F, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     BIE_HIP(hipStreamSynchronize(s));
     BIE_HIP(device_malloc(&out.list, std::max<int64_t>(out.n, 1) * sizeof(int32_t)));
-    hipLaunchKernelGGL(k_near<true>, grid, dim3(64 * PW), 0, s, F, (const Tri *)tri.p, near_factor, out.ptr, out.list);
+    hipLaunchKernelGGL(k_near<true>, grid, dim3(64 * PW), 0, s, F, (const Tri *)tri.p, near_factor, slack, out.ptr, out.list);
     BIE_HIP(hipGetLastError());
     BIE_HIP(hipStreamSynchronize(s));   // the triangles' copy ends with the call
 }
