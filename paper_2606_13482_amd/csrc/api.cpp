@@ -68,7 +68,7 @@ int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t 
         if (o.star != 0 && o.star != 1) return fail(BIE_EINVAL, "star must be 0 or 1");
         if (o.star && o.storage == BIE_SPLIT_BF16) return fail(BIE_EINVAL, "the star-split form has no split-BF16 copy");
         if (!(o.near_factor >= 0.0)) return fail(BIE_EINVAL, "near_factor must be >= 0");
-        bie::Mesh mesh = bie::build_mesh(verts, nv, tris, nt, o.near_factor, !bie::near_on_device(nt));   // host only: EMESH first
+        bie::Mesh mesh = bie::build_mesh(verts, nv, tris, nt, o.near_factor, false);   // host only: EMESH first
         bie_op *op = new bie_op();
         try {
             op->mesh = std::move(mesh);

@@ -1079,7 +1079,7 @@ bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
     std::unique_ptr<bie_op, void (*)(bie_op *)> hold(new bie_op(), bie_op_destroy);
     bie_op *opb = hold.get();
     const int64_t Fb = int64_t(Tb.size() / 3);
-    opb->mesh = build_mesh(Vb.data(), int64_t(Vb.size() / 3), Tb.data(), Fb, 2.0, !near_on_device(Fb));
+    opb->mesh = build_mesh(Vb.data(), int64_t(Vb.size() / 3), Tb.data(), Fb, 2.0, false);   // pairs: ranked_near
     opb->device = op->device;
     opb->k = op->k;
     const int64_t Nb = opb->mesh.N;

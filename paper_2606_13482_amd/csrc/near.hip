@@ -203,8 +203,8 @@ void near_search(const Mesh &M, double near_factor, const std::vector<int32_t> *
 void flag_pairs(bie_op *op, double near_factor, bool device_list, hipStream_t s)
 {
     Mesh &M = op->mesh;
-    const std::vector<int32_t> &rank = op->tri.rank;
     if (near_on_device(M.F)) {
+        const std::vector<int32_t> &rank = op->tri.rank;
         NearDev nd;
         near_search(M, near_factor, nullptr, nd, s);
         std::vector<int64_t> ptr(M.F + 1);
@@ -224,15 +224,8 @@ void flag_pairs(bie_op *op, double near_factor, bool device_list, hipStream_t s)
                 M.near[2 * e] = int32_t(p);
                 M.near[2 * e + 1] = list[e];
             }
-    } else if (device_list) {
-        std::vector<int32_t> h(M.near.size());
-        for (size_t i = 0; i < h.size(); i += 2) {
-            const int32_t p = rank[M.near[i]], q = rank[M.near[i + 1]];
-            h[i] = std::min(p, q);
-            h[i + 1] = std::max(p, q);
-        }
-        BIE_HIP(device_malloc(&op->flagged, std::max<size_t>(h.size(), 1) * sizeof(int32_t)));
-        BIE_HIP(hipMemcpy(op->flagged, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    } else if (device_list) {   // its matrix would take terabytes
+        throw Error(BIE_ENOMEM, "no device holds a dense operator of " + std::to_string(M.F) + " triangles");
     }
 }
 
