@@ -82,8 +82,8 @@ int bie_op_create(const double *verts, int64_t nv, const int32_t *tris, int64_t 
             const bool want64 = o.storage == BIE_C128 || o.storage == BIE_SPLIT_BF16 || o.keep_fp64;
             const bool want32 = o.storage == BIE_C64;
             if (op->star) {
-                bie::packed_setup(op->pk, op->mesh.N);
-                bie::packed_setup(op->pkv, op->mesh.F);
+                bie::packed_setup(op->pk, op->mesh.N, want64);
+                bie::packed_setup(op->pkv, op->mesh.F, want64);
             } else {
                 bie::packed_setup_tuned(op->pk, op->mesh.N, want64);
             }

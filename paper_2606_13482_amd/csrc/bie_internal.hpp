@@ -267,8 +267,9 @@ void farfield(const bie_op *op, const void *X, int64_t R, const double *obs, int
               hipStream_t s);
 
 // blas.hip: products with the packed symmetric matrix.
-void packed_setup(Packed &pk, int64_t n);
-void packed_setup_tuned(Packed &pk, int64_t n, bool mat64);   // tables of the packed n x n tiles
+// tables of the packed n x n tiles (mat64: of an FP64 matrix), tuned: with the autotuner's units
+void packed_setup(Packed &pk, int64_t n, bool mat64);
+void packed_setup_tuned(Packed &pk, int64_t n, bool mat64);
 // work units of U tiles along each tile row, and the partial-vector slots
 void build_units(int64_t nT, int U, std::vector<int32_t> &units, std::vector<int32_t> &uptr,
                  std::vector<int64_t> &seg);

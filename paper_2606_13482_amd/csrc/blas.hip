@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "bie_internal.hpp"
+#include "lanes.hpp"
 
 namespace bie {
 
@@ -93,15 +94,24 @@ void prof_read(int kernel, int64_t *launches, double *total_ms, int64_t *columns
 
 namespace {
 
-// Tiles per unit of the single-operator tile pass, one unit per block: 16 from 208
-// blocks of them on (5202 unknowns, six vectors with units of 8 / 16 / 32: 92 / 83 / 87 us),
-// else 8, and fewer where that would leave less than 1.5 blocks per CU, for a small matrix
-// is bound by how many CUs read it (product of one FP64 vector, units of 1 / 2 / 4 / 8 / 16
-// tiles and balanced runs: 450 unknowns 7.0 / 7.9 / 9.4 / 12.5 / 12.6 / 19.7 us, 1152
-// 8.6 / 9.8 / 12.6 / 18.1 / 29.2 / 25.7, 2592 17.3 / 14.7 / 15.5 / 20.6 / 32.2 / 27.9, 3528
-// 27.6 / 25.2 / 22.5 / 23.9 / 34.3 / 29.9, 5202 51.0 / 44.8 / 43.2 / 43.2 / 42.5 / 45.9).
+// Tiles per unit of the single-operator tile pass, one unit per block, the same for any
+// number of vectors (the units set the order of the sums).  Short units spread a small
+// matrix over more CUs; long ones have fewer row sums and blocks, which is what several
+// vectors ask for.  us, one and 16 FP64 vectors; one and 16 FP32 vectors (FP32 matrix; 16:
+// the better of the passes below):
+//   unknowns  1 tile               2                    4                    8
+//     480       7   9;   6   7      7   9;   7   8      9  10;   8   9     12  12;  11  12
+//     882       8  20;   6  11      8  15;   7  10     10  14;   8  11     15  19;  12  15
+//    1800      10  61;   7  38     10  46;   8  29     13  36;   9  24     19  39;  12  21
+//    2592      16 112;   9  74     14  79;  10  51     15  66;  10  44     20  58;  13  38
+//    4608      39 328;  22 199     36 219;  20 144     37 171;  20 112     36 156;  21 102
+//    7680      98 960;  48 540     90 635;  43 402     87 496;  44 308     88 454;  44 270
+//   11250     200 2070; 113 1280  183 1361; 105 842   182 1049; 108 637   185 955; 109 560
+// (16 tiles, one FP64 vector: 127 at 8712 against 115 with 8, 193 at 11250).  The lines lie
+// where a longer unit starts to cost one vector little (FP32 products of 16 at 1800
+// unknowns earlier than FP64 ones).
 // BIE_SYM_UNIT = 1..64 fixes the length, 0 balanced runs (measurement).
-int unit_tiles(int64_t nT)
+int unit_tiles(int64_t nT, bool mat64)
 {
     static const int env = [] {
         const char *e = getenv("BIE_SYM_UNIT");
@@ -110,10 +120,7 @@ int unit_tiles(int64_t nT)
     }();
     if (env >= 0) return env;
     const int64_t tiles = nT * (nT + 1) / 2;
-    if (tiles >= 208 * 16) return 16;
-    int u = 8;
-    while (u > 1 && tiles < 384 * u) u /= 2;
-    return u;
+    return tiles < 60 ? 1 : tiles < (mat64 ? 600 : 300) ? 2 : tiles < 3072 ? 4 : 8;
 }
 
 typedef double nd2 __attribute__((ext_vector_type(2)));
@@ -149,47 +156,6 @@ __device__ inline T wsum(T v)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
-}
-
-// Sums 8 complex values over a wave: each exchange halves what a lane carries
-// (4+2+1 exchanges, then 3 plain steps).  pr[0], pi[0] of lane L end with the
-// total of value (L >> 3) & 7.
-template <typename T>
-__device__ inline void wave_sum8(T pr[8], T pi[8])
-{
-    const int lane = threadIdx.x & 63;
-    {
-        const bool b = lane & 32;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const T sr = b ? pr[i] : pr[i + 4], si = b ? pi[i] : pi[i + 4];
-            const T kr = b ? pr[i + 4] : pr[i], ki = b ? pi[i + 4] : pi[i];
-            pr[i] = kr + __shfl_xor(sr, 32, 64);
-            pi[i] = ki + __shfl_xor(si, 32, 64);
-        }
-    }
-    {
-        const bool b = lane & 16;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const T sr = b ? pr[i] : pr[i + 2], si = b ? pi[i] : pi[i + 2];
-            const T kr = b ? pr[i + 2] : pr[i], ki = b ? pi[i + 2] : pi[i];
-            pr[i] = kr + __shfl_xor(sr, 16, 64);
-            pi[i] = ki + __shfl_xor(si, 16, 64);
-        }
-    }
-    {
-        const bool b = lane & 8;
-        const T sr = b ? pr[0] : pr[1], si = b ? pi[0] : pi[1];
-        const T kr = b ? pr[1] : pr[0], ki = b ? pi[1] : pi[0];
-        pr[0] = kr + __shfl_xor(sr, 8, 64);
-        pi[0] = ki + __shfl_xor(si, 8, 64);
-    }
-#pragma unroll
-    for (int o = 4; o > 0; o >>= 1) {
-        pr[0] += __shfl_xor(pr[0], o, 64);
-        pi[0] += __shfl_xor(pi[0], o, 64);
-    }
 }
 
 // Tile pass of one work unit: tiles (I, J0 .. J1-1) of row block I, the
@@ -1199,7 +1165,7 @@ static void packed_setup_units(Packed &pk, int64_t n, int U)
     pk.h_seg = std::move(seg);
 }
 
-void packed_setup(Packed &pk, int64_t n) { packed_setup_units(pk, n, unit_tiles((n + TB - 1) / TB)); }
+void packed_setup(Packed &pk, int64_t n, bool mat64) { packed_setup_units(pk, n, unit_tiles((n + TB - 1) / TB, mat64)); }
 
 static std::string tune_key(int64_t N, bool mat64) { return "sym:" + std::to_string(N) + (mat64 ? ":f64" : ":f32"); }
 static bool tuned_unit(const std::string &key, int &unit)
@@ -1213,7 +1179,7 @@ static bool tuned_unit(const std::string &key, int &unit)
 // With the autotuner's units where it has met the size (tune_packed then has nothing to rebuild).
 void packed_setup_tuned(Packed &pk, int64_t n, bool mat64)
 {
-    int unit = unit_tiles((n + TB - 1) / TB);
+    int unit = unit_tiles((n + TB - 1) / TB, mat64);
     if (!getenv("BIE_SYM_UNIT") && tune_enabled()) (void)tuned_unit(tune_key(n, mat64), unit);
     packed_setup_units(pk, n, unit);
 }
@@ -1275,11 +1241,12 @@ void tune_packed(bie_op *op, hipStream_t s)
             BIE_HIP(device_malloc(&y, size_t(N) * 16));
             BIE_HIP(hipMemsetAsync(x, 0, size_t(N) * 16, s));
             float best = 0.f;
-            const int def = unit_tiles((N + TB - 1) / TB);
+            const int def = unit_tiles((N + TB - 1) / TB, mat64);
             v = { def };
-            // below the rule's 8 tiles a launch is some microseconds: its neighbours, and more launches
-            const std::vector<int> cand = def >= 8 ? std::vector<int>{ def, 24 - def, 0, 4 }
-                                                   : std::vector<int>{ def, 2 * def, std::max(1, def / 2) };
+            // below the rule's 8 tiles a launch is some microseconds: more launches, and the
+            // next longer units (shorter ones cost the products of several vectors more than
+            // this one vector gains)
+            const std::vector<int> cand = def >= 8 ? std::vector<int>{ def, 4, 0, 16 } : std::vector<int>{ def, 2 * def };
             for (int U : cand) {
                 Packed c;
                 try {
@@ -1419,7 +1386,7 @@ void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64
     // a call is judged by units of 16 tiles and, where its own do not fit, made in several passes,
     // each of one vector at least: units fixed too short for a large matrix are refused.
     int64_t slots = pk.nslots;
-    if (unit_tiles(pk.nT) < 8) {
+    if (unit_tiles(pk.nT, op->Z64 != nullptr) < 8) {
         int64_t most = pk.nT * (pk.nT - 1) / 2;
         for (int64_t I = 0; I < pk.nT; ++I) most += (pk.nT - I + 15) / 16;
         slots = std::min(slots, most);

@@ -1126,7 +1126,7 @@ bie_calderon *calderon_create(const bie_op *op, hipStream_t s)
     v->k = op->k;
     v->storage = BIE_C128;
     v->mesh.N = N;
-    packed_setup(v->pk, N);
+    packed_setup(v->pk, N, true);
     BIE_HIP(pool_get(&v->Z64, size_t(v->pk.ntiles) * TB * TB * sizeof(double2)));
     hipLaunchKernelGGL(k_pack_sym, dim3(unsigned(v->pk.nT), unsigned(v->pk.nT)), dim3(256), 0, s, N, v->pk.nT,
                        T, -1.0, (double2 *)v->Z64);

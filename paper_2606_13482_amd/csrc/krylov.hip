@@ -38,6 +38,7 @@
 #include <vector>
 
 #include "bie_internal.hpp"
+#include "lanes.hpp"
 
 // No automatic fusion of multiplies and adds in this file: the rounding of
 // every result follows the source expression, so kernels instantiated with
@@ -109,35 +110,6 @@ template <typename VT> __device__ inline VT st2(double2 v);
 template <> __device__ inline double2 st2<double2>(double2 v) { return v; }
 template <> __device__ inline float2 st2<float2>(double2 v) { return make_float2(float(v.x), float(v.y)); }
 template <> __device__ inline c32h st2<c32h>(double2 v) { return c32h{ (_Float16)v.x, (_Float16)v.y }; }
-
-// Exchanges between lanes in registers (a permute through LDS takes its latency and
-// its bandwidth for every 4 bytes).  xor_add<O>(v): v + the value of lane ^ O.
-template <int CTRL, int BANKS = 0xf> __device__ inline int2 dpp2(int2 old, int2 v)
-{
-    return make_int2(__builtin_amdgcn_update_dpp(old.x, v.x, CTRL, 0xf, BANKS, false),
-                     __builtin_amdgcn_update_dpp(old.y, v.y, CTRL, 0xf, BANKS, false));
-}
-// a of lane and lane ^ O in the lanes whose bit O is clear, b in the others, added
-template <int O> __device__ inline double pair_add(double a, double b)
-{
-    const int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
-    const auto lo = O == 32 ? __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false)
-                            : __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
-    const auto hi = O == 32 ? __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false)
-                            : __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
-    return __builtin_bit_cast(double, make_int2(int(lo[0]), int(hi[0]))) +
-           __builtin_bit_cast(double, make_int2(int(lo[1]), int(hi[1])));
-}
-template <int O> __device__ inline double lane_xor(double v)
-{
-    const int2 w = __builtin_bit_cast(int2, v), z = make_int2(0, 0);
-    int2 r;
-    if (O == 8) r = dpp2<0x128>(z, w);                                   // rotation of 16 lanes by 8
-    else if (O == 4) r = dpp2<0x114, 0xa>(dpp2<0x104, 0x5>(z, w), w);    // shifts of 16 lanes by 4, for every other quad
-    else if (O == 2) r = dpp2<0x4e>(z, w);
-    else r = dpp2<0xb1>(z, w);
-    return __builtin_bit_cast(double, r);
-}
 
 __device__ inline double wsum(double v)
 {
