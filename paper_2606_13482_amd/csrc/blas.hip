@@ -1022,9 +1022,10 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
     // one (measured: 92 vs 144 us, 52 vs 47 us at N = 7680)
     constexpr bool NT = sizeof(M) == 8;
     // Several vectors share the tile reads in groups of up to 3 (FP64 vectors; 4
-    // spill) or 4, as even as they come.  A matrix with fewer blocks than two per CU
-    // over all vectors stays in the caches, and one block per vector fills more CUs
-    // (480 unknowns, 16 vectors: 16 us either way; 1152: 31 against 29 us).
+    // spill) or 4, as even as they come.  A matrix below 10 MB comes from the L2s whatever
+    // reads it, and one block per vector fills more CUs (us, a block per vector / groups, of
+    // 3 and 16 vectors: FP64, 882 unknowns, 6.9 MB 9 / 10, 15 / 17; 1152, 11.2 MB 12 / 10,
+    // 29 / 23; FP32, 1458, 9.0 MB 9 / 9, 18 / 22; 2178, 20.6 MB 16 / 12, 54 / 33).
     constexpr int MAXNC = sizeof(T) == 8 ? 3 : 4;
     auto several = [&](auto kern, int nc) {
         const int64_t G = (R + nc - 1) / nc;
@@ -1032,7 +1033,7 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
                            pk.N, pk.nT, pk.units, pk.unit_ptr, pk.run_ptr, pk.seg, pk.nslots, int(G), R, (const T *)X, ldx,
                            (T *)part, skip, sks);
     };
-    if (R > 1 && pk.nruns * R >= 512) {
+    if (R > 1 && pk.ntiles * TB * TB * int64_t(2 * sizeof(M)) >= 10000000) {
         const int64_t G = (R + MAXNC - 1) / MAXNC, nc = (R + G - 1) / G;
         // a matrix beyond the 256 MB last-level cache is streamed past it (7680
         // unknowns, FP64, 6 vectors: 179 against 226 us; 5202, within it: 107 against 86)
