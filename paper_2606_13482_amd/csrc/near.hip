@@ -10,9 +10,9 @@
 // read once for PR tests.  One launch counts, a scan places the rows, and a second
 // launch counts each wave's share again and writes the partners in ascending
 // order.  FP64 vector issue bounds it, at about 15 instructions per 64 pairs and
-// row.  The host search is linear in the triangles but takes about 1.1 us each
-// (a hash grid, a sort per row): at 5120 triangles 4.5 ms against 60 us for
-// both launches.
+// row.  The host search is linear in the triangles but takes 0.6 to 0.9 us each
+// (a hash grid, a sort per row): at 5292 triangles 4.7 ms against 0.27 with both
+// launches, the upload and the waits.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,9 +25,11 @@
 
 namespace bie {
 
-// The device search grows with the square of the triangles and passes the host's
-// time near 2.5 M of them; the line lies at 2^20 (0.4 against 1.2 s).
-bool near_on_device(int64_t F) { return F <= (int64_t(1) << 20); }
+// The device search grows with the square of the triangles.  A fast operator, which
+// alone has so many, needs the list in the mesh's order and in the device's: two searches
+// here, on the host a search and a sort.  ms, device / host: 80 688 triangles 25 / 142,
+// 326 700 300 / 590, 480 000 630 / 880, 691 200 1280 / 1280, 1 044 300 2870 / 1940.
+bool near_on_device(int64_t F) { return F <= 655360; }
 
 namespace {
 
