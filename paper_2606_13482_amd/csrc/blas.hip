@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // The same for several vectors: a block of 8 waves takes a run for NC of them at
 // once, each wave 8 rows of the row block, so that a tile read serves NC products
 // (one block per vector read the matrix R times: 6 FP64 vectors at 5202 unknowns
-// 238 -> 88 us, 16 at 7680 1283 -> 463 us).  The row sums of NC vectors fill the registers (2 waves per SIMD at
+// 237 -> 80 us, 16 at 7680 1307 -> 454 us).  The row sums of NC vectors fill the registers (2 waves per SIMD at
 // NC = 3); x of the tile rows comes from LDS, the same address for every lane.  The
 // groups of one run start together on one XCD, so that its L2 serves all but one of
 // them.  NT: as in the single-vector pass.  Every column has the bits of a product
@@ -1035,8 +1035,9 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
     };
     if (R > 1 && pk.ntiles * TB * TB * int64_t(2 * sizeof(M)) >= 10000000) {
         const int64_t G = (R + MAXNC - 1) / MAXNC, nc = (R + G - 1) / G;
-        // a matrix beyond the 256 MB last-level cache is streamed past it (7680
-        // unknowns, FP64, 6 vectors: 179 against 226 us; 5202, within it: 107 against 86)
+        // a matrix beyond the 256 MB last-level cache is streamed past it (us, cached /
+        // streamed, 2, 3 and 6 FP64 vectors: 5202 unknowns, 213 MiB 44 / 53, 50 / 62, 82 / 94;
+        // 7200, 403 MiB 109 / 99, 120 / 113, 162 / 160)
         const bool stream = pk.ntiles * TB * TB * int64_t(2 * sizeof(M)) > (int64_t(256) << 20);
         if (nc == 2) stream ? several(k_sym_tiles_n<M, T, CONJ, 2, true>, 2) : several(k_sym_tiles_n<M, T, CONJ, 2, false>, 2);
         else if (nc == 3) stream ? several(k_sym_tiles_n<M, T, CONJ, 3, true>, 3) : several(k_sym_tiles_n<M, T, CONJ, 3, false>, 3);
