@@ -531,6 +531,84 @@ __global__ __launch_bounds__(256) void k_rhs(int64_t N, int64_t R, const int4 *_
 // the exponentials depend on the direction alone and the vectors enter by a
 // contraction over the triangles.
 //
+// F itself, or with RCS the bistatic RCS (k^2 / (4 pi)) |r x F|^2 of direction r = o
+// (unit): the part of F transverse to r, squared.
+template <bool RCS, typename O>
+__device__ inline void far_write(const double (&f)[6], const double (&o)[3], double k, O *__restrict__ out, int64_t at)
+{
+    if constexpr (RCS) {
+        double dr = 0.0, di = 0.0, t2 = 0.0;
+        for (int c = 0; c < 3; ++c) {
+            dr += o[c] * f[2 * c];
+            di += o[c] * f[2 * c + 1];
+        }
+        for (int c = 0; c < 3; ++c) {
+            const double tr = f[2 * c] - dr * o[c], ti = f[2 * c + 1] - di * o[c];
+            t2 += tr * tr + ti * ti;
+        }
+        out[at] = k * k / (4.0 * M_PI) * t2;
+    } else {
+        for (int c = 0; c < 3; ++c) out[at * 3 + c] = make_double2(f[2 * c], f[2 * c + 1]);
+    }
+}
+
+// Few directions or a small mesh: one block per (vector, direction), its threads over the
+// triangles, the exponentials evaluated for every vector again.  One launch and no
+// work arrays (see farfield for the line).
+template <bool RCS, typename O>
+__global__ __launch_bounds__(256) void k_far_direct(int64_t F, int64_t N, int64_t M,
+                                                    const int32_t *__restrict__ slot_m,
+                                                    const int8_t *__restrict__ sgn, const double *__restrict__ cent,
+                                                    const double *__restrict__ loc, const double *__restrict__ vfree,
+                                                    const double *__restrict__ obs, double k,
+                                                    const double2 *__restrict__ X, O *__restrict__ out)
+{
+    const int64_t mo = blockIdx.x, r = blockIdx.y;
+    const double o[3] = { obs[3 * mo], obs[3 * mo + 1], obs[3 * mo + 2] };
+    const double2 *x = X + r * N;
+    double acc[6] = { 0, 0, 0, 0, 0, 0 };
+    for (int64_t t = threadIdx.x; t < F; t += blockDim.x) {
+        double br = 0.0, bi = 0.0, ar[3] = { 0, 0, 0 }, ai[3] = { 0, 0, 0 };   // J(y) = b y - a
+        for (int a = 0; a < 3; ++a) {
+            const double2 xa = x[slot_m[t * 3 + a]];
+            const double sa = 0.5 * double(sgn[t * 3 + a]);
+            br += sa * xa.x;
+            bi += sa * xa.y;
+            for (int c = 0; c < 3; ++c) {
+                const double v = sa * vfree[t * 9 + a * 3 + c];
+                ar[c] += v * xa.x;
+                ai[c] += v * xa.y;
+            }
+        }
+        for (int i = 0; i < NQ; ++i) {
+            double y[3], ph = 0.0;
+            for (int c = 0; c < 3; ++c) {
+                y[c] = loc[(t * NQ + i) * 3 + c];
+                ph += o[c] * (cent[t * 3 + c] + y[c]);
+            }
+            double sn, cs;
+            sincos_reduced(k * ph, sn, cs);
+            sn *= c_w[i];
+            cs *= c_w[i];
+            for (int c = 0; c < 3; ++c) {
+                const double jr = br * y[c] - ar[c], ji = bi * y[c] - ai[c];
+                acc[2 * c] += jr * cs - ji * sn;
+                acc[2 * c + 1] += jr * sn + ji * cs;
+            }
+        }
+    }
+    __shared__ double red[6][4];
+    for (int c = 0; c < 6; ++c) {
+        for (int h = 32; h > 0; h >>= 1) acc[c] += __shfl_xor(acc[c], h, 64);
+        if ((threadIdx.x & 63) == 0) red[c][threadIdx.x >> 6] = acc[c];
+    }
+    __syncthreads();
+    if (threadIdx.x) return;
+    double f[6];
+    for (int c = 0; c < 6; ++c) f[c] = (red[c][0] + red[c][1]) + (red[c][2] + red[c][3]);
+    far_write<RCS>(f, o, k, out, r * M + mo);
+}
+
 // (b, a) of every triangle and vector: 8 doubles at ((t R) + r) 8.
 __global__ __launch_bounds__(256) void k_far_coef(int64_t F, int64_t N, int64_t R, const int32_t *__restrict__ slot_m,
                                                   const int8_t *__restrict__ sgn, const double *__restrict__ vfree,
@@ -633,8 +711,7 @@ __global__ __launch_bounds__(256) void k_far_sum(int64_t F, int64_t R, int64_t M
             for (int c = 0; c < 6; ++c) part[((int64_t(blockIdx.z) * R + r0 + r) * 6 + c) * M + mo] = f[r][c];
 }
 
-// The splits' sums in order; F itself, or with RCS the bistatic RCS (k^2 / (4 pi)) |r x F|^2 of
-// direction r (unit): the part of F transverse to r, squared.
+// The splits' sums in order, and what is asked for.
 template <bool RCS, typename O>
 __global__ __launch_bounds__(256) void k_far_out(int64_t nm, int64_t ld, int64_t splits, const double *__restrict__ part,
                                                 const double *__restrict__ obs, double k, O *__restrict__ out)
@@ -662,21 +739,8 @@ __global__ __launch_bounds__(256) void k_far_out(int64_t nm, int64_t ld, int64_t
     if (w || mo >= nm) return;
     for (int u = 0; u < 3; ++u)
         for (int c = 0; c < 6; ++c) f[c] += red[u][c][lane];
-    if constexpr (RCS) {
-        const double o[3] = { obs[3 * mo], obs[3 * mo + 1], obs[3 * mo + 2] };
-        double dr = 0.0, di = 0.0, t2 = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            dr += o[c] * f[2 * c];
-            di += o[c] * f[2 * c + 1];
-        }
-        for (int c = 0; c < 3; ++c) {
-            const double tr = f[2 * c] - dr * o[c], ti = f[2 * c + 1] - di * o[c];
-            t2 += tr * tr + ti * ti;
-        }
-        out[r * ld + mo] = k * k / (4.0 * M_PI) * t2;
-    } else {
-        for (int c = 0; c < 3; ++c) out[(r * ld + mo) * 3 + c] = make_double2(f[2 * c], f[2 * c + 1]);
-    }
+    const double o[3] = { obs[3 * mo], obs[3 * mo + 1], obs[3 * mo + 2] };
+    far_write<RCS>(f, o, k, out, r * ld + mo);
 }
 
 }  // namespace
@@ -917,6 +981,30 @@ void farfield(const bie_op *op, const void *X, int64_t R, const double *obs, int
     double *w = nullptr;
     Plan p = {};
     const size_t nobs = size_t(3 * M);
+    // One block per (vector, direction) where that is estimated faster (us: its chain over the
+    // triangles or all blocks' issue, against two more launches, their chain and the
+    // coefficients; wall time direct / three launches: 72 unknowns, one vector and direction 35 /
+    // 48; 480, 512 vectors, one direction 41 / 98, 64 directions 371 / 102; 7200, 512 vectors, 4
+    // directions 393 / 831, 16 1440 / 816; 30720, one vector, 361 directions 349 / 292).
+    const double fr = double(F) * double(R);
+    if (std::max(0.01 * double(F), 3.3e-5 * fr * double(M)) < 16.0 + 0.002 * double(F) + 2e-4 * fr) {
+        BIE_HIP(device_malloc(&w, nobs * sizeof(double)));
+        hipError_t e = hipMemcpy(w, obs, nobs * sizeof(double), hipMemcpyHostToDevice);
+        auto go = [&](auto kern, auto *to) {
+            hipLaunchKernelGGL(kern, dim3(unsigned(M), unsigned(R)), dim3(256), 0, s, F, N, M, D.slot_m, D.sgn, D.cent,
+                               D.loc, D.vfree, w, op->k, (const double2 *)X, to);
+        };
+        if (e == hipSuccess) {
+            if (rcs) go(k_far_direct<true, double>, static_cast<double *>(out));
+            else go(k_far_direct<false, double2>, static_cast<double2 *>(out));
+            e = hipGetLastError();
+        }
+        const hipError_t e2 = hipStreamSynchronize(s);
+        (void)hipFree(w);
+        BIE_HIP(e);
+        BIE_HIP(e2);
+        return;
+    }
     hipError_t e = hipErrorOutOfMemory;
     for (int64_t limit : { int64_t(1) << 23, int64_t(1) << 19, int64_t(0) }) {
         p = plan(limit);
