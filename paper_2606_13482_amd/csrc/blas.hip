@@ -872,25 +872,26 @@ __global__ __launch_bounds__(512) void k_sym_reduce_gf(const GProb *__restrict__
                        reinterpret_cast<double2 *>(Y) + gc.yoff[c], SUB ? reinterpret_cast<const double2 *>(B) + gc.yoff[c] : nullptr);
 }
 
-// The full matrix from the packed tiles: block b reads tile b once, writes its
-// rows as they lie and, through LDS, its columns as the rows of the mirrored
-// block, both in runs of 64 entries (one thread per output entry read the mirrored
-// half 1 KiB apart, lane by lane: 7680
-// unknowns 444 -> 277 us, 5.1 TB/s).
-template <typename T, typename O>
+// The full matrix from the packed tiles: a block reads RPB rows of a tile once, writes
+// them as they lie and, through LDS, their columns as rows of the mirrored block, in runs
+// of 64 and RPB entries (one thread per output entry read the mirrored half 1 KiB apart, lane by
+// lane: 7680 unknowns 444 -> 277 us, 5.1 TB/s).  RPB: the whole tile, or a quarter where
+// there are fewer tiles than CUs.
+template <typename T, typename O, int RPB>
 __global__ __launch_bounds__(256) void k_unpack(const T *__restrict__ Zp, int64_t N, int64_t nT,
                                                 typename Cx<O>::type *__restrict__ out)
 {
     using V2 = typename Cx<T>::type;
     using W2 = typename Cx<O>::type;
-    __shared__ V2 sz[TB][TB + 1];
+    __shared__ V2 sz[RPB][TB + 1];
     int64_t I, J;
     tile_decode(blockIdx.x, nT, I, J);
-    const V2 *Z = reinterpret_cast<const V2 *>(Zp) + int64_t(blockIdx.x) * TB * TB;
+    const int r0 = RPB == TB ? 0 : int(blockIdx.y) * RPB;
+    const V2 *Z = reinterpret_cast<const V2 *>(Zp) + int64_t(blockIdx.x) * TB * TB + r0 * TB;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t m0 = I * TB, n0 = J * TB;
+    const int64_t m0 = I * TB + r0, n0 = J * TB;
 #pragma unroll
-    for (int i = 0; i < TB / 4; ++i) {
+    for (int i = 0; i < RPB / 4; ++i) {
         const int r = w + 4 * i;
         const V2 z = __builtin_nontemporal_load(Z + r * TB + lane);
         sz[r][lane] = z;
@@ -899,10 +900,10 @@ __global__ __launch_bounds__(256) void k_unpack(const T *__restrict__ Zp, int64_
     if (I == J) return;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < TB / 4; ++i) {
-        const int c = w + 4 * i;
-        const V2 z = sz[lane][c];
-        if (n0 + c < N && m0 + lane < N) __builtin_nontemporal_store(W2{ O(z.x), O(z.y) }, out + (n0 + c) * N + m0 + lane);
+    for (int i = 0; i < RPB / 4; ++i) {
+        const int r = RPB == TB ? lane : threadIdx.x % RPB, c = RPB == TB ? w + 4 * i : (threadIdx.x + 256 * i) / RPB;
+        const V2 z = sz[r][c];
+        if (n0 + c < N && m0 + r < N) __builtin_nontemporal_store(W2{ O(z.x), O(z.y) }, out + (n0 + c) * N + m0 + r);
     }
 }
 
@@ -1459,13 +1460,15 @@ void grouped_product(bool mat64, const GProb *probs, const GCols &gc, const int3
 void unpack_full(const bie_op *op, bool from64, bool to64, void *dst, hipStream_t s)
 {
     const Packed &pk = op->pk;
-    const dim3 grid{ unsigned(pk.ntiles) };
-    if (from64) hipLaunchKernelGGL((k_unpack<double, double>), grid, dim3(256), 0, s, (const double *)op->Z64, pk.N, pk.nT,
-                                   (nd2 *)dst);
-    else if (to64) hipLaunchKernelGGL((k_unpack<float, double>), grid, dim3(256), 0, s, (const float *)op->Z32, pk.N,
-                                      pk.nT, (nd2 *)dst);
-    else hipLaunchKernelGGL((k_unpack<float, float>), grid, dim3(256), 0, s, (const float *)op->Z32, pk.N, pk.nT,
-                            (nf2 *)dst);
+    auto go = [&](auto whole, auto quarter, const auto *Z, auto *out) {
+        if (pk.ntiles < 256) hipLaunchKernelGGL(quarter, dim3(unsigned(pk.ntiles), 4), dim3(256), 0, s, Z, pk.N, pk.nT, out);
+        else hipLaunchKernelGGL(whole, dim3(unsigned(pk.ntiles)), dim3(256), 0, s, Z, pk.N, pk.nT, out);
+    };
+    const double *Z64 = static_cast<const double *>(op->Z64);
+    const float *Z32 = static_cast<const float *>(op->Z32);
+    if (from64) go(k_unpack<double, double, TB>, k_unpack<double, double, TB / 4>, Z64, static_cast<nd2 *>(dst));
+    else if (to64) go(k_unpack<float, double, TB>, k_unpack<float, double, TB / 4>, Z32, static_cast<nd2 *>(dst));
+    else go(k_unpack<float, float, TB>, k_unpack<float, float, TB / 4>, Z32, static_cast<nf2 *>(dst));
     BIE_HIP(hipGetLastError());
 }
 
