@@ -6,7 +6,8 @@
 //
 // A block of at least 1 MiB that is given up is kept for the next request of its
 // size (up to a quarter less) on its device.  The kept blocks are bounded (4 GiB, or
-// 1/64 of the device's memory if that is less; the oldest go first), those unused for two
+// 1/64 of the device's memory if that is less; the oldest go first, but not where they
+// hold more than the newcomer, which is then not kept), those unused for two
 // seconds are released at the next request or return, and all are released when an
 // allocation of the library fails, before it is tried again, or when the caller asks
 // for it (bie_release_memory).
@@ -162,17 +163,20 @@ void pool_put(void *p)
             st.kept.splice(st.kept.end(), st.used, b);
             const int device = b->device;
             const size_t limit = b->limit;
-            size_t sum = 0;
-            if (b->bytes > limit) {
+            size_t sum = 0, old = 0;   // of the device's kept blocks; of those that would go
+            for (const Block &k : st.kept) sum += k.device == device ? k.bytes : 0;
+            for (const Block &k : st.kept) {
+                if (sum - old <= limit) break;
+                if (k.device == device && k.p != p) old += k.bytes;
+            }
+            if (sum - old > limit || old > b->bytes)   // dropped rather than blocks that took longer to get
                 out.splice(out.end(), st.kept, b);
-            } else {
-                for (const Block &k : st.kept) sum += k.device == device ? k.bytes : 0;
+            else
                 take(st, out, [&](const Block &k) {
                     if (k.device != device || sum <= limit) return false;
                     sum -= k.bytes;
                     return true;
                 });
-            }
         }
         take_idle(st, out);
     }

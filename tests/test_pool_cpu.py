@@ -95,7 +95,7 @@ static void no_host_memory()
         CHECK(!"thrown");
     }
     full = false;
-    CHECK(held[0] == 600 * MiB);   // the oldest went
+    CHECK(held[0] == 604 * MiB);   // b went: 4 + 600 MiB are more
     bie::pool_release();
     CHECK(held[0] == 0);
 }
@@ -117,30 +117,51 @@ static void release_all()
     CHECK(held[0] == 8 * MiB && bie::pool_release_all() == 8 * MiB && held[0] == 0);
 }
 
-// kept blocks stay within the limit of their device, the oldest going first, also where
-// they differ in size by so much that none serves another's request
+// kept blocks stay within the limit of their device, also where they differ in size by so
+// much that none serves another's request: the oldest go for a newcomer that is no smaller
 static void bounded()
 {
-    const size_t sizes[] = { 300 * MiB, 200 * MiB, 450 * MiB, 120 * MiB, 700 * MiB, 64 * MiB };
-    size_t kept = 0;
-    for (size_t n : sizes) {
-        bie::pool_put(get(n));
-        CHECK(held[0] <= GiB && held[0] >= n);
-        kept = std::max(kept, held[0]);
+    const size_t sizes[] = { 120 * MiB, 64 * MiB, 450 * MiB, 300 * MiB, 200 * MiB, 700 * MiB, 40 * MiB };
+    const size_t want[] = { 120, 184, 634, 934, 1014, 1014, 1014 };   // 200 for 120; neither 700 for 814 nor 40 for 64
+    for (int i = 0; i < 7; ++i) {
+        bie::pool_put(get(sizes[i]));
+        CHECK(held[0] <= GiB && held[0] == want[i] * MiB);
     }
-    CHECK(kept > 900 * MiB);
-    CHECK(held[0] == 884 * MiB);   // the last three
-    void *a = get(96 * MiB);       // 120 MiB serve it: a quarter more
-    CHECK(held[0] == 884 * MiB);
-    void *b = get(94 * MiB);       // nothing left of up to a quarter more
-    CHECK(held[0] == 978 * MiB);
+    void *a = get(162 * MiB);      // 200 MiB serve it: up to a quarter more
+    CHECK(held[0] == 1014 * MiB);
+    void *b = get(158 * MiB);      // nothing left that does
+    CHECK(held[0] == 1172 * MiB);
     bie::pool_put(get(2 * GiB));   // beyond the limit: not kept
-    CHECK(held[0] == 978 * MiB);
-    bie::pool_put(a);
+    CHECK(held[0] == 1172 * MiB);
     bie::pool_put(b);
+    CHECK(held[0] == 1172 * MiB);
+    bie::pool_put(a);              // 200 for 64 + 450: not kept
+    CHECK(held[0] == 972 * MiB);
     std::this_thread::sleep_for(std::chrono::milliseconds(2100));
     bie::pool_put(get(2 * MiB));   // what was idle goes
     CHECK(held[0] == 2 * MiB);
+}
+
+// operators made and dropped whose blocks pass the limit together: what is allocated anew for
+// each is the smallest that does not fit, not the largest
+static void cycles()
+{
+    const size_t part[] = { 820, 90, 200, 90 };   // pair blocks, pair values, matrix, matrix
+    size_t before = 0, fresh = 0;
+    for (int i = 0; i < 4; ++i) {
+        before = next;
+        void *p[4];
+        p[2] = get(part[2] * MiB);
+        p[3] = get(part[3] * MiB);
+        p[0] = get(part[0] * MiB);
+        p[1] = get(part[1] * MiB);
+        bie::pool_put(p[1]);
+        bie::pool_put(p[0]);
+        bie::pool_put(p[2]);
+        bie::pool_put(p[3]);
+        fresh = next - before;
+    }
+    CHECK(fresh <= 200 * MiB && held[0] <= GiB);
 }
 
 int main(int, char **argv)
@@ -150,6 +171,7 @@ int main(int, char **argv)
     else if (what == "no_host_memory") no_host_memory();
     else if (what == "release_all") release_all();
     else if (what == "bounded") bounded();
+    else if (what == "cycles") cycles();
     else return 2;
     std::printf("ok\n");
     return 0;
@@ -171,7 +193,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["other_device", "no_host_memory", "release_all", "bounded"])
+@pytest.mark.parametrize("what", ["other_device", "no_host_memory", "release_all", "bounded", "cycles"])
 def test_kept_blocks(driver, what):
     p = subprocess.run([str(driver), what], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
