@@ -96,20 +96,19 @@ namespace {
 
 // Tiles per unit of the single-operator tile pass, one unit per block, the same for any
 // number of vectors (the units set the order of the sums).  Short units spread a small
-// matrix over more CUs; long ones have fewer row sums and blocks, which is what several
-// vectors ask for.  us, one and 16 FP64 vectors; one and 16 FP32 vectors (FP32 matrix; 16:
-// the better of the passes below):
-//   unknowns  1 tile               2                    4                    8
-//     480       7   9;   6   7      7   9;   7   8      9  10;   8   9     12  12;  11  12
-//     882       8  20;   6  11      8  15;   7  10     10  14;   8  11     15  19;  12  15
-//    1800      10  61;   7  38     10  46;   8  29     13  36;   9  24     19  39;  12  21
-//    2592      16 112;   9  74     14  79;  10  51     15  66;  10  44     20  58;  13  38
-//    4608      39 328;  22 199     36 219;  20 144     37 171;  20 112     36 156;  21 102
-//    7680      98 960;  48 540     90 635;  43 402     87 496;  44 308     88 454;  44 270
-//   11250     200 2070; 113 1280  183 1361; 105 842   182 1049; 108 637   185 955; 109 560
-// (16 tiles, one FP64 vector: 127 at 8712 against 115 with 8, 193 at 11250).  The lines lie
-// where a longer unit starts to cost one vector little (FP32 products of 16 at 1800
-// unknowns earlier than FP64 ones).
+// matrix over more CUs; long ones have fewer row sums and blocks, which is what many
+// vectors ask for.  us, 1, 16 and 256 vectors (16 and 256: the better of the passes below):
+//               FP64                                        FP32 matrix, FP64 vectors
+//   unknowns    1 tile       2            4            8      1 tile       2           4
+//     450       7  9  78     8  9  63     9 10  59    12 12   6  9  68     7  9  53    9 10  47
+//     882       8 20 202     8 15 134    10 14 115    15 19   7 18 188     8 14 132   10 13 114
+//    1152       8 30 313     9 23 222    12 22 179    14 20   7 27 302     8 20 216   10 19 173
+//    1800      10 61 774    10 46 520    13 36 406    19 39   8 57 745     8 42 506   10 33 394
+//    2592      16 112 1532  14 79 1026   15 66 797    20 58  12 107 1473  11 75 994   11 62 769
+//    4608      39 328       36 219       37 171       36 156  28 310      25 209      24 162
+//    7680      98 960       90 635       87 496       88 454  67 880      53 582      47 443
+// (8 against 16 tiles, one FP64 vector: 115 / 127 at 8712, 185 / 193 at 11250).  A unit of one
+// tile gains one vector under 1 us over two and costs 128 and more up to a third.
 // BIE_SYM_UNIT = 1..64 fixes the length, 0 balanced runs (measurement).
 int unit_tiles(int64_t nT, bool mat64)
 {
@@ -120,7 +119,7 @@ int unit_tiles(int64_t nT, bool mat64)
     }();
     if (env >= 0) return env;
     const int64_t tiles = nT * (nT + 1) / 2;
-    return tiles < 60 ? 1 : tiles < (mat64 ? 600 : 300) ? 2 : tiles < 3072 ? 4 : 8;
+    return tiles < (mat64 ? 600 : 150) ? 2 : tiles < 3072 ? 4 : 8;
 }
 
 typedef double nd2 __attribute__((ext_vector_type(2)));
@@ -1026,7 +1025,9 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
     // spill) or 4, as even as they come.  A matrix below 10 MB comes from the L2s whatever
     // reads it, and one block per vector fills more CUs (us, a block per vector / groups, of
     // 3 and 16 vectors: FP64, 882 unknowns, 6.9 MB 9 / 10, 15 / 17; 1152, 11.2 MB 12 / 10,
-    // 29 / 23; FP32, 1458, 9.0 MB 9 / 9, 18 / 22; 2178, 20.6 MB 16 / 12, 54 / 33).
+    // 29 / 23; FP32, 1458, 9.0 MB 9 / 9, 18 / 22; 2178, 20.6 MB 16 / 12, 54 / 33).  With many
+    // vectors every CU is busy either way, and FP64 tiles are better read once (648
+    // unknowns, 64 and 256 vectors 30 / 29, 123 / 99; 882 45 / 37, 181 / 134).
     constexpr int MAXNC = sizeof(T) == 8 ? 3 : 4;
     auto several = [&](auto kern, int nc) {
         const int64_t G = (R + nc - 1) / nc;
@@ -1034,7 +1035,7 @@ void launch_product(const Packed &pk, void *part, const void *Z, const void *X, 
                            pk.N, pk.nT, pk.units, pk.unit_ptr, pk.run_ptr, pk.seg, pk.nslots, int(G), R, (const T *)X, ldx,
                            (T *)part, skip, sks);
     };
-    if (R > 1 && pk.ntiles * TB * TB * int64_t(2 * sizeof(M)) >= 10000000) {
+    if (R > 1 && (pk.ntiles * TB * TB * int64_t(2 * sizeof(M)) >= 10000000 || (sizeof(M) == 8 && pk.ntiles * R >= 5000))) {
         const int64_t G = (R + MAXNC - 1) / MAXNC, nc = (R + G - 1) / G;
         // a matrix beyond the 256 MB last-level cache is streamed past it (us, cached /
         // streamed, 2, 3 and 6 FP64 vectors: 5202 unknowns, 213 MiB 44 / 53, 50 / 62, 82 / 94;
