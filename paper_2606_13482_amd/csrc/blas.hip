@@ -1225,9 +1225,10 @@ static void ensure_part(Packed &pk, int64_t R, hipStream_t s)
 }
 
 // The packed product's work units for this operator: the autotuner's choice
-// for (N, matrix precision) among units of 4, 8, 16 tiles and balanced runs,
-// timed (tile pass and reduction of one vector) the first time the size
-// occurs; the operator's tables are rebuilt if the choice is not the default.
+// for (N, matrix precision) among the rule's units and, where those are of 8
+// tiles, 4, 16 and balanced runs, else twice the rule's, timed (tile pass and
+// reduction of one vector) the first time the size occurs; the operator's
+// tables are rebuilt if the choice is not the rule's.
 // Fixed by BIE_SYM_UNIT (measurement) or with tuning off.
 void tune_packed(bie_op *op, hipStream_t s)
 {

@@ -101,7 +101,7 @@ struct Bands {
 // launch of their own (NARROW false), made only if the mesh can have any: in one
 // kernel with them the narrow form has two waves per SIMD instead of three.  A
 // block takes the band's rows p = blockIdx.z, blockIdx.z + gridDim.z, ...  FP64 vector issue bounds it: 13.1 M pairs
-// (7680 unknowns) 2.92 -> 1.52 ms, 54 vector instructions a kernel value, the vector
+// (7680 unknowns) 2.92 -> 1.50 ms, 54 vector instructions a kernel value, the vector
 // units busy 73 % of the time at 2.0 GHz; three waves per SIMD instead of two (y in
 // LDS) measured the same.
 template <typename R, bool SPLIT, bool NARROW>
