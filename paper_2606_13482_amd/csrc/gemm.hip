@@ -624,6 +624,25 @@ int split_most(int64_t Mp, int64_t Kp)
     return split_cfg_env() >= 0 || env_int("BIE_GEMM_SPLITK", 0) > 0 ? ks : gemm_splitk(blocks, nst, 2 * ks);
 }
 
+// Partial sums of at least elems floats.  Growing frees what a captured product may still
+// use, so that it is done only where elems asks for it, and then for every width of one column of
+// blocks too.
+void ensure_split_part(bie_op *op, size_t elems, hipStream_t s)
+{
+    if (op->gemm_part_elems >= elems) return;
+    if (stream_capturing(s))
+        throw Error(BIE_EINVAL, "split-BF16 product: partial sums of " + std::to_string(elems) + " (have " +
+                                    std::to_string(op->gemm_part_elems) + ", N " + std::to_string(op->mesh.N) +
+                                    ") cannot grow inside a captured graph");
+    BIE_HIP(hipStreamSynchronize(s));
+    if (op->gemm_part) (void)hipFree(op->gemm_part);
+    op->gemm_part = nullptr;
+    op->gemm_part_elems = 0;
+    const size_t cap = std::max(elems, size_t(split_most(op->gemm_Mp, op->gemm_Kp)) * size_t(op->gemm_Mp) * GBN);
+    BIE_HIP(device_malloc(&op->gemm_part, cap * sizeof(float)));
+    op->gemm_part_elems = cap;
+}
+
 // Wave-tile form and K slices of a split-BF16 product of this shape: the
 // environment's if set; else the autotuner's choice for (Mp, Kp, NCp, terms),
 // timing every form with the default, half and twice the default K slices on
@@ -650,15 +669,7 @@ void split_choice(int64_t Mp, int64_t Kp, int64_t NCp, int terms, hipStream_t s,
             if (std::find(kss.begin(), kss.end(), k2) == kss.end()) kss.push_back(k2);
         }
         const int kmax = *std::max_element(kss.begin(), kss.end());
-        const size_t pelems = size_t(kmax) * size_t(Mp) * size_t((NCp + GBN - 1) / GBN * GBN);
-        if (op->gemm_part_elems < pelems) {
-            BIE_HIP(hipStreamSynchronize(s));
-            if (op->gemm_part) (void)hipFree(op->gemm_part);
-            op->gemm_part = nullptr;
-            op->gemm_part_elems = 0;
-            BIE_HIP(device_malloc(&op->gemm_part, pelems * sizeof(float)));
-            op->gemm_part_elems = pelems;
-        }
+        ensure_split_part(op, size_t(kmax) * size_t(Mp) * size_t((NCp + GBN - 1) / GBN * GBN), s);
         float *P = static_cast<float *>(op->gemm_part);
         float best = 0.f;
         v = { 0, ks };
@@ -746,20 +757,7 @@ void gemm_product(const bie_op *opc, const void *X, int64_t ldx, int vtype, void
                            Kp, Bh, Bl, terms == 3);
     int cfg = 0, KS = 1;
     split_choice(Mp, Kp, NCp, terms, s, Ah, Al, Bh, Bl, op, cfg, KS);
-    const size_t pelems = size_t(KS) * size_t(Mp) * size_t(NCp), wide = size_t(Mp) * size_t(wide_cols(R));
-    const size_t cap = wide_cols(R) == GBN ? size_t(std::max(KS, split_most(Mp, Kp))) * wide : size_t(KS) * wide;
-    if (op->gemm_part_elems < cap && (op->gemm_part_elems < pelems || !stream_capturing(s))) {
-        if (stream_capturing(s))
-            throw Error(BIE_EINVAL, "split-BF16 product: partial sums of " + std::to_string(pelems) + " (have " +
-                                        std::to_string(op->gemm_part_elems) + ", K slices " + std::to_string(KS) +
-                                        ", N " + std::to_string(N) + ") cannot grow inside a captured graph");
-        BIE_HIP(hipStreamSynchronize(s));
-        if (op->gemm_part) (void)hipFree(op->gemm_part);
-        op->gemm_part = nullptr;
-        op->gemm_part_elems = 0;
-        BIE_HIP(device_malloc(&op->gemm_part, cap * sizeof(float)));
-        op->gemm_part_elems = cap;
-    }
+    ensure_split_part(op, size_t(KS) * size_t(Mp) * size_t(NCp), s);
     float *P = static_cast<float *>(op->gemm_part);
     prof_begin(1, s, R);
     split_launch(NCp, cfg)(terms, dim3(unsigned(Mp / GBM), unsigned(NCp / split_width(NCp)), unsigned(KS)), s, Ah, Al,
