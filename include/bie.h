@@ -181,9 +181,9 @@ int bie_apply(const bie_op *op, const void *X, void *Y, int64_t R, int vec, int 
  * product's partial sums (R x P x 64 complex values, P the operator's partial
  * slots: about 8 MB per complex128 vector at N = 7680) go to a static device
  * array of 128 MiB that each device holds for the life of the process; larger
- * requests return BIE_EINVAL before any launch (use fewer vectors per call; a
- * small matrix's, with up to twice the slots of units of 16 tiles, are judged by
- * those and made in several passes).
+ * requests return BIE_EINVAL before any launch (use fewer vectors per call;
+ * what fits with units of 16 tiles is taken, in several passes where the
+ * operator's shorter units need more).
  * Nothing is allocated and no profiling events are recorded.  Every call on a
  * device shares that array: calls that overlap on one device (other streams or
  * threads) race; calls ordered on one stream do not.  The operator's device

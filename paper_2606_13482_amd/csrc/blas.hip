@@ -1387,15 +1387,12 @@ void product_noalloc(const bie_op *op, bool vec64, const void *X, void *Y, int64
 {
     if (op->star) throw Error(BIE_EINVAL, "the allocation-free product takes an assembled operator");
     const Packed &pk = op->pk;
-    // The short units of a small matrix take up to twice the partial slots of long ones: such
-    // a call is judged by units of 16 tiles and, where its own do not fit, made in several passes,
-    // each of one vector at least: units fixed too short for a large matrix are refused.
-    int64_t slots = pk.nslots;
-    if (unit_tiles(pk.nT, op->Z64 != nullptr) < 8) {
-        int64_t most = pk.nT * (pk.nT - 1) / 2;
-        for (int64_t I = 0; I < pk.nT; ++I) most += (pk.nT - I + 15) / 16;
-        slots = std::min(slots, most);
-    }
+    // Short units take up to twice the partial slots of long ones: a call is judged by units of 16
+    // tiles, whatever the operator's are, and where its own do not fit made in several passes,
+    // each of one vector at least: units too short for a large matrix are refused.
+    int64_t most = pk.nT * (pk.nT - 1) / 2;
+    for (int64_t I = 0; I < pk.nT; ++I) most += (pk.nT - I + 15) / 16;
+    const int64_t slots = std::min(pk.nslots, most);
     const size_t per = TB * (vec64 ? 16 : 8), one = size_t(pk.nslots) * per,
                  need = std::max(size_t(R) * size_t(slots) * per, one);
     if (need > NOALLOC_SCRATCH_BYTES)
